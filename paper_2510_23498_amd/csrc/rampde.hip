@@ -281,17 +281,27 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     int mt = is_backward ? 2 : 4;
     const int want_rows = pol ? pol->row_tile : 0;
     if (want_rows == 16 || want_rows == 32 || (want_rows == 64 && !is_backward)) mt = want_rows / 16;
-    // largest row tile that still gives every compute unit a workgroup and fits the LDS tiles
-    while (mt > 1 && ((want_rows == 0 && (p.R + 16 * mt - 1) / (16 * mt) < 256) || lds_need(mt, false) > lds_limit)) mt >>= 1;
+    // The smallest tile whose workgroups all run at once (a tile's time grows by 1.2 per doubling of its rows --
+    // weights are fetched per tile, not per row --, a second round of workgroups doubles the launch), else the
+    // largest that fits the LDS tiles.  Measured, 3 x 512 hidden, bf16, 16 RK4 steps forward, ms with 16 / 32 / 64
+    // rows: B = 4096 0.85 / 0.88 / 1.20, B = 5000 1.49 / 0.88 / 1.20, B = 8000 1.65 / 1.00 / 1.24, B = 12000
+    // 2.43 / 1.79 / 1.37; forward and backward at B = 5000 6.9 / 4.75 / 5.05.
+    const int64_t cus = device_compute_units();
+    if (want_rows == 0) {
+      int one_round = 1;
+      while (one_round < mt && (p.R + 16 * one_round - 1) / (16 * one_round) > cus) one_round *= 2;
+      mt = one_round;
+    }
+    while (mt > 1 && lds_need(mt, false) > lds_limit) mt >>= 1;
     // Networks with 512-wide hidden layers and a 128-wide state: the 64-row-tile kernels of wide.hpp,
-    // forward and adjoint, when the batch gives at least half of the compute units a tile (or on
-    // request).  Not for the time-grid gradient, and not where a fixed scale lets the other adjoint
-    // kernel run groups of steps per launch.
+    // forward and adjoint, when 32-row tiles no longer run in one round (or on request).  Not for the time-grid
+    // gradient.  A fixed scale takes them too there, step by step, except with one hidden layer: B = 16384, 16 RK4 steps,
+    // bf16, ms with groups of steps on 32-row tiles / with these: 3 x 512 10.5 / 8.5, 2 x 512 6.6 / 6.1, 512 2.9 / 3.4.
     bool all512 = p.L >= 2;
     for (int l = 0; l + 1 < p.L; ++l) all512 = all512 && p.layers[l].Npad == 512;
-    const bool fixed_scale = pol && resolve_scaling(pol) == RAMPDE_SCALE_NONE;
-    if (allow_wide && all512 && p.d == 128 && !(is_backward && fixed_scale) &&
-        (want_rows == 64 || (want_rows == 0 && (p.R + 63) / 64 >= 128)) &&
+    const bool groups_better = is_backward && p.L == 2 && pol && resolve_scaling(pol) == RAMPDE_SCALE_NONE;
+    if (allow_wide && all512 && p.d == 128 && !(groups_better && want_rows == 0) &&
+        (want_rows == 64 || (want_rows == 0 && (p.R + 31) / 32 > cus)) &&
         (size_t)p.nparam * 4 + 64 * (size_t)(128 + 8) * 2 + 2 * 64 * (size_t)(512 + 8) * 2 <= lds_limit) {
       p.wide = true;
       mt = 4;
@@ -356,7 +366,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // set of buffers; groups are as long as about 4 GiB of sets allow.
         const int64_t want_group = (pol && pol->step_group > 0) ? pol->step_group : kMaxWgradSteps;
         const int64_t cap = std::min<int64_t>(want_group, std::min<int64_t>(fit, kMaxWgradSteps));
-        if (pol && resolve_scaling(pol) == RAMPDE_SCALE_NONE && cap >= 2) {
+        if (pol && resolve_scaling(pol) == RAMPDE_SCALE_NONE && cap >= 2 && !p.wide) {
           p.step_group = (int)std::min<int64_t>(N, cap);
           p.nsets = p.step_group;
           p.overlap_wgrad = false;
@@ -533,6 +543,15 @@ __global__ void fill_u32(uint32_t* p, size_t n, uint32_t v) {
 
 __global__ void fill_zero_u32(uint32_t* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
+}
+
+// Rows R .. Rp of every (feature group, stage) run of Rp 8-byte words to zero: one wavefront per run.  Writes only the
+// padding (at most 63 words a run): clearing the whole buffer sets took 290 us at 2000 rows (32 sets of 512-wide
+// activations), this 9 us.
+__global__ __launch_bounds__(256) void fill_pad_rows(uint2* p, size_t runs, int R, int Rp) {
+  const int lane = threadIdx.x & 63;
+  for (size_t q = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); q < runs; q += (size_t)gridDim.x * 4)
+    if (R + lane < Rp) p[q * Rp + R + lane] = make_uint2(0u, 0u);
 }
 
 // ---------------------------------------------------------------- optional per-kernel timing
@@ -1444,7 +1463,9 @@ struct Runner {
       fill_zero_u32<<<1024, 256, 0, st>>>((uint32_t*)(ws + p.gpart), (size_t)p.ksplits * p.P);
       if (p.Rp != p.R) {
         // rows R..Rp of every stage are padding of the contraction: they must read as zero
-        fill_zero_u32<<<1024, 256, 0, st>>>((uint32_t*)(ws + p.ZT), (size_t)p.nsets * p.fm_stride / 4);
+        // (the sets are one array of feature groups x stages of Rp 8-byte words each)
+        const size_t runs = (size_t)p.nsets * p.fm_stride / 8 / p.Rp;
+        fill_pad_rows<<<(unsigned)std::min<size_t>((runs + 3) / 4, 8192), 256, 0, st>>>((uint2*)(ws + p.ZT), runs, (int)p.R, (int)p.Rp);
       }
       fa.ctl = ctl;
       fa.scale_hist = f32(p.scale_hist);

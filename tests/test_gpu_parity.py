@@ -449,3 +449,10 @@ def test_slab_parameter_gradient_groups_of_steps_nonuniform_grid(group):
     par.compare(cfg, gpu, emu, par.TOL_EMUL, "emulation oracle", tol_max=par.TOL_EMUL_MAX[cfg.low])
     assert par.rel_err(gpu["grad_t"], emu["grad_t"]) <= par.TOL_EMUL
     np.testing.assert_array_equal(gpu["scale_hist"].astype(np.float64), emu["scale_hist"])
+
+
+@pytest.mark.parametrize("B", [4097, 8193])
+def test_row_tile_rule_just_past_one_round_of_workgroups(B):
+    # one row more than 256 tiles of 16 / 32 rows: 32-row tiles, and the 64-row-tile kernels under a fixed scale; the
+    # last tile holds one row, and 63 rows of every stage are padding of the parameter-gradient contraction
+    _both(wl.CONFIGS["cfg3"].with_(name=f"round{B}", B=B, N=1, t1=2.0 / 64, tableau="heun", low="bf16", scaling="none"))
