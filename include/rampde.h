@@ -91,6 +91,10 @@ typedef enum {
 #define RAMPDE_NAIVE_STATE 8u       /* comparison baseline, not the paper's scheme: the state y and the adjoint a are
                                      themselves kept in low precision (rounded after every update), i.e. without
                                      the fp32 accumulators of Algorithms 1-2 (the "naive" rows of the paper's Table 5) */
+#define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale within a launch (narrow dense
+                                     networks under overflow detection) give up at the first word that is not there
+                                     yet, as they do when other work keeps them from running at the same time; the
+                                     pass is then redone with one launch per step.  Same results */
 
 /* Explicit Butcher tableau, host memory, fp64.  A is s*s row-major; only the strictly
  * lower triangle may be non-zero (checked).  Consistency (sum b = 1, ...) is not checked. */

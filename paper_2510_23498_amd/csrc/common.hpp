@@ -29,7 +29,8 @@ struct Ctl {
   float s_min, s_max;
   int done;            // workgroups of the current adjoint-step kernel that have finished
   float S_step;        // scale of the most recently accepted step (used by its parameter-gradient kernels)
-  int pad[5];
+  int stalled;         // a wait between the workgroups of a launch ran out (they never ran at the same time)
+  int pad[4];
 };
 static_assert(sizeof(Ctl) == 64, "control block layout");
 

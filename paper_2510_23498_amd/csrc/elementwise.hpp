@@ -154,6 +154,7 @@ __global__ void ctl_reset(Ctl* ctl, float* scale_hist, int N) {
   for (int i = 0; i < N; ++i) scale_hist[i] = 0.f;
   ctl->S = 1.f; ctl->attempt = 1; ctl->poison = 0; ctl->failed_step = -1; ctl->nonfinite = 0;
   ctl->amax_bits = 0; ctl->retries = 0; ctl->s_min = 1.f; ctl->s_max = 1.f; ctl->done = 0; ctl->S_step = 1.f;
+  ctl->stalled = 0;
 }
 
 // a <- dL/dy_N (+ running-cost cotangent), max|a|   (paper Alg. 2, initialisation)
@@ -450,9 +451,11 @@ __global__ __launch_bounds__(256) void time_grid_terms(const float* __restrict__
 // slots [b * per_step, (b + 1) * per_step) (pairs) and adds their sum to dst[2 (step0 - b)], dst[2 (step0 - b) + 1];
 // thread t sums the slots t, t + 256, ... and the 256 partial sums are added up in order.  The slots are cleared for
 // the next launch (the kernels that fill them write only the slots of the workgroups that have something to add).
+// assign: the sums replace dst (launches that run several steps before any of them is known to be accepted: a step
+// that is run again overwrites what its rejected run left).
 __global__ __launch_bounds__(256) void fold_time_slots(float* __restrict__ slots, int per_step, float* __restrict__ dst, int step0,
-                                                       const Ctl* ctl) {
-  if (ctl->poison) return;
+                                                       const Ctl* ctl, int assign = 0) {
+  if (ctl->poison && !assign) return;
   __shared__ float part[256][2];
   float* base = slots + 2 * (size_t)blockIdx.x * per_step;
   float s0 = 0.f, s1 = 0.f;
@@ -472,8 +475,8 @@ __global__ __launch_bounds__(256) void fold_time_slots(float* __restrict__ slots
       b += part[i][1];
     }
     float* d = dst + 2 * (size_t)(step0 - (int)blockIdx.x);
-    d[0] += a;
-    d[1] += b;
+    d[0] = assign ? a : d[0] + a;
+    d[1] = assign ? b : d[1] + b;
   }
 }
 

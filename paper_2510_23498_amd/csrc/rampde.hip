@@ -19,6 +19,7 @@
 #include "common.hpp"
 #include "elementwise.hpp"
 #include "fused_launch.hpp"
+#include "resident_launch.hpp"
 #include "wide.hpp"
 #include "gemm.hpp"
 #include "wgrad_slab.hpp"
@@ -96,6 +97,8 @@ struct Plan {
   // row-tile-persistent path (dense networks whose widest layer fits the LDS tiles)
   bool fused = false;
   int MT = 1;          // row tile = 16 * MT
+  int resident = 0;    // hidden width (64, 128, 256) of the kernels of resident.hpp, 0: not those
+  size_t slots = 0;    // their workgroups' words, [N][workgroups]
   bool wide = false;   // 64-row tiles of the kernels for 512-wide networks (wide.hpp)
   int ldp = 0;         // LDS row pitch (elements)
   size_t lds_bytes = 0;
@@ -233,13 +236,29 @@ static bool fused_candidate(const rampde_velocity* vel, const rampde_policy* pol
   return dp == 64 || dp == 128 || dp == 256;
 }
 
+// Hidden width (64, 128 or 256: all hidden layers padded to it) with which the kernels of resident.hpp take a network,
+// or 0.  They hold a quarter of every layer per wavefront in registers, so the bound is the register file: state width
+// up to 64, two to four layers.  B = 4096, 64 -> 256 -> 256 -> 64, bf16, 32 RK4 steps, forward / adjoint:
+// 400 / 940 us with the weights streamed (fused.hpp), 218 / 491 with these; one row 322 / 193 us forward.
+static int resident_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol) {
+  if (!fused_candidate(vel, pol) || !tab || tab->s < 1 || tab->s > kResidentStages) return 0;
+  if (vel->n_layers < 2 || vel->n_layers > 4 || vel->widths[0] < 1 || vel->widths[0] > 64) return 0;
+  for (int i = 2; i < tab->s; ++i)
+    for (int j = 0; j + 1 < i; ++j)
+      if (tab->A[i * tab->s + j] != 0.0) return 0;
+  int w = 1;
+  for (int l = 1; l < vel->n_layers; ++l) w = std::max(w, vel->widths[l]);
+  return w <= 64 ? 64 : w <= 128 ? 128 : w <= 256 ? 256 : 0;
+}
+
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
 // gradient runs on the other row-tile kernels)
 static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab,
-                      const rampde_policy* pol, int is_backward, bool allow_wide = true) {
+                      const rampde_policy* pol, int is_backward, bool allow_wide = true, bool allow_resident = true) {
   Plan p;
   const bool allow_fused = fused_candidate(vel, pol);
-  if (!build_layers(vel, p, allow_fused ? 256 : kPad)) return p;
+  const int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
+  if (!build_layers(vel, p, rhp ? rhp : allow_fused ? 256 : kPad)) return p;
   if (B < 1 || N < 1 || !tab || tab->s < 1 || tab->s > kMaxStages) return p;
   p.s = tab->s;
   p.cw_blocks = pol && pol->wgrad_tile == 64;
@@ -262,7 +281,32 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     y.bias_f = take(sizeof(float) * y.Npad);
     y.wt_f = take(sizeof(float) * y.Npad * (p.conv ? 9 : 1));
   }
-  if (allow_fused) {
+  if (rhp) {
+    // 16-row tiles as long as they run in one round, 32-row tiles (hidden width 256) beyond
+    const int64_t cus = device_compute_units();
+    const int want_rows = pol ? pol->row_tile : 0;
+    int mt = (rhp == 256 && (want_rows == 32 || (want_rows == 0 && p.R > 16 * cus))) ? 2 : 1;
+    const size_t lds_limit = 159 * 1024;
+    if (mt == 2 && resident_lds_bytes(rhp, p.L, p.s, mt, is_backward) > lds_limit) mt = 1;
+    const size_t lds = resident_lds_bytes(rhp, p.L, p.s, mt, is_backward);
+    const int64_t tiles = (p.R + 16 * mt - 1) / (16 * mt);
+    // (under overflow detection the workgroups of a launch wait for each other: all of them have to fit)
+    const bool detects = is_backward && pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE;
+    // (and a lane's part of a gradient operand has a 32-bit byte offset)
+    const bool offsets_fit = !is_backward || (size_t)rhp * p.s * ((p.R + 63) / 64 * 64) * 2 < (size_t(1) << 32);
+    if (lds > lds_limit || !offsets_fit || (detects && tiles > cus * resident_per_cu(rhp, lds)))
+      return make_plan(vel, B, N, tab, pol, is_backward, allow_wide, false);
+    p.resident = rhp;
+    p.fused = true;
+    p.MT = mt;
+    for (auto& y : p.layers) {
+      y.Wf = take((size_t)y.Npad * y.Kpad * 2);
+      y.WTf = take((size_t)y.Npad * y.Kpad * 2);
+    }
+    p.steptab = take(sizeof(float) * (size_t)N * (1 + p.s));
+    if (is_backward) p.a_alt = take(sizeof(float) * (size_t)p.n);
+    if (detects) p.slots = take(sizeof(unsigned long long) * (size_t)N * tiles);
+  } else if (allow_fused) {
     int maxw = 0, nparam = 0;
     for (auto& y : p.layers) {
       maxw = std::max(maxw, std::max(y.Npad, y.Kpad));
@@ -350,10 +394,10 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     // row-tile-persistent kernels: slopes / stage cotangents only when they do not fit in LDS;
     // the adjoint stores everything the parameter-gradient contraction (and tanh') reads
     // feature-group-major
-    p.K = take((size_t)p.s * p.R * p.dpad * 2);
+    if (!p.resident) p.K = take((size_t)p.s * p.R * p.dpad * 2);
     if (p.wide && !is_backward) p.bsum = take(sizeof(float) * (size_t)p.R * p.dpad);
     if (is_backward) {
-      p.ZBAR = take((size_t)p.s * p.R * p.dpad * 2);
+      if (!p.resident) p.ZBAR = take((size_t)p.s * p.R * p.dpad * 2);
       p.Rp = (p.R + 63) / 64 * 64;
       p.ldk = (int64_t)p.s * p.Rp;
       size_t per_set = 2 * (size_t)p.dpad * p.ldk * 2;
@@ -366,8 +410,8 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // set of buffers; groups are as long as about 4 GiB of sets allow.
         const int64_t want_group = (pol && pol->step_group > 0) ? pol->step_group : kMaxWgradSteps;
         const int64_t cap = std::min<int64_t>(want_group, std::min<int64_t>(fit, kMaxWgradSteps));
-        if (pol && resolve_scaling(pol) == RAMPDE_SCALE_NONE && cap >= 2 && !p.wide) {
-          p.step_group = (int)std::min<int64_t>(N, cap);
+        if (pol && (p.resident || (resolve_scaling(pol) == RAMPDE_SCALE_NONE && cap >= 2)) && !p.wide) {
+          p.step_group = (int)std::max<int64_t>(1, std::min<int64_t>(N, cap));
           p.nsets = p.step_group;
           p.overlap_wgrad = false;
         }
@@ -387,7 +431,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // (the kernel addresses a lane's part of an operand tensor by a 32-bit byte offset)
         bool offsets_fit = (size_t)p.dpad * p.ldk * 2 < (size_t(1) << 32);
         for (auto& y : p.layers) offsets_fit = offsets_fit && (size_t)std::max(y.Npad, y.Kpad) * p.ldk * 2 < (size_t(1) << 32);
-        p.wgrad_slab = !p.overlap_wgrad && p.step_group <= 1 && offsets_fit &&
+        p.wgrad_slab = !p.overlap_wgrad && !p.resident && p.step_group <= 1 && offsets_fit &&
                        (want_tile == 256 || (want_tile != 128 && group * p.ldk >= kSlabMinK));
         if (p.wgrad_slab) {
           p.wgrad_group = (int)group;
@@ -620,6 +664,10 @@ struct SideStream {
   hipEvent_t adjoint_done(int i) { return ev[2 * i]; }
   hipEvent_t wgrad_done(int i) { return ev[2 * i + 1]; }
 };
+
+// The workgroups of a launch that wait for each other did not run at the same time (other work held the device for
+// longer than their waits last): nothing was added to the caller's gradients, the pass is redone step by step.
+constexpr int kStalled = -1;
 
 // ---------------------------------------------------------------- typed launch sequences
 template <class T>
@@ -854,6 +902,7 @@ struct Runner {
 
   // ------------------------------------------------ row-tile-persistent path (dense networks)
   bool use_fused = false;
+  unsigned long long wait_ticks = kWaitTicks;
 
   void cast_fragments(const float* theta) {
     CastArgs c{};
@@ -974,6 +1023,22 @@ struct Runner {
     return RAMPDE_OK;
   }
 
+  int launch_resident(bool adjoint, const FusedArgs& a) {
+    ResidentLaunch l{};
+    l.adjoint = adjoint ? 1 : 0;
+    l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
+    l.MT = p.MT;
+    l.grid = blocks_for(p.R, 16 * p.MT);
+    l.stream = st;
+    ResidentArgs ra{};
+    ra.f = a;
+    ra.slots = p.slots ? (unsigned long long*)(ws + p.slots) : nullptr;
+    ra.wait_ticks = wait_ticks;
+    const hipError_t e = resident_launch(p.resident, l, ra);
+    if (e != hipSuccess) return hip_fail(e, "register-resident kernel launch");
+    return RAMPDE_OK;
+  }
+
   double step_flops() const {  // one velocity evaluation of the whole batch, padded shapes
     double f = 0.0;
     for (const Layer& y : p.layers) f += 2.0 * (double)p.R * y.Npad * y.Kpad;
@@ -992,7 +1057,7 @@ struct Runner {
     int rc;
     {
       TimeScope ts(RAMPDE_K_FUSED_FORWARD, step_flops() * p.s * N, st);
-      rc = launch_fused(false, a);
+      rc = p.resident ? launch_resident(false, a) : launch_fused(false, a);
     }
     if (rc) return rc;
     HIP_TRY(hipGetLastError());
@@ -1003,14 +1068,14 @@ struct Runner {
     int rc;
     {
       TimeScope ts(RAMPDE_K_FUSED_ADJOINT_STEP, step_flops() * p.s * (a.skip_recompute ? 1.0 : 2.0) * a.nsteps, st);
-      rc = launch_fused(true, a);
+      rc = p.resident ? launch_resident(true, a) : launch_fused(true, a);
     }
     if (rc) return rc;
     if (a.tpart) {
       // the launch's per-workgroup slots of the time-grid sums -> the per-step sums (steps a.step, a.step - 1, ...)
       const int grid = blocks_for(p.R, 16 * p.MT);
       if ((size_t)grid * a.nsteps > kTimeSlotPairs) return RAMPDE_EUNSUPPORTED;
-      fold_time_slots<<<a.nsteps, 256, 0, st>>>(a.tpart, grid, f32(p.tpart), a.step, ctl);
+      fold_time_slots<<<a.nsteps, 256, 0, st>>>(a.tpart, grid, f32(p.tpart), a.step, ctl, p.resident ? 1 : 0);
     }
     return RAMPDE_OK;
   }
@@ -1378,11 +1443,11 @@ struct Runner {
                rampde_scaling scaling, const uint16_t* ckpt, const float* grad_yN, const float* grad_ys,
                float* grad_y0, float* grad_theta, float* grad_t, float* scale_hist, rampde_stats* stats) {
     const int dynamic = scaling == RAMPDE_SCALE_DYNAMIC;
+    if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
     if (grad_t) fill_zero_u32<<<1, 256, 0, st>>>((uint32_t*)(ws + p.tpart), 2 * (size_t)N);
     if (grad_t) fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.tslots), 2 * kTimeSlotPairs);
     const int detect = dynamic || scaling == RAMPDE_SCALE_NONE_SAFE;
     const int k_max = pol->k_max > 0 ? pol->k_max : 16;
-    const int HW = p.H * p.Wd;
     if (p.conv) HIP_TRY(allow_conv_tile_lds());
     if (p.wgrad_slab)  // (its ring of operand slabs takes most of a CU's LDS)
       for (const void* f : {reinterpret_cast<const void*>(&wgrad_slab<T, false>), reinterpret_cast<const void*>(&wgrad_slab<T, true>)})
@@ -1432,6 +1497,8 @@ struct Runner {
     };
     if (!use_fused && !p.parabolic) cast_weights(theta);
     SideStream& side = SideStream::get();
+    if (p.slots)
+      fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.slots), 2 * (size_t)N * blocks_for(p.R, 16 * p.MT));
     if (use_fused && p.overlap_wgrad) {
       int rc = side.prepare(N);
       if (rc) return rc;
@@ -1473,7 +1540,9 @@ struct Runner {
       fa.dynamic = dynamic;
       fa.raw_norm = (pol->flags & RAMPDE_GROW_RAW_NORM) ? 1 : 0;
     }
-    float* a = use_fused ? a_buf(N) : grad_y0;
+    // (groups of steps: the adjoint stays in a buffer of its own until the last group writes grad_y0)
+    float* a = p.resident ? f32(p.a_alt) : use_fused ? a_buf(N) : grad_y0;
+    const float* resident_a = a;
     const int naive_low = (pol->flags & RAMPDE_NAIVE_STATE) ? (std::is_same<T, BF16>::value ? 2 : 1) : 0;
     float* gys_rows = nullptr;
     auto gys_at = [&](int i) -> const float* {
@@ -1500,7 +1569,25 @@ struct Runner {
     int status = RAMPDE_OK;
     const bool must_sync = detect || stats || scale_hist;
     for (;;) {
-      if (use_fused && p.step_group > 1) {
+      if (p.resident) {
+        // groups of steps, also under overflow detection: a group's launch takes the accept / grow decisions itself
+        // and ends early, with the adjoint as it was before that step, where one is rejected; the launches behind it
+        // then do nothing
+        for (int hi = from; hi >= 0;) {
+          const int n = std::min(p.step_group, hi + 1);
+          fa.step = hi;
+          fa.nsteps = n;
+          fa.a_in = resident_a;
+          fa.a_out = hi - n < 0 ? grad_y0 : f32(p.a_alt);
+          resident_a = f32(p.a_alt);
+          fa.gys = gys_at(hi);
+          fa.gys_stride = step_elems;
+          int rc = adjoint_step_fused(fa);
+          if (rc) return rc;
+          param_grads_fused(hi, 0.f, Coefs{}, st, n);
+          hi -= n;
+        }
+      } else if (use_fused && p.step_group > 1) {
         // groups of steps: one adjoint launch and one parameter-gradient launch per group, all on
         // the caller's stream; the adjoint ping-pongs between two buffers per launch so that the
         // last launch writes grad_y0
@@ -1524,7 +1611,7 @@ struct Runner {
         }
       }
       int pending_hi = -1, pending_n = 0;  // steps whose parameter gradients wait for their group's launch
-      for (int i = (use_fused && p.step_group > 1) ? -1 : from; i >= 0; --i) {
+      for (int i = (p.resident || (use_fused && p.step_group > 1)) ? -1 : from; i >= 0; --i) {
         if (use_fused) {
           // this set was last read by the parameter-gradient kernel of step i + 2
           if (p.overlap_wgrad && i + 2 <= N - 1) HIP_TRY(hipStreamWaitEvent(st, side.wgrad_done(i + 2), 0));
@@ -1595,6 +1682,7 @@ struct Runner {
       if (!must_sync) break;
       HIP_TRY(hipMemcpyAsync(&hctl, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
+      if (hctl.stalled) return kStalled;
       if (!hctl.poison) break;
       if (!dynamic) break;  // NONE_SAFE: handled below
       if (hctl.failed_step >= N || hctl.attempt >= k_max) {
@@ -1602,6 +1690,12 @@ struct Runner {
         break;
       }
       chain_retry<<<1, 1, 0, st>>>(ctl);
+      if (p.resident) {
+        // the adjoint before the rejected step is where that step's group wrote it (the groups start at `from`)
+        const int in_group = (from - hctl.failed_step) % p.step_group;
+        const int hi = hctl.failed_step + in_group;
+        resident_a = hi - std::min(p.step_group, hi + 1) < 0 ? grad_y0 : f32(p.a_alt);
+      }
       from = hctl.failed_step;
       if (grad_t) fill_zero_u32<<<1, 64, 0, st>>>((uint32_t*)(ws + p.tpart) + 2 * (size_t)from, 2);
       recompute_first = false;  // the stage values of the failed step are still in the workspace
@@ -1696,9 +1790,10 @@ size_t rampde_workspace_bytes(const rampde_velocity* vel, int64_t B, int N, cons
   Plan p = make_plan(vel, B, N, tab, pol, is_backward);
   if (!p.ok) return 0;
   size_t total = p.total;
-  if (is_backward && p.wide) {
-    // the backward pass with the time-grid gradient uses the other row-tile kernels: room for either
-    Plan q = make_plan(vel, B, N, tab, pol, is_backward, false);
+  if (is_backward && (p.wide || p.resident)) {
+    // the backward pass with the time-grid gradient (wide) or redone step by step (resident) uses the other row-tile
+    // kernels: room for either
+    Plan q = make_plan(vel, B, N, tab, pol, is_backward, !p.wide, false);
     if (q.ok) total = std::max(total, q.total);
   }
   return total;
@@ -1760,24 +1855,24 @@ static int backward_rows(const rampde_velocity* vel, const float* theta, int64_t
                          const double* tgrid, int N, const rampde_tableau* tab, const rampde_policy* pol,
                          const void* ckpt, const float* grad_yN, const float* grad_ys, float* grad_y0,
                          float* grad_theta, float* grad_t, float* scale_hist, rampde_stats* stats, void* workspace,
-                         size_t workspace_bytes, hipStream_t st) {
-  Plan p = make_plan(vel, B, N, tab, pol, 1, grad_t == nullptr);
+                         size_t workspace_bytes, hipStream_t st, bool allow_resident = true) {
+  // (a pass that has to be redone starts from grad_yN again: not possible when grad_y0 is the same buffer)
+  const bool in_place = grad_yN == grad_y0 && resolve_scaling(pol) != RAMPDE_SCALE_NONE;
+  Plan p = make_plan(vel, B, N, tab, pol, 1, grad_t == nullptr, allow_resident && !in_place);
   if (!p.ok) return RAMPDE_EINVAL;
   if (workspace_bytes < p.total || ((uintptr_t)workspace & 255)) return RAMPDE_EWORKSPACE;
   const rampde_scaling sc = resolve_scaling(pol);
-  const bool fused = p.fused;
-  if (pol->low == RAMPDE_F16) {
-    Runner<F16> r(p, workspace, st);
-    r.use_fused = fused;
+  auto run = [&](auto low) -> int {
+    Runner<decltype(low)> r(p, workspace, st);
+    r.use_fused = p.fused;
     if (step_elems) r.step_elems = step_elems;
     return r.backward(theta, tgrid, N, tab, pol, sc, (const uint16_t*)ckpt, grad_yN, grad_ys, grad_y0, grad_theta,
                       grad_t, scale_hist, stats);
-  }
-  Runner<BF16> r(p, workspace, st);
-  r.use_fused = fused;
-  if (step_elems) r.step_elems = step_elems;
-  return r.backward(theta, tgrid, N, tab, pol, sc, (const uint16_t*)ckpt, grad_yN, grad_ys, grad_y0, grad_theta,
-                    grad_t, scale_hist, stats);
+  };
+  const int rc = pol->low == RAMPDE_F16 ? run(F16{}) : run(BF16{});
+  if (rc != kStalled) return rc;
+  return backward_rows(vel, theta, B, step_elems, tgrid, N, tab, pol, ckpt, grad_yN, grad_ys, grad_y0, grad_theta, grad_t,
+                       scale_hist, stats, workspace, workspace_bytes, st, false);
 }
 
 int rampde_odeint_bwd_tgrid(const rampde_velocity* vel, const float* theta, int64_t B, const double* tgrid, int N,

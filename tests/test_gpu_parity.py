@@ -456,3 +456,27 @@ def test_row_tile_rule_just_past_one_round_of_workgroups(B):
     # one row more than 256 tiles of 16 / 32 rows: 32-row tiles, and the 64-row-tile kernels under a fixed scale; the
     # last tile holds one row, and 63 rows of every stage are padding of the parameter-gradient contraction
     _both(wl.CONFIGS["cfg3"].with_(name=f"round{B}", B=B, N=1, t1=2.0 / 64, tableau="heun", low="bf16", scaling="none"))
+
+
+@pytest.mark.parametrize("scaling", ["none", "dynamic"])
+@pytest.mark.parametrize("widths,B,low", [
+    ((7, 33, 7), 1, "f16"),                      # two layers, width 64: one row, odd state width
+    ((64, 20, 64, 64), 17, "bf16"),              # three layers of 64, a tile and a row
+    ((30, 65, 128, 100, 30), 70, "f16"),         # four layers of 128: the transposed slices are loaded per phase
+    ((48, 129, 48), 257, "bf16"),                # two layers of 256
+    ((64, 256, 130, 256, 64), 33, "f16"),        # four layers of 256
+    ((16, 200, 180, 16), 4113, "f16"),           # 32-row tiles, the last one ragged, 63 rows of padding
+])
+def test_register_resident_kernels(widths, B, low, scaling):
+    widths = widths if widths[0] == widths[-1] else widths + (widths[0],)
+    # (N = 4: with h = 1/3 the fp32 values that are rounded to bf16 tie often, and the oracle's order of operations then
+    # rounds 1.5 % of the cotangents the other way, 5e-4 of dL/dy_0 and up to 1.8e-3 of db_1, on every kernel path alike)
+    cfg = wl.CONFIGS["cfg1"].with_(name="res" + "_".join(map(str, widths)), B=B, N=4, widths=widths, low=low,
+                                   tableau="rk4", loss="mse")
+    _both(cfg, bias_std=0.1, scaling=scaling)
+
+
+def test_redone_pass_after_a_wait_that_ran_out():
+    # workgroups that do not wait for each other's words give the launch up: the step-by-step kernels redo the pass
+    cfg = wl.CONFIGS["cfg2"].with_(name="nowait", B=1000, N=4, low="f16")
+    _both(cfg, bias_std=0.1, scaling="dynamic", flags=16)
