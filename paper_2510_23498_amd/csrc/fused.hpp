@@ -138,6 +138,7 @@ struct CastLayer {
   float* wt_f;      // [Npad]
   int out, in, in_full, has_time, Npad, Kpad;
   int frag0;        // index of the layer's first fragment among all layers' fragments
+  int perm_f, perm_t;  // contraction order of shallow.hpp (accumulator order of the tile pair in front) in Wf / WTf
 };
 struct CastArgs {
   CastLayer layer[kMaxLayers];
@@ -157,11 +158,11 @@ __global__ void cast_dense_fragments(CastArgs c) {
   const int nfw = (y.Kpad / 32) * (y.Npad / 16);
   if (frag < nfw) {
     const int kb = frag / (y.Npad / 16), nt = frag % (y.Npad / 16);
-    const int n = nt * 16 + (lane & 15), k0 = kb * 32 + (lane >> 4) * 8;
+    const int n = nt * 16 + (lane & 15), k0 = kb * 32 + (lane >> 4) * (y.perm_f ? 4 : 8);
     u16x8 v;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int k = k0 + e;
+      const int k = k0 + e + (y.perm_f && e >= 4 ? 12 : 0);
       v[e] = (n < y.out && k < y.in) ? Low<T>::from_f32(y.W[(size_t)n * y.in_full + k]) : (uint16_t)0;
     }
     y.Wf[(size_t)frag * 64 + lane] = v;
@@ -172,11 +173,11 @@ __global__ void cast_dense_fragments(CastArgs c) {
   } else {
     const int f = frag - nfw;
     const int nb = f / (y.Kpad / 16), kt = f % (y.Kpad / 16);
-    const int k = kt * 16 + (lane & 15), n0 = nb * 32 + (lane >> 4) * 8;
+    const int k = kt * 16 + (lane & 15), n0 = nb * 32 + (lane >> 4) * (y.perm_t ? 4 : 8);
     u16x8 v;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int n = n0 + e;
+      const int n = n0 + e + (y.perm_t && e >= 4 ? 12 : 0);
       v[e] = (n < y.out && k < y.in) ? Low<T>::from_f32(y.W[(size_t)n * y.in_full + k]) : (uint16_t)0;
     }
     y.WTf[(size_t)f * 64 + lane] = v;

@@ -20,6 +20,7 @@
 #include "elementwise.hpp"
 #include "fused_launch.hpp"
 #include "resident_launch.hpp"
+#include "shallow_launch.hpp"
 #include "wide.hpp"
 #include "gemm.hpp"
 #include "wgrad_slab.hpp"
@@ -98,7 +99,9 @@ struct Plan {
   bool fused = false;
   int MT = 1;          // row tile = 16 * MT
   int resident = 0;    // hidden width (64, 128, 256) of the kernels of resident.hpp, 0: not those
+  bool shallow = false;  // (resident != 0) one hidden layer: the kernels of shallow.hpp
   size_t slots = 0;    // their workgroups' words, [N][workgroups]
+  size_t trace_slots = 0;  // shallow flows: the trace row's per-step sums, [N][hidden width] fp32
   bool wide = false;   // 64-row tiles of the kernels for 512-wide networks (wide.hpp)
   int ldp = 0;         // LDS row pitch (elements)
   size_t lds_bytes = 0;
@@ -240,15 +243,34 @@ static bool fused_candidate(const rampde_velocity* vel, const rampde_policy* pol
 // or 0.  They hold a quarter of every layer per wavefront in registers, so the bound is the register file: state width
 // up to 64, two to four layers.  B = 4096, 64 -> 256 -> 256 -> 64, bf16, 32 RK4 steps, forward / adjoint:
 // 400 / 940 us with the weights streamed (fused.hpp), 218 / 491 with these; one row 322 / 193 us forward.
-static int resident_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol) {
-  if (!fused_candidate(vel, pol) || !tab || tab->s < 1 || tab->s > kResidentStages) return 0;
-  if (vel->n_layers < 2 || vel->n_layers > 4 || vel->widths[0] < 1 || vel->widths[0] > 64) return 0;
+static bool chained_stages(const rampde_tableau* tab) {  // every stage is built from the one before it
+  if (!tab || tab->s < 1 || tab->s > kResidentStages) return false;
   for (int i = 2; i < tab->s; ++i)
     for (int j = 0; j + 1 < i; ++j)
-      if (tab->A[i * tab->s + j] != 0.0) return 0;
+      if (tab->A[i * tab->s + j] != 0.0) return false;
+  return true;
+}
+static int resident_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol) {
+  if (!fused_candidate(vel, pol) || !chained_stages(tab)) return 0;
+  if (vel->n_layers < 2 || vel->n_layers > 4 || vel->widths[0] < 1 || vel->widths[0] > 64) return 0;
   int w = 1;
   for (int l = 1; l < vel->n_layers; ++l) w = std::max(w, vel->widths[l]);
   return w <= 64 ? 64 : w <= 128 ? 128 : w <= 256 ? 256 : 0;
+}
+
+// ... with which the kernels of shallow.hpp take it: one hidden layer, up to 1024 wide; the normalising flow with up to
+// 64 state columns, plain networks wider than what resident.hpp takes.  Forward and backward of 16 RK4 steps, ms before /
+// with these: 128 -> 512 -> 128, 4096 rows, bf16 1.02 / 0.80, f16 1.48 / 0.85; 64 -> 1024 -> 64 1.42 / 1.01, 1.93 / 1.08.
+static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol) {
+  if (!vel || (vel->kind != RAMPDE_VEL_MLP && vel->kind != RAMPDE_VEL_CNF) || !vel->widths || vel->n_layers != 2) return 0;
+  if ((pol && (pol->flags & RAMPDE_PER_LAYER_KERNELS)) || !chained_stages(tab)) return 0;
+  const bool flow = vel->kind == RAMPDE_VEL_CNF;
+  const int d = vel->widths[0] + (flow ? 1 : 0), h = vel->widths[1];
+  if (d < 1 || h < 1) return 0;
+  const int hp = h <= 128 ? 128 : h <= 256 ? 256 : h <= 512 ? 512 : h <= 1024 ? 1024 : 0;
+  if (flow) return d <= 64 ? hp : 0;
+  if (d <= 64) return hp > 256 ? hp : 0;
+  return d <= 128 && hp >= 256 && hp <= 512 ? hp : 0;
 }
 
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
@@ -257,7 +279,11 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
                       const rampde_policy* pol, int is_backward, bool allow_wide = true, bool allow_resident = true) {
   Plan p;
   const bool allow_fused = fused_candidate(vel, pol);
-  const int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
+  int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
+  if (rhp == 0 && allow_resident && allow_wide) {  // (the time-grid gradient is formed by the other kernels)
+    rhp = shallow_width(vel, tab, pol);
+    p.shallow = rhp != 0;
+  }
   if (!build_layers(vel, p, rhp ? rhp : allow_fused ? 256 : kPad)) return p;
   if (B < 1 || N < 1 || !tab || tab->s < 1 || tab->s > kMaxStages) return p;
   p.s = tab->s;
@@ -285,16 +311,16 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     // 16-row tiles as long as they run in one round, 32-row tiles (hidden width 256) beyond
     const int64_t cus = device_compute_units();
     const int want_rows = pol ? pol->row_tile : 0;
-    int mt = (rhp == 256 && (want_rows == 32 || (want_rows == 0 && p.R > 16 * cus))) ? 2 : 1;
+    int mt = (rhp == 256 && !p.shallow && (want_rows == 32 || (want_rows == 0 && p.R > 16 * cus))) ? 2 : 1;
     const size_t lds_limit = 159 * 1024;
     if (mt == 2 && resident_lds_bytes(rhp, p.L, p.s, mt, is_backward) > lds_limit) mt = 1;
-    const size_t lds = resident_lds_bytes(rhp, p.L, p.s, mt, is_backward);
+    const size_t lds = p.shallow ? 0 : resident_lds_bytes(rhp, p.L, p.s, mt, is_backward);
     const int64_t tiles = (p.R + 16 * mt - 1) / (16 * mt);
     // (under overflow detection the workgroups of a launch wait for each other: all of them have to fit)
     const bool detects = is_backward && pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE;
     // (and a lane's part of a gradient operand has a 32-bit byte offset)
     const bool offsets_fit = !is_backward || (size_t)rhp * p.s * ((p.R + 63) / 64 * 64) * 2 < (size_t(1) << 32);
-    if (lds > lds_limit || !offsets_fit || (detects && tiles > cus * resident_per_cu(rhp, lds)))
+    if (lds > lds_limit || !offsets_fit || (detects && tiles > cus * (p.shallow ? 1 : resident_per_cu(rhp, lds))))
       return make_plan(vel, B, N, tab, pol, is_backward, allow_wide, false);
     p.resident = rhp;
     p.fused = true;
@@ -306,6 +332,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     p.steptab = take(sizeof(float) * (size_t)N * (1 + p.s));
     if (is_backward) p.a_alt = take(sizeof(float) * (size_t)p.n);
     if (detects) p.slots = take(sizeof(unsigned long long) * (size_t)N * tiles);
+    if (is_backward && p.cnf) p.trace_slots = take(sizeof(float) * (size_t)N * rhp);
   } else if (allow_fused) {
     int maxw = 0, nparam = 0;
     for (auto& y : p.layers) {
@@ -331,6 +358,9 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     // rows: B = 4096 0.85 / 0.88 / 1.20, B = 5000 1.49 / 0.88 / 1.20, B = 8000 1.65 / 1.00 / 1.24, B = 12000
     // 2.43 / 1.79 / 1.37; forward and backward at B = 5000 6.9 / 4.75 / 5.05.
     const int64_t cus = device_compute_units();
+    // (one hidden layer of more than 512: the adjoint kernel of 32-row tiles is the slower one even where 16-row tiles
+    // take two rounds: 1024 wide, 128 state columns, 8192 rows, forward and backward 2.2 against 2.7 ms)
+    if (want_rows == 0 && is_backward && p.L == 2 && p.layers[0].Npad > 512 && p.dpad <= 128) mt = 1;
     if (want_rows == 0) {
       int one_round = 1;
       while (one_round < mt && (p.R + 16 * one_round - 1) / (16 * one_round) > cus) one_round *= 2;
@@ -919,6 +949,8 @@ struct Runner {
       d.wt_f = f32(y.wt_f);
       d.out = y.out; d.in = y.in; d.in_full = y.in_full; d.has_time = y.has_time;
       d.Npad = y.Npad; d.Kpad = y.Kpad;
+      d.perm_f = p.shallow && l == 1;
+      d.perm_t = p.shallow && l == 0;
       d.frag0 = nfrag;
       nfrag += (y.Kpad / 32) * (y.Npad / 16) + (y.Npad / 32) * (y.Kpad / 16);
     }
@@ -1023,17 +1055,38 @@ struct Runner {
     return RAMPDE_OK;
   }
 
+  // c_h of the trace row from theta (shallow flows)
+  void trace_coefficients(const float* theta) {
+    const Layer &y0 = p.layers[0], &y1 = p.layers[1];
+    cnf_trace_coef_theta<T><<<blocks_for(y0.Npad, 64), 64, 0, st>>>(theta + y0.theta_w, y0.in_full, theta + y1.theta_w, y0.in,
+                                                                   y0.out, y0.Npad, f32(p.cnf_c));
+  }
+
   int launch_resident(bool adjoint, const FusedArgs& a) {
+    ResidentArgs ra{};
+    ra.f = a;
+    ra.slots = p.slots ? (unsigned long long*)(ws + p.slots) : nullptr;
+    ra.wait_ticks = wait_ticks;
+    if (p.shallow) {
+      ShallowLaunch l{};
+      l.adjoint = adjoint ? 1 : 0;
+      l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
+      l.NTL = p.dpad / 64;
+      l.trace = p.cnf ? 1 : 0;
+      l.grid = blocks_for(p.R, 16);
+      l.stream = st;
+      ShallowArgs sa{};
+      sa.r = ra;
+      sa.trace_c = p.cnf ? f32(p.cnf_c) : nullptr;
+      const hipError_t e = shallow_launch(p.resident, l, sa);
+      return e == hipSuccess ? RAMPDE_OK : hip_fail(e, "one-hidden-layer kernel launch");
+    }
     ResidentLaunch l{};
     l.adjoint = adjoint ? 1 : 0;
     l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
     l.MT = p.MT;
     l.grid = blocks_for(p.R, 16 * p.MT);
     l.stream = st;
-    ResidentArgs ra{};
-    ra.f = a;
-    ra.slots = p.slots ? (unsigned long long*)(ws + p.slots) : nullptr;
-    ra.wait_ticks = wait_ticks;
     const hipError_t e = resident_launch(p.resident, l, ra);
     if (e != hipSuccess) return hip_fail(e, "register-resident kernel launch");
     return RAMPDE_OK;
@@ -1048,6 +1101,7 @@ struct Runner {
   int forward_fused(const float* theta, const float* y0, const double* tgrid, int N, const rampde_tableau* tab,
                     const rampde_policy* pol, uint16_t* ckpt, float* yN) {
     cast_fragments(theta);
+    if (p.cnf) trace_coefficients(theta);
     write_steptab(tgrid, N, tab, pol->low);
     FusedArgs a = fused_args(tab, N);
     a.y0 = y0;
@@ -1509,6 +1563,7 @@ struct Runner {
     FusedArgs fa{};
     if (use_fused) {
       cast_fragments(theta);
+      if (p.cnf) trace_coefficients(theta);
       write_steptab(tgrid, N, tab, pol->low);
       fa = fused_args(tab, N);
       fa.ckpt = const_cast<uint16_t*>(ckpt);
@@ -1585,6 +1640,18 @@ struct Runner {
           int rc = adjoint_step_fused(fa);
           if (rc) return rc;
           param_grads_fused(hi, 0.f, Coefs{}, st, n);
+          if (p.cnf) {  // the trace row's share: sums of every accepted step of the group
+            TraceSums t{};
+            t.ACTT = u16(p.ACTT[0]);
+            t.KBART = u16(p.KBART);
+            t.set_stride = (int64_t)(p.fm_stride / 2);
+            t.ldk = p.ldk;
+            t.step = hi; t.nsets = p.nsets; t.HP = p.resident; t.l_col = p.d - 1; t.s = p.s;
+            t.steptab = f32(p.steptab);
+            t.scale_hist = f32(p.scale_hist);
+            t.slots = f32(p.trace_slots);
+            cnf_trace_slots<T><<<dim3(p.resident / 16, n), 256, 0, st>>>(t);
+          }
           hi -= n;
         }
       } else if (use_fused && p.step_group > 1) {
@@ -1666,6 +1733,12 @@ struct Runner {
         a = grad_y0;
         if (p.overlap_wgrad) HIP_TRY(hipStreamWaitEvent(st, side.wgrad_done(0), 0));  // helper stream is in order: joins all
         reduce_partial_gradients<<<blocks_for(p.P, 256), 256, 0, st>>>(grad_theta, f32(p.gpart), p.P, p.ksplits, ctl);
+        if (p.cnf) {
+          const Layer &y0 = p.layers[0], &y1 = p.layers[1];
+          cnf_trace_fold<T><<<blocks_for(y0.out, 4), 256, 0, st>>>(f32(p.trace_slots), N, p.resident, theta + y0.theta_w,
+                                                                  theta + y1.theta_w, y0.in, y0.out, y0.in_full,
+                                                                  grad_theta + y0.theta_w, grad_theta + y1.theta_w, ctl);
+        }
       }
       if (grad_t) fold_time_sums<<<blocks_for(N + 1, 256), 256, 0, st>>>(grad_t, f32(p.tpart), N, ctl);
       if (p.parabolic) {

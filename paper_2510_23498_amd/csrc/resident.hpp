@@ -399,6 +399,116 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_forward_resident(R
   for (int mt = 0; mt < MT; ++mt) store4f(g.y, row0 + mt * 16 + lm, g.R, ns, g.d, yv[mt]);
 }
 
+// The accept / reject / grow bookkeeping of a launch that runs several steps (Algorithm 2), one object per thread with
+// the same contents in every thread of every workgroup.
+struct StepExchange {
+  const ResidentArgs& ra;
+  float S, s_min, s_max;
+  int attempt;
+  bool stalled = false;
+  __device__ __forceinline__ StepExchange(const ResidentArgs& r)
+      : ra(r), S(r.f.ctl->S), s_min(r.f.ctl->s_min), s_max(r.f.ctl->s_max), attempt(r.f.ctl->attempt) {}
+
+  // post this workgroup's word of step `step`: bits of its max|a|, and whether its cotangent chain left the range
+  __device__ __forceinline__ void post(const FusedArgs& g, int step, unsigned bits, bool nonfinite) {
+    __shared__ unsigned s_post[16];
+    if (nonfinite) bits |= 0x80000000u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) bits = max(bits, (unsigned)__shfl_xor((int)bits, o));
+    if ((threadIdx.x & 63) == 0) s_post[threadIdx.x >> 6] = bits;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      unsigned m = 0;
+      for (int w = 0; w < (int)(blockDim.x >> 6); ++w) m = max(m, s_post[w]);
+      __hip_atomic_store(ra.slots + (size_t)step * gridDim.x + blockIdx.x, ((unsigned long long)attempt << 32) | m,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+
+  // the outcome of step `step` over all tiles, from every workgroup's word.  Returns false if a wait ran out.
+  __device__ __forceinline__ bool collect(int step, unsigned& pay) {
+    __shared__ unsigned s_pay[16];
+    __shared__ int s_late[16];
+    const unsigned long long* row = ra.slots + (size_t)step * gridDim.x;
+    unsigned m = 0;
+    bool late = false;
+    unsigned long long t0 = 0;
+    for (int q = threadIdx.x; q < (int)gridDim.x; q += blockDim.x) {
+      unsigned long long v = __hip_atomic_load(row + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      while ((int)(v >> 32) != attempt && !late) {
+        if (t0 == 0) t0 = wall_clock64();
+        __builtin_amdgcn_s_sleep(1);
+        v = __hip_atomic_load(row + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        late = wall_clock64() - t0 >= ra.wait_ticks;
+      }
+      m = max(m, (unsigned)v);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
+    const int any_late = __any(late ? 1 : 0);
+    if ((threadIdx.x & 63) == 0) {
+      s_pay[threadIdx.x >> 6] = m;
+      s_late[threadIdx.x >> 6] = any_late;
+    }
+    __syncthreads();
+    bool ok = true;
+    pay = 0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+      pay = max(pay, s_pay[w]);
+      ok = ok && s_late[w] == 0;
+    }
+    return ok;  // (the next write to the shared words is a whole step of barriers away)
+  }
+
+  // accept / grow; false: the step is rejected, or the wait ran out (stalled)
+  template <class T>
+  __device__ __forceinline__ bool decide(const FusedArgs& g, int step) {
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (g.detect) {
+      unsigned pay;
+      if (!collect(step, pay)) {
+        stalled = true;
+        if (threadIdx.x == 0) {  // (poison: every later kernel of the pass does nothing)
+          __hip_atomic_store(&g.ctl->stalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(&g.ctl->poison, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return false;
+      }
+      if (pay & 0x80000000u) {
+        if (first) {
+          g.ctl->poison = 1;
+          g.ctl->failed_step = step;
+        }
+        return false;
+      }
+      s_min = fminf(s_min, S);
+      s_max = fmaxf(s_max, S);
+      if (first) {
+        g.scale_hist[step] = S;
+        g.ctl->S_step = S;
+      }
+      if (g.dynamic && attempt == 1) {
+        const float amax = __builtin_bit_cast(float, pay);
+        const float test = g.raw_norm ? amax : S * amax;
+        if (test <= ldexpf(1.f, Low<T>::p_bits - 1) && S < ldexpf(1.f, 126)) S *= 2.f;
+      }
+      attempt = 1;
+    } else if (first) {
+      g.scale_hist[step] = S;
+    }
+    return true;
+  }
+
+  __device__ __forceinline__ void finish(const FusedArgs& g) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      g.ctl->S = S;
+      g.ctl->attempt = attempt;
+      g.ctl->s_min = s_min;
+      g.ctl->s_max = s_max;
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------------------
 // A group of adjoint steps of a tile.  PHASED: the forward and the transposed slices do not fit in the registers
 // together (four layers of 256): each phase of a step loads its own.
@@ -414,8 +524,6 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
   const int64_t row0 = (int64_t)blockIdx.x * TM;
   const int s = g.s;
   const int ns = wave * 16 + lq * 4, nh = wave * TPW * 16 + lq * 4;
-  __shared__ unsigned s_pay[4], s_post[4];
-  __shared__ int s_stalled;
 
   // (the transposed last slice in LDS where it fits beside the activations: 32 registers for the rest)
   constexpr bool LDS_LAST = HP >= 128 && L >= 3 && MT == 1;
@@ -427,10 +535,7 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
     wb.template load<false, 6>(g, wave, lane);
   }
   lds.fill(g);
-  if (tid == 0) s_stalled = 0;
-  float S = g.ctl->S;
-  int attempt = g.ctl->attempt;
-  float s_min = g.ctl->s_min, s_max = g.ctl->s_max;
+  StepExchange ex(ra);
   float av[MT][4], a_old[MT][4];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) load4f(g.a_in, row0 + mt * 16 + lm, g.R, ns, g.d, av[mt]);
@@ -451,70 +556,6 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
 
   // activations (later: cotangents, in place) of stage j, hidden layer l
   auto tile = [&](int j, int l) __attribute__((always_inline)) { return lds.tiles + (size_t)(j * (L - 1) + l) * TM * Sh::LDP; };
-
-  // the outcome of step `step` over all tiles, from every workgroup's word.  Returns false if a wait ran out.
-  auto collect = [&](int step, unsigned& pay) __attribute__((always_inline)) -> bool {
-    const unsigned long long* row = ra.slots + (size_t)step * gridDim.x;
-    unsigned m = 0;
-    bool late = false;
-    unsigned long long t0 = 0;
-    for (int q = tid; q < (int)gridDim.x; q += 256) {
-      unsigned long long v = __hip_atomic_load(row + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      while ((int)(v >> 32) != attempt && !late) {
-        if (t0 == 0) t0 = wall_clock64();
-        __builtin_amdgcn_s_sleep(1);
-        v = __hip_atomic_load(row + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        late = wall_clock64() - t0 >= ra.wait_ticks;
-      }
-      m = max(m, (unsigned)v);
-    }
-    if (late) s_stalled = 1;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
-    if (lane == 0) s_pay[wave] = m;
-    __syncthreads();
-    pay = max(max(s_pay[0], s_pay[1]), max(s_pay[2], s_pay[3]));
-    const bool ok = s_stalled == 0;
-    __syncthreads();
-    return ok;
-  };
-  // accept / grow (Algorithm 2); the same in every workgroup.  false: the step is rejected or the wait ran out.
-  bool stalled = false;
-  auto decide = [&](int step) __attribute__((always_inline)) -> bool {
-    if (g.detect) {
-      unsigned pay;
-      if (!collect(step, pay)) {
-        stalled = true;
-        if (tid == 0) {  // (poison: every later kernel of the pass does nothing)
-          __hip_atomic_store(&g.ctl->stalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(&g.ctl->poison, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        return false;
-      }
-      if (pay & 0x80000000u) {
-        if (blockIdx.x == 0 && tid == 0) {
-          g.ctl->poison = 1;
-          g.ctl->failed_step = step;
-        }
-        return false;
-      }
-      s_min = fminf(s_min, S);
-      s_max = fmaxf(s_max, S);
-      if (blockIdx.x == 0 && tid == 0) {
-        g.scale_hist[step] = S;
-        g.ctl->S_step = S;
-      }
-      if (g.dynamic && attempt == 1) {
-        const float amax = __builtin_bit_cast(float, pay);
-        const float test = g.raw_norm ? amax : S * amax;
-        if (test <= ldexpf(1.f, Low<T>::p_bits - 1) && S < ldexpf(1.f, 126)) S *= 2.f;
-      }
-      attempt = 1;
-    } else if (blockIdx.x == 0 && tid == 0) {
-      g.scale_hist[step] = S;
-    }
-    return true;
-  };
 
   bool rejected = false;
 #pragma unroll 1
@@ -614,7 +655,7 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
     }
 
     // ---- the previous step's outcome: its scale is needed from here on
-    if (it > 0 && !decide(step + 1)) {
+    if (it > 0 && !ex.template decide<T>(g, step + 1)) {
       rejected = true;
       break;
     }
@@ -629,7 +670,7 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
     for (int mt = 0; mt < MT; ++mt) {
       float sa[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sa[r] = S * av[mt][r];
+      for (int r = 0; r < 4; ++r) sa[r] = ex.S * av[mt][r];
       lamq[mt] = pack4<T>(sa);
       track(big, lamq[mt]);
 #pragma unroll
@@ -740,7 +781,7 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
     }
 
     // ---- a <- a + (h / S) sum_j zbar_j (+ running-cost cotangent), fp32
-    const float hs = h / S;
+    const float hs = h / ex.S;
     if constexpr (TG)
       block_sum2(fmaf(hs, t_dt - t_dh, -t_phia), fmaf(hs, t_dh, t_phia), g.tpart + 2 * ((size_t)it * gridDim.x + blockIdx.x));
     unsigned bits = 0;
@@ -757,22 +798,11 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
         if (mask[mt] && ns + r < g.d) bits = max(bits, bb);
       }
     }
-    if (g.detect) {
-      if (tracked_nonfinite<T>(big)) bits |= 0x80000000u;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) bits = max(bits, (unsigned)__shfl_xor((int)bits, o));
-      if (lane == 0) s_post[wave] = bits;
-      __syncthreads();
-      if (tid == 0) {
-        const unsigned m = max(max(s_post[0], s_post[1]), max(s_post[2], s_post[3]));
-        __hip_atomic_store(ra.slots + (size_t)step * gridDim.x + blockIdx.x, ((unsigned long long)attempt << 32) | m,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-    if (!g.detect) decide(step);
+    if (g.detect) ex.post(g, step, bits, tracked_nonfinite<T>(big));
+    else ex.template decide<T>(g, step);
   }
-  if (g.detect && !rejected) rejected = !decide(g.step - g.nsteps + 1);
-  if (stalled) return;
+  if (g.detect && !rejected) rejected = !ex.template decide<T>(g, g.step - g.nsteps + 1);
+  if (ex.stalled) return;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     // (a rejected step leaves the adjoint as it was before it)
@@ -782,12 +812,7 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_adjoint_resident(R
     }
     store4f(g.a_out, row0 + mt * 16 + lm, g.R, ns, g.d, av[mt]);
   }
-  if (blockIdx.x == 0 && tid == 0) {
-    g.ctl->S = S;
-    g.ctl->attempt = attempt;
-    g.ctl->s_min = s_min;
-    g.ctl->s_max = s_max;
-  }
+  ex.finish(g);
 }
 
 }  // namespace rampde

@@ -57,3 +57,17 @@ def test_cnf_state_wider_than_one_padding_block():
 
 def test_cnf_time_grid_gradient():
     _case(BASE.with_(name="cnft", B=48, N=3, widths=(7, 64, 7), grad_scale=1.0), want_grad_t=True)
+
+
+@pytest.mark.parametrize("H,B,low", [(128, 1, "f16"), (129, 17, "bf16"), (300, 33, "f16"), (513, 100, "f16")])
+def test_cnf_hidden_widths_of_every_kernel(H, B, low):
+    # the four compiled hidden widths; one row, a tile and a row, two tiles and a row, a batch that is no tile multiple
+    _case(BASE.with_(name=f"cnfw{H}", B=B, N=3, widths=(10, H, 10), low=low, grad_scale=1.0))
+
+
+def test_cnf_redone_pass_after_a_wait_that_ran_out():
+    cfg = BASE.with_(name="cnfwait", B=200, N=4, widths=(15, 200, 15))
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    gpu = par.run_gpu(cfg, theta, y0, target, flags=16)
+    emu = par.run_oracle(cfg, theta, y0, target, "emul")
+    par.compare(cfg, gpu, emu, par.TOL_EMUL, "emulation oracle", tol_max=par.TOL_EMUL_MAX[cfg.low])

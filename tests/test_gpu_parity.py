@@ -480,3 +480,10 @@ def test_redone_pass_after_a_wait_that_ran_out():
     # workgroups that do not wait for each other's words give the launch up: the step-by-step kernels redo the pass
     cfg = wl.CONFIGS["cfg2"].with_(name="nowait", B=1000, N=4, low="f16")
     _both(cfg, bias_std=0.1, scaling="dynamic", flags=16)
+
+
+@pytest.mark.parametrize("scaling", ["none", "dynamic"])
+@pytest.mark.parametrize("d,H,B,low", [(64, 257, 40, "f16"), (5, 1024, 17, "bf16"), (65, 200, 35, "f16"), (128, 512, 16, "bf16")])
+def test_one_hidden_layer_kernels(d, H, B, low, scaling):
+    cfg = wl.CONFIGS["cfg1"].with_(name=f"shallow{d}_{H}", B=B, N=4, widths=(d, H, d), low=low, loss="mse")
+    _both(cfg, bias_std=0.1, scaling=scaling)
