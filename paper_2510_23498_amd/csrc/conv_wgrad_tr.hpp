@@ -376,9 +376,17 @@ __global__ void conv_wgrad_tr_reduce(float* __restrict__ G, int ldg, const float
 // block multiply the cotangent fragment with a 0/1 fragment built in registers -- column t < 9: [pixel + tap t inside],
 // column 9: ones -- into one more accumulator block, which is folded into fp32 sums with the stage's time factors
 // whenever the stage changes (a K-chunk can span stages).
+// Image lines of any width up to W = 16 W16: the pixels from the line's end to W are fetched from a page of zeros, so
+// they add nothing and the input's first one is the zero pixel after the line.  Lines of 28 pixels thus pay for 32,
+// against gemm_tn (a read of both operands per tap, one block of 64 x 64 out of its 128 x 128) and column_sums: 20 images
+// of 28 x 28, 24 channels, 8 steps of two stages: 4.72 -> 2.99 ms per pass.  Lines of 8 and 24 pixels, where conv_wgrad
+// is the alternative (64 channels, 8 RK4 steps, per pass): 8 x 8, 128 images, 5.41 against 5.31 ms; 24 x 24, 64 images,
+// 6.60 against 6.45 ms.
+__device__ __align__(16) uint16_t kZeroPage[64];
 template <class T, bool TS, int W16>
 __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
   if (g.ctl->poison) return;
+  const int Wr = g.Wd;                                         // pixels per image line
   constexpr int W = 16 * W16, LPS = 4 / W16, NL = 32 / W16;   // lines per step, lines in the ring
   constexpr int GB = W * 128, LSLOT = (2 * W + 2) * 128;      // cotangent line, then the input line with its zero rows
   constexpr int NG = NL / LPS;                                 // groups in the ring (8)
@@ -391,14 +399,15 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
   const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int64_t total_lines = g.rows / W;
-  const int64_t c0 = (int64_t)blockIdx.z * (g.rows_per_split / W);
-  int64_t c1 = c0 + g.rows_per_split / W;
+  const int64_t total_lines = g.rows / Wr;
+  const int lines_per_split = g.rows_per_split / Wr;
+  const int64_t c0 = (int64_t)blockIdx.z * lines_per_split;
+  int64_t c1 = c0 + lines_per_split;
   if (c1 > total_lines) c1 = total_lines;
   if (c0 >= c1) return;
   const int nl = (int)(c1 - c0);
   const int nsteps = (nl + LPS - 1) / LPS;
-  const int lines_per_stage = (int)(g.R / W);
+  const int lines_per_stage = (int)(g.R / Wr);
 
   // the zero rows before and after the input line of every ring slot (never overwritten)
   for (int i = tid; i < NL * 16; i += 256) {
@@ -415,7 +424,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
   const int lr = lane >> 3, sp = lane & 7;
   int ld_line[4], ld_px[4], ld_dst[4];
   const uint16_t* ld_src[4];
-  int ld_ldx[4];
+  int ld_ldx[4], ld_linelen[4];   // elements per pixel and per line; both 0 for a lane's pixel past the line's end
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int u = 4 * wave + i, op = u >> 3, px = 8 * (u & 7) + lr;   // pixel within the group
@@ -423,8 +432,10 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
     ld_px[i] = px % W;
     const int prow = op ? ld_px[i] + 1 : ld_px[i];                    // LDS row of the lane's pixel
     const int piece = sp ^ (((prow >> 1) & 1) << 2);
-    ld_src[i] = (op ? g.B : g.A) + piece * 8;
-    ld_ldx[i] = op ? g.ldb : g.lda;
+    const bool off = ld_px[i] >= Wr;
+    ld_src[i] = (off ? kZeroPage : op ? g.B : g.A) + piece * 8;
+    ld_ldx[i] = off ? 0 : op ? g.ldb : g.lda;
+    ld_linelen[i] = ld_ldx[i] * Wr;
     ld_dst[i] = (op ? GB + 128 : 0) + (8 * (u & 7) % W) * 128;        // (+ the line's slot)
   }
   int ld_group = 0;
@@ -435,7 +446,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
       int64_t line = c0 - 1 + lam;
       line = line < 0 ? 0 : (line >= total_lines ? total_lines - 1 : line);
       const int slot = lam % NL;
-      __builtin_amdgcn_global_load_lds(ld_src[i] + ((size_t)line * W + ld_px[i]) * ld_ldx[i],
+      __builtin_amdgcn_global_load_lds(ld_src[i] + (size_t)line * ld_linelen[i] + ld_px[i] * ld_ldx[i],
                                        (__attribute__((address_space(3))) void*)(ring + slot * LSLOT + ld_dst[i]), 16, 0, 0);
     }
     ++ld_group;
@@ -497,7 +508,8 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
   const uint32_t one2 = (uint32_t)Low<T>::from_f32(1.f) * 0x10001u;
   const int vsel = ncol < 9 ? ncol / 3 : (ncol == 9 ? 3 : 4);           // bit of the validity word that switches the column on
   const bool edge_l = ncol < 9 && ncol % 3 == 0 && kg == 0;             // dx = -1: pixel 0 of the line is off
-  const bool edge_r = ncol < 9 && ncol % 3 == 2 && kg == 1;             // dx = +1: pixel W - 1 of the line is off
+  const int last = Wr - 1;                                              // dx = +1: the line's last pixel is off
+  const bool edge_r = ncol < 9 && ncol % 3 == 2 && kg == ((last >> 3) & 1);
   float s_tau[16], s_one[16], s_c[16];   // tau-, un- and c_j-weighted sums of this lane's column
 #pragma unroll
   for (int q = 0; q < 16; ++q) s_tau[q] = s_one[q] = s_c[q] = 0.f;
@@ -634,7 +646,11 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
         // this lane's 8 pixels of the k-step against its column's tap: all on, except the line's first / last pixel
         uint32_t mk[4] = {cur.mbase, cur.mbase, cur.mbase, cur.mbase};
         if (edge_l && ks == 0) mk[0] &= 0xffff0000u;
-        if (edge_r && ks == W16 - 1) mk[3] &= 0x0000ffffu;
+        if (edge_r && ks == last >> 4) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (((last >> 1) & 3) == q) mk[q] &= (last & 1) ? 0x0000ffffu : 0xffff0000u;
+        }
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         am = Low<T>::mfma32(fa, __builtin_bit_cast(u16x8, u32x4{mk[0], mk[1], mk[2], mk[3]}), am);
       }

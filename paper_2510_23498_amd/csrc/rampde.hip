@@ -213,8 +213,8 @@ static bool build_layers(const rampde_velocity* vel, Plan& p, int hidden_pad = k
 
 static rampde_scaling resolve_scaling(const rampde_policy* pol);
 struct Plan;
-// the all-taps convolution weight-gradient kernel: image lines of a multiple of 8 pixels, at most
-// 64, and whole 128-row k-steps within a stage
+// the all-taps convolution weight-gradient kernels: image lines of at most 64 pixels, and with other than 64 x 64 padded
+// channels a multiple of 8 pixels and whole 128-row k-steps within a stage
 static bool conv_wgrad_applies(const Plan& p);
 // Time-grid gradient: every workgroup that adds to a step's sums writes a slot of its own, and a one-workgroup kernel
 // folds the launch's slots in a fixed order (no floating-point atomics: the result does not depend on the order in
@@ -222,6 +222,8 @@ static bool conv_wgrad_applies(const Plan& p);
 constexpr size_t kTimeSlotPairs = size_t(1) << 19;
 static bool conv_wgrad_tr_applies(const Plan& p);
 static bool conv_wgrad_tr64_applies(const Plan& p, const Layer& y);
+// image lines of a pipeline step of conv_wgrad_tr64 (64 pixels with the lines padded to 16, 32 or 64)
+static int tr64_step_lines(int Wd) { return Wd <= 16 ? 4 : Wd <= 32 ? 2 : 1; }
 // compute units of the current device (256 on MI355X; also the answer when no device is visible,
 // e.g. a workspace query on a host without a GPU)
 static int device_compute_units() {
@@ -551,8 +553,9 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         for (auto& y : p.layers) {
           const int tiles = (y.Npad / 64) * (y.Kpad / 64);
           const int64_t want = std::max<int64_t>(1, device_compute_units() / tiles);
-          int64_t per = ((rows + want - 1) / want + CW_KS - 1) / CW_KS * CW_KS;
-          if (per < 4 * CW_KS) per = 4 * CW_KS;
+          const int64_t unit = conv_wgrad_tr64_applies(p, y) ? (int64_t)2 * tr64_step_lines(p.Wd) * p.Wd : CW_KS;
+          int64_t per = ((rows + want - 1) / want + unit - 1) / unit * unit;
+          if (per < 4 * unit) per = 4 * unit;
           y.cw_per = (int)per;
           y.cw_splits = (int)((rows + per - 1) / per);
           y.cw_floats = (size_t)y.cw_splits * tiles * CW_SLOT;
@@ -569,14 +572,20 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
   return p;
 }
 
-static bool conv_wgrad_applies(const Plan& p) { return p.conv && !p.fused && p.Wd % 8 == 0 && p.Wd <= 64 && p.R % CW_KS == 0; }
-// (64 x 64 channels, 16 / 32 / 64 pixels per line: conv_wgrad's drop-in built on transposing LDS reads)
+static bool conv_wgrad_lines_applies(const Plan& p) { return p.conv && !p.fused && p.Wd % 8 == 0 && p.Wd <= 64 && p.R % CW_KS == 0; }
+// (64 x 64 channels, image lines of up to 64 pixels: conv_wgrad's drop-in built on transposing LDS reads)
 static bool conv_wgrad_tr64_applies(const Plan& p, const Layer& y) {
-  return conv_wgrad_applies(p) && !p.cw_blocks && y.Npad == 64 && y.Kpad == 64 && (p.Wd == 16 || p.Wd == 32 || p.Wd == 64);
+  return p.conv && !p.fused && !p.cw_blocks && y.Npad == 64 && y.Kpad == 64 && p.Wd <= 64;
+}
+static bool conv_wgrad_applies(const Plan& p) {
+  if (conv_wgrad_lines_applies(p)) return true;
+  for (const Layer& y : p.layers)
+    if (!conv_wgrad_tr64_applies(p, y)) return false;
+  return true;
 }
 // (the kernel built on transposing LDS reads: the parabolic block's one layer, channel counts in multiples of 128)
 static bool conv_wgrad_tr_applies(const Plan& p) {
-  return conv_wgrad_applies(p) && p.parabolic && !p.cw_blocks &&
+  return conv_wgrad_lines_applies(p) && p.parabolic && !p.cw_blocks &&
          (p.Wd == 16 || p.Wd == 32 || p.Wd == 64) && p.layers[0].Npad % 128 == 0 && p.layers[0].Kpad % 128 == 0 &&
          !p.layers[0].has_time;
 }
@@ -1334,22 +1343,21 @@ struct Runner {
         c.tpart = tpart_i ? f32(p.tslots) : nullptr;
         dim3 cgrid(y.Npad / 64, y.Kpad / 64, y.cw_splits);
         TimeScope ts(RAMPDE_K_WGRAD_GEMM, 2.0 * rows * (double)y.Npad * y.Kpad * 9, st);
-        const size_t lds = conv_wgrad_lds_bytes(p.Wd);
         const bool tsum = c.tpart && c.wt;
         if (conv_wgrad_tr64_applies(p, y)) {
           // 64 x 64 channels: the kernel built on transposing LDS reads (same private copies)
-          const size_t l64 = conv_wgrad_tr64_lds_bytes(p.Wd);
-          if (p.Wd == 16) {
+          const size_t l64 = conv_wgrad_tr64_lds_bytes(p.Wd <= 16 ? 16 : p.Wd <= 32 ? 32 : 64);
+          if (p.Wd <= 16) {
             if (tsum) conv_wgrad_tr64<T, true, 1><<<cgrid, 256, l64, st>>>(c);
             else conv_wgrad_tr64<T, false, 1><<<cgrid, 256, l64, st>>>(c);
-          } else if (p.Wd == 32) {
+          } else if (p.Wd <= 32) {
             if (tsum) conv_wgrad_tr64<T, true, 2><<<cgrid, 256, l64, st>>>(c);
             else conv_wgrad_tr64<T, false, 2><<<cgrid, 256, l64, st>>>(c);
           } else {
             if (tsum) conv_wgrad_tr64<T, true, 4><<<cgrid, 256, l64, st>>>(c);
             else conv_wgrad_tr64<T, false, 4><<<cgrid, 256, l64, st>>>(c);
           }
-        } else if (p.Wd <= 32) {
+        } else if (const size_t lds = conv_wgrad_lds_bytes(p.Wd); p.Wd <= 32) {
           if (tsum) conv_wgrad<T, true, CW_MAXI_LO><<<cgrid, 256, lds, st>>>(c);
           else conv_wgrad<T, false, CW_MAXI_LO><<<cgrid, 256, lds, st>>>(c);
         } else {
@@ -1516,6 +1524,8 @@ struct Runner {
                               reinterpret_cast<const void*>(&conv_wgrad_tr64<T, false, 2>), reinterpret_cast<const void*>(&conv_wgrad_tr64<T, true, 2>),
                               reinterpret_cast<const void*>(&conv_wgrad_tr64<T, false, 4>), reinterpret_cast<const void*>(&conv_wgrad_tr64<T, true, 4>)})
           HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)conv_wgrad_tr64_lds_bytes(16)));
+    }
+    if (conv_wgrad_lines_applies(p) && !conv_wgrad_tr_applies(p)) {
       const int lds = (int)conv_wgrad_lds_bytes(p.Wd);
       HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad<T, false, CW_MAXI_LO>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds));

@@ -221,6 +221,19 @@ def test_conv_weight_gradient_64_channels_transposing_reads_bf16():
     np.testing.assert_array_equal(gpu["grad_y0"], old["grad_y0"])
 
 
+@pytest.mark.parametrize("C,H,W,B,low", [(64, 3, 1, 5, "f16"), (24, 1, 15, 3, "f16"), (64, 14, 14, 2, "f16"), (20, 5, 17, 2, "bf16"),
+                                         (24, 28, 28, 2, "f16"), (64, 2, 31, 9, "f16"), (8, 7, 33, 2, "f16"), (64, 3, 63, 2, "f16"),
+                                         (32, 8, 8, 3, "f16")])
+def test_conv_weight_gradient_ragged_image_lines(C, H, W, B, low):
+    # image lines padded to 16, 32 or 64 pixels in LDS (one pixel, one less and one more than a padded line, odd pixels
+    # counts per stage), against the generic contraction of the same rounded operands: fp32 summation order only
+    cfg = wl.CONFIGS["cfg4"].with_(name=f"convrag{C}x{H}x{W}", B=B, N=2, C=C, H=H, W=W, tableau="kutta3", low=low)
+    gpu, _, _ = _both(cfg, bias_std=0.1, tol_emul=2e-3 if low == "bf16" else par.TOL_EMUL)
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    old = par.run_gpu(cfg, theta, y0, target, wgrad_tile=64)
+    assert par.rel_err(gpu["grad_theta"], old["grad_theta"]) <= 1e-5
+
+
 def test_conv_small_odd_geometry():
     cfg = wl.CONFIGS["cfg4"].with_(name="convodd", B=2, N=2, C=5, H=7, W=6, tableau="kutta3")
     _both(cfg, bias_std=0.1)
@@ -291,7 +304,7 @@ def test_time_grid_gradient_small_mlp_all_tableaux(tab, flags):
 
 @pytest.mark.parametrize("C,H,W,B,tab", [(64, 32, 32, 2, "rk4"), (64, 16, 16, 3, "heun"), (64, 4, 64, 2, "kutta3"),
                                           (5, 7, 6, 2, "kutta3"), (70, 4, 8, 4, "heun"),
-                                          (70, 4, 8, 3, "heun"), (8, 16, 24, 1, "kutta3")])
+                                          (70, 4, 8, 3, "heun"), (8, 16, 24, 1, "kutta3"), (24, 9, 28, 2, "rk4"), (64, 3, 33, 1, "heun")])
 def test_time_grid_gradient_conv(C, H, W, B, tab):
     # both convolutions carry a time channel; all-taps weight-gradient kernel and the generic one (W = 6)
     cfg = wl.CONFIGS["cfg4"].with_(name=f"dtconv{C}x{H}x{W}", B=B, N=2, C=C, H=H, W=W, tableau=tab)
