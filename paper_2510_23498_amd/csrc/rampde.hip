@@ -754,17 +754,25 @@ struct Runner {
       e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, NtLines<4>::LDS);
       if (e != hipSuccess) return e;
     }
-    if (p.Wd < 8 || p.Wd > 64) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&conv3x3_tile<T, 8>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)conv_tile_lds_bytes(p.Wd));
+    for (const void* f : {reinterpret_cast<const void*>(&conv3x3_tile<T, 1, 2, 1>), reinterpret_cast<const void*>(&conv3x3_tile<T, 2, 4, 1>),
+                          reinterpret_cast<const void*>(&conv3x3_tile<T, 2, 4, 2>)}) {
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
 
   void launch_nt(const GemmNT& g) {
     TimeScope ts(RAMPDE_K_VELOCITY_GEMM, 2.0 * g.M * (double)g.N * g.K, st);
-    if (p.conv && !p.parabolic && conv_tile_applies(g.Cpad, g.N, g.H, g.Wd, g.M)) {
-      // persistent: one workgroup per CU (its LDS holds the layer's weights), tiles of 256 pixels
-      const int ntiles = (int)(g.M / CT_TILE);
-      conv3x3_tile<T, 8><<<std::min(ntiles, device_compute_units()), 512, conv_tile_lds_bytes(g.Wd), st>>>(g);
+    if (p.conv && !p.parabolic && conv_tile_applies(g.Cpad, g.N, g.Wd)) {
+      // persistent: one workgroup per CU (its LDS holds the layer's weights), tiles of whole image lines
+      const int64_t images = g.M / ((int64_t)g.H * g.Wd);
+      const bool few = p.d <= 32;
+      const ConvTileShape sh = conv_tile_shape(few ? 1 : 2, few ? 2 : 4, g.H, g.Wd, images, device_compute_units());
+      const size_t lds = conv_tile_lds_bytes(few ? 1 : 2, few ? 2 : 4, sh.lines, g.Wd);
+      if (few) conv3x3_tile<T, 1, 2, 1><<<sh.blocks, 512, lds, st>>>(g, sh);
+      else if (sh.aw == 2) conv3x3_tile<T, 2, 4, 2><<<sh.blocks, 512, lds, st>>>(g, sh);
+      else conv3x3_tile<T, 2, 4, 1><<<sh.blocks, 512, lds, st>>>(g, sh);
     } else if (p.conv && !p.cw_blocks && conv_nt_lines_applies(g)) {
       // ... with the input staged by image lines: a block of input channels serves all nine taps from LDS
       dim3 grid(g.M / 512, g.N / 128);

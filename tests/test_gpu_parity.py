@@ -234,6 +234,13 @@ def test_conv_weight_gradient_ragged_image_lines(C, H, W, B, low):
     assert par.rel_err(gpu["grad_theta"], old["grad_theta"]) <= 1e-5
 
 
+@pytest.mark.parametrize("C,H,W,B", [(64, 5, 1, 2), (33, 9, 20, 2), (64, 30, 30, 3), (40, 70, 2, 2), (3, 15, 15, 260), (32, 3, 64, 3)])
+def test_conv_tiles_of_whole_lines(C, H, W, B):
+    # tiles of lines that do not fill the pixel blocks, a last tile with fewer lines, one and two wavefronts per pixel
+    # block, 33 channels (two output blocks), several tiles per workgroup
+    _both(wl.CONFIGS["cfg4"].with_(name=f"convtile{C}x{H}x{W}", B=B, N=1, C=C, H=H, W=W, tableau="heun"), bias_std=0.1)
+
+
 def test_conv_small_odd_geometry():
     cfg = wl.CONFIGS["cfg4"].with_(name="convodd", B=2, N=2, C=5, H=7, W=6, tableau="kutta3")
     _both(cfg, bias_std=0.1)
