@@ -1882,10 +1882,13 @@ size_t rampde_workspace_bytes(const rampde_velocity* vel, int64_t B, int N, cons
   if (!p.ok) return 0;
   size_t total = p.total;
   if (is_backward && (p.wide || p.resident)) {
-    // the backward pass with the time-grid gradient (wide) or redone step by step (resident) uses the other row-tile
-    // kernels: room for either
-    Plan q = make_plan(vel, B, N, tab, pol, is_backward, !p.wide, false);
-    if (q.ok) total = std::max(total, q.total);
+    // the backward pass with the time-grid gradient (neither wide nor shallow) or redone step by step (not resident)
+    // uses the other row-tile kernels: room for any of them
+    for (const bool wide : {false, true})
+      for (const bool resident : {false, true}) {
+        const Plan q = make_plan(vel, B, N, tab, pol, is_backward, wide, resident);
+        if (q.ok) total = std::max(total, q.total);
+      }
   }
   return total;
 }

@@ -507,3 +507,14 @@ def test_redone_pass_after_a_wait_that_ran_out():
 def test_one_hidden_layer_kernels(d, H, B, low, scaling):
     cfg = wl.CONFIGS["cfg1"].with_(name=f"shallow{d}_{H}", B=B, N=4, widths=(d, H, d), low=low, loss="mse")
     _both(cfg, bias_std=0.1, scaling=scaling)
+
+
+@pytest.mark.parametrize("scaling", ["none", "dynamic"])
+def test_time_grid_gradient_of_one_hidden_layer_with_row_tile_64(scaling):
+    # dL/dt and everything else come from different kernels here; the workspace that the query names holds either
+    cfg = wl.CONFIGS["cfg1"].with_(name="tgrid128_512", B=100, N=4, widths=(128, 512, 128), low="f16", loss="mse")
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    gpu = par.run_gpu(cfg, theta, y0, target, scaling=scaling, row_tile=64, want_grad_t=True)
+    emu = par.run_oracle(cfg, theta, y0, target, "emul", scaling=scaling)
+    par.compare(cfg, gpu, emu, par.TOL_EMUL, "emulation oracle", tol_max=par.TOL_EMUL_MAX[cfg.low])
+    assert par.rel_err(gpu["grad_t"], emu["grad_t"]) <= par.TOL_EMUL
