@@ -51,8 +51,24 @@ inline ConvTileShape conv_tile_shape(int NA, int KC, int H, int Wd, int64_t imag
   return t;
 }
 
+// What a tile reads and writes goes through buffer descriptors of its own image lines: a lane without a pixel reads zeros
+// and stores nowhere, and every lane issues the same number of loads and stores.  Loads and stores share a counter, so
+// only then can the compiler wait for the next tile's input without waiting for this tile's stores.
+//
+// The loads are not in flight beside the matrix instructions: the activations of the tanh' factor have arrived before the
+// multiplication, the next tile's input is requested behind it and arrives during the epilogue.  Some cards run the two
+// together slower than one after the other.  64 channels, 32 x 32, 128 images, 16 RK4 steps, ms per training pass on four
+// cards (equal in a plain copy and a plain matrix product) with the kernel for powers of two that this one replaced /
+// everything in flight beside the multiplication and waited for ahead of the epilogue / as here: 12.8 / 12.5 / (12.1 with
+// counted stores), 13.6 / 13.9 / 13.0, 13.7 / 14.1 / 13.2, 14.2 / 14.8 / 13.7.
+constexpr int kOutside = 0x40000000;  // (a byte offset past every window)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const uint16_t* p, int elements) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, elements * 2, 0x00020000);
+}
+
 // 8 wavefronts: pixel block (wave / AW), output blocks (wave % AW) * NB ...
-template <class T, int NA, int KC, int AW>
+enum ConvEpilogue { kConvPlain, kConvTanh, kConvFactor };  // nothing, tanh, tanh' of the stored activation
+template <class T, int NA, int KC, int AW, int EPI>
 __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) {
   constexpr int NT = 512;
   constexpr int NB = NA / AW;                        // output blocks of a wavefront
@@ -71,26 +87,28 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // ---- input chunks of a tile: chunk id -> (staged line ly, pixel x, 8 channels c8), the same in every tile
-  int c_ly[MAXC], c_src[MAXC], c_dst[MAXC];          // ly = 0 is the line above the tile; -1: no chunk
+  int c_ly[MAXC], c_src[MAXC], c_dst[MAXC];          // ly = 0 is the line above the tile; -1: no chunk; c_src in bytes
 #pragma unroll
   for (int i = 0; i < MAXC; ++i) {
     const int id = tid + NT * i;
     const int c8 = id % C8, px = id / C8;
     const int ly = px / W, x = px - ly * W;
     c_ly[i] = px < (PR + 2) * W ? ly : -1;
-    c_src[i] = ((ly - 1) * W + x) * g.lda + c8 * 8;
+    c_src[i] = (ly * W + x) * g.lda * 2 + c8 * 16;
     c_dst[i] = (ly * LW + x + 1) * PITCH + c8 * 8;
   }
   u16x8 reg[MAXC];
   auto load_tile = [&](int t) __attribute__((always_inline)) {
     const int img = t / sh.per_image, y0 = (t - img * sh.per_image) * PR;
-    const uint16_t* src = g.A + ((size_t)img * H + y0) * W * g.lda;
+    // lines first .. y0 + PR of the image, those of them that it has
+    const int first = y0 > 0 ? y0 - 1 : 0, lines = min(y0 + PR + 1, H) - first;
+    const auto src = window(g.A + ((size_t)img * H + first) * W * g.lda, lines * W * g.lda);
+    const int skip = (first - (y0 - 1)) * W * g.lda * 2;
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
-      u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
       const int y = y0 + c_ly[i] - 1;
-      if (c_ly[i] >= 0 && y >= 0 && y < H) v = *reinterpret_cast<const u16x8*>(src + c_src[i]);
-      reg[i] = v;
+      const int off = c_ly[i] >= 0 && y >= 0 && y < H ? c_src[i] - skip : kOutside;
+      reg[i] = __builtin_bit_cast(u16x8, __builtin_amdgcn_raw_buffer_load_b128(src, off, 0, 0));
     }
   };
   auto store_tile = [&]() __attribute__((always_inline)) {
@@ -99,10 +117,7 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
       if (c_ly[i] >= 0) *reinterpret_cast<u16x8*>(&sIn[c_dst[i]]) = reg[i];
   };
 
-  // Wait for the requested input here, before the epilogue's stores are issued: stores count with the loads, and since a
-  // lane past the tile's pixels issues none, a wait behind them would be for all of them.  64 channels, 32 x 32, 128
-  // images, 16 RK4 steps, per pass against a kernel for powers of two that counted its stores: 14.6 against 13.5 ms with
-  // the wait at the LDS writes, 12.1 against 12.5 ms here (another card).
+  // wait for the requested input: where no stores were issued behind the request
   auto settle = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) asm volatile("" : "+v"(reg[i]));
@@ -168,17 +183,30 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
   const int ly = on ? p / W : 0, x = on ? p - ly * W : 0;
   const int in_base = ((ly + 1) * LW + x + 1) * PITCH + fk;
   const int w_base = (a0 * 32 + (lane & 31)) * PITCH + fk;
+  const int n0 = a0 * 32 + 4 * (lane >> 5);           // this lane's first output channel
 
   bool bad = false;
+  settle();
   for (int t = blockIdx.x; t < sh.tiles; t += gridDim.x) {
     __syncthreads();  // the previous tile's fragments have been read (and the tables are written)
     store_tile();
     __syncthreads();
-    if (t + (int)gridDim.x < sh.tiles) load_tile(t + gridDim.x);
-    const int img = t / sh.per_image, y = (t - img * sh.per_image) * PR + ly;
+    const int img = t / sh.per_image, y0 = (t - img * sh.per_image) * PR, y = y0 + ly;
     const bool live = on && y < H;
-    const size_t m = ((size_t)img * H + y) * W + x;
+    const size_t row0 = ((size_t)img * H + y0) * W;
+    const int pixels = min(PR, H - y0) * W;  // of the tile; lanes past them read zeros and their stores go nowhere
+    // the stored activations for the tanh' factor of this lane's outputs
+    uint2 dv[NB][4];
+    if constexpr (EPI == kConvFactor) {
+      const auto act = window(g.dact + row0 * g.ldd, pixels * g.ldd);
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          dv[a][q4] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(act, (p * g.ldd + n0 + a * 32 + 8 * q4) * 2, 0, 0));
+    }
     if (pb * 32 >= PR * W) {  // (uniform: no pixel block for this wavefront)
+      if (t + (int)gridDim.x < sh.tiles) load_tile(t + gridDim.x);
       settle();
       continue;
     }
@@ -188,16 +216,6 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
     for (int a = 0; a < NB; ++a)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[a][q] = 0.f;
-    // the stored activations for the tanh' factor of this lane's outputs: in flight during the
-    // multiplication
-    uint2 dv[NB][4];
-    if (g.dact && live) {
-#pragma unroll
-      for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          dv[a][q4] = *reinterpret_cast<const uint2*>(g.dact + m * g.ldd + (a0 + a) * 32 + 8 * q4 + 4 * (lane >> 5));
-    }
     // 9 KC k-blocks of 16 (9 taps x 16 KC channels); the fragments of block i + 1 are read from LDS
     // before the MFMAs of block i are issued (a workgroup is alone on its CU: nothing else hides
     // the LDS latency)
@@ -209,6 +227,12 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
         fa[a] = *reinterpret_cast<const u16x8*>(&sW[(tap * NCH + a * 32) * PITCH + w_base + kk * 16]);
       fb = *reinterpret_cast<const u16x8*>(&sIn[in_base + shift + kk * 16]);
     };
+    if constexpr (EPI == kConvFactor) {  // (wait for them)
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) asm volatile("" : "+v"(dv[a][q4].x), "+v"(dv[a][q4].y));
+    }
     u16x8 fa[2][NB], fb[2];
     load_frags(0, fa[0], fb[0]);
 #pragma unroll
@@ -220,10 +244,11 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
       __builtin_amdgcn_sched_barrier(0);
     }
 
+    if (t + (int)gridDim.x < sh.tiles) load_tile(t + gridDim.x);
+
     // ---- epilogue: accumulator row = output channel 8 (q / 4) + 4 (lane / 32) + q % 4 of block a,
     //      column = pixel lane % 32
-    settle();
-    if (!live) continue;
+    const auto out = window(g.C + row0 * g.ldc, pixels * g.ldc);
     int combo = 0;
     if (g.wt) combo = ((y > 0) << 3) | ((y < H - 1) << 2) | ((x > 0) << 1) | (x < W - 1 ? 1 : 0);
     float4 tv[NB][4];
@@ -231,31 +256,29 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
     for (int a = 0; a < NB; ++a)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
-        tv[a][q4] = *reinterpret_cast<const float4*>(&s_tt[combo * NCH + (a0 + a) * 32 + 8 * q4 + 4 * (lane >> 5)]);
+        tv[a][q4] = *reinterpret_cast<const float4*>(&s_tt[combo * NCH + n0 + a * 32 + 8 * q4]);
 #pragma unroll
-    for (int a = 0; a < NB; ++a) {
+    for (int a = 0; a < NB; ++a)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const int n = (a0 + a) * 32 + 8 * q4 + 4 * (lane >> 5);
         float v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = acc[a][q4 * 4 + r];
         v[0] += tv[a][q4].x; v[1] += tv[a][q4].y; v[2] += tv[a][q4].z; v[3] += tv[a][q4].w;
-        if (g.act_tanh) {
+        if constexpr (EPI == kConvTanh) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = tanh_fast(v[r]);
         }
-        if (g.dact) {
+        if constexpr (EPI == kConvFactor) {
           float av[4];
           unpack4<T>(dv[a][q4], av);
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = v[r] * (1.f - av[r] * av[r]);
         }
         const uint2 q = pack4<T>(v);
-        bad = bad || any_nonfinite4<T>(q);
-        *reinterpret_cast<uint2*>(g.C + m * g.ldc + n) = q;
+        bad |= live & any_nonfinite4<T>(q);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, q), out, (p * g.ldc + n0 + a * 32 + 8 * q4) * 2, 0, 0);
       }
-    }
   }
   if (g.detect) raise_if_any(bad, g.ctl);
 }

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -754,25 +755,35 @@ struct Runner {
       e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, NtLines<4>::LDS);
       if (e != hipSuccess) return e;
     }
-    for (const void* f : {reinterpret_cast<const void*>(&conv3x3_tile<T, 1, 2, 1>), reinterpret_cast<const void*>(&conv3x3_tile<T, 2, 4, 1>),
-                          reinterpret_cast<const void*>(&conv3x3_tile<T, 2, 4, 2>)}) {
-      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+    if (p.parabolic || !conv_tile_applies(p.layers[0].Kpad, p.layers[0].Npad, p.Wd)) return hipSuccess;
+    for (ConvTileKernel f : conv_tile_kernels(conv_tile())) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
+  }
+
+  // conv3x3_tile by shape (32 channels; 64 channels with two, with one wavefront per pixel block) and epilogue
+  using ConvTileKernel = void (*)(GemmNT, ConvTileShape);
+  template <int NA, int KC, int AW>
+  static constexpr std::array<ConvTileKernel, 3> conv_tile_epilogues() {
+    return {&conv3x3_tile<T, NA, KC, AW, kConvPlain>, &conv3x3_tile<T, NA, KC, AW, kConvTanh>, &conv3x3_tile<T, NA, KC, AW, kConvFactor>};
+  }
+  bool few_channels() const { return p.d <= 32; }
+  ConvTileShape conv_tile() const {
+    return conv_tile_shape(few_channels() ? 1 : 2, few_channels() ? 2 : 4, p.H, p.Wd, p.R / ((int64_t)p.H * p.Wd), device_compute_units());
+  }
+  std::array<ConvTileKernel, 3> conv_tile_kernels(const ConvTileShape& sh) const {
+    return few_channels() ? conv_tile_epilogues<1, 2, 1>() : sh.aw == 2 ? conv_tile_epilogues<2, 4, 2>() : conv_tile_epilogues<2, 4, 1>();
   }
 
   void launch_nt(const GemmNT& g) {
     TimeScope ts(RAMPDE_K_VELOCITY_GEMM, 2.0 * g.M * (double)g.N * g.K, st);
     if (p.conv && !p.parabolic && conv_tile_applies(g.Cpad, g.N, g.Wd)) {
       // persistent: one workgroup per CU (its LDS holds the layer's weights), tiles of whole image lines
-      const int64_t images = g.M / ((int64_t)g.H * g.Wd);
-      const bool few = p.d <= 32;
-      const ConvTileShape sh = conv_tile_shape(few ? 1 : 2, few ? 2 : 4, g.H, g.Wd, images, device_compute_units());
-      const size_t lds = conv_tile_lds_bytes(few ? 1 : 2, few ? 2 : 4, sh.lines, g.Wd);
-      if (few) conv3x3_tile<T, 1, 2, 1><<<sh.blocks, 512, lds, st>>>(g, sh);
-      else if (sh.aw == 2) conv3x3_tile<T, 2, 4, 2><<<sh.blocks, 512, lds, st>>>(g, sh);
-      else conv3x3_tile<T, 2, 4, 1><<<sh.blocks, 512, lds, st>>>(g, sh);
+      const ConvTileShape sh = conv_tile();
+      const size_t lds = conv_tile_lds_bytes(few_channels() ? 1 : 2, few_channels() ? 2 : 4, sh.lines, g.Wd);
+      conv_tile_kernels(sh)[g.dact ? kConvFactor : g.act_tanh ? kConvTanh : kConvPlain]<<<sh.blocks, 512, lds, st>>>(g, sh);
     } else if (p.conv && !p.cw_blocks && conv_nt_lines_applies(g)) {
       // ... with the input staged by image lines: a block of input channels serves all nine taps from LDS
       dim3 grid(g.M / 512, g.N / 128);
