@@ -379,9 +379,7 @@ __global__ void conv_wgrad_tr_reduce(float* __restrict__ G, int ldg, const float
 // Image lines of any width up to W = 16 W16: the pixels from the line's end to W are fetched from a page of zeros, so
 // they add nothing and the input's first one is the zero pixel after the line.  Lines of 28 pixels thus pay for 32,
 // against gemm_tn (a read of both operands per tap, one block of 64 x 64 out of its 128 x 128) and column_sums: 20 images
-// of 28 x 28, 24 channels, 8 steps of two stages: 4.72 -> 2.99 ms per pass.  Lines of 8 and 24 pixels, where conv_wgrad
-// is the alternative (64 channels, 8 RK4 steps, per pass): 8 x 8, 128 images, 5.41 against 5.31 ms; 24 x 24, 64 images,
-// 6.60 against 6.45 ms.
+// of 28 x 28, 24 channels, 8 steps of two stages: 4.72 -> 2.99 ms per pass.
 __device__ __align__(16) uint16_t kZeroPage[64];
 template <class T, bool TS, int W16>
 __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {

@@ -574,9 +574,14 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
 }
 
 static bool conv_wgrad_lines_applies(const Plan& p) { return p.conv && !p.fused && p.Wd % 8 == 0 && p.Wd <= 64 && p.R % CW_KS == 0; }
-// (64 x 64 channels, image lines of up to 64 pixels: conv_wgrad's drop-in built on transposing LDS reads)
+// (64 x 64 channels, image lines of up to 64 pixels: conv_wgrad's drop-in built on transposing LDS reads.  Not lines of 8
+// pixels, padded to 16 there, where conv_wgrad takes them and the contraction is long enough for its chunks of 512 rows to
+// occupy half of the chip: per pass of 4 RK4 steps, 8 x 8, 64 channels, transposing / conv_wgrad, us: 128 images
+// (32768 rows in the contraction) 1277 / 1301, 256 images 1479 / 1430, 512 1816 / 1796, 2048 4290 / 4233; parabolic block
+// 64 images 2716 / 2750, 256 images 3108 / 2992.  Lines of 24 pixels, 682 images of 8 lines: 3750 / 4052)
 static bool conv_wgrad_tr64_applies(const Plan& p, const Layer& y) {
-  return p.conv && !p.fused && !p.cw_blocks && y.Npad == 64 && y.Kpad == 64 && p.Wd <= 64;
+  return p.conv && !p.fused && !p.cw_blocks && y.Npad == 64 && y.Kpad == 64 && p.Wd <= 64 &&
+         !(p.Wd == 8 && conv_wgrad_lines_applies(p) && p.s * p.R >= 65536);
 }
 static bool conv_wgrad_applies(const Plan& p) {
   if (conv_wgrad_lines_applies(p)) return true;

@@ -223,7 +223,7 @@ def test_conv_weight_gradient_64_channels_transposing_reads_bf16():
 
 @pytest.mark.parametrize("C,H,W,B,low", [(64, 3, 1, 5, "f16"), (24, 1, 15, 3, "f16"), (64, 14, 14, 2, "f16"), (20, 5, 17, 2, "bf16"),
                                          (24, 28, 28, 2, "f16"), (64, 2, 31, 9, "f16"), (8, 7, 33, 2, "f16"), (64, 3, 63, 2, "f16"),
-                                         (32, 8, 8, 3, "f16")])
+                                         (32, 8, 8, 3, "f16"), (64, 8, 8, 342, "bf16")])
 def test_conv_weight_gradient_ragged_image_lines(C, H, W, B, low):
     # image lines padded to 16, 32 or 64 pixels in LDS (one pixel, one less and one more than a padded line, odd pixels
     # counts per stage), against the generic contraction of the same rounded operands: fp32 summation order only

@@ -65,6 +65,19 @@ def test_parameter_count_and_workspace_sizes(name):
             > rb.rampde_workspace_bytes(vel, cfg.B, cfg.N, tab, p1, True))
 
 
+@pytest.mark.parametrize("C", [64, 20])
+def test_weight_gradient_of_eight_pixel_lines_pads_only_short_contractions(C):
+    # 256 images of 8 x 8: the default plan is that of wgrad_tile = 64 (conv_wgrad), not the one that pads lines to 16
+    # pixels, which stays for shorter contractions; the two cut the contraction differently, so their private gradient
+    # copies tell them apart
+    cfg = wl.CONFIGS["cfg4"].with_(C=C, H=8, W=8)
+    vel, tab, pol = _descr(cfg)
+    blocks = rb.Policy(low=cfg.low, wgrad_tile=64)
+    same = [rb.rampde_workspace_bytes(vel, B, cfg.N, tab, pol, True) == rb.rampde_workspace_bytes(vel, B, cfg.N, tab, blocks, True)
+            for B in (128, 256, 1024)]
+    assert same == [False, True, True]
+
+
 def test_checkpoint_store_is_half_of_fp32():
     # only the low-precision states are kept (paper Sec. 3): (N+1) * n * 2 bytes
     for cfg in wl.CONFIGS.values():
