@@ -435,16 +435,24 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       p.ldk = (int64_t)p.s * p.Rp;
       size_t per_set = 2 * (size_t)p.dpad * p.ldk * 2;
       for (int l = 0; l + 1 < p.L; ++l) per_set += 2 * (size_t)p.layers[l].Npad * p.ldk * 2;
-      const int64_t fit = (int64_t)((size_t(4) << 30) / per_set);  // buffer sets in about 4 GiB
+      // buffer sets in about 4 GiB, or in 1 GiB where a plan with one launch per step would keep two: register-resident
+      // networks under overflow detection, flows.  64 -> 256 -> 256 -> 64, 4096 rows, f16, 32 RK4 steps under detection,
+      // us per pass with groups of 1 / 2 / 4 / 8 / 16 / 32 steps (37 MB each): 2397 / 1715 / 1363 / 1353 / 1279 / 1218
+      const bool one_gib = p.resident && (p.cnf || (pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE));
+      const int64_t fit = (int64_t)((size_t(one_gib ? 1 : 4) << 30) / per_set);
       {
-        // Without overflow detection nothing is decided between steps: a launch of the adjoint
-        // kernel then runs a group of steps (the adjoint stays in registers) and the parameter
-        // gradients of the whole group are one contraction.  Every step of a group needs its own
-        // set of buffers; groups are as long as about 4 GiB of sets allow.
+        // Without overflow detection nothing is decided between steps, and the register-resident kernels
+        // decide within a launch: a launch of the adjoint kernel then runs a group of steps (the adjoint
+        // stays in registers) and the parameter gradients of the whole group are one contraction.  Every
+        // step of a group needs its own set of buffers; groups are as long as the sets may take memory.
         const int64_t want_group = (pol && pol->step_group > 0) ? pol->step_group : kMaxWgradSteps;
         const int64_t cap = std::min<int64_t>(want_group, std::min<int64_t>(fit, kMaxWgradSteps));
         if (pol && (p.resident || (resolve_scaling(pol) == RAMPDE_SCALE_NONE && cap >= 2)) && !p.wide) {
           p.step_group = (int)std::max<int64_t>(1, std::min<int64_t>(N, cap));
+          if (one_gib) {  // (as many launches, of equal length)
+            const int launches = (N + p.step_group - 1) / p.step_group;
+            p.step_group = (N + launches - 1) / launches;
+          }
           p.nsets = p.step_group;
           p.overlap_wgrad = false;
         }

@@ -78,6 +78,22 @@ def test_weight_gradient_of_eight_pixel_lines_pads_only_short_contractions(C):
     assert same == [False, True, True]
 
 
+@pytest.mark.parametrize("base,kw", [
+    ("cfg2", dict(low="f16", B=4096, N=64)),
+    ("cfg2", dict(low="f16", B=4096, N=64, widths=(128, 512, 128))),
+    ("cnf", dict(B=4000, N=64)),
+    ("cnf", dict(B=4000, N=64, low="bf16")),
+])
+def test_workspace_of_grouped_steps_under_detection_and_of_flows(base, kw):
+    # include/rampde.h: about 1 GiB of per-step buffers (and what else a pass keeps); fewer with a smaller step_group
+    cfg = wl.CONFIGS[base].with_(**kw)
+    vel, tab, pol = _descr(cfg)
+    size = rb.rampde_workspace_bytes(vel, cfg.B, cfg.N, tab, pol, True)
+    assert size <= (1 << 30) + (200 << 20)
+    small = rb.rampde_workspace_bytes(vel, cfg.B, cfg.N, tab, rb.Policy(low=cfg.low, step_group=2), True)
+    assert small <= 200 << 20
+
+
 def test_checkpoint_store_is_half_of_fp32():
     # only the low-precision states are kept (paper Sec. 3): (N+1) * n * 2 bytes
     for cfg in wl.CONFIGS.values():
