@@ -190,8 +190,10 @@ def _gain_case(base, **kw):
 MULTI_WG = [
     # the 8-wavefront adjoint kernel (wide network), several row tiles and a ragged tail
     ("cfg3", dict(name="retry512", B=300, N=6, t1=0.09, gain=256.0, scaling="dynamic")),
-    # the 4-wavefront adjoint kernel with the parameter gradients on the helper stream
+    # the register-resident kernels (all steps in one launch)
     ("cfg2", dict(name="retry256", B=300, N=6, t1=0.09, gain=256.0, scaling="dynamic")),
+    # the 4-wavefront adjoint kernel with the parameter gradients on the helper stream (stages that are not a chain)
+    ("cfg2", dict(name="retry256k", B=300, N=6, t1=0.09, gain=256.0, scaling="dynamic", tableau="kutta3")),
     # the convolution path (per-layer kernels)
     ("cfg4", dict(name="retryconv", B=2, N=4, C=8, H=8, W=16, t1=0.02, gain=256.0, scaling="dynamic")),
 ]
@@ -250,6 +252,78 @@ def test_unscaled_safe_many_workgroups(base, kw):
     gpu = par.run_gpu(cfg, theta, y0, target)
     assert gpu["status"] == 1 and gpu["failed_step"] == emu["failed_step"]
     assert np.all(np.isinf(gpu["grad_theta"])) and np.all(np.isinf(gpu["grad_y0"]))
+
+
+# Kernels that run several adjoint steps in a launch and take the accept / grow decisions themselves
+GROUPED = [
+    ("cfg2", dict(name="retry256", B=300, N=6, t1=0.09, gain=256.0, scaling="dynamic")),
+    ("cfg2", dict(name="retry128", B=300, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(30, 100, 100, 100, 30))),
+    # one hidden layer, activations from memory and from LDS; flows, whose trace row adds sums of every accepted step
+    ("cfg2", dict(name="retry1h", B=300, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(64, 600, 64))),
+    ("cfg2", dict(name="retry1h2", B=40, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(128, 512, 128))),
+    ("cnf", dict(name="retrycnf", B=100, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(20, 200, 20))),
+    ("cnf", dict(name="retrycnfw", B=40, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(15, 600, 15))),
+]
+
+
+def _compare_amplifying(cfg, theta, y0, target, gpu, emu, flags=None, want_grad_t=False):
+    """Every tensor within the fp64 tolerance or four times the oracle's own response to weights that are perturbed by
+    3e-7 relative (a couple of fp32 roundings; the largest of three draws), where that is more: a network whose last layer
+    has gain 256 turns one flipped 16-bit rounding into up to 5 % of the early gradients."""
+    rng = np.random.default_rng(7)
+    errs, sens = {}, {}
+    outs = {"yN": lambda r: r["yN"], "grad_y0": lambda r: r["grad_y0"], "grad_theta": lambda r: r["grad_theta"]}
+    if want_grad_t:
+        outs["grad_t"] = lambda r: r["grad_t"]
+    for name, sl in par.layer_slices(cfg):
+        outs["grad_" + name] = lambda r, sl=sl: r["grad_theta"][sl]
+    alts = [par.run_oracle(cfg, (theta * (1.0 + 3e-7 * rng.standard_normal(theta.shape))).astype(np.float32), y0, target, "emul",
+                           flags=flags) for _ in range(3)]
+    for k, get in outs.items():
+        errs[k] = par.rel_err(get(gpu), get(emu))
+        sens[k] = max(par.rel_err(get(a), get(emu)) for a in alts)
+    print("  vs emul / oracle's response:", {k: f"{errs[k]:.1e} / {sens[k]:.1e}" for k in errs}, flush=True)
+    bad = {k: (errs[k], sens[k]) for k in errs if not errs[k] <= max(par.TOL_F64[cfg.low], 4.0 * sens[k])}
+    assert not bad, bad
+
+
+@pytest.mark.parametrize("base,kw", GROUPED, ids=[k["name"] for _, k in GROUPED])
+@pytest.mark.parametrize("step_group,want_grad_t", [(0, False), (1, False), (2, False), (4, False), (2, True), (0, True)])
+def test_retry_inside_and_across_groups_of_steps(base, kw, step_group, want_grad_t):
+    # a rejected step ends its launch; the pass goes on from the adjoint that this launch wrote (its own buffer, or
+    # dL/dy_0 if it was the last group), and what the rejected run added to dL/dt is replaced
+    cfg, theta, y0, target = _gain_case(base, **dict(kw))
+    print(f"[case] retry in groups of {step_group}: {cfg.name} grad_t={want_grad_t}", flush=True)
+    emu = par.run_oracle(cfg, theta, y0, target, "emul")
+    hist = emu["scale_hist"]
+    assert emu["status"] == "ok" and emu["retries"] >= 3
+    assert np.sum(hist[:-1] < hist[1:]) >= 3, "the scale must drop at several steps"
+    gpu = par.run_gpu(cfg, theta, y0, target, step_group=step_group, want_grad_t=want_grad_t)
+    assert gpu["status"] == 0 and gpu["retries"] == emu["retries"]
+    np.testing.assert_array_equal(gpu["scale_hist"].astype(np.float64), hist)
+    _compare_amplifying(cfg, theta, y0, target, gpu, emu, want_grad_t=want_grad_t)
+
+
+@pytest.mark.parametrize("base,kw", GROUPED[1:], ids=[k["name"] for _, k in GROUPED[1:]])
+def test_failure_overflow_and_scale_groups_with_grouped_steps(base, kw):
+    cfg, theta, y0, target = _gain_case(base, **dict(kw))
+    print(f"[case] failure, unscaled-safe overflow, scale groups: {cfg.name}", flush=True)
+    emu = par.run_oracle(cfg, theta, y0, target, "emul", k_max=1)
+    gpu = par.run_gpu(cfg, theta, y0, target, k_max=1, expect_error=True, step_group=4)
+    assert emu["status"] == "scale_failed" and gpu.get("error") == rb.ESCALE
+    assert gpu["info"].failed_step == emu["failed_step"] and gpu["info"].status == 2
+    big = cfg.with_(scaling="none_safe", grad_scale=1e3 if cfg.loss == "half_sse" else 1e3 * cfg.B * cfg.d)
+    emu = par.run_oracle(big, theta, y0, target, "emul")
+    gpu = par.run_gpu(big, theta, y0, target, step_group=4)
+    assert emu["status"] == "overflow_inf" and gpu["status"] == 1 and gpu["failed_step"] == emu["failed_step"]
+    assert np.all(np.isposinf(gpu["grad_y0"])) and np.all(np.isposinf(gpu["grad_theta"]))
+    # two scale groups, each with its own retries (G times the state width is a multiple of 8)
+    G = (cfg.B // 2 + 8) // 8 * 8
+    emu = par.run_oracle(cfg, theta, y0, target, "emul", flags={"scale_group": G})
+    gpu = par.run_gpu(cfg, theta, y0, target, scale_group=G, step_group=4)
+    assert emu["status"] == "ok" and gpu["status"] == 0 and gpu["retries"] == emu["retries"] >= 4
+    np.testing.assert_array_equal(gpu["scale_hist"].astype(np.float64), emu["scale_hist"])
+    _compare_amplifying(cfg, theta, y0, target, gpu, emu, flags={"scale_group": G})
 
 
 @PATHS
