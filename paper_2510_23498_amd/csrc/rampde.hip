@@ -351,8 +351,10 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       return (size_t)p.nparam * 4 + tm * (p.dpad + 8) * 2 + 2 * tm * p.ldp * 2 +
              (with_k ? (size_t)p.s * tm * (p.dpad + 8) * 2 : 0);
     };
-    // (the adjoint kernel carries more per-tile state in registers: it spills beyond 32-row tiles)
-    int mt = is_backward ? 2 : 4;
+    // (the adjoint kernel carries more per-tile state in registers: it spills beyond 32-row tiles.  At a 256-wide state
+    // the slopes of 64 rows do not fit in LDS beside the tiles: 200 -> 256 -> 256 -> 200, 6 RK4 steps forward, us with
+    // 32 / 64 rows: B = 9000 290 / 359, B = 16384 298 / 397, B = 30000 569 / 764)
+    int mt = is_backward || p.dpad == 256 ? 2 : 4;
     const int want_rows = pol ? pol->row_tile : 0;
     if (want_rows == 16 || want_rows == 32 || (want_rows == 64 && !is_backward)) mt = want_rows / 16;
     // The smallest tile whose workgroups all run at once (a tile's time grows by 1.2 per doubling of its rows --
