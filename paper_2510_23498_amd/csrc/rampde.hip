@@ -264,7 +264,10 @@ static int resident_width(const rampde_velocity* vel, const rampde_tableau* tab,
 // ... with which the kernels of shallow.hpp take it: one hidden layer, up to 1024 wide; the normalising flow with up to
 // 64 state columns, plain networks wider than what resident.hpp takes.  Forward and backward of 16 RK4 steps, ms before /
 // with these: 128 -> 512 -> 128, 4096 rows, bf16 1.02 / 0.80, f16 1.48 / 0.85; 64 -> 1024 -> 64 1.42 / 1.01, 1.93 / 1.08.
-static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol) {
+// Not a forward pass with 65 to 128 state columns and up to 256 hidden units whose batch fills at least 85 % of the rounds
+// of the streaming kernels' 32- or 64-row tiles: 128 -> 256 -> 128, 8 RK4 steps, bf16, us with those / with these: B = 8192
+// 109 / 113, B = 12000 (73 % of a round) 197 / 162, B = 16384 179 / 209, B = 20000 (61 %) 330 / 257, B = 60000 653 / 731.
+static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol, int64_t B, int is_backward) {
   if (!vel || (vel->kind != RAMPDE_VEL_MLP && vel->kind != RAMPDE_VEL_CNF) || !vel->widths || vel->n_layers != 2) return 0;
   if ((pol && (pol->flags & RAMPDE_PER_LAYER_KERNELS)) || !chained_stages(tab)) return 0;
   const bool flow = vel->kind == RAMPDE_VEL_CNF;
@@ -273,6 +276,8 @@ static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, 
   const int hp = h <= 128 ? 128 : h <= 256 ? 256 : h <= 512 ? 512 : h <= 1024 ? 1024 : 0;
   if (flow) return d <= 64 ? hp : 0;
   if (d <= 64) return hp > 256 ? hp : 0;
+  const int64_t cus = device_compute_units(), round = (B > 32 * cus ? 64 : 32) * cus, rounds = (B + round - 1) / round;
+  if (!is_backward && hp <= 256 && B > 16 * cus && 20 * B >= 17 * round * rounds) return 0;
   return d <= 128 && hp >= 256 && hp <= 512 ? hp : 0;
 }
 
@@ -284,7 +289,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
   const bool allow_fused = fused_candidate(vel, pol);
   int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
   if (rhp == 0 && allow_resident && allow_wide) {  // (the time-grid gradient is formed by the other kernels)
-    rhp = shallow_width(vel, tab, pol);
+    rhp = shallow_width(vel, tab, pol, B, is_backward);
     p.shallow = rhp != 0;
   }
   if (!build_layers(vel, p, rhp ? rhp : allow_fused ? 256 : kPad)) return p;
