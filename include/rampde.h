@@ -133,16 +133,23 @@ typedef struct {
                              the memory-side cache) */
   int row_tile;           /* dense networks: batch rows per workgroup of the row-tile kernels: 16, 32 or 64.
                              64 selects the kernels built for 512-wide networks (state width 128) where
-                             they apply; values that do not apply fall back to the automatic choice  */
+                             they apply.  The kernels for narrow networks (see step_group) have tiles of 16 rows, at
+                             hidden widths above 128 also of 32, those for one hidden layer of 16: another value that
+                             applies selects the kernels that have it; values that do not apply fall back to the
+                             automatic choice (flows have tiles of 16 rows only) */
   int wgrad_tile;         /* dense networks, row-tile kernels, one launch per adjoint step: which kernel forms the
                              parameter gradients.  128: workgroups with a 128 x 128 block of dW_l; 256: wavefronts
                              with a 128 x 128 block each, operands streamed through LDS by direct loads (built for
                              long batch contractions).  0: chosen by the contraction length (stages x batch rows).
-                             Convolutions with 64 channels, or PARABOLIC with channel counts in multiples of 128, and W in {16, 32, 64}: 64 keeps the
-                             convolution weight-gradient kernel with 64 x 64 channel blocks per workgroup instead of
-                             the one with 128 x 128 x 3-tap blocks built on transposing LDS reads (the default there),
-                             and the convolution kernel that fetches an input slab per tap instead of the one that
-                             stages the input by image lines */
+                             Does not apply to narrow networks, networks with one hidden layer and flows that run
+                             groups of steps per launch (see step_group).
+                             Convolutions with at most 64 channels and W up to 64, or PARABOLIC with channel counts in
+                             multiples of 128 and W in {16, 32, 64}: 64 keeps the convolution weight-gradient kernel
+                             with 64 x 64 channel blocks per workgroup (lines that are a multiple of 8 pixels, else
+                             the generic contraction) instead of the ones built on transposing LDS reads (the
+                             default there but for long contractions of 8-pixel lines), and for PARABOLIC the
+                             convolution kernel that fetches an input slab per tap instead of the one that stages
+                             the input by image lines */
   /* Scope of the adjoint scale within a batch (Alg. 2 is stated for one sample).  0: one scale S for the
    * whole batch (the default).  G > 0: every G consecutive samples (the last group: the remainder) share a
    * scale of their own -- initial value from the group's own max-norm, own overflow retries, own growth --

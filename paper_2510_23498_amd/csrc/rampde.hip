@@ -235,6 +235,8 @@ static int device_compute_units() {
   return cus;
 }
 
+constexpr size_t kRowTileLds = 159 * 1024;  // 160 KB per compute unit minus the row-tile kernels' small static arrays
+
 static bool fused_candidate(const rampde_velocity* vel, const rampde_policy* pol) {
   if (!vel || vel->kind != RAMPDE_VEL_MLP || (pol && (pol->flags & RAMPDE_PER_LAYER_KERNELS))) return false;
   if (vel->n_layers < 1 || vel->n_layers > kMaxLayers || !vel->widths) return false;
@@ -281,6 +283,14 @@ static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, 
   return d <= 128 && hp >= 256 && hp <= 512 ? hp : 0;
 }
 
+// Whether they have the row tile that the policy asks for: 16 rows, resident.hpp at hidden width 256 also 32.  A tile that
+// only the streaming kernels have selects those (32 rows; 64 forward, and in wide.hpp); one that none has is no choice.
+static bool resident_takes_rows(const rampde_velocity* vel, const rampde_tableau* tab, int want_rows, int rhp, bool shallow, int is_backward) {
+  if (vel->kind != RAMPDE_VEL_MLP || (want_rows != 32 && want_rows != 64)) return true;
+  if (want_rows == 32) return !shallow && rhp == 256 && resident_lds_bytes(rhp, vel->n_layers, tab->s, 2, is_backward) <= kRowTileLds;
+  return is_backward && !(vel->widths[0] == 128 && rhp == 512);
+}
+
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
 // gradient runs on the other row-tile kernels)
 static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab,
@@ -291,6 +301,10 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
   if (rhp == 0 && allow_resident && allow_wide) {  // (the time-grid gradient is formed by the other kernels)
     rhp = shallow_width(vel, tab, pol, B, is_backward);
     p.shallow = rhp != 0;
+  }
+  if (rhp && pol && !resident_takes_rows(vel, tab, pol->row_tile, rhp, p.shallow, is_backward)) {
+    rhp = 0;
+    p.shallow = false;
   }
   if (!build_layers(vel, p, rhp ? rhp : allow_fused ? 256 : kPad)) return p;
   if (B < 1 || N < 1 || !tab || tab->s < 1 || tab->s > kMaxStages) return p;
@@ -320,7 +334,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     const int64_t cus = device_compute_units();
     const int want_rows = pol ? pol->row_tile : 0;
     int mt = (rhp == 256 && !p.shallow && (want_rows == 32 || (want_rows == 0 && p.R > 16 * cus))) ? 2 : 1;
-    const size_t lds_limit = 159 * 1024;
+    const size_t lds_limit = kRowTileLds;
     if (mt == 2 && resident_lds_bytes(rhp, p.L, p.s, mt, is_backward) > lds_limit) mt = 1;
     const size_t lds = p.shallow ? 0 : resident_lds_bytes(rhp, p.L, p.s, mt, is_backward);
     const int64_t tiles = (p.R + 16 * mt - 1) / (16 * mt);
@@ -350,7 +364,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     p.wt_off = nparam;
     p.nparam = nparam + p.layers[0].Npad;
     p.ldp = maxw + 8;
-    const size_t lds_limit = 159 * 1024;  // 160 KB per compute unit minus the kernels' small static arrays
+    const size_t lds_limit = kRowTileLds;
     auto lds_need = [&](int mt, bool with_k) {
       const size_t tm = 16 * (size_t)mt;
       return (size_t)p.nparam * 4 + tm * (p.dpad + 8) * 2 + 2 * tm * p.ldp * 2 +

@@ -509,6 +509,14 @@ def test_one_hidden_layer_kernels(d, H, B, low, scaling):
     _both(cfg, bias_std=0.1, scaling=scaling)
 
 
+@pytest.mark.parametrize("widths,B,row_tile", [((128, 512, 128), 70, 64), ((128, 512, 128), 70, 32), ((64, 256, 256, 64), 70, 64),
+                                               ((64, 200, 200, 64), 40, 32), ((20, 60, 20), 33, 32), ((128, 256, 128), 6964, 0)])
+def test_row_tiles_of_networks_with_kernels_of_their_own(widths, B, row_tile):
+    # a row tile that only the streaming kernels have, and a batch that fills their round (forward)
+    cfg = wl.CONFIGS["cfg1"].with_(name=f"rows{row_tile}_" + "_".join(map(str, widths)), B=B, N=2, widths=widths, low="f16", loss="mse")
+    _both(cfg, bias_std=0.1, scaling="dynamic", row_tile=row_tile)
+
+
 @pytest.mark.parametrize("scaling", ["none", "dynamic"])
 def test_time_grid_gradient_of_one_hidden_layer_with_row_tile_64(scaling):
     # dL/dt and everything else come from different kernels here; the workspace that the query names holds either

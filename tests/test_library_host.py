@@ -94,6 +94,34 @@ def test_workspace_of_grouped_steps_under_detection_and_of_flows(base, kw):
     assert small <= 200 << 20
 
 
+def test_row_tile_that_only_the_streaming_kernels_have_selects_them():
+    # what tells the plans apart: the 64-row kernels keep sum_j b_j k_j of every row in the forward workspace, the
+    # streaming kernels their slopes, the kernels for narrow networks and one hidden layer neither
+    cfg = wl.CONFIGS["cfg2"].with_(B=4096, low="f16")
+
+    def forward_bytes(widths, row_tile):
+        vel, tab, _ = _descr(cfg.with_(widths=widths))
+        return rb.rampde_workspace_bytes(vel, cfg.B, cfg.N, tab, rb.Policy(low="f16", row_tile=row_tile), False)
+
+    wide, slopes = cfg.B * 128 * 4, 4 * cfg.B * 64 * 2
+    assert forward_bytes((128, 512, 128), 64) >= forward_bytes((128, 512, 128), 0) + wide
+    for widths, tiles in (((64, 256, 256, 64), (32,)), ((64, 100, 100, 64), ()), ((64, 600, 64), ())):
+        auto = forward_bytes(widths, 0)
+        assert forward_bytes(widths, 16) == auto
+        for rows in (32, 64):
+            got = forward_bytes(widths, rows)
+            assert (got == auto) if rows in tiles else (got > auto + slopes // 2)
+
+
+def test_forward_rule_of_one_hidden_layer_at_the_edges_of_a_round():
+    # 128 -> 256 -> 128: streaming kernels (slopes in the workspace) where their tiles fill at least 85 % of the rounds
+    cfg = wl.CONFIGS["cfg2"].with_(widths=(128, 256, 128))
+    vel, tab, pol = _descr(cfg)
+    for B, streaming in ((4096, False), (6963, False), (6964, True), (8192, True), (12000, False), (16384, True), (20000, False),
+                         (60000, True)):
+        assert (rb.rampde_workspace_bytes(vel, B, cfg.N, tab, pol, False) > 4 * B * 128 * 2) == streaming, B
+
+
 def test_checkpoint_store_is_half_of_fp32():
     # only the low-precision states are kept (paper Sec. 3): (N+1) * n * 2 bytes
     for cfg in wl.CONFIGS.values():
