@@ -342,7 +342,9 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     const bool detects = is_backward && pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE;
     // (and a lane's part of a gradient operand has a 32-bit byte offset)
     const bool offsets_fit = !is_backward || (size_t)rhp * p.s * ((p.R + 63) / 64 * 64) * 2 < (size_t(1) << 32);
-    if (lds > lds_limit || !offsets_fit || (detects && tiles > cus * (p.shallow ? 1 : resident_per_cu(rhp, lds))))
+    // (and with the time-grid gradient every workgroup of a launch writes a slot; the 32-row tiles below need half as many)
+    const bool slots_fit = allow_wide || !is_backward || (size_t)tiles <= kTimeSlotPairs;
+    if (lds > lds_limit || !offsets_fit || !slots_fit || (detects && tiles > cus * (p.shallow ? 1 : resident_per_cu(rhp, lds))))
       return make_plan(vel, B, N, tab, pol, is_backward, allow_wide, false);
     p.resident = rhp;
     p.fused = true;

@@ -8,6 +8,7 @@ the retry count are compared exactly: they are powers of two and integers.
 """
 import numpy as np
 import pytest
+import torch
 
 from paper_2510_23498_amd import workloads as wl
 
@@ -526,3 +527,28 @@ def test_time_grid_gradient_of_one_hidden_layer_with_row_tile_64(scaling):
     emu = par.run_oracle(cfg, theta, y0, target, "emul", scaling=scaling)
     par.compare(cfg, gpu, emu, par.TOL_EMUL, "emulation oracle", tol_max=par.TOL_EMUL_MAX[cfg.low])
     assert par.rel_err(gpu["grad_t"], emu["grad_t"]) <= par.TOL_EMUL
+
+
+def test_time_grid_gradient_of_more_row_tiles_than_slots():
+    # a launch of the narrow-network kernels writes a slot per 16 rows; past 2^19 of them the 32-row kernels form dL/dt
+    from paper_2510_23498_amd import binding as rb
+    rows = 16 * (1 << 19) + 16
+    cfg = wl.CONFIGS["cfg1"].with_(name="slots", B=rows, N=1, tableau="euler", low="bf16", scaling="none")
+    vel, tab, pol = par.gpu_descriptors(cfg)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    theta = torch.randn(rb.rampde_num_params(vel), generator=gen, device="cuda") * 0.3
+    y0 = torch.randn((rows, 2), generator=gen, device="cuda")
+    gyN = torch.rand((rows, 2), generator=gen, device="cuda") * 1e-6
+
+    def backward(sl):
+        y, g = y0[sl].contiguous(), gyN[sl].contiguous()
+        _, ck = rb.rampde_odeint_fwd(vel, theta, y, cfg.tgrid(), tab, pol)
+        return rb.rampde_odeint_bwd_tgrid(vel, theta, cfg.tgrid(), tab, pol, ck, g)
+
+    whole = backward(slice(0, rows))
+    halves = [backward(slice(0, rows // 2)), backward(slice(rows // 2, rows))]
+    # (fp32 sums of a few thousand terms per slot and of the slots, in another order: 1e-4 of sums without cancellation)
+    for i, join in ((0, lambda a, b: torch.cat([a, b])), (1, torch.add), (2, torch.add)):
+        ref = join(halves[0][i], halves[1][i])
+        assert par.rel_err(whole[i].cpu().numpy(), ref.cpu().numpy()) <= par.TOL_EMUL
