@@ -30,6 +30,13 @@
  *   - Calls that share a workspace must not overlap; distinct workspaces on distinct streams may.
  *     The host side is not thread safe: calls from several host threads must be serialised by
  *     the caller.
+ *   - Under overflow detection the backward kernels of narrow networks, networks with one hidden
+ *     layer and flows (policy.step_group) exchange the adjoint scale between the workgroups of a
+ *     launch, at most as many as the device runs at once.  Where other work (another stream or
+ *     process, a stream with a CU mask) keeps some of them from running for 2 ms, the launch gives
+ *     up and the pass is redone on kernels with one launch per step or layer, on the same
+ *     workspace: same results within rounding, a few ms later, and decided anew by every call.
+ *     rampde_odeint_bwd in place (grad_y0 = grad_yN) takes those kernels from the start.
  *   - theta layout (flat fp32, also the layout of grad_theta):
  *       MLP  : for each layer l: W_l[out_l][in_l] row-major, then b_l[out_l];
  *              layer 1 has in_1 = d + 1 when time_input is set (time column LAST).
@@ -91,10 +98,9 @@ typedef enum {
 #define RAMPDE_NAIVE_STATE 8u       /* comparison baseline, not the paper's scheme: the state y and the adjoint a are
                                      themselves kept in low precision (rounded after every update), i.e. without
                                      the fp32 accumulators of Algorithms 1-2 (the "naive" rows of the paper's Table 5) */
-#define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale within a launch (narrow dense
-                                     networks under overflow detection) give up at the first word that is not there
-                                     yet, as they do when other work keeps them from running at the same time; the
-                                     pass is then redone with one launch per step.  Same results */
+#define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale within a launch (see the notes on
+                                     concurrency above) give up at the first exchange, and the pass is redone with
+                                     one launch per step.  Same results */
 
 /* Explicit Butcher tableau, host memory, fp64.  A is s*s row-major; only the strictly
  * lower triangle may be non-zero (checked).  Consistency (sum b = 1, ...) is not checked. */

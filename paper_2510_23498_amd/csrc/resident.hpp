@@ -26,7 +26,9 @@
 //
 // The waits need the workgroups of a launch to run at the same time; the host launches no more of them than the device
 // holds.  If others occupy the device (another stream's kernels), a wait ends after kWaitTicks, the launch raises
-// Ctl.stalled, writes no result, and the host redoes the pass with one launch per step.
+// Ctl.stalled, writes no result, and the host redoes the pass with one launch per step.  A word that is on its way comes
+// within a step (at most about 0.1 ms); kernels that hold compute units for longer than 2 ms cost less as a redone pass
+// (a few ms) than as a wait for their end.
 #pragma once
 #include "fused.hpp"
 
@@ -37,11 +39,11 @@ struct ResidentArgs {
   // [steps of the pass][workgroups] words {tag : 32, payload : 32}; payload = bits of max|a| of the tile after the
   // step, top bit: a value of the step's cotangent chain was not finite; tag = the attempt number (0: not posted)
   unsigned long long* slots;
-  unsigned long long wait_ticks;  // how long a workgroup waits for a word
+  unsigned long long wait_ticks;  // how long a workgroup waits for a word; 0: it gives up without looking
 };
 
 constexpr int kResidentStages = 4;
-constexpr unsigned long long kWaitTicks = 20ull * 1000 * 1000;  // of the 100 MHz counter: 0.2 s
+constexpr unsigned long long kWaitTicks = 200ull * 1000;  // of the 100 MHz counter: 2 ms
 
 template <int L, int HP>
 struct ResidentShape {
@@ -431,7 +433,7 @@ struct StepExchange {
     __shared__ int s_late[16];
     const unsigned long long* row = ra.slots + (size_t)step * gridDim.x;
     unsigned m = 0;
-    bool late = false;
+    bool late = ra.wait_ticks == 0;
     unsigned long long t0 = 0;
     for (int q = threadIdx.x; q < (int)gridDim.x; q += blockDim.x) {
       unsigned long long v = __hip_atomic_load(row + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

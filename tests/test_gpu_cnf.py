@@ -6,6 +6,7 @@ rounding-emulation oracle, 2e-2 (fp16) / 5e-2 (bf16) against fp64; scale history
 import numpy as np
 import pytest
 
+from paper_2510_23498_amd import binding as rb
 from paper_2510_23498_amd import workloads as wl
 
 import parity as par
@@ -66,8 +67,15 @@ def test_cnf_hidden_widths_of_every_kernel(H, B, low):
 
 
 def test_cnf_redone_pass_after_a_wait_that_ran_out():
+    # (the per-layer kernels redo the pass: their launches show it)
     cfg = BASE.with_(name="cnfwait", B=200, N=4, widths=(15, 200, 15))
     theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
-    gpu = par.run_gpu(cfg, theta, y0, target, flags=16)
     emu = par.run_oracle(cfg, theta, y0, target, "emul")
-    par.compare(cfg, gpu, emu, par.TOL_EMUL, "emulation oracle", tol_max=par.TOL_EMUL_MAX[cfg.low])
+    redone = {}
+    for flags in (0, rb.NO_WAITS):
+        rb.rampde_timing_enable(True)
+        gpu = par.run_gpu(cfg, theta, y0, target, flags=flags)
+        redone[flags] = rb.rampde_timing_read(rb.K_ADJOINT_UPDATE)[1]
+        rb.rampde_timing_enable(False)
+        par.compare(cfg, gpu, emu, par.TOL_EMUL, "emulation oracle", tol_max=par.TOL_EMUL_MAX[cfg.low])
+    assert redone == {0: 0, rb.NO_WAITS: cfg.N}

@@ -497,10 +497,19 @@ def test_register_resident_kernels(widths, B, low, scaling):
     _both(cfg, bias_std=0.1, scaling=scaling)
 
 
-def test_redone_pass_after_a_wait_that_ran_out():
-    # workgroups that do not wait for each other's words give the launch up: the step-by-step kernels redo the pass
-    cfg = wl.CONFIGS["cfg2"].with_(name="nowait", B=1000, N=4, low="f16")
-    _both(cfg, bias_std=0.1, scaling="dynamic", flags=16)
+@pytest.mark.parametrize("widths", [(64, 256, 256, 64), (64, 300, 64)])
+def test_redone_pass_after_a_wait_that_ran_out(widths):
+    # workgroups that do not wait for each other's words give the launch up: the step-by-step kernels redo the pass, seen
+    # as their launches (one per step) beside the one that gave up; gradients are added to the caller's once
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg2"].with_(name="nowait", B=1000, N=4, low="f16", widths=widths)
+    launches = {}
+    for flags in (0, rb.NO_WAITS):
+        rb.rampde_timing_enable(True)
+        _both(cfg, bias_std=0.1, scaling="dynamic", flags=flags)
+        launches[flags] = rb.rampde_timing_read(rb.K_FUSED_ADJOINT_STEP)[1]
+        rb.rampde_timing_enable(False)
+    assert launches == {0: 1, rb.NO_WAITS: 1 + cfg.N}
 
 
 @pytest.mark.parametrize("scaling", ["none", "dynamic"])
