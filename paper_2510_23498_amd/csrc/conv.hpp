@@ -59,8 +59,8 @@ inline ConvTileShape conv_tile_shape(int NA, int KC, int H, int Wd, int64_t imag
 // multiplication, the next tile's input is requested behind it and arrives during the epilogue.  Some cards run the two
 // together slower than one after the other.  64 channels, 32 x 32, 128 images, 16 RK4 steps, ms per training pass on four
 // cards (equal in a plain copy and a plain matrix product) with the kernel for powers of two that this one replaced /
-// everything in flight beside the multiplication and waited for ahead of the epilogue / as here: 12.8 / 12.5 / (12.1 with
-// counted stores), 13.6 / 13.9 / 13.0, 13.7 / 14.1 / 13.2, 14.2 / 14.8 / 13.7.
+// all loads in flight beside the multiplication / as here: 13.1 / 12.4 / 12.3, 13.6 / 13.9 / 13.0, 13.7 / 14.1 / 13.2,
+// 14.2 / 14.8 / 13.7.
 constexpr int kOutside = 0x40000000;  // (a byte offset past every window)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const uint16_t* p, int elements) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, elements * 2, 0x00020000);

@@ -123,7 +123,7 @@ struct Plan {
   size_t fm_stride = 0;             // distance between the sets of feature-group-major buffers
   int act_lds_off = 0;              // adjoint kernel: LDS offset (16-bit elements) of the activation copy, 0 = none
   int nsets = 2;                    // sets: step i uses set i % nsets
-  int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, no detection)
+  int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, or kernels that decide inside a launch)
   std::vector<size_t> ACTT, DELTAT;
 };
 

@@ -1,5 +1,6 @@
-// Row-tile kernels for dense networks with ONE hidden layer (up to 1024 wide, state width up to 64): the velocity of a
-// normalising flow with its exact trace row, dl/dt = -sum_h c_h (1 - a_h^2) (paper Sec. 6.1; TRACE), and plain networks.
+// Row-tile kernels for dense networks with ONE hidden layer: the velocity of a normalising flow with its exact trace row,
+// dl/dt = -sum_h c_h (1 - a_h^2) (paper Sec. 6.1; TRACE), up to 64 state columns and 1024 hidden units, and plain networks
+// (the same, or up to 128 state columns and 512 hidden units).
 //
 // Every wavefront owns a slice of the hidden layer and keeps the slices of both weight matrices in registers.  With the
 // weight fragment as first operand a lane ends a 16 x 16 tile with 4 consecutive hidden columns of one row; two tiles
@@ -12,8 +13,8 @@
 // plus the exchange; a tile per 16 rows, so 512 rows occupy 32 compute units.  At 1024 columns the forward and the
 // transposed slices (128 registers each) do not fit together: the recomputation and the cotangent chain of a step load
 // their own (2 x 256 KB from L2 per step).  The steps of a pass run in one launch as in resident.hpp, scale exchange
-// included.  Measured on flows of 63 features, width 1024, fp16, 16 RK4 steps of 512 rows: 745 us per pass; one
-// launch per layer, 900 launches, 6514 us.
+// included.  Measured on flows of 63 features, width 1024, fp16, 16 RK4 steps of 512 rows: 812 to 836 us per
+// pass; one launch per layer, 900 launches, 6456 to 6514 us.
 #pragma once
 #include "resident.hpp"
 
