@@ -128,13 +128,13 @@ typedef struct {
   unsigned flags;
   /* Launch-shape choices; 0 = let the library choose.  They change how the work is cut into
    * kernels, never what is computed (results agree to fp32 summation order). */
-  int step_group;         /* dense networks: cap on the adjoint steps that one launch runs.  Default: with a fixed
+  int step_group;         /* dense networks and flows: cap on the adjoint steps that one launch runs.  Default: with a fixed
                              scale (SCALE_NONE) as many as about 4 GiB of workspace hold, at most 64; with overflow
                              detection one step per launch, except for narrow networks (2 to 4 layers, state up to 64
                              wide, hidden layers up to 256 wide), networks with one hidden layer (state up to 64 wide
                              and hidden layer up to 1024, or 128 and 512) and flows (up to 64 state columns), which
-                             run as many as about 1 GiB holds, at most 64: a smaller value is the way to a smaller
-                             workspace there.  Where wgrad_tile = 256 applies this is the number of accepted steps
+                             run as many as about 1 GiB holds, at most 64.  A smaller value is the way to a smaller
+                             workspace.  Where wgrad_tile = 256 applies this is the number of accepted steps
                              whose parameter gradients one launch forms (default: as many as keep their buffers in
                              the memory-side cache) */
   int row_tile;           /* dense networks: batch rows per workgroup of the row-tile kernels: 16, 32 or 64.
@@ -182,9 +182,9 @@ int64_t rampde_num_params(const rampde_velocity *vel);
 /* Bytes of device workspace needed by fwd (is_backward = 0) or bwd (= 1). 0 if invalid.
  * The size depends on the policy: the backward pass of a dense network keeps the low-precision
  * stage inputs, activations and cotangents of all the steps that one launch runs (policy.step_group:
- * up to 64 steps, with a fixed scale at most about 4 GiB, with overflow detection and for flows at
- * most about 1 GiB, or of two steps where a launch runs one).  Pass the same policy to the query and
- * to the call. */
+ * up to 64 steps, with a fixed scale at most about 4 GiB, with overflow detection at most about
+ * 1 GiB, or of two steps where a launch runs one).  Pass the same policy to the query and to the
+ * call. */
 size_t rampde_workspace_bytes(const rampde_velocity *vel, int64_t B, int N,
                               const rampde_tableau *tab, const rampde_policy *pol,
                               int is_backward);

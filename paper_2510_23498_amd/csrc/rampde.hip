@@ -458,10 +458,11 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       p.ldk = (int64_t)p.s * p.Rp;
       size_t per_set = 2 * (size_t)p.dpad * p.ldk * 2;
       for (int l = 0; l + 1 < p.L; ++l) per_set += 2 * (size_t)p.layers[l].Npad * p.ldk * 2;
-      // buffer sets in about 4 GiB, or in 1 GiB where a plan with one launch per step would keep two: register-resident
-      // networks under overflow detection, flows.  64 -> 256 -> 256 -> 64, 4096 rows, f16, 32 RK4 steps under detection,
-      // us per pass with groups of 1 / 2 / 4 / 8 / 16 / 32 steps (37 MB each): 2397 / 1715 / 1363 / 1353 / 1279 / 1218
-      const bool one_gib = p.resident && (p.cnf || (pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE));
+      // buffer sets in about 4 GiB, or in 1 GiB under overflow detection (at most 75 MB a set there: its tiles run at
+      // once).  64 -> 256 -> 256 -> 64, 4096 rows, f16, 32 RK4 steps under detection, us per pass with groups of 1 / 2 /
+      // 4 / 8 / 16 / 32 steps (37 MB each): 2397 / 1715 / 1363 / 1353 / 1279 / 1218.  Without it a set can be larger and
+      // few steps fit: flow of 63 features, width 1024, 20000 rows, bf16, 8 RK4 steps, 1 / 4 GiB: 4293 / 3070
+      const bool one_gib = p.resident && pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE;
       const int64_t fit = (int64_t)((size_t(one_gib ? 1 : 4) << 30) / per_set);
       {
         // Without overflow detection nothing is decided between steps, and the register-resident kernels
