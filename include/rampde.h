@@ -210,7 +210,8 @@ int rampde_odeint_fwd(const rampde_velocity *vel, const float *theta, const floa
  * facility does not record it).  The first call on each device looks the array's address up (that
  * may load the library's code object): make it once before capturing.
  *   - RAMPDE_EWORKSPACE, with nothing launched, if rampde_workspace_bytes(vel, B, N, tab, pol, 0)
- *     exceeds RAMPDE_STATIC_SCRATCH_BYTES.  (Full-size dense workloads of the paper fit; the
+ *     exceeds RAMPDE_STATIC_SCRATCH_BYTES (where a choice of kernels, the caller's row_tile among
+ *     them, is what makes it exceed, the kernels that need less run instead).  (Full-size dense workloads of the paper fit; the
  *     128 x 64 x 32 x 32 convolutional one does not.)
  *   - All calls on one GPU share that GPU's array, on whatever stream: calls that overlap in time on
  *     one GPU race.  Nothing in the array has to survive from one call to the next, and nothing in it

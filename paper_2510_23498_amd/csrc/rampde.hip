@@ -269,7 +269,8 @@ static int resident_width(const rampde_velocity* vel, const rampde_tableau* tab,
 // Not a forward pass with 65 to 128 state columns and up to 256 hidden units whose batch fills at least 85 % of the rounds
 // of the streaming kernels' 32- or 64-row tiles: 128 -> 256 -> 128, 8 RK4 steps, bf16, us with those / with these: B = 8192
 // 109 / 113, B = 12000 (73 % of a round) 197 / 162, B = 16384 179 / 209, B = 20000 (61 %) 330 / 257, B = 60000 653 / 731.
-static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol, int64_t B, int is_backward) {
+static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol, int64_t B, int is_backward,
+                         bool small) {
   if (!vel || (vel->kind != RAMPDE_VEL_MLP && vel->kind != RAMPDE_VEL_CNF) || !vel->widths || vel->n_layers != 2) return 0;
   if ((pol && (pol->flags & RAMPDE_PER_LAYER_KERNELS)) || !chained_stages(tab)) return 0;
   const bool flow = vel->kind == RAMPDE_VEL_CNF;
@@ -279,7 +280,7 @@ static int shallow_width(const rampde_velocity* vel, const rampde_tableau* tab, 
   if (flow) return d <= 64 ? hp : 0;
   if (d <= 64) return hp > 256 ? hp : 0;
   const int64_t cus = device_compute_units(), round = (B > 32 * cus ? 64 : 32) * cus, rounds = (B + round - 1) / round;
-  if (!is_backward && hp <= 256 && B > 16 * cus && 20 * B >= 17 * round * rounds) return 0;
+  if (!small && !is_backward && hp <= 256 && B > 16 * cus && 20 * B >= 17 * round * rounds) return 0;
   return d <= 128 && hp >= 256 && hp <= 512 ? hp : 0;
 }
 
@@ -292,17 +293,19 @@ static bool resident_takes_rows(const rampde_velocity* vel, const rampde_tableau
 }
 
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
-// gradient runs on the other row-tile kernels)
+// gradient runs on the other row-tile kernels).  small: no choice of the streaming kernels, which keep slopes in the
+// workspace, where the register-resident ones can run
 static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab,
-                      const rampde_policy* pol, int is_backward, bool allow_wide = true, bool allow_resident = true) {
+                      const rampde_policy* pol, int is_backward, bool allow_wide = true, bool allow_resident = true,
+                      bool small = false) {
   Plan p;
   const bool allow_fused = fused_candidate(vel, pol);
   int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
   if (rhp == 0 && allow_resident && allow_wide) {  // (the time-grid gradient is formed by the other kernels)
-    rhp = shallow_width(vel, tab, pol, B, is_backward);
+    rhp = shallow_width(vel, tab, pol, B, is_backward, small);
     p.shallow = rhp != 0;
   }
-  if (rhp && pol && !resident_takes_rows(vel, tab, pol->row_tile, rhp, p.shallow, is_backward)) {
+  if (rhp && pol && !small && !resident_takes_rows(vel, tab, pol->row_tile, rhp, p.shallow, is_backward)) {
     rhp = 0;
     p.shallow = false;
   }
@@ -1941,17 +1944,16 @@ size_t rampde_workspace_bytes(const rampde_velocity* vel, int64_t B, int N, cons
   return total;
 }
 
-int rampde_odeint_fwd(const rampde_velocity* vel, const float* theta, const float* y0, int64_t B,
-                      const double* tgrid, int N, const rampde_tableau* tab, const rampde_policy* pol, void* ckpt,
-                      float* yN, void* workspace, size_t workspace_bytes, void* hip_stream) {
+static int forward_call(const rampde_velocity* vel, const float* theta, const float* y0, int64_t B, const double* tgrid, int N,
+                        const rampde_tableau* tab, const rampde_policy* pol, void* ckpt, float* yN, void* workspace,
+                        size_t workspace_bytes, hipStream_t st, bool small) {
   int rc = check_common(vel, tgrid, N, tab, pol);
   if (rc) return rc;
   if (!theta || !y0 || !ckpt || !yN || !workspace || B < 1) return RAMPDE_EINVAL;
   if (!aligned16(theta) || !aligned16(y0) || !aligned16(ckpt) || !aligned16(yN)) return RAMPDE_EINVAL;
-  Plan p = make_plan(vel, B, N, tab, pol, 0);
+  Plan p = make_plan(vel, B, N, tab, pol, 0, true, true, small);
   if (!p.ok) return RAMPDE_EINVAL;
   if (workspace_bytes < p.total || ((uintptr_t)workspace & 255)) return RAMPDE_EWORKSPACE;
-  hipStream_t st = (hipStream_t)hip_stream;
   const bool fused = p.fused;
   if (pol->low == RAMPDE_F16) {
     Runner<F16> r(p, workspace, st);
@@ -1963,6 +1965,12 @@ int rampde_odeint_fwd(const rampde_velocity* vel, const float* theta, const floa
   return r.forward(theta, y0, tgrid, N, tab, pol, (uint16_t*)ckpt, yN);
 }
 
+int rampde_odeint_fwd(const rampde_velocity* vel, const float* theta, const float* y0, int64_t B,
+                      const double* tgrid, int N, const rampde_tableau* tab, const rampde_policy* pol, void* ckpt,
+                      float* yN, void* workspace, size_t workspace_bytes, void* hip_stream) {
+  return forward_call(vel, theta, y0, B, tgrid, N, tab, pol, ckpt, yN, workspace, workspace_bytes, (hipStream_t)hip_stream, false);
+}
+
 int rampde_odeint_fwd_static(const rampde_velocity* vel, const float* theta, const float* y0, int64_t B,
                              const double* tgrid, int N, const rampde_tableau* tab, const rampde_policy* pol,
                              void* ckpt, float* yN, void* hip_stream) {
@@ -1970,16 +1978,20 @@ int rampde_odeint_fwd_static(const rampde_velocity* vel, const float* theta, con
   int rc = check_common(vel, tgrid, N, tab, pol);
   if (rc) return rc;
   if (B < 1) return RAMPDE_EINVAL;
-  const Plan p = make_plan(vel, B, N, tab, pol, 0);
-  if (!p.ok) return RAMPDE_EINVAL;
-  if (p.total > kStaticScratchBytes) return RAMPDE_EWORKSPACE;
+  bool small = false;
+  {
+    const Plan p = make_plan(vel, B, N, tab, pol, 0);
+    if (!p.ok) return RAMPDE_EINVAL;
+    small = p.total > kStaticScratchBytes;
+    if (small && make_plan(vel, B, N, tab, pol, 0, true, true, true).total > kStaticScratchBytes) return RAMPDE_EWORKSPACE;
+  }
   void* ws = nullptr;
   rc = static_scratch(&ws);
   if (rc) return rc;
   // the timing facility creates events: not in a call that promises to allocate nothing
   const bool timing = g_timing;
   g_timing = false;
-  rc = rampde_odeint_fwd(vel, theta, y0, B, tgrid, N, tab, pol, ckpt, yN, ws, kStaticScratchBytes, hip_stream);
+  rc = forward_call(vel, theta, y0, B, tgrid, N, tab, pol, ckpt, yN, ws, kStaticScratchBytes, (hipStream_t)hip_stream, small);
   g_timing = timing;
   return rc;
 }

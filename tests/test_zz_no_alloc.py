@@ -100,3 +100,21 @@ def test_problem_beyond_the_static_array_is_rejected_before_anything_runs():
     got, ref = _fwd_pair(wl.CONFIGS["cfg3"].with_(name="static_after_refusal", B=33, N=2))
     np.testing.assert_array_equal(got[0], ref[0])
     np.testing.assert_array_equal(got[1], ref[1])
+
+
+@pytest.mark.parametrize("widths,row_tile", [((128, 256, 128), 0), ((64, 200, 200, 64), 64)])
+def test_kernels_with_a_smaller_workspace_run_where_the_chosen_ones_do_not_fit(widths, row_tile):
+    # the streaming kernels (faster on this batch, or asked for) keep slopes in the workspace: more than the array holds
+    import torch
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg2"].with_(name="static_small", B=65536, N=2, widths=widths)
+    vel, tab, pol = par.gpu_descriptors(cfg, None, 16, 0, 0, row_tile)
+    assert rb.rampde_workspace_bytes(vel, cfg.B, cfg.N, tab, pol, False) > rb.STATIC_SCRATCH_BYTES
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    th, y0d = torch.from_numpy(theta).cuda(), torch.from_numpy(y0).cuda()
+    ck = torch.empty(vel.ckpt_shape(cfg.B, cfg.N), dtype=pol.torch_low, device="cuda")
+    yN = torch.empty_like(y0d)
+    rb.rampde_odeint_fwd_static(vel, th, y0d, cfg.tgrid(), tab, pol, ck, yN)
+    yN_w, ck_w = rb.rampde_odeint_fwd(vel, th, y0d, cfg.tgrid(), tab, pol)
+    assert par.rel_err(yN.cpu().numpy(), yN_w.cpu().numpy()) <= par.TOL_EMUL
+    assert par.rel_err(ck.float().cpu().numpy(), ck_w.float().cpu().numpy()) <= par.TOL_EMUL
