@@ -757,6 +757,77 @@ __global__ __launch_bounds__(64 * NW) void mlp_forward_fused(FusedArgs g) {
 }
 
 // ---------------------------------------------------------------------------------------
+// Stage recomputation of several adjoint steps in one launch: stage inputs and hidden activations of steps g.step,
+// g.step - 1, ... (one per ceil(R / TM) workgroups) from the stored states, into the steps' buffer sets.  The steps'
+// states are all known, so their recomputation is as parallel as steps x rows, where the cotangent chain of Algorithm 2
+// is serial in the steps: with it taken out of mlp_adjoint_step (skip_recompute), a batch of a few row tiles no longer
+// streams the weights once per tile and step, but once per TM rows of a full device.  For tableaux whose stages are a
+// chain (no slope but the last enters a stage input); the slope of the last stage is not formed.
+// Measured, 256 -> 1024 -> 1024 -> 256, f16, 1024 rows (64 tiles of 16 rows), RK4, groups of 8 steps: adjoint step 245 us
+// with the recomputation inside; pass of 256 steps 94.9 -> 72.3 ms.  128 -> 3 x 512 -> 128, bf16, 2000 rows, 32 steps in one
+// group: 5.87 -> 4.88 ms.
+template <class T, int MT, int NTL, int NW, int HP>
+__global__ __launch_bounds__(64 * NW) void mlp_recompute_fused(FusedArgs g) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  if (g.ctl->poison) return;
+  constexpr int TM = 16 * MT;
+  const TileLds<MT> lds((lds_u16*)smem, g);
+  const int tid = threadIdx.x;
+  TileEngine<T, MT, NTL, NW, HP> eng;
+  constexpr int NTS = Shape<NTL, NW, HP>::NTS;
+  eng.lane = tid & 63;
+  eng.wave = tid >> 6;
+  const int lm = eng.lane & 15, lq = eng.lane >> 4;
+  const int tiles = (int)((g.R + TM - 1) / TM);
+  const int step = g.step - (int)blockIdx.x / tiles;
+  const int64_t row0 = (int64_t)((int)blockIdx.x % tiles) * TM;
+  const int L = g.L, s = g.s;
+  const int64_t set_off = (int64_t)(step % g.nsets) * g.set_stride;
+  uint16_t* const ZT = g.ZT + set_off;
+  const float* st = g.steptab + (size_t)step * (1 + s);
+  const float h = st[0];
+
+  const PassDesc first = fwd_pass(g, 0);
+  const PassDesc last = fwd_pass(g, L - 1);
+  eng.template preload_hidden<true>(first, 0);
+  load_params(lds.param, g);
+  uint2 yhat[NTS][MT];
+#pragma unroll
+  for (int nt = 0; nt < NTS; ++nt)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int n = eng.state_col(nt, lq), m = mt * 16 + lm;
+      yhat[nt][mt] = make_uint2(0u, 0u);
+      if (eng.state_wave()) {
+        yhat[nt][mt] = load4h(g.ckpt + (size_t)step * g.ckpt_stride, row0 + m, g.R, n, g.d);
+        lds_store_u2(&lds.zbuf[m * lds.ldz + n], yhat[nt][mt]);
+        if (row0 + m < g.R) RAMPDE_STORE_G4(group4(ZT, g.ldk, row0 + m, n), yhat[nt][mt]);
+      }
+    }
+  __syncthreads();
+  for (int j = 0; j < s; ++j) {
+    const float tau = st[1 + j];
+    hidden_layers<T, MT, NTL, NW, HP, true>(eng, lds, g, j, tau, row0, set_off);
+    if (j + 1 == s) break;
+    auto pre0 = [](int, int) { return make_uint2(0u, 0u); };
+    auto epi_last = [&](const f32x4& acc, uint2, int nt, int mt, int n, int m) {
+      float v[4], kf[4], yh[4], z[4];
+      last_layer_values(acc, lds.param, g, tau, n, v);
+      unpack4<T>(pack4<T>(v), kf);
+      unpack4<T>(yhat[nt][mt], yh);
+      const float aj = g.A[(j + 1) * s + j];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z[r] = fmaf(h, aj * kf[r], yh[r]);
+      const uint2 zq = pack4<T>(z);
+      lds_store_u2(&lds.zbuf[m * lds.ldz + n], zq);
+      if (row0 + m < g.R) RAMPDE_STORE_G4(group4(ZT, g.ldk, (int64_t)(j + 1) * g.Rp + row0 + m, n), zq);
+    };
+    auto nxt_last = [&]() { eng.template preload_hidden<true>(first, 0); };
+    eng.template run_state<false>(last, lds.in(L - 1), lds.ld_in(L - 1), false, pre0, epi_last, nxt_last);
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // One step of the adjoint for a row tile (paper Algorithm 2, the body of the loop over steps).
 // TG: also collect the per-step sums of the time-grid gradient (g.tpart).
 template <class T, int MT, int NTL, int NW, int HP, bool MULTI, bool TG>

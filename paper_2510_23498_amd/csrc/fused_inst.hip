@@ -31,6 +31,10 @@ hipError_t pick_kernel(const FusedLaunch& l, const FusedArgs& a) {
     if (!l.adjoint && l.waves == 16)
       return launch_kernel(mlp_forward_fused<T, MT, NTL, 16, RAMPDE_INST_HP>, 16, l, a);
   }
+  if (l.recompute) {
+    if constexpr (MT >= 2) return launch_kernel(mlp_recompute_fused<T, MT, NTL, kForwardWaves, RAMPDE_INST_HP>, kForwardWaves, l, a);
+    return hipErrorInvalidValue;
+  }
   if (l.adjoint) {
     // (the host caps the adjoint's row tile at 32 rows: 64-row tiles spill; several steps per launch
     // only with 8 wavefronts)

@@ -15,6 +15,7 @@ constexpr int kForwardWaves = 8;
 
 struct FusedLaunch {
   int adjoint;   // 0: mlp_forward_fused, 1: mlp_adjoint_step
+  int recompute; // 1: mlp_recompute_fused (MT 2 or 4)
   int waves;     // adjoint only: 4 or 8 wavefronts per workgroup
   int bf16;      // 0: fp16, 1: bfloat16
   int MT;        // row tile = 16 * MT rows, MT in {1, 2, 4}

@@ -123,6 +123,8 @@ struct Plan {
   size_t fm_stride = 0;             // distance between the sets of feature-group-major buffers
   int act_lds_off = 0;              // adjoint kernel: LDS offset (16-bit elements) of the activation copy, 0 = none
   int nsets = 2;                    // sets: step i uses set i % nsets
+  int ahead_MT = 0;                 // > 0: the stages of a group of steps are recomputed in a launch of their own, in tiles of 16 ahead_MT rows
+  size_t ahead_lds = 0;
   int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, or kernels that decide inside a launch)
   std::vector<size_t> ACTT, DELTAT;
 };
@@ -248,13 +250,13 @@ static bool fused_candidate(const rampde_velocity* vel, const rampde_policy* pol
 // or 0.  They hold a quarter of every layer per wavefront in registers, so the bound is the register file: state width
 // up to 64, two to four layers.  B = 4096, 64 -> 256 -> 256 -> 64, bf16, 32 RK4 steps, forward / adjoint:
 // 400 / 940 us with the weights streamed (fused.hpp), 218 / 491 with these; one row 322 / 193 us forward.
-static bool chained_stages(const rampde_tableau* tab) {  // every stage is built from the one before it
-  if (!tab || tab->s < 1 || tab->s > kResidentStages) return false;
+static bool dense_stages(const rampde_tableau* tab) {  // some stage is built from others than the one before it
   for (int i = 2; i < tab->s; ++i)
     for (int j = 0; j + 1 < i; ++j)
-      if (tab->A[i * tab->s + j] != 0.0) return false;
-  return true;
+      if (tab->A[i * tab->s + j] != 0.0) return true;
+  return false;
 }
+static bool chained_stages(const rampde_tableau* tab) { return tab && tab->s >= 1 && tab->s <= kResidentStages && !dense_stages(tab); }
 static int resident_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol) {
   if (!fused_candidate(vel, pol) || !chained_stages(tab)) return 0;
   if (vel->n_layers < 2 || vel->n_layers > 4 || vel->widths[0] < 1 || vel->widths[0] > 64) return 0;
@@ -423,6 +425,13 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
           p.act_lds_off = (int)(p.lds_bytes / 2);
           p.lds_bytes += act_bytes;
         }
+        // stages recomputed ahead for several steps at once (not for the time-grid gradient, whose sums need the slopes)
+        if (allow_wide && !p.overlap_wgrad && !dense_stages(tab))
+          for (int m = 4; m >= 2 && !p.ahead_MT; m >>= 1)
+            if (lds_need(m, false) <= lds_limit) {
+              p.ahead_MT = m;
+              p.ahead_lds = lds_need(m, false);
+            }
       }
       for (auto& y : p.layers) {
         y.Wf = take((size_t)y.Npad * y.Kpad * 2);
@@ -494,17 +503,26 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // (about half of its 256 MB is left to them); the headline workload's set is larger than that.
         const int want_tile = pol ? pol->wgrad_tile : 0;
         const int64_t cached = std::max<int64_t>(1, (int64_t)((size_t(128) << 20) / per_set));
-        const int64_t want = (pol && pol->step_group > 0) ? pol->step_group : cached;
+        // (steps whose stages are recomputed in one launch: as many as fill the device once.  Where one or two do not fill
+        // it, the buffers' way through memory costs more than the larger tile saves: 3 x 512, f16, 16 RK4 steps, recomputed
+        // inside / ahead, us: B = 4096 (4 steps) 4171 / 3731, B = 8192 (2 steps, a full round) 5934 / 5540, B = 6000
+        // (2 steps, 0.7 rounds) 4949 / 5026, 2 x 300 with B = 12000 7247 / 7533)
+        int64_t ahead = 1;
+        if (p.ahead_MT) {
+          const int64_t cus = device_compute_units(), t = (p.R + 16 * p.ahead_MT - 1) / (16 * p.ahead_MT);
+          ahead = cus / t;
+          if (ahead == 2 && 40 * t < 17 * cus) ahead = 1;
+        }
+        const int64_t want = (pol && pol->step_group > 0) ? pol->step_group : std::max(cached, ahead);
         const int64_t group = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, fit), std::min<int64_t>(N, kMaxWgradSteps)));
         // (the kernel addresses a lane's part of an operand tensor by a 32-bit byte offset)
         bool offsets_fit = (size_t)p.dpad * p.ldk * 2 < (size_t(1) << 32);
         for (auto& y : p.layers) offsets_fit = offsets_fit && (size_t)std::max(y.Npad, y.Kpad) * p.ldk * 2 < (size_t(1) << 32);
         p.wgrad_slab = !p.overlap_wgrad && !p.resident && p.step_group <= 1 && offsets_fit &&
                        (want_tile == 256 || (want_tile != 128 && group * p.ldk >= kSlabMinK));
-        if (p.wgrad_slab) {
-          p.wgrad_group = (int)group;
-          p.nsets = p.wgrad_group;
-        }
+        if (p.step_group <= 1 && std::min(group, ahead) < 2) p.ahead_MT = 0;
+        if (p.wgrad_slab) p.wgrad_group = (int)group;
+        if (p.wgrad_slab || (p.ahead_MT && p.step_group <= 1)) p.nsets = (int)group;
         int tiles = 0;
         for (auto& y : p.layers) {
           if (p.wgrad_slab) {
@@ -1096,6 +1114,34 @@ struct Runner {
     return (hp == 256 || hp == 512 || hp == 1024) ? hp : 0;
   }
 
+  // stages of steps a.step, a.step - 1, ..., n of them, into their buffer sets
+  int recompute_ahead(FusedArgs a, int n) {
+    const int64_t tiles = (p.R + 16 * p.ahead_MT - 1) / (16 * p.ahead_MT);
+    a.act_lds_off = 0;
+    a.k_in_lds = 0;
+    FusedLaunch l{};
+    l.recompute = 1;
+    l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
+    l.MT = p.ahead_MT;
+    l.NTL = p.dpad / 64;
+    l.grid = (unsigned)(tiles * n);
+    l.lds_bytes = p.ahead_lds;
+    l.stream = st;
+    return launch_fused_width(l, a);
+  }
+
+  int launch_fused_width(const FusedLaunch& l, const FusedArgs& a) {
+    hipError_t e;
+    switch (static_hidden_width()) {
+      case 256: e = fused_launch_hp256(l, a); break;
+      case 512: e = fused_launch_hp512(l, a); break;
+      case 1024: e = fused_launch_hp1024(l, a); break;
+      default: e = fused_launch_hp0(l, a); break;
+    }
+    if (e != hipSuccess) return hip_fail(e, "row-tile-persistent kernel launch");
+    return RAMPDE_OK;
+  }
+
   int launch_fused(bool adjoint, const FusedArgs& a) {
     FusedLaunch l{};
     l.adjoint = adjoint ? 1 : 0;
@@ -1107,20 +1153,12 @@ struct Runner {
     l.grid = blocks_for(p.R, 16 * p.MT);
     l.lds_bytes = p.lds_bytes;
     l.stream = st;
-    hipError_t e;
     if (p.wide) {
-      e = wide_launch(l, a);
+      const hipError_t e = wide_launch(l, a);
       if (e != hipSuccess) return hip_fail(e, "wide row-tile kernel launch");
       return RAMPDE_OK;
     }
-    switch (static_hidden_width()) {
-      case 256: e = fused_launch_hp256(l, a); break;
-      case 512: e = fused_launch_hp512(l, a); break;
-      case 1024: e = fused_launch_hp1024(l, a); break;
-      default: e = fused_launch_hp0(l, a); break;
-    }
-    if (e != hipSuccess) return hip_fail(e, "row-tile-persistent kernel launch");
-    return RAMPDE_OK;
+    return launch_fused_width(l, a);
   }
 
   // c_h of the trace row from theta (shallow flows)
@@ -1186,11 +1224,13 @@ struct Runner {
     return RAMPDE_OK;
   }
 
-  int adjoint_step_fused(const FusedArgs& a) {
-    int rc;
+  // ahead: steps from a.step on whose stages are recomputed first, in a launch of their own (timed with this step)
+  int adjoint_step_fused(const FusedArgs& a, int ahead = 0) {
+    int rc = RAMPDE_OK;
     {
-      TimeScope ts(RAMPDE_K_FUSED_ADJOINT_STEP, step_flops() * p.s * (a.skip_recompute ? 1.0 : 2.0) * a.nsteps, st);
-      rc = p.resident ? launch_resident(true, a) : launch_fused(true, a);
+      TimeScope ts(RAMPDE_K_FUSED_ADJOINT_STEP, step_flops() * p.s * ((a.skip_recompute ? 1.0 : 2.0) * a.nsteps + ahead), st);
+      if (ahead) rc = recompute_ahead(a, ahead);
+      if (!rc) rc = p.resident ? launch_resident(true, a) : launch_fused(true, a);
     }
     if (rc) return rc;
     if (a.tpart) {
@@ -1739,8 +1779,8 @@ struct Runner {
           cur = fa.a_out;
           fa.gys = gys_at(hi);
           fa.gys_stride = step_elems;
-          fa.skip_recompute = 0;
-          int rc = adjoint_step_fused(fa);
+          fa.skip_recompute = p.ahead_MT ? 1 : 0;
+          int rc = adjoint_step_fused(fa, p.ahead_MT ? n : 0);
           if (rc) return rc;
           param_grads_fused(hi, 0.f, Coefs{}, st, n);
           hi -= n;
@@ -1757,8 +1797,8 @@ struct Runner {
           fa.a_out = a_buf(i);
           fa.gys = gys_at(i);
           // (with the time-grid gradient the step's slopes are needed again: they are recomputed)
-          fa.skip_recompute = (i == from && !recompute_first && !grad_t) ? 1 : 0;
-          int rc = adjoint_step_fused(fa);
+          fa.skip_recompute = p.ahead_MT || (i == from && !recompute_first && !grad_t) ? 1 : 0;
+          int rc = adjoint_step_fused(fa, p.ahead_MT && (from - i) % p.nsets == 0 ? std::min(p.nsets, i + 1) : 0);
           if (rc) return rc;
           const float h = (float)(tgrid[i + 1] - tgrid[i]);
           Coefs taus{};

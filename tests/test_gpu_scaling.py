@@ -179,7 +179,7 @@ def _gain_case(base, **kw):
     the scaled adjoint beyond the fp16 range at the initial scale, and the adjoint itself grows from
     step to step going backward, so that the scale has to be halved again in the middle of the pass."""
     gain = kw.pop("gain")
-    cfg = wl.CONFIGS[base].with_(low="f16", **kw)
+    cfg = wl.CONFIGS[base].with_(**{"low": "f16", **kw})
     theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
     name, shp, off = [x for x in wl.theta_layout(cfg) if x[0].startswith("W")][-1]
     theta = theta.copy()
@@ -511,3 +511,33 @@ def test_backward_pass_beside_a_long_forward_pass_on_another_stream():
     np.testing.assert_array_equal(beside[2].scale_hist, alone[2].scale_hist)
     for a, b in zip(beside[:2], alone[:2]):
         assert par.rel_err(a.cpu().numpy(), b.cpu().numpy()) <= par.TOL_EMUL
+
+
+@pytest.mark.parametrize("widths,B,N,low,tab,gain", [
+    ((128, 512, 512, 128), 1, 5, "f16", "rk4", 1.0),            # one row: a tile nearly empty; a group cut by the grid's end
+    ((128, 512, 512, 128), 65, 7, "bf16", "heun", 1.0),         # fixed scale: all steps of a group in one launch
+    ((200, 1024, 1024, 200), 33, 9, "f16", "euler", 1.0),       # the 32-row tile of the widest networks, odd batch
+    ((70, 300, 190, 70), 130, 6, "f16", "rk4", 1.0),            # run-time widths
+    ((128, 512, 512, 512, 128), 300, 6, "f16", "rk4", 256.0),   # rejected steps inside a group
+    ((128, 512, 512, 128), 4096, 3, "f16", "rk4", 1.0),         # several groups of whole rounds
+])
+def test_stages_recomputed_ahead_equal_those_recomputed_inside(widths, B, N, low, tab, gain):
+    # one step per group recomputes inside the adjoint kernel.  The contractions sum in the same order in both: in bf16
+    # the cotangents agree bit for bit.  In fp16 the compiler rounds fp32 -> fp16 with the multiply-add in front of it in
+    # one instruction (v_fma_mixlo_f16, one rounding) in some places of a kernel and in two in others: a value whose
+    # fp32 rounding meets a tie of the fp16 one (2^-13 of them) moves by one unit 2^-10, 1.1e-5 in the norm of a tensor;
+    # eight such tensors in a row stay below 1e-4.  The parameter gradients are also summed in another fp32 order.
+    # (With a gain of 256 in the last layer such a flip grows from step to step: the bound of this workload against the
+    # oracle.)
+    cfg, theta, y0, target = _gain_case("cfg3", name="ahead", widths=widths, B=B, N=N, t1=0.015 * N, low=low, tableau=tab,
+                                        gain=gain, scaling="dynamic" if low == "f16" else "none")
+    one = par.run_gpu(cfg, theta, y0, target, step_group=1)
+    for group in (0, 2):
+        got = par.run_gpu(cfg, theta, y0, target, step_group=group)
+        assert got["retries"] == one["retries"] and (gain == 1.0 or one["retries"] > 0)
+        np.testing.assert_array_equal(got["scale_hist"], one["scale_hist"])
+        if low == "bf16":
+            np.testing.assert_array_equal(got["grad_y0"], one["grad_y0"])
+        tol = 1e-4 if gain == 1.0 else par.TOL_EMUL
+        assert par.rel_err(got["grad_y0"], one["grad_y0"]) <= tol
+        assert par.rel_err(got["grad_theta"], one["grad_theta"]) <= tol
