@@ -37,6 +37,13 @@
  *     up and the pass is redone on kernels with one launch per step or layer, on the same
  *     workspace: same results within rounding, a few ms later, and decided anew by every call.
  *     rampde_odeint_bwd in place (grad_y0 = grad_yN) takes those kernels from the start.
+ *   - Dense networks whose hidden layers are all 257 to 512 wide (two or three of them, state up to
+ *     128) with up to 2048 rows, or 769 to 1024 wide (one or two, state of 65 to 256) with up to 1024
+ *     rows: workgroups share row tiles and exchange activations within a launch, in forward and
+ *     backward passes alike.  Where some of them are kept from running for 2 ms, the launch gives up,
+ *     and kernels that do not wait do its work: behind it on the stream (forward passes and a fixed
+ *     scale; nothing synchronises), or as above under overflow detection.  An explicit row_tile
+ *     selects those kernels from the start.
  *   - theta layout (flat fp32, also the layout of grad_theta):
  *       MLP  : for each layer l: W_l[out_l][in_l] row-major, then b_l[out_l];
  *              layer 1 has in_1 = d + 1 when time_input is set (time column LAST).
@@ -98,9 +105,9 @@ typedef enum {
 #define RAMPDE_NAIVE_STATE 8u       /* comparison baseline, not the paper's scheme: the state y and the adjoint a are
                                      themselves kept in low precision (rounded after every update), i.e. without
                                      the fp32 accumulators of Algorithms 1-2 (the "naive" rows of the paper's Table 5) */
-#define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale within a launch (see the notes on
-                                     concurrency above) give up at the first exchange, and the pass is redone with
-                                     one launch per step.  Same results */
+#define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale or activations within a launch (see
+                                     the notes on concurrency above) give up at the first exchange, and the pass is
+                                     redone by the kernels that do not.  Same results */
 
 /* Explicit Butcher tableau, host memory, fp64.  A is s*s row-major; only the strictly
  * lower triangle may be non-zero (checked).  Consistency (sum b = 1, ...) is not checked. */
@@ -133,7 +140,8 @@ typedef struct {
                              detection one step per launch, except for narrow networks (2 to 4 layers, state up to 64
                              wide, hidden layers up to 256 wide), networks with one hidden layer (state up to 64 wide
                              and hidden layer up to 1024, or 128 and 512) and flows (up to 64 state columns), which
-                             run as many as about 1 GiB holds, at most 64.  A smaller value is the way to a smaller
+                             run as many as about 1 GiB holds, at most 64, and for wide networks, whose stages are
+                             recomputed for as many steps at once as fill the device (and 4 GiB hold).  A smaller value is the way to a smaller
                              workspace.  Where wgrad_tile = 256 applies this is the number of accepted steps
                              whose parameter gradients one launch forms (default: as many as keep their buffers in
                              the memory-side cache) */
@@ -183,7 +191,7 @@ int64_t rampde_num_params(const rampde_velocity *vel);
  * The size depends on the policy: the backward pass of a dense network keeps the low-precision
  * stage inputs, activations and cotangents of all the steps that one launch runs (policy.step_group:
  * up to 64 steps, with a fixed scale at most about 4 GiB, with overflow detection at most about
- * 1 GiB, or of two steps where a launch runs one).  Pass the same policy to the query and to the
+ * 1 GiB, or, for wide networks, of as many steps as are recomputed at once).  Pass the same policy to the query and to the
  * call. */
 size_t rampde_workspace_bytes(const rampde_velocity *vel, int64_t B, int N,
                               const rampde_tableau *tab, const rampde_policy *pol,

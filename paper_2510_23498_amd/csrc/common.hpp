@@ -30,7 +30,8 @@ struct Ctl {
   int done;            // workgroups of the current adjoint-step kernel that have finished
   float S_step;        // scale of the most recently accepted step (used by its parameter-gradient kernels)
   int stalled;         // a wait between the workgroups of a launch ran out (they never ran at the same time)
-  int pad[4];
+  int cluster_stalled; // ... of a launch whose work the launches behind it redo (cluster.hpp)
+  int pad[3];
 };
 static_assert(sizeof(Ctl) == 64, "control block layout");
 

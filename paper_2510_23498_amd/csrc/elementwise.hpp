@@ -154,7 +154,7 @@ __global__ void ctl_reset(Ctl* ctl, float* scale_hist, int N) {
   for (int i = 0; i < N; ++i) scale_hist[i] = 0.f;
   ctl->S = 1.f; ctl->attempt = 1; ctl->poison = 0; ctl->failed_step = -1; ctl->nonfinite = 0;
   ctl->amax_bits = 0; ctl->retries = 0; ctl->s_min = 1.f; ctl->s_max = 1.f; ctl->done = 0; ctl->S_step = 1.f;
-  ctl->stalled = 0;
+  ctl->stalled = 0; ctl->cluster_stalled = 0;
 }
 
 // a <- dL/dy_N (+ running-cost cotangent), max|a|   (paper Alg. 2, initialisation)

@@ -125,6 +125,7 @@ struct FusedArgs {
   // sums by fold_time_slots after the launch)
   // added to by every workgroup; folded into dL/dt once the steps are accepted
   float* tpart;
+  const int* only_if;  // null, or: nothing is done unless this is raised (a launch that redoes another one's work)
 };
 
 // theta (fp32) -> fragment-major low-precision copies of all dense layers (see FusedLayer) and the
@@ -143,10 +144,12 @@ struct CastLayer {
 struct CastArgs {
   CastLayer layer[kMaxLayers];
   int L, nfrag;
+  const int* only_if;  // as in FusedArgs
 };
 
 template <class T>
 __global__ void cast_dense_fragments(CastArgs c) {
+  if (c.only_if && !*c.only_if) return;
   const int lane = threadIdx.x & 63;
   int frag = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (frag >= c.nfrag) return;
@@ -644,6 +647,7 @@ __device__ __forceinline__ void last_layer_values(const f32x4& acc, const lds_f3
 template <class T, int MT, int NTL, int NW, int HP>
 __global__ __launch_bounds__(64 * NW) void mlp_forward_fused(FusedArgs g) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  if (g.only_if && !*g.only_if) return;
   constexpr int TM = 16 * MT;
   const TileLds<MT> lds((lds_u16*)smem, g);
   const int tid = threadIdx.x;
@@ -833,7 +837,7 @@ __global__ __launch_bounds__(64 * NW) void mlp_recompute_fused(FusedArgs g) {
 template <class T, int MT, int NTL, int NW, int HP, bool MULTI, bool TG>
 __global__ __launch_bounds__(64 * NW) void mlp_adjoint_step(FusedArgs g) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-  if (g.ctl->poison) return;
+  if (g.ctl->poison || (g.only_if && !*g.only_if)) return;
   constexpr int TM = 16 * MT;
   const TileLds<MT> lds((lds_u16*)smem, g);
   const int tid = threadIdx.x;

@@ -22,6 +22,7 @@
 #include "fused_launch.hpp"
 #include "resident_launch.hpp"
 #include "shallow_launch.hpp"
+#include "cluster_launch.hpp"
 #include "wide.hpp"
 #include "gemm.hpp"
 #include "wgrad_slab.hpp"
@@ -125,6 +126,9 @@ struct Plan {
   int nsets = 2;                    // sets: step i uses set i % nsets
   int ahead_MT = 0;                 // > 0: the stages of a group of steps are recomputed in a launch of their own, in tiles of 16 ahead_MT rows
   size_t ahead_lds = 0;
+  int cluster = 0;                  // hidden width of the kernels of cluster.hpp (512, 1024), 0: not those
+  int cl_RTN = 0, cl_n = 0;         // their row tiles of 32 per cluster, and clusters
+  size_t cl_W = 0, cl_x = 0, cl_tickets = 0;
   int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, or kernels that decide inside a launch)
   std::vector<size_t> ACTT, DELTAT;
 };
@@ -294,6 +298,24 @@ static bool resident_takes_rows(const rampde_velocity* vel, const rampde_tableau
   return is_backward && !(vel->widths[0] == 128 && rhp == 512);
 }
 
+// The kernels of cluster.hpp: networks that they are built for, batches of at most one cluster of 64 rows per HP / 64
+// compute units, and a whole device (its eight XCDs; a partition of it has fewer).  32 rows per cluster while those run
+// at once.  Forward pass of 16 RK4 steps, us with row tiles / clusters: 256 -> 2 x 1024 -> 256, f16, 16 rows 1493 / 360,
+// 512 rows 1552 / 380, 520 rows (64 per cluster) 1575 / 516, 1024 rows 1545 / 522; 128 -> 3 x 512 -> 128, bf16, 16 rows
+// 718 / 358, 1024 rows 719 / 373, 2048 rows 725 / 509; 100 -> 2 x 400 -> 100, f16, Heun, 2000 rows 244 / 197;
+// 200 -> 1000 -> 200, bf16, Euler, 128 rows 158 / 77, 1024 rows 158 / 99.
+static void choose_clusters(Plan& p) {
+  const int hp = p.L >= 2 ? p.layers[0].Npad : 0;
+  for (int l = 0; l + 1 < p.L; ++l)
+    if (p.layers[l].Npad != hp) return;
+  if (!cluster_shape(hp, p.L, p.dpad) || device_compute_units() != 256) return;
+  const int64_t most = 256 / (hp / 64), n32 = (p.R + 31) / 32, n64 = (p.R + 63) / 64;
+  if (n64 > most) return;
+  p.cluster = hp;
+  p.cl_RTN = n32 <= most ? 1 : 2;
+  p.cl_n = (int)(n32 <= most ? n32 : n64);
+}
+
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
 // gradient runs on the other row-tile kernels).  small: no choice of the streaming kernels, which keep slopes in the
 // workspace, where the register-resident ones can run
@@ -433,6 +455,8 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
               p.ahead_lds = lds_need(m, false);
             }
       }
+      if (allow_resident && allow_wide && !small && want_rows == 0 && !p.wide && (p.ahead_MT || !is_backward) && !dense_stages(tab))
+        choose_clusters(p);
       for (auto& y : p.layers) {
         y.Wf = take((size_t)y.Npad * y.Kpad * 2);
         y.WTf = take((size_t)y.Npad * y.Kpad * 2);
@@ -483,7 +507,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // step of a group needs its own set of buffers; groups are as long as the sets may take memory.
         const int64_t want_group = (pol && pol->step_group > 0) ? pol->step_group : kMaxWgradSteps;
         const int64_t cap = std::min<int64_t>(want_group, std::min<int64_t>(fit, kMaxWgradSteps));
-        if (pol && (p.resident || (resolve_scaling(pol) == RAMPDE_SCALE_NONE && cap >= 2)) && !p.wide) {
+        if (pol && (p.resident || (resolve_scaling(pol) == RAMPDE_SCALE_NONE && cap >= 2)) && !p.wide && !p.cluster) {
           p.step_group = (int)std::max<int64_t>(1, std::min<int64_t>(N, cap));
           if (one_gib) {  // (as many launches, of equal length)
             const int launches = (N + p.step_group - 1) / p.step_group;
@@ -520,7 +544,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         for (auto& y : p.layers) offsets_fit = offsets_fit && (size_t)std::max(y.Npad, y.Kpad) * p.ldk * 2 < (size_t(1) << 32);
         p.wgrad_slab = !p.overlap_wgrad && !p.resident && p.step_group <= 1 && offsets_fit &&
                        (want_tile == 256 || (want_tile != 128 && group * p.ldk >= kSlabMinK));
-        if (p.step_group <= 1 && std::min(group, ahead) < 2) p.ahead_MT = 0;
+        if (p.step_group <= 1 && std::min(group, ahead) < 2) p.ahead_MT = p.cluster = 0;
         if (p.wgrad_slab) p.wgrad_group = (int)group;
         if (p.wgrad_slab || (p.ahead_MT && p.step_group <= 1)) p.nsets = (int)group;
         int tiles = 0;
@@ -617,6 +641,12 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         }
       }
     }
+  }
+  if (p.cluster) {
+    p.cl_W = take((size_t)p.cluster / 64 * 4 * cluster_frags(p.cluster, p.L, p.dpad) * 1024);
+    p.cl_x = take((size_t)p.cl_n * cluster_exchange_bytes(p.cluster, p.L, p.dpad, p.cl_RTN));
+    p.cl_tickets = take(8 * sizeof(unsigned));
+    if (is_backward && pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE) p.slots = take(sizeof(unsigned long long) * (size_t)N * p.cl_n * (p.cluster / 64));
   }
   if (is_backward) p.tpart = take(sizeof(float) * 2 * (size_t)N);
   if (is_backward) p.tslots = take(sizeof(float) * 2 * (size_t)kTimeSlotPairs);
@@ -1020,9 +1050,10 @@ struct Runner {
   bool use_fused = false;
   unsigned long long wait_ticks = kWaitTicks;
 
-  void cast_fragments(const float* theta) {
+  void cast_fragments(const float* theta, const int* only_if = nullptr) {
     CastArgs c{};
     c.L = p.L;
+    c.only_if = only_if;
     int nfrag = 0;
     for (int l = 0; l < p.L; ++l) {
       const Layer& y = p.layers[l];
@@ -1198,6 +1229,48 @@ struct Runner {
     return RAMPDE_OK;
   }
 
+  void cast_cluster(const float* theta, bool transposed) {
+    ClusterCast c{};
+    for (int l = 0; l < p.L; ++l) {
+      const Layer& y = p.layers[l];
+      c.layer[l] = ClusterCastLayer{theta + y.theta_w, theta + y.theta_b, f32(y.bias_f), f32(y.wt_f), y.out, y.in, y.in_full, y.has_time, y.Npad};
+    }
+    c.W = (u16x8*)(ws + p.cl_W);
+    c.L = p.L;
+    c.C = p.cluster / 64;
+    c.NTL = p.dpad / 64;
+    c.KSH = p.cluster / 64;
+    c.frags = cluster_frags(p.cluster, p.L, p.dpad);
+    c.transposed = transposed ? 1 : 0;
+    c.write_bias = transposed ? 0 : 1;
+    cast_cluster_fragments<T><<<std::max(c.C * c.frags, p.L * 4), 256, 0, st>>>(c);
+  }
+
+  // reset_stalled: the first launch of a pass
+  int launch_cluster(bool chain, const FusedArgs& a, bool reset_stalled) {
+    ClusterArgs ca{};
+    ca.r.f = a;
+    ca.r.slots = p.slots ? (unsigned long long*)(ws + p.slots) : nullptr;
+    ca.r.wait_ticks = wait_ticks;
+    ca.W = (const u16x8*)(ws + p.cl_W);
+    ca.exchange = (uint32_t*)(ws + p.cl_x);
+    ca.tickets = (unsigned*)(ws + p.cl_tickets);
+    ca.stalled = &ctl->cluster_stalled;
+    ca.clusters = p.cl_n;
+    const size_t words = (size_t)p.cl_n * cluster_exchange_bytes(p.cluster, p.L, p.dpad, p.cl_RTN) / 16;
+    cluster_reset<<<(unsigned)std::min<size_t>((words + 255) / 256, 2048), 256, 0, st>>>((u32x4c*)ca.exchange, words, ca.tickets,
+                                                                                       reset_stalled ? ca.stalled : nullptr);
+    ClusterLaunch l{};
+    l.chain = chain ? 1 : 0;
+    l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
+    l.L = p.L;
+    l.NTL = p.dpad / 64;
+    l.RTN = p.cl_RTN;
+    l.stream = st;
+    const hipError_t e = cluster_launch(p.cluster, l, ca);
+    return e == hipSuccess ? RAMPDE_OK : hip_fail(e, "cluster kernel launch");
+  }
+
   double step_flops() const {  // one velocity evaluation of the whole batch, padded shapes
     double f = 0.0;
     for (const Layer& y : p.layers) f += 2.0 * (double)p.R * y.Npad * y.Kpad;
@@ -1206,10 +1279,12 @@ struct Runner {
 
   int forward_fused(const float* theta, const float* y0, const double* tgrid, int N, const rampde_tableau* tab,
                     const rampde_policy* pol, uint16_t* ckpt, float* yN) {
-    cast_fragments(theta);
+    if (p.cluster) cast_cluster(theta, false);
+    else cast_fragments(theta);
     if (p.cnf) trace_coefficients(theta);
     write_steptab(tgrid, N, tab, pol->low);
     FusedArgs a = fused_args(tab, N);
+    if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
     a.y0 = y0;
     a.y = yN;
     a.ckpt = ckpt;
@@ -1217,6 +1292,13 @@ struct Runner {
     int rc;
     {
       TimeScope ts(RAMPDE_K_FUSED_FORWARD, step_flops() * p.s * N, st);
+      if (p.cluster) {
+        rc = launch_cluster(false, a, true);
+        if (rc) return rc;
+        // (two launches that do nothing unless a wait of that one ran out)
+        a.only_if = &ctl->cluster_stalled;
+        cast_fragments(theta, a.only_if);
+      }
       rc = p.resident ? launch_resident(false, a) : launch_fused(false, a);
     }
     if (rc) return rc;
@@ -1230,7 +1312,15 @@ struct Runner {
     {
       TimeScope ts(RAMPDE_K_FUSED_ADJOINT_STEP, step_flops() * p.s * ((a.skip_recompute ? 1.0 : 2.0) * a.nsteps + ahead), st);
       if (ahead) rc = recompute_ahead(a, ahead);
-      if (!rc) rc = p.resident ? launch_resident(true, a) : launch_fused(true, a);
+      if (!rc && p.cluster) {
+        rc = launch_cluster(true, a, false);
+        // under a fixed scale the row-tile kernel redoes a launch whose waits ran out (else it does nothing)
+        if (!rc && !a.detect) {
+          FusedArgs again = a;
+          again.only_if = &ctl->cluster_stalled;
+          rc = launch_fused(true, again);
+        }
+      } else if (!rc) rc = p.resident ? launch_resident(true, a) : launch_fused(true, a);
     }
     if (rc) return rc;
     if (a.tpart) {
@@ -1661,7 +1751,8 @@ struct Runner {
     if (!use_fused && !p.parabolic) cast_weights(theta);
     SideStream& side = SideStream::get();
     if (p.slots)
-      fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.slots), 2 * (size_t)N * blocks_for(p.R, 16 * p.MT));
+      fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.slots),
+                                         2 * (size_t)N * (p.cluster ? p.cl_n * (p.cluster / 64) : (int)blocks_for(p.R, 16 * p.MT)));
     if (use_fused && p.overlap_wgrad) {
       int rc = side.prepare(N);
       if (rc) return rc;
@@ -1672,6 +1763,7 @@ struct Runner {
     FusedArgs fa{};
     if (use_fused) {
       cast_fragments(theta);
+      if (p.cluster) cast_cluster(theta, true);
       if (p.cnf) trace_coefficients(theta);
       write_steptab(tgrid, N, tab, pol->low);
       fa = fused_args(tab, N);
@@ -1705,7 +1797,10 @@ struct Runner {
       fa.raw_norm = (pol->flags & RAMPDE_GROW_RAW_NORM) ? 1 : 0;
     }
     // (groups of steps: the adjoint stays in a buffer of its own until the last group writes grad_y0)
-    float* a = p.resident ? f32(p.a_alt) : use_fused ? a_buf(N) : grad_y0;
+    // (clusters under a fixed scale: a group's input has to outlive its launch, the groups alternate between two buffers)
+    const int cl_groups = p.cluster ? (N + p.nsets - 1) / p.nsets : 0;
+    auto cl_buf = [&](int left) -> float* { return left % 2 == 0 ? grad_y0 : f32(p.a_alt); };
+    float* a = p.resident || (p.cluster && detect) ? f32(p.a_alt) : p.cluster ? cl_buf(cl_groups) : use_fused ? a_buf(N) : grad_y0;
     const float* resident_a = a;
     const int naive_low = (pol->flags & RAMPDE_NAIVE_STATE) ? (std::is_same<T, BF16>::value ? 2 : 1) : 0;
     float* gys_rows = nullptr;
@@ -1763,6 +1858,24 @@ struct Runner {
           }
           hi -= n;
         }
+      } else if (p.cluster) {
+        // groups of steps as with the register-resident kernels, their stages recomputed by the row-tile kernels
+        int left = cl_groups;
+        for (int hi = from; hi >= 0;) {
+          const int n = std::min(p.nsets, hi + 1);
+          fa.step = hi;
+          fa.nsteps = n;
+          fa.a_in = resident_a;
+          fa.a_out = detect ? (hi - n < 0 ? grad_y0 : f32(p.a_alt)) : cl_buf(--left);
+          resident_a = fa.a_out;
+          fa.gys = gys_at(hi);
+          fa.gys_stride = step_elems;
+          fa.skip_recompute = 1;
+          int rc = adjoint_step_fused(fa, n);
+          if (rc) return rc;
+          param_grads_fused(hi, 0.f, Coefs{}, st, n);
+          hi -= n;
+        }
       } else if (use_fused && p.step_group > 1) {
         // groups of steps: one adjoint launch and one parameter-gradient launch per group, all on
         // the caller's stream; the adjoint ping-pongs between two buffers per launch so that the
@@ -1787,7 +1900,7 @@ struct Runner {
         }
       }
       int pending_hi = -1, pending_n = 0;  // steps whose parameter gradients wait for their group's launch
-      for (int i = (p.resident || (use_fused && p.step_group > 1)) ? -1 : from; i >= 0; --i) {
+      for (int i = (p.resident || p.cluster || (use_fused && p.step_group > 1)) ? -1 : from; i >= 0; --i) {
         if (use_fused) {
           // this set was last read by the parameter-gradient kernel of step i + 2
           if (p.overlap_wgrad && i + 2 <= N - 1) HIP_TRY(hipStreamWaitEvent(st, side.wgrad_done(i + 2), 0));
@@ -1872,11 +1985,12 @@ struct Runner {
         break;
       }
       chain_retry<<<1, 1, 0, st>>>(ctl);
-      if (p.resident) {
+      if (p.resident || p.cluster) {
         // the adjoint before the rejected step is where that step's group wrote it (the groups start at `from`)
-        const int in_group = (from - hctl.failed_step) % p.step_group;
+        const int group = p.cluster ? p.nsets : p.step_group;
+        const int in_group = (from - hctl.failed_step) % group;
         const int hi = hctl.failed_step + in_group;
-        resident_a = hi - std::min(p.step_group, hi + 1) < 0 ? grad_y0 : f32(p.a_alt);
+        resident_a = hi - std::min(group, hi + 1) < 0 ? grad_y0 : f32(p.a_alt);
       }
       from = hctl.failed_step;
       if (grad_t) fill_zero_u32<<<1, 64, 0, st>>>((uint32_t*)(ws + p.tpart) + 2 * (size_t)from, 2);
@@ -1972,8 +2086,8 @@ size_t rampde_workspace_bytes(const rampde_velocity* vel, int64_t B, int N, cons
   Plan p = make_plan(vel, B, N, tab, pol, is_backward);
   if (!p.ok) return 0;
   size_t total = p.total;
-  if (is_backward && (p.wide || p.resident)) {
-    // the backward pass with the time-grid gradient (neither wide nor shallow) or redone step by step (not resident)
+  if (is_backward && (p.wide || p.resident || p.cluster)) {
+    // the backward pass with the time-grid gradient (neither wide nor shallow) or redone step by step (not resident, no clusters)
     // uses the other row-tile kernels: room for any of them
     for (const bool wide : {false, true})
       for (const bool resident : {false, true}) {

@@ -408,8 +408,10 @@ struct StepExchange {
   float S, s_min, s_max;
   int attempt;
   bool stalled = false;
-  __device__ __forceinline__ StepExchange(const ResidentArgs& r)
-      : ra(r), S(r.f.ctl->S), s_min(r.f.ctl->s_min), s_max(r.f.ctl->s_max), attempt(r.f.ctl->attempt) {}
+  int me, posts;  // this workgroup's number among those that post
+  __device__ __forceinline__ StepExchange(const ResidentArgs& r, int me_, int posts_)
+      : ra(r), S(r.f.ctl->S), s_min(r.f.ctl->s_min), s_max(r.f.ctl->s_max), attempt(r.f.ctl->attempt), me(me_), posts(posts_) {}
+  __device__ __forceinline__ StepExchange(const ResidentArgs& r) : StepExchange(r, blockIdx.x, gridDim.x) {}
 
   // post this workgroup's word of step `step`: bits of its max|a|, and whether its cotangent chain left the range
   __device__ __forceinline__ void post(const FusedArgs& g, int step, unsigned bits, bool nonfinite) {
@@ -422,7 +424,7 @@ struct StepExchange {
     if (threadIdx.x == 0) {
       unsigned m = 0;
       for (int w = 0; w < (int)(blockDim.x >> 6); ++w) m = max(m, s_post[w]);
-      __hip_atomic_store(ra.slots + (size_t)step * gridDim.x + blockIdx.x, ((unsigned long long)attempt << 32) | m,
+      __hip_atomic_store(ra.slots + (size_t)step * posts + me, ((unsigned long long)attempt << 32) | m,
                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -431,11 +433,11 @@ struct StepExchange {
   __device__ __forceinline__ bool collect(int step, unsigned& pay) {
     __shared__ unsigned s_pay[16];
     __shared__ int s_late[16];
-    const unsigned long long* row = ra.slots + (size_t)step * gridDim.x;
+    const unsigned long long* row = ra.slots + (size_t)step * posts;
     unsigned m = 0;
     bool late = ra.wait_ticks == 0;
     unsigned long long t0 = 0;
-    for (int q = threadIdx.x; q < (int)gridDim.x; q += blockDim.x) {
+    for (int q = threadIdx.x; q < posts; q += blockDim.x) {
       unsigned long long v = __hip_atomic_load(row + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       while ((int)(v >> 32) != attempt && !late) {
         if (t0 == 0) t0 = wall_clock64();
@@ -465,7 +467,7 @@ struct StepExchange {
   // accept / grow; false: the step is rejected, or the wait ran out (stalled)
   template <class T>
   __device__ __forceinline__ bool decide(const FusedArgs& g, int step) {
-    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    const bool first = me == 0 && threadIdx.x == 0;
     if (g.detect) {
       unsigned pay;
       if (!collect(step, pay)) {
@@ -502,7 +504,7 @@ struct StepExchange {
   }
 
   __device__ __forceinline__ void finish(const FusedArgs& g) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (me == 0 && threadIdx.x == 0) {
       g.ctl->S = S;
       g.ctl->attempt = attempt;
       g.ctl->s_min = s_min;

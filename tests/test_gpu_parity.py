@@ -561,3 +561,38 @@ def test_time_grid_gradient_of_more_row_tiles_than_slots():
     for i, join in ((0, lambda a, b: torch.cat([a, b])), (1, torch.add), (2, torch.add)):
         ref = join(halves[0][i], halves[1][i])
         assert par.rel_err(whole[i].cpu().numpy(), ref.cpu().numpy()) <= par.TOL_EMUL
+
+
+@pytest.mark.parametrize("widths,B,low,scaling,tab", [
+    ((256, 1024, 1024, 256), 70, "f16", "dynamic", "rk4"),       # 32 rows per cluster, the last one ragged
+    ((200, 1024, 900, 200), 513, "bf16", "none", "heun"),        # 64 rows per cluster, the last one holds one row
+    ((128, 1000, 128), 33, "f16", "dynamic", "rk4"),             # one hidden layer
+    ((140, 1024, 140), 1024, "bf16", "none", "euler"),           # ... at the largest batch
+    ((100, 1024, 800, 100), 1, "f16", "none_safe", "heun"),      # one row
+    ((128, 512, 512, 512, 128), 1030, "f16", "dynamic", "heun"),
+    ((128, 512, 400, 300, 128), 2048, "bf16", "none", "euler"),  # ... at the largest batch
+    ((50, 300, 512, 50), 41, "f16", "dynamic", "rk4"),
+    ((64, 512, 512, 512, 64), 1025, "bf16", "none", "euler"),
+])
+def test_cluster_kernels(widths, B, low, scaling, tab):
+    cfg = wl.CONFIGS["cfg1"].with_(name="cl" + "_".join(map(str, widths)), B=B, N=4, widths=widths, low=low, tableau=tab, loss="mse")
+    _both(cfg, bias_std=0.1, scaling=scaling)
+
+
+@pytest.mark.parametrize("widths,B", [((256, 1024, 1024, 256), 70), ((128, 512, 512, 512, 128), 1030)])
+def test_cluster_launches_that_were_given_up(widths, B):
+    # the row-tile kernels redo them: forward and under a fixed scale behind them on the stream, else by way of the host.
+    # In bf16 the row-tile kernels agree bit for bit among themselves, but not with the clusters' order of sums
+    from paper_2510_23498_amd import binding as rb
+    for low, scaling in (("bf16", "none"), ("f16", "dynamic")):
+        cfg = wl.CONFIGS["cfg1"].with_(name="given_up", B=B, N=5, widths=widths, low=low, loss="mse")
+        theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+        got = par.run_gpu(cfg, theta, y0, target, scaling=scaling, flags=rb.NO_WAITS)
+        rows = par.run_gpu(cfg, theta, y0, target, scaling=scaling, row_tile=16)
+        clusters = par.run_gpu(cfg, theta, y0, target, scaling=scaling)
+        par.compare(cfg, got, clusters, par.TOL_EMUL, "the cluster kernels")
+        par.compare(cfg, got, rows, par.TOL_EMUL, "the row-tile kernels")
+        if low == "bf16":
+            for key in ("yN", "ckpt", "grad_y0"):
+                np.testing.assert_array_equal(got[key], rows[key])
+            assert np.any(got["yN"] != clusters["yN"])

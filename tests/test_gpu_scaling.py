@@ -531,9 +531,10 @@ def test_stages_recomputed_ahead_equal_those_recomputed_inside(widths, B, N, low
     # oracle.)
     cfg, theta, y0, target = _gain_case("cfg3", name="ahead", widths=widths, B=B, N=N, t1=0.015 * N, low=low, tableau=tab,
                                         gain=gain, scaling="dynamic" if low == "f16" else "none")
-    one = par.run_gpu(cfg, theta, y0, target, step_group=1)
+    # (row_tile: the row-tile kernels, not the clusters of cluster.hpp)
+    one = par.run_gpu(cfg, theta, y0, target, step_group=1, row_tile=16)
     for group in (0, 2):
-        got = par.run_gpu(cfg, theta, y0, target, step_group=group)
+        got = par.run_gpu(cfg, theta, y0, target, step_group=group, row_tile=16)
         assert got["retries"] == one["retries"] and (gain == 1.0 or one["retries"] > 0)
         np.testing.assert_array_equal(got["scale_hist"], one["scale_hist"])
         if low == "bf16":
