@@ -17,7 +17,8 @@
 // complete (which nobody publishes before everybody has read evaluation e), three evaluations before it is used again.
 // With several row tiles of 32 per cluster, one tile's exchange runs beside the next one's contraction.
 //
-//   mlp_forward_cluster : Algorithm 1, all steps in one launch
+//   mlp_forward_cluster : Algorithm 1, as many steps per launch as take about 3 ms (a launch holds the whole device; other
+//                         streams' kernels get in between two of them), the fp32 state in yN from one to the next
 //   mlp_chain_cluster   : Algorithm 2 for a group of steps whose stages have been recomputed (mlp_recompute_fused): the
 //                         cotangent chain, the fp32 adjoint and the scale decisions (StepExchange of resident.hpp)
 //
@@ -440,17 +441,17 @@ __global__ __launch_bounds__(256, 1) void mlp_forward_cluster(ClusterArgs a) {
     for (int u = 0; u < NU; ++u) {
       const int rt = c.unit_rt + u * APC;
       const int64_t row = row0 + rt * 32 + c.lr;
-      load4f(g.y0, row, g.R, ns, g.d, y[u]);
+      load4f(g.step > 0 ? g.y : g.y0, row, g.R, ns, g.d, y[u]);
       const uint2 q = pack4<T>(y[u]);
       if (g.round_incr & 2) unpack4<T>(q, y[u]);
       unpack4<T>(q, yh[u]);
-      store4h(g.ckpt, row, g.R, ns, g.d, q);
+      if (g.step == 0) store4h(g.ckpt, row, g.R, ns, g.d, q);
       c.publish_z(0, rt, q);
     }
   }
   int e = 0;
 #pragma unroll 1
-  for (int i = 0; i < g.N; ++i) {
+  for (int i = g.step; i < g.step + g.nsteps; ++i) {
     const float* stp = g.steptab + (size_t)i * (1 + s);
     const float h = stp[0];
 #pragma unroll

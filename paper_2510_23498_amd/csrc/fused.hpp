@@ -105,6 +105,7 @@ struct FusedArgs {
   uint16_t* ACTT[kMaxLayers];  // [Npad_l / 4][ldk][4] hidden activations, l = 0..L-2
   uint16_t* DELTAT[kMaxLayers];// [Npad_l / 4][ldk][4] their cotangents
   uint16_t* KBART;             // [dpad / 4][ldk][4] cotangents of the slopes
+  uint16_t* KT;                // [dpad / 4][ldk][4] slopes (register-resident kernels, time-grid gradient)
   int64_t ldk, Rp;
   uint16_t* ZBAR;              // [s][R][dpad] (used when they do not fit in LDS)
   // The kernel runs steps step, step - 1, ..., step - nsteps + 1 (nsteps > 1 only when nothing is

@@ -120,7 +120,7 @@ struct Plan {
   bool wgrad_slab = false;          // per-step parameter gradients by the 128 x 128-per-wavefront kernel
   int wgrad_group = 1;              // ... of this many adjoint steps per launch (each step has a buffer set of its own)
   size_t gpart = 0;                 // ksplits copies of the gradient vector
-  size_t ZT = 0, KBART = 0;
+  size_t ZT = 0, KBART = 0, KT = 0;
   size_t fm_stride = 0;             // distance between the sets of feature-group-major buffers
   int act_lds_off = 0;              // adjoint kernel: LDS offset (16-bit elements) of the activation copy, 0 = none
   int nsets = 2;                    // sets: step i uses set i % nsets
@@ -297,6 +297,8 @@ static bool resident_takes_rows(const rampde_velocity* vel, const rampde_tableau
   if (want_rows == 32) return !shallow && rhp == 256 && resident_lds_bytes(rhp, vel->n_layers, tab->s, 2, is_backward) <= kRowTileLds;
   return is_backward && !(vel->widths[0] == 128 && rhp == 512);
 }
+
+constexpr int kClusterEvaluations = 384;  // of the velocity per launch of a forward pass: about 3 ms
 
 // The kernels of cluster.hpp: networks that they are built for, batches of at most one cluster of 64 rows per HP / 64
 // compute units, and a whole device (its eight XCDs; a partition of it has fewer).  32 rows per cluster while those run
@@ -574,6 +576,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       const size_t fm_begin = off;
       p.ZT = take((size_t)p.dpad * p.ldk * 2);
       p.KBART = take((size_t)p.dpad * p.ldk * 2);
+      if (p.resident && !p.shallow && !allow_wide) p.KT = take((size_t)p.dpad * p.ldk * 2);
       for (int l = 0; l + 1 < p.L; ++l) {
         p.ACTT.push_back(take((size_t)p.layers[l].Npad * p.ldk * 2));
         p.DELTAT.push_back(take((size_t)p.layers[l].Npad * p.ldk * 2));
@@ -1199,7 +1202,21 @@ struct Runner {
                                                                    y0.out, y0.Npad, f32(p.cnf_c));
   }
 
-  int launch_resident(bool adjoint, const FusedArgs& a) {
+  // Groups of steps of the register-resident kernels: recomputed ahead, except where one kernel holds both directions'
+  // slices (up to three layers, 16-row tiles) and its tiles already fill the device.  64 -> 256 -> 256 -> 64, 32 RK4 steps,
+  // us per pass with one kernel / recomputed ahead: bf16 4096 rows 1084 / 1095, 3000 rows 991 / 946, 2000 rows 889 / 818,
+  // 8192 rows (32-row tiles) 1072 / 1040 with 16 steps; 40 -> 100 -> 100 -> 40, 8000 rows (two workgroups per compute
+  // unit) 561 / 579; four layers of 256, 4000 rows 886 / 808; 2 -> 32 -> 32 -> 2, f16, 256 rows, 8 steps 237 / 222;
+  // 50 -> 200 -> 200 -> 50 with the time-grid gradient, 1003 rows, Heun 414 / 347.
+  bool resident_ahead() const {
+    if (!p.resident || p.shallow || p.step_group < 2) return false;
+    const int64_t slots = (int64_t)device_compute_units() * (p.resident == 256 ? 1 : 2), tiles = blocks_for(p.R, 16 * p.MT);
+    return p.MT == 2 || p.L == 4 || 8 * tiles <= 7 * slots;
+  }
+
+  // kind: of the kernels of resident.hpp (of shallow.hpp: forward or adjoint)
+  int launch_resident(ResidentKind kind, const FusedArgs& a) {
+    const bool adjoint = kind != kResidentForward;
     ResidentArgs ra{};
     ra.f = a;
     ra.slots = p.slots ? (unsigned long long*)(ws + p.slots) : nullptr;
@@ -1219,10 +1236,16 @@ struct Runner {
       return e == hipSuccess ? RAMPDE_OK : hip_fail(e, "one-hidden-layer kernel launch");
     }
     ResidentLaunch l{};
-    l.adjoint = adjoint ? 1 : 0;
+    l.kind = kind;
     l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
     l.MT = p.MT;
     l.grid = blocks_for(p.R, 16 * p.MT);
+    if (kind == kResidentRecompute) {
+      const int64_t cus = device_compute_units();
+      if (p.resident == 256 && (int64_t)blocks_for(p.R, 16) * a.nsteps > 2 * cus) l.MT = 2;
+      const size_t lds = resident_lds_bytes(p.resident, p.L, 0, l.MT, false);
+      l.grid = (unsigned)std::min<int64_t>((int64_t)blocks_for(p.R, 16 * l.MT) * a.nsteps, cus * resident_per_cu(p.resident, lds));
+    }
     l.stream = st;
     const hipError_t e = resident_launch(p.resident, l, ra);
     if (e != hipSuccess) return hip_fail(e, "register-resident kernel launch");
@@ -1293,13 +1316,17 @@ struct Runner {
     {
       TimeScope ts(RAMPDE_K_FUSED_FORWARD, step_flops() * p.s * N, st);
       if (p.cluster) {
-        rc = launch_cluster(false, a, true);
-        if (rc) return rc;
+        const int per = std::max(1, kClusterEvaluations / p.s), launches = (N + per - 1) / per, even = (N + launches - 1) / launches;
+        for (a.step = 0; a.step < N; a.step += even) {
+          a.nsteps = std::min(even, N - a.step);
+          rc = launch_cluster(false, a, a.step == 0);
+          if (rc) return rc;
+        }
         // (two launches that do nothing unless a wait of that one ran out)
         a.only_if = &ctl->cluster_stalled;
         cast_fragments(theta, a.only_if);
       }
-      rc = p.resident ? launch_resident(false, a) : launch_fused(false, a);
+      rc = p.resident ? launch_resident(kResidentForward, a) : launch_fused(false, a);
     }
     if (rc) return rc;
     HIP_TRY(hipGetLastError());
@@ -1320,7 +1347,10 @@ struct Runner {
           again.only_if = &ctl->cluster_stalled;
           rc = launch_fused(true, again);
         }
-      } else if (!rc) rc = p.resident ? launch_resident(true, a) : launch_fused(true, a);
+      } else if (!rc && resident_ahead()) {
+        rc = launch_resident(kResidentRecompute, a);
+        if (!rc) rc = launch_resident(kResidentChain, a);
+      } else if (!rc) rc = p.resident ? launch_resident(kResidentAdjoint, a) : launch_fused(true, a);
     }
     if (rc) return rc;
     if (a.tpart) {
@@ -1778,6 +1808,7 @@ struct Runner {
       }
       fa.ZT = u16(p.ZT);
       fa.KBART = u16(p.KBART);
+      fa.KT = p.KT ? u16(p.KT) : nullptr;
       fa.nsets = p.nsets;
       fa.set_stride = (int64_t)(p.fm_stride / 2);
       fa.nsteps = 1;
@@ -2105,7 +2136,8 @@ static int forward_call(const rampde_velocity* vel, const float* theta, const fl
   if (rc) return rc;
   if (!theta || !y0 || !ckpt || !yN || !workspace || B < 1) return RAMPDE_EINVAL;
   if (!aligned16(theta) || !aligned16(y0) || !aligned16(ckpt) || !aligned16(yN)) return RAMPDE_EINVAL;
-  Plan p = make_plan(vel, B, N, tab, pol, 0, true, true, small);
+  // (a launch of the cluster kernels that is given up may have written yN: not where that is y0 as well)
+  Plan p = make_plan(vel, B, N, tab, pol, 0, true, true, small || y0 == yN);
   if (!p.ok) return RAMPDE_EINVAL;
   if (workspace_bytes < p.total || ((uintptr_t)workspace & 255)) return RAMPDE_EWORKSPACE;
   const bool fused = p.fused;

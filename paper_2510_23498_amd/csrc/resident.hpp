@@ -18,11 +18,15 @@
 // branches or 64-bit lane addresses.
 //
 //   mlp_forward_resident : Algorithm 1, all steps of a tile in one launch
-//   mlp_adjoint_resident : Algorithm 2, a group of steps in one launch, also under overflow detection.  The scale is
-//     the only thing that couples tiles between steps.  Every workgroup posts max|a| and its overflow flag of a step
-//     as ONE 64-bit word (payload and tag together: no fence, no second round trip) and reads the others' words when it
-//     needs the next step's scale, which is not before its last stage has been recomputed: the exchange is hidden
-//     behind that recomputation.  All workgroups fold the same words, so they take the same decision.
+//   mlp_recompute_resident, mlp_chain_resident : Algorithm 2 for a group of steps in two launches: all steps' stages side
+//     by side, then the cotangent chains one after the other.  50 -> 200 -> 200 -> 50, bf16, 1003 rows (63 tiles), 20
+//     Heun steps with the time-grid gradient: 213 us in one kernel, pass 414 -> 347 us
+//   mlp_adjoint_resident : the same in one launch (tiles that fill the device, single steps)
+//     Both also under overflow detection.  The scale is the only thing that couples tiles between steps.  Every
+//     workgroup posts max|a| and its overflow flag of a step as ONE 64-bit word (payload and tag together: no fence, no
+//     second round trip).  It reads the others' words when it needs the next step's scale, which in one launch is not
+//     before its last stage has been recomputed; the chain alone goes on with the scale at hand and looks after one
+//     stage.  All workgroups fold the same words, so they take the same decision.
 //
 // The waits need the workgroups of a launch to run at the same time; the host launches no more of them than the device
 // holds.  If others occupy the device (another stream's kernels), a wait ends after kWaitTicks, the launch raises
@@ -512,6 +516,370 @@ struct StepExchange {
     }
   }
 };
+
+// ---------------------------------------------------------------------------------------
+// Stage recomputation of the g.nsteps steps g.step, g.step - 1, ... from their stored states: stage inputs and hidden
+// activations into the steps' buffer sets.  The stored states are all known, so steps x tiles run side by side; a
+// workgroup takes every gridDim.x-th of them and loads its weight slices once.  TG: also the slopes (g.KT), for the
+// time-grid terms of the chain.
+template <class T, int L, int HP, int MT, bool TG>
+__global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_recompute_resident(ResidentArgs ra) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  using Sh = ResidentShape<L, HP>;
+  const FusedArgs& g = ra.f;
+  if (g.ctl->poison) return;
+  ResidentLds<L, HP> lds((lds_u16*)smem, MT);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lm = lane & 15, lq = lane >> 4;
+  constexpr int TPW = Sh::TPW, TM = 16 * MT;
+  const int s = g.s;
+  const int ns = wave * 16 + lq * 4, nh = wave * TPW * 16 + lq * 4;
+  lds_u16* const buf[2] = {lds.tiles, lds.tiles + TM * Sh::LDP};
+  const int tiles = (int)((g.R + TM - 1) / TM), total = tiles * g.nsteps;
+  const size_t tile_bytes = (size_t)g.ldk * 32, stage_bytes = (size_t)g.Rp * 8;
+
+  ResidentWeights<L, HP> w;
+  w.template load<true, MT == 1 ? 14 : 12>(g, wave, lane);
+  lds.fill(g);
+  uint2 yh_next[MT];
+  auto fetch_state = [&](int idx) __attribute__((always_inline)) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      yh_next[mt] = load_state(g.ckpt + (size_t)(g.step - idx / tiles) * g.ckpt_stride, (int64_t)(idx % tiles) * TM + mt * 16 + lm, g.R, ns, g.d);
+  };
+  fetch_state(min((int)blockIdx.x, total - 1));
+#pragma unroll 1
+  for (int idx = blockIdx.x; idx < total; idx += gridDim.x) {
+    const int step = g.step - idx / tiles;
+    const int64_t row0 = (int64_t)(idx % tiles) * TM;
+    const float* st = g.steptab + (size_t)step * (1 + s);
+    const float h = st[0];
+    float tau[kResidentStages];
+#pragma unroll
+    for (int j = 0; j < kResidentStages; ++j) tau[j] = st[1 + min(j, s - 1)];
+    const int64_t set_off = (int64_t)(step % g.nsets) * g.set_stride;
+    char* const ZT = (char*)(g.ZT + set_off);
+    const uint32_t off_h = (uint32_t)(((size_t)(nh >> 2) * g.ldk + row0 + lm) * 8);
+    const uint32_t off_s = (uint32_t)(((size_t)(ns >> 2) * g.ldk + row0 + lm) * 8);
+    uint32_t mask[MT];
+    float yh[MT][4];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      mask[mt] = row0 + mt * 16 + lm < g.R ? 0xFFFFFFFFu : 0u;
+      unpack4<T>(yh_next[mt], yh[mt]);
+      lds_store_u2(&lds.z[(mt * 16 + lm) * Sh::LDZ + ns], yh_next[mt]);
+      store_word(ZT, off_s + mt * 128, yh_next[mt], mask[mt]);
+    }
+    __syncthreads();
+    fetch_state(min(idx + (int)gridDim.x, total - 1));
+    auto store_act = [&](const f32x4 (&acc)[TPW][MT], int j, int l) __attribute__((always_inline)) {
+      char* gout = (char*)(g.ACTT[l] + set_off) + j * stage_bytes;
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = tanh_fast(acc[t][mt][r]);
+          const uint2 q = pack4<T>(v);
+          lds_store_u2(&buf[l & 1][(mt * 16 + lm) * Sh::LDP + nh + t * 16], q);
+          store_word(gout + t * tile_bytes, off_h + mt * 128, q, mask[mt]);
+        }
+    };
+    f32x4 acc[TPW][MT];
+#pragma unroll 1
+    for (int j = 0; j < s; ++j) {
+      const bool last_stage = j + 1 == s;
+      init_acc_time(acc, lds.bias, lds.wt, j == 0 ? tau[0] : j == 1 ? tau[1] : j == 2 ? tau[2] : tau[3], nh);
+      resident_mma<T, MT>(acc, w.first, lds.z, Sh::LDZ, lane);
+      store_act(acc, j, 0);
+      f32x4 ks[MT];
+      const f32x4 bl = *(const RAMPDE_LDS f32x4*)(lds.bias + (L - 1) * HP + ns);
+      const f32x4 cf = *(const RAMPDE_LDS f32x4*)(lds.coef + j * 4);
+#pragma unroll
+      for (int m = 0; m < Sh::MIDS; ++m) {
+        init_acc(acc, lds.bias + (m + 1) * HP, nh);
+        __syncthreads();
+        resident_mma<T, MT>(acc, w.mid[m], buf[m & 1], Sh::LDP, lane);
+        store_act(acc, j, m + 1);
+      }
+      if (last_stage && !TG) break;  // (the slope of the last stage is not needed)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) ks[mt] = bl;
+      __syncthreads();
+      resident_mma_state<T, MT>(ks, w.last, buf[Sh::MIDS & 1], Sh::LDP, lane);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const float v[4] = {ks[mt][0], ks[mt][1], ks[mt][2], ks[mt][3]};
+        const uint2 q = pack4<T>(v);
+        float kf[4], z[4];
+        unpack4<T>(q, kf);
+        if constexpr (TG) store_word((char*)(g.KT + set_off) + j * stage_bytes, off_s + mt * 128, q, mask[mt]);
+        if (!last_stage) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) z[r] = fmaf(h, cf[0] * kf[r], yh[mt][r]);
+          const uint2 zq = pack4<T>(z);
+          lds_store_u2(&lds.z[(mt * 16 + lm) * Sh::LDZ + ns], zq);
+          store_word(ZT + (j + 1) * stage_bytes, off_s + mt * 128, zq, mask[mt]);
+        }
+      }
+      __syncthreads();
+    }
+    __syncthreads();  // (the stage-input tile and the ping-pong tiles are free again)
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// The cotangent chain of a group of adjoint steps of a tile, from the stages that mlp_recompute_resident has stored.
+// A step's scale depends on the outcome of the step before, which takes an exchange between all workgroups: the step
+// starts with the scale at hand and looks at the outcome after its first stage; where that changed the scale, the stage
+// is redone (everything that it has written is written again).
+template <class T, int L, int HP, int MT, bool TG>
+__global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_chain_resident(ResidentArgs ra) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  using Sh = ResidentShape<L, HP>;
+  const FusedArgs& g = ra.f;
+  if (g.ctl->poison) return;
+  ResidentLds<L, HP> lds((lds_u16*)smem, MT);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lm = lane & 15, lq = lane >> 4;
+  constexpr int TPW = Sh::TPW, TM = 16 * MT;
+  const int64_t row0 = (int64_t)blockIdx.x * TM;
+  const int s = g.s;
+  const int ns = wave * 16 + lq * 4, nh = wave * TPW * 16 + lq * 4;
+
+  ResidentWeights<L, HP> wb;
+  wb.template load<false, MT == 1 ? 14 : 12>(g, wave, lane);
+  lds.fill(g);
+  StepExchange ex(ra);
+  float av[MT][4], a_old[MT][4];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) load4f(g.a_in, row0 + mt * 16 + lm, g.R, ns, g.d, av[mt]);
+  // lane offsets (bytes) into the feature-group-major arrays: hidden and state columns, and the batch-row masks
+  const uint32_t off_h = (uint32_t)(((size_t)(nh >> 2) * g.ldk + row0 + lm) * 8);
+  const uint32_t off_s = (uint32_t)(((size_t)(ns >> 2) * g.ldk + row0 + lm) * 8);
+  const size_t tile_bytes = (size_t)g.ldk * 32;  // 16 columns further
+  const size_t stage_bytes = (size_t)g.Rp * 8;
+  uint32_t mask[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) mask[mt] = row0 + mt * 16 + lm < g.R ? 0xFFFFFFFFu : 0u;
+  // activations at the lane's own elements, requested a stage ahead
+  uint2 act[L - 1][TPW][MT];
+  auto fetch_act = [&](uint2 (&q)[L - 1][TPW][MT], int step, int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int l = 0; l < L - 1; ++l) {
+      const char* base = (const char*)(g.ACTT[l] + (int64_t)(step % g.nsets) * g.set_stride) + j * stage_bytes;
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) q[l][t][mt] = *reinterpret_cast<const uint2*>(base + t * tile_bytes + (off_h + mt * 128));
+    }
+  };
+  fetch_act(act, g.step, s - 1);
+  // cotangents of hidden layer l
+  auto tile = [&](int l) __attribute__((always_inline)) { return lds.tiles + (size_t)l * TM * Sh::LDP; };
+  float h_next = g.steptab[(size_t)g.step * (1 + s)];
+  __syncthreads();
+
+  bool rejected = false;
+#pragma unroll 1
+  for (int it = 0; it < g.nsteps; ++it) {
+    const int step = g.step - it, step_next = it + 1 < g.nsteps ? step - 1 : step;
+    const int64_t set_off = (int64_t)(step % g.nsets) * g.set_stride;
+    char* const KBART = (char*)(g.KBART + set_off);
+    const float h = h_next;
+    h_next = g.steptab[(size_t)step_next * (1 + s)];
+    float t_phia = 0.f, t_dt = 0.f, t_dh = 0.f;
+    uint2 k[TG ? kResidentStages : 1][MT];  // slopes
+    if constexpr (TG) {
+#pragma unroll
+      for (int j = 0; j < kResidentStages; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          k[j][mt] = *reinterpret_cast<const uint2*>((const char*)(g.KT + set_off) + min(j, s - 1) * stage_bytes + (off_s + mt * 128));
+    }
+    uint32_t big = 0;  // largest magnitudes of the step's cotangents
+    uint2 lamq[MT];
+    float zf[MT][4];  // cotangent of the stage input behind the slope at hand
+    float da[MT][4];
+    // cotangent of the slope of stage j:  kbar_j = Q( b_j lambda + h a_{j+1,j} zbar_{j+1} )
+    auto make_kbar = [&](int j) __attribute__((always_inline)) {
+      const f32x4 cf = *(const RAMPDE_LDS f32x4*)(lds.coef + j * 4);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        float lam[4], v[4];
+        unpack4<T>(lamq[mt], lam);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fmaf(h, cf[0] * zf[mt][r], cf[1] * lam[r]);
+        const uint2 q = pack4<T>(v);
+        track(big, q);
+        lds_store_u2(&lds.z[(mt * 16 + lm) * Sh::LDZ + ns], q);
+        store_word(KBART + j * stage_bytes, off_s + mt * 128, q, mask[mt]);
+      }
+    };
+    auto start = [&]() __attribute__((always_inline)) {
+      big = 0;
+      t_dt = t_dh = 0.f;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        float sa[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sa[r] = ex.S * av[mt][r];
+        lamq[mt] = pack4<T>(sa);
+        track(big, lamq[mt]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) da[mt][r] = zf[mt][r] = 0.f;
+      }
+      make_kbar(s - 1);
+      __syncthreads();
+    };
+    start();
+
+    f32x4 acc[TPW][MT];
+    auto store_delta = [&](int j, int l) __attribute__((always_inline)) {
+      lds_u16* io = tile(l);
+      char* gout = (char*)(g.DELTAT[l] + set_off) + j * stage_bytes;
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          float a[4], v[4];
+          unpack4<T>(act[l][t][mt], a);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = acc[t][mt][r] * (1.f - a[r] * a[r]);
+          uint2 q = pack4<T>(v);
+          q.x &= mask[mt];
+          q.y &= mask[mt];
+          if constexpr (TG) {
+            if (l == 0) {
+              float dv[4];
+              unpack4<T>(q, dv);
+              const float4 tv = lds_load_f4(&lds.wt[nh + t * 16]);
+              const float tb = dv[0] * tv.x + dv[1] * tv.y + dv[2] * tv.z + dv[3] * tv.w;
+              t_dt += tb;
+              t_dh = fmaf(lds.coef[j * 4 + 2], tb, t_dh);
+            }
+          }
+          lds_store_u2(&io[(mt * 16 + lm) * Sh::LDP + nh + t * 16], q);
+          *reinterpret_cast<uint2*>(gout + t * tile_bytes + (off_h + mt * 128)) = q;
+          track(big, q);
+        }
+    };
+    bool open = it > 0 && g.detect;  // the outcome of the step before is not known yet
+#pragma unroll 1
+    for (int j = s - 1; j >= 0;) {
+      // (the next stage's activations: see StepRows)
+      uint2 act_next[L - 1][TPW][MT];
+      fetch_act(act_next, j > 0 ? step : step_next, j > 0 ? j - 1 : s - 1);
+      zero_acc(acc);
+      resident_mma<T, MT>(acc, wb.first, lds.z, Sh::LDZ, lane);
+      store_delta(j, L - 2);
+#pragma unroll
+      for (int m = Sh::MIDS - 1; m >= 0; --m) {
+        __syncthreads();
+        zero_acc(acc);
+        resident_mma<T, MT>(acc, wb.mid[m], tile(m + 1), Sh::LDP, lane);
+        store_delta(j, m);
+      }
+      __syncthreads();
+      f32x4 zs[MT];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) zs[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      resident_mma_state<T, MT>(zs, wb.last, tile(0), Sh::LDP, lane);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const float v[4] = {zs[mt][0], zs[mt][1], zs[mt][2], zs[mt][3]};
+        uint2 q = pack4<T>(v);
+        q.x &= mask[mt];
+        q.y &= mask[mt];
+        track(big, q);
+        unpack4<T>(q, zf[mt]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) da[mt][r] += zf[mt][r];
+        if constexpr (TG) {
+          if (j > 0) {
+            const float a = lds.coef[j * 4 + 3];
+            float kl[4];
+            unpack4<T>(j == 1 ? k[0][mt] : j == 2 ? k[1][mt] : k[2][mt], kl);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) t_dh = fmaf(a * kl[r], zf[mt][r], t_dh);
+          }
+        }
+      }
+      if (open) {
+        open = false;
+        const float used = ex.S;
+        if (!ex.template decide<T>(g, step + 1)) {
+          rejected = true;
+          break;
+        }
+        if (ex.S != used) {
+          start();
+          continue;
+        }
+      }
+      if (j > 0) {
+        make_kbar(j - 1);
+        __syncthreads();
+      }
+#pragma unroll
+      for (int l = 0; l < L - 1; ++l)
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            asm volatile("" : "+v"(act_next[l][t][mt].x), "+v"(act_next[l][t][mt].y));
+            act[l][t][mt] = act_next[l][t][mt];
+          }
+      --j;
+    }
+    if (rejected) break;
+
+    // ---- a <- a + (h / S) sum_j zbar_j (+ running-cost cotangent), fp32
+    const float hs = h / ex.S;
+    if constexpr (TG) {
+#pragma unroll
+      for (int j = 0; j < kResidentStages; ++j)
+        if (j < s) {
+          const float b = lds.coef[j * 4 + 1];
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            float kf[4];
+            unpack4<T>(k[j][mt], kf);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) t_phia = fmaf(b * kf[r], av[mt][r], t_phia);
+          }
+        }
+      block_sum2(fmaf(hs, t_dt - t_dh, -t_phia), fmaf(hs, t_dh, t_phia), g.tpart + 2 * ((size_t)it * gridDim.x + blockIdx.x));
+    }
+    unsigned bits = 0;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      float gy[4] = {0.f, 0.f, 0.f, 0.f};
+      if (g.gys) load4f(g.gys - (int64_t)it * g.gys_stride, row0 + mt * 16 + lm, g.R, ns, g.d, gy);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        a_old[mt][r] = av[mt][r];
+        av[mt][r] = fmaf(hs, da[mt][r], av[mt][r]) + gy[r];
+        if (g.round_incr & 2) av[mt][r] = Low<T>::to_f32(Low<T>::from_f32(av[mt][r]));
+        const unsigned bb = __builtin_bit_cast(unsigned, fabsf(av[mt][r]));
+        if (mask[mt] && ns + r < g.d) bits = max(bits, bb);
+      }
+    }
+    if (g.detect) ex.post(g, step, bits, tracked_nonfinite<T>(big));
+    else ex.template decide<T>(g, step);
+  }
+  if (g.detect && !rejected) rejected = !ex.template decide<T>(g, g.step - g.nsteps + 1);
+  if (ex.stalled) return;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    // (a rejected step leaves the adjoint as it was before it)
+    if (rejected) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) av[mt][r] = a_old[mt][r];
+    }
+    store4f(g.a_out, row0 + mt * 16 + lm, g.R, ns, g.d, av[mt]);
+  }
+  ex.finish(g);
+}
 
 // ---------------------------------------------------------------------------------------
 // A group of adjoint steps of a tile.  PHASED: the forward and the transposed slices do not fit in the registers

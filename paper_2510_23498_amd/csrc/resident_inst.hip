@@ -16,7 +16,7 @@ constexpr int HP = RAMPDE_INST_HP;
 
 template <class Kern>
 hipError_t launch_kernel(Kern kern, const ResidentLaunch& l, const ResidentArgs& a) {
-  const size_t lds = resident_lds_bytes(HP, a.f.L, a.f.s, l.MT, l.adjoint != 0);
+  const size_t lds = l.kind == kResidentAdjoint ? resident_lds_bytes(HP, a.f.L, a.f.s, l.MT, true) : resident_lds_bytes(HP, a.f.L, 0, l.MT, false);
   if (lds > 48 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -30,7 +30,11 @@ hipError_t pick_kernel(const ResidentLaunch& l, const ResidentArgs& a) {
   // forward and transposed weight slices together: 384 of 512 registers at three layers of 256, 640 at four; 192 of
   // 256 at four layers of 128
   constexpr bool phased = (HP == 256 && (L == 4 || MT == 2)) || (HP == 128 && L == 4);
-  if (!l.adjoint) return launch_kernel(mlp_forward_resident<T, L, HP, MT>, l, a);
+  if (l.kind == kResidentForward) return launch_kernel(mlp_forward_resident<T, L, HP, MT>, l, a);
+  if (l.kind == kResidentRecompute)
+    return a.f.KT ? launch_kernel(mlp_recompute_resident<T, L, HP, MT, true>, l, a) : launch_kernel(mlp_recompute_resident<T, L, HP, MT, false>, l, a);
+  if (l.kind == kResidentChain)
+    return a.f.KT ? launch_kernel(mlp_chain_resident<T, L, HP, MT, true>, l, a) : launch_kernel(mlp_chain_resident<T, L, HP, MT, false>, l, a);
   if (a.f.tpart) return launch_kernel(mlp_adjoint_resident<T, L, HP, MT, true, phased>, l, a);
   return launch_kernel(mlp_adjoint_resident<T, L, HP, MT, false, phased>, l, a);
 }

@@ -7,8 +7,9 @@
 
 namespace rampde {
 
+enum ResidentKind { kResidentForward, kResidentAdjoint, kResidentRecompute, kResidentChain };
 struct ResidentLaunch {
-  int adjoint;
+  ResidentKind kind;
   int bf16;
   int MT;        // row tile = 16 MT rows; 2 only at hidden width 256
   unsigned grid;
@@ -32,10 +33,11 @@ inline hipError_t resident_launch(int hp, const ResidentLaunch& l, const Residen
   }
 }
 
-// LDS of a launch: s * (L - 1) activation tiles in the adjoint kernel, two ping-pong tiles in the forward kernel
+// LDS of a launch: s * (L - 1) activation tiles in the adjoint kernel, two ping-pong tiles (three in the chain of
+// four layers) in the others
 inline size_t resident_lds_bytes(int hp, int L, int s, int MT, bool adjoint) {
   const size_t param = ((size_t)hp * L + 64 + 32) * 4, rows = 16 * (size_t)MT;
-  const size_t tiles = adjoint ? (size_t)s * (L - 1) : 2;
+  const size_t tiles = adjoint ? (size_t)s * (L - 1) : L > 2 ? L - 1 : 2;
   const size_t last = adjoint && hp >= 128 && L >= 3 && MT == 1 ? 64 * (size_t)hp * 2 : 0;  // (the transposed last slice)
   return param + 2 * rows * (64 + 8 + tiles * (hp + 8)) + last;
 }

@@ -542,3 +542,44 @@ def test_stages_recomputed_ahead_equal_those_recomputed_inside(widths, B, N, low
         tol = 1e-4 if gain == 1.0 else par.TOL_EMUL
         assert par.rel_err(got["grad_y0"], one["grad_y0"]) <= tol
         assert par.rel_err(got["grad_theta"], one["grad_theta"]) <= tol
+
+
+@pytest.mark.parametrize("widths,B,low,tab", [
+    ((64, 256, 256, 64), 300, "f16", "rk4"),         # scale changes in mid-group: the first stage of a step is redone
+    ((30, 128, 100, 90, 30), 17, "f16", "heun"),
+    ((7, 33, 7), 1, "bf16", "euler"),
+    ((64, 256, 256, 200, 64), 4113, "bf16", "rk4"),  # 32-row tiles, the last one with one row
+])
+def test_stages_recomputed_ahead_of_the_register_resident_chain(widths, B, low, tab):
+    # one step per group runs in one kernel; the same sums in the same order, gradients of the time grid included
+    cfg, theta, y0, target = _gain_case("cfg2", name="ahead_res", widths=widths, B=B, N=9, t1=0.135, low=low, tableau=tab,
+                                        gain=64.0, scaling="dynamic" if low == "f16" else "none")
+    for want_t in (False, True):
+        one = par.run_gpu(cfg, theta, y0, target, step_group=1, want_grad_t=want_t)
+        for group in (0, 4):
+            got = par.run_gpu(cfg, theta, y0, target, step_group=group, want_grad_t=want_t)
+            assert got["retries"] == one["retries"]
+            np.testing.assert_array_equal(got["scale_hist"], one["scale_hist"])
+            # (fp16: see test_stages_recomputed_ahead_equal_those_recomputed_inside)
+            for key in ("grad_y0", "grad_theta") + (("grad_t",) if want_t else ()):
+                assert par.rel_err(got[key], one[key]) <= (1e-5 if low == "bf16" else par.TOL_EMUL), key
+    if B == 300:
+        assert one["retries"] > 0
+
+
+def test_scale_that_grows_within_a_launch_of_the_register_resident_chain():
+    # v = -32 tanh(y) per component, close to y = 0: the adjoint shrinks by a constant factor from step to step, so the scale
+    # that a step starts with is often the one before its doubling, and its first stage is redone
+    cfg = wl.CONFIGS["cfg1"].with_(name="shrink", widths=(16, 64, 16), B=40, N=12, t1=12.0 / 64, low="f16", scaling="dynamic", loss="mse")
+    theta, y0, target = par.make_inputs(cfg)
+    theta = np.zeros_like(theta)
+    for name, shp, off in wl.theta_layout(cfg):
+        if name == "W1":
+            theta[off:off + 64 * 17].reshape(64, 17)[:, :16] = np.tile(np.eye(16), (4, 1))
+        elif name == "W2":
+            theta[off:off + 16 * 64].reshape(16, 64)[:] = -8.0 * np.tile(np.eye(16), (1, 4))
+    gpu = par.run_gpu(cfg, theta, y0 * 0.01, target)
+    emu = par.run_oracle(cfg, theta, y0 * 0.01, target, "emul")
+    assert emu["scale_hist"][0] >= 16 * emu["scale_hist"][-1]
+    np.testing.assert_array_equal(gpu["scale_hist"].astype(np.float64), emu["scale_hist"])
+    par.compare(cfg, gpu, emu, par.TOL_EMUL, "emulation oracle")
