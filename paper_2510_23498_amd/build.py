@@ -46,7 +46,7 @@ _DEPS = {
                    os.path.join("..", "..", "include", "rampde.h")),
     "fused_inst.hip": ("common.hpp", "fused.hpp", "fused_launch.hpp"),
     "resident_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "resident_launch.hpp"),
-    "shallow_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "shallow.hpp", "shallow_launch.hpp"),
+    "shallow_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "resident_launch.hpp", "shallow.hpp", "shallow_launch.hpp"),
     "cluster_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "cluster.hpp", "cluster_launch.hpp"),
     "wide_inst.hip": ("common.hpp", "fused.hpp", "fused_launch.hpp", "wide.hpp"),
 }

@@ -1209,25 +1209,28 @@ struct Runner {
   // unit) 561 / 579; four layers of 256, 4000 rows 886 / 808; 2 -> 32 -> 32 -> 2, f16, 256 rows, 8 steps 237 / 222;
   // 50 -> 200 -> 200 -> 50 with the time-grid gradient, 1003 rows, Heun 414 / 347.
   bool resident_ahead() const {
-    if (!p.resident || p.shallow || p.step_group < 2) return false;
+    if (!p.resident || p.step_group < 2) return false;
+    // (one hidden layer: flow of 63 features, width 1024, f16, 512 rows 793 / 584, 4096 rows 1462 / 1411; 128 -> 512 -> 128,
+    // bf16, 1000 rows 550 / 399, 16000 rows 2578 / 2308; flow of 10 features, width 100, 8000 rows 705 / 710)
+    if (p.shallow) return p.resident > 128 || 8 * (int64_t)blocks_for(p.R, 16) <= 7 * 2 * (int64_t)device_compute_units();
     const int64_t slots = (int64_t)device_compute_units() * (p.resident == 256 ? 1 : 2), tiles = blocks_for(p.R, 16 * p.MT);
     return p.MT == 2 || p.L == 4 || 8 * tiles <= 7 * slots;
   }
 
-  // kind: of the kernels of resident.hpp (of shallow.hpp: forward or adjoint)
   int launch_resident(ResidentKind kind, const FusedArgs& a) {
-    const bool adjoint = kind != kResidentForward;
     ResidentArgs ra{};
     ra.f = a;
     ra.slots = p.slots ? (unsigned long long*)(ws + p.slots) : nullptr;
     ra.wait_ticks = wait_ticks;
     if (p.shallow) {
       ShallowLaunch l{};
-      l.adjoint = adjoint ? 1 : 0;
+      l.kind = kind;
       l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
       l.NTL = p.dpad / 64;
       l.trace = p.cnf ? 1 : 0;
       l.grid = blocks_for(p.R, 16);
+      // (two wavefronts per SIMD: one workgroup of eight or two of four on a compute unit)
+      if (kind == kResidentRecompute) l.grid = (unsigned)std::min<int64_t>((int64_t)l.grid * a.nsteps, (int64_t)device_compute_units() * (p.resident <= 128 ? 2 : 1));
       l.stream = st;
       ShallowArgs sa{};
       sa.r = ra;

@@ -11,10 +11,11 @@
 //
 // Bound: tanh (and the trace's two multiply-adds) on 16 rows x 1024 columns per compute unit, 1.3 us per evaluation,
 // plus the exchange; a tile per 16 rows, so 512 rows occupy 32 compute units.  At 1024 columns the forward and the
-// transposed slices (128 registers each) do not fit together: the recomputation and the cotangent chain of a step load
-// their own (2 x 256 KB from L2 per step).  The steps of a pass run in one launch as in resident.hpp, scale exchange
-// included.  Measured on flows of 63 features, width 1024, fp16, 16 RK4 steps of 512 rows: 812 to 836 us per
-// pass; one launch per layer, 900 launches, 6456 to 6514 us.
+// transposed slices (128 registers each) do not fit together, and in one kernel the recomputation and the cotangent
+// chain of a step load their own (2 x 256 KB from L2 per step).  So a group of steps runs in two launches as in
+// resident.hpp, scale exchange included: all stages side by side, then the chain; the one-launch kernel is left to
+// single steps and to tiles of narrow networks that fill the device.  Measured on flows of 63 features, width 1024,
+// fp16, 16 RK4 steps of 512 rows: 793 -> 584 us per pass; one launch per layer, 900 launches, 6456 to 6514 us.
 #pragma once
 #include "resident.hpp"
 
@@ -300,6 +301,296 @@ __global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) v
     }
   }
   store_elems(g.y, row, g.R, ec, g.d, y);
+}
+
+// Stage recomputation of the g.nsteps steps g.step, g.step - 1, ... (the counterpart of mlp_recompute_resident).
+template <class T, int NTL, int HP, bool TRACE>
+__global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) void mlp_recompute_shallow(ShallowArgs sa) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  using Sh = ShallowShape<NTL, HP>;
+  using Tile = ShallowTile<T, NTL, HP>;
+  constexpr int EPT = Sh::EPT;
+  const FusedArgs& g = sa.r.f;
+  if (g.ctl->poison) return;
+  ShallowLds l;
+  l.carve<NTL, HP>((lds_u16*)smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lm = lane & 15;
+  const int nh = wave * Sh::TPW * 16 + (lane >> 4) * 4;
+  const int er = tid / (Sh::NT / 16), ec = (tid % (Sh::NT / 16)) * EPT;
+  const int s = g.s, tiles = (int)((g.R + 15) / 16), total = tiles * g.nsteps;
+  const size_t tile_bytes = (size_t)g.ldk * 32, stage_bytes = (size_t)g.Rp * 8;
+  const bool copies = tid < 256 * NTL;  // (threads that copy a word of the stage-input tile, see mlp_chain_shallow)
+  typename Tile::Weights w;
+  w.template load<false>(g.layer[0].Wf, g.layer[1].Wf, wave, lane);
+  Tile::fill(sa, l, TRACE);
+  uint16_t yh_next[EPT];
+  auto fetch_state = [&](int idx) __attribute__((always_inline)) {
+    load_elems_clamped(g.ckpt + (size_t)(g.step - idx / tiles) * g.ckpt_stride, (int64_t)(idx % tiles) * 16 + er, g.R, ec, g.d, yh_next);
+  };
+  fetch_state(min((int)blockIdx.x, total - 1));
+  __syncthreads();
+  float b2[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) b2[e] = l.b2[ec + e];
+#pragma unroll 1
+  for (int idx = blockIdx.x; idx < total; idx += gridDim.x) {
+    const int step = g.step - idx / tiles;
+    const int64_t row0 = (int64_t)(idx % tiles) * 16;
+    const float* st = g.steptab + (size_t)step * (1 + s);
+    const float h = st[0];
+    float taus[kResidentStages];
+#pragma unroll
+    for (int j = 0; j < kResidentStages; ++j) taus[j] = st[1 + min(j, s - 1)];
+    const int64_t set_off = (int64_t)(step % g.nsets) * g.set_stride;
+    char* const ZT = (char*)(g.ZT + set_off);
+    char* const ACTT = (char*)(g.ACTT[0] + set_off);
+    const uint32_t off_h = (uint32_t)(((size_t)(nh >> 2) * g.ldk + row0 + lm) * 8);
+    const uint32_t mask = row0 + lm < g.R ? 0xFFFFFFFFu : 0u;
+    const uint32_t off_z = (uint32_t)(((size_t)(tid >> 4) * g.ldk + row0 + (tid & 15)) * 8);
+    const uint32_t mask_z = row0 + (tid & 15) < g.R ? 0xFFFFFFFFu : 0u;
+    float yh[EPT];
+    uint16_t q[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      q[e] = yh_next[e];
+      yh[e] = Low<T>::to_f32(q[e]);
+    }
+    put_z(l.z + er * Sh::LDZ + ec, q);
+    __syncthreads();
+    fetch_state(min(idx + (int)gridDim.x, total - 1));
+#pragma unroll 1
+    for (int j = 0; j < s; ++j) {
+      const float tau = j == 0 ? taus[0] : j == 1 ? taus[1] : j == 2 ? taus[2] : taus[3];
+      u16x8 a[Sh::KS];
+      Tile::read_z(a, l.z, lane);
+      if (copies) store_word(ZT + j * stage_bytes, off_z, lds_load_u2(l.z + (tid & 15) * Sh::LDZ + (tid >> 4) * 4), mask_z);
+      f32x4 out[Sh::NS];
+#pragma unroll
+      for (int n = 0; n < Sh::NS; ++n) out[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      float tr = 0.f;
+      char* gout = ACTT + j * stage_bytes;
+#pragma unroll
+      for (int p = 0; p < Sh::KP; ++p) {
+        f32x4 acc[2];
+        Tile::start(acc, l, tau, nh, p);
+        Tile::pre(acc, w, a, p);
+        uint2 hq[2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = tanh_fast(acc[hh][r]);
+          hq[hh] = pack4<T>(v);
+          store_word(gout + (2 * p + hh) * tile_bytes, off_h, hq[hh], mask);
+          if constexpr (TRACE) {
+            const f32x4 c = *(const RAMPDE_LDS f32x4*)(l.cf + nh + (2 * p + hh) * 16);
+            unpack4<T>(hq[hh], v);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tr = fmaf(c[r], fmaf(-v[r], v[r], 1.f), tr);
+          }
+        }
+        const u16x8 op = Tile::operand(hq[0], hq[1]);
+#pragma unroll
+        for (int n = 0; n < Sh::NS; ++n) out[n] = Low<T>::mfma16(w.V[n][p], op, out[n]);
+      }
+      if (j + 1 == s) break;  // (the slope of the last stage is not needed)
+      Tile::put_part(out, l, wave, lane);
+      if constexpr (TRACE) Tile::put_trace(tr, l, wave, lane);
+      const float cz = l.coef[j * 4];
+      __syncthreads();
+      float v[EPT];
+      Tile::sum_parts(v, l, er, ec);
+      float trace = 0.f;
+      if constexpr (TRACE) trace = Tile::trace_of(l, er);
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        float k = v[e] + b2[e];
+        if constexpr (TRACE) k = ec + e == g.d - 1 ? -trace : k;
+        k = Low<T>::to_f32(Low<T>::from_f32(k));
+        q[e] = Low<T>::from_f32(fmaf(h, cz * k, yh[e]));
+      }
+      put_z(l.z + er * Sh::LDZ + ec, q);
+      __syncthreads();
+    }
+    __syncthreads();  // (the stage-input tile is free again)
+  }
+}
+
+// The cotangent chain of a group of adjoint steps of a tile, without the time-grid gradient (the counterpart of
+// mlp_chain_resident: the outcome of the step before is looked at after a step's first stage).  Activations are requested
+// a stage ahead.
+template <class T, int NTL, int HP, bool TRACE>
+__global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) void mlp_chain_shallow(ShallowArgs sa) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  using Sh = ShallowShape<NTL, HP>;
+  using Tile = ShallowTile<T, NTL, HP>;
+  constexpr int EPT = Sh::EPT;
+  const FusedArgs& g = sa.r.f;
+  if (g.ctl->poison) return;
+  ShallowLds l;
+  l.carve<NTL, HP>((lds_u16*)smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lm = lane & 15;
+  const int nh = wave * Sh::TPW * 16 + (lane >> 4) * 4;
+  const int er = tid / (Sh::NT / 16), ec = (tid % (Sh::NT / 16)) * EPT;
+  const int64_t row0 = (int64_t)blockIdx.x * 16, row = row0 + er;
+  const int s = g.s;
+  StepExchange ex(sa.r);
+
+  typename Tile::Weights wb;
+  wb.template load<false>(g.layer[1].WTf, g.layer[0].WTf, wave, lane);
+  Tile::fill(sa, l, TRACE);
+  const uint32_t off_h = (uint32_t)(((size_t)(nh >> 2) * g.ldk + row0 + lm) * 8);
+  const size_t tile_bytes = (size_t)g.ldk * 32, stage_bytes = (size_t)g.Rp * 8;
+  const uint32_t mask = row0 + lm < g.R ? 0xFFFFFFFFu : 0u;
+  const uint32_t emask = row < g.R ? 0xFFFFu : 0u;
+  // the 8-byte word of the state-shaped operand arrays that this thread copies out of the stage-input tile
+  const bool copies = tid < 256 * NTL;
+  const uint32_t off_z = (uint32_t)(((size_t)(tid >> 4) * g.ldk + row0 + (tid & 15)) * 8);
+  const uint32_t mask_z = row0 + (tid & 15) < g.R ? 0xFFFFFFFFu : 0u;
+  float av[EPT], a_old[EPT];
+  load_elems(g.a_in, row, g.R, ec, g.d, av);
+  uint2 act[Sh::TPW];
+  auto fetch_act = [&](uint2 (&w)[Sh::TPW], int step, int j) __attribute__((always_inline)) {
+    const char* base = (const char*)(g.ACTT[0] + (int64_t)(step % g.nsets) * g.set_stride) + j * stage_bytes;
+#pragma unroll
+    for (int t = 0; t < Sh::TPW; ++t) w[t] = *reinterpret_cast<const uint2*>(base + t * tile_bytes + off_h);
+  };
+  fetch_act(act, g.step, s - 1);
+  float h_next = g.steptab[(size_t)g.step * (1 + s)];
+  __syncthreads();
+
+  bool rejected = false;
+#pragma unroll 1
+  for (int it = 0; it < g.nsteps; ++it) {
+    const int step = g.step - it, step_next = it + 1 < g.nsteps ? step - 1 : step;
+    const int64_t set_off = (int64_t)(step % g.nsets) * g.set_stride;
+    char* const KBART = (char*)(g.KBART + set_off);
+    char* const DELTAT = (char*)(g.DELTAT[0] + set_off);
+    const float h = h_next;
+    h_next = g.steptab[(size_t)step_next * (1 + s)];
+    uint32_t big = 0;
+    uint16_t q[EPT];
+    float lam[EPT], zf[EPT], da[EPT];
+    auto make_kbar = [&](int j) __attribute__((always_inline)) {
+      const float ca = l.coef[j * 4], cb = l.coef[j * 4 + 1];
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        q[e] = Low<T>::from_f32(fmaf(h, ca * zf[e], cb * lam[e]));
+        track(big, make_uint2(q[e], 0u));
+      }
+      put_z(l.z + er * Sh::LDZ + ec, q);
+    };
+    auto start = [&]() __attribute__((always_inline)) {
+      big = 0;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        const uint16_t lq = Low<T>::from_f32(ex.S * av[e]);
+        track(big, make_uint2(lq, 0u));
+        lam[e] = Low<T>::to_f32(lq);
+        zf[e] = da[e] = 0.f;
+      }
+      make_kbar(s - 1);
+      __syncthreads();
+    };
+    start();
+    bool open = it > 0 && g.detect;  // the outcome of the step before is not known yet
+#pragma unroll 1
+    for (int j = s - 1; j >= 0;) {
+      uint2 act_next[Sh::TPW];
+      fetch_act(act_next, j > 0 ? step : step_next, j > 0 ? j - 1 : s - 1);
+      u16x8 a[Sh::KS];
+      Tile::read_z(a, l.z, lane);
+      float kl = 0.f;
+      if constexpr (TRACE) kl = Low<T>::to_f32(l.z[lm * Sh::LDZ + g.d - 1]);
+      if (copies) store_word(KBART + j * stage_bytes, off_z, lds_load_u2(l.z + (tid & 15) * Sh::LDZ + (tid >> 4) * 4), mask_z);
+      f32x4 out[Sh::NS];
+#pragma unroll
+      for (int n = 0; n < Sh::NS; ++n) out[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      char* gout = DELTAT + j * stage_bytes;
+#pragma unroll
+      for (int p = 0; p < Sh::KP; ++p) {
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        Tile::pre(acc, wb, a, p);
+        uint2 dq[2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          float ac[4], v[4];
+          unpack4<T>(act[2 * p + hh], ac);
+          f32x4 c;
+          if constexpr (TRACE) c = *(const RAMPDE_LDS f32x4*)(l.cf + nh + (2 * p + hh) * 16);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            float x = acc[hh][r];
+            if constexpr (TRACE) x = fmaf(2.f * c[r] * ac[r], kl, x);
+            v[r] = x * (1.f - ac[r] * ac[r]);
+          }
+          dq[hh] = pack4<T>(v);
+          dq[hh].x &= mask;
+          dq[hh].y &= mask;
+          *reinterpret_cast<uint2*>(gout + (2 * p + hh) * tile_bytes + off_h) = dq[hh];
+          track(big, dq[hh]);
+        }
+        const u16x8 op = Tile::operand(dq[0], dq[1]);
+#pragma unroll
+        for (int n = 0; n < Sh::NS; ++n) out[n] = Low<T>::mfma16(wb.V[n][p], op, out[n]);
+      }
+      Tile::put_part(out, l, wave, lane);
+      __syncthreads();
+      float v[EPT];
+      Tile::sum_parts(v, l, er, ec);
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        const uint16_t zq = Low<T>::from_f32(v[e]) & (uint16_t)emask;
+        track(big, make_uint2(zq, 0u));
+        zf[e] = Low<T>::to_f32(zq);
+        da[e] += zf[e];
+      }
+      if (open) {
+        open = false;
+        const float used = ex.S;
+        if (!ex.template decide<T>(g, step + 1)) {
+          rejected = true;
+          break;
+        }
+        if (ex.S != used) {
+          start();
+          continue;
+        }
+      }
+      if (j > 0) make_kbar(j - 1);
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < Sh::TPW; ++t) {
+        asm volatile("" : "+v"(act_next[t].x), "+v"(act_next[t].y));
+        act[t] = act_next[t];
+      }
+      --j;
+    }
+    if (rejected) break;
+
+    // ---- a <- a + (h / S) sum_j zbar_j (+ running-cost cotangent), fp32
+    const float hs = h / ex.S;
+    unsigned bits = 0;
+    float gy[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) gy[e] = 0.f;
+    if (g.gys) load_elems(g.gys - (int64_t)it * g.gys_stride, row, g.R, ec, g.d, gy);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      a_old[e] = av[e];
+      av[e] = fmaf(hs, da[e], av[e]) + gy[e];
+      if (g.round_incr & 2) av[e] = Low<T>::to_f32(Low<T>::from_f32(av[e]));
+      if (row < g.R && ec + e < g.d) bits = max(bits, __builtin_bit_cast(unsigned, fabsf(av[e])));
+    }
+    if (g.detect) ex.post(g, step, bits, tracked_nonfinite<T>(big));
+    else ex.template decide<T>(g, step);
+  }
+  if (g.detect && !rejected) rejected = !ex.template decide<T>(g, g.step - g.nsteps + 1);
+  if (ex.stalled) return;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) av[e] = rejected ? a_old[e] : av[e];
+  store_elems(g.a_out, row, g.R, ec, g.d, av);
+  ex.finish(g);
 }
 
 // A group of adjoint steps of a tile (the counterpart of mlp_adjoint_resident; without the time-grid gradient).

@@ -16,7 +16,7 @@ constexpr int HP = RAMPDE_INST_HP;
 
 template <int NTL, class Kern>
 hipError_t launch_kernel(Kern kern, const ShallowLaunch& l, const ShallowArgs& a) {
-  const size_t lds = ShallowLds::bytes<NTL, HP>(l.adjoint != 0, a.r.f.s);
+  const size_t lds = ShallowLds::bytes<NTL, HP>(l.kind == kResidentAdjoint, a.r.f.s);
   if (lds > 48 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -25,17 +25,24 @@ hipError_t launch_kernel(Kern kern, const ShallowLaunch& l, const ShallowArgs& a
   return hipGetLastError();
 }
 
+template <class T, int NTL, bool TRACE>
+hipError_t pick_kind(const ShallowLaunch& l, const ShallowArgs& a) {
+  switch (l.kind) {
+    case kResidentForward: return launch_kernel<NTL>(mlp_forward_shallow<T, NTL, HP, TRACE>, l, a);
+    case kResidentRecompute: return launch_kernel<NTL>(mlp_recompute_shallow<T, NTL, HP, TRACE>, l, a);
+    case kResidentChain: return launch_kernel<NTL>(mlp_chain_shallow<T, NTL, HP, TRACE>, l, a);
+    default: return launch_kernel<NTL>(mlp_adjoint_shallow<T, NTL, HP, TRACE>, l, a);
+  }
+}
+
 // (plain networks up to 256 wide with up to 64 state columns are those of resident.hpp)
 template <class T>
 hipError_t pick(const ShallowLaunch& l, const ShallowArgs& a) {
-  if (l.NTL == 1 && l.trace)
-    return l.adjoint ? launch_kernel<1>(mlp_adjoint_shallow<T, 1, HP, true>, l, a) : launch_kernel<1>(mlp_forward_shallow<T, 1, HP, true>, l, a);
+  if (l.NTL == 1 && l.trace) return pick_kind<T, 1, true>(l, a);
   if constexpr (HP >= 512)
-    if (l.NTL == 1)
-      return l.adjoint ? launch_kernel<1>(mlp_adjoint_shallow<T, 1, HP, false>, l, a) : launch_kernel<1>(mlp_forward_shallow<T, 1, HP, false>, l, a);
+    if (l.NTL == 1) return pick_kind<T, 1, false>(l, a);
   if constexpr (HP == 256 || HP == 512)
-    if (l.NTL == 2 && !l.trace)
-      return l.adjoint ? launch_kernel<2>(mlp_adjoint_shallow<T, 2, HP, false>, l, a) : launch_kernel<2>(mlp_forward_shallow<T, 2, HP, false>, l, a);
+    if (l.NTL == 2 && !l.trace) return pick_kind<T, 2, false>(l, a);
   return hipErrorInvalidValue;
 }
 

@@ -2,12 +2,13 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "resident_launch.hpp"
 #include "shallow.hpp"
 
 namespace rampde {
 
 struct ShallowLaunch {
-  int adjoint;
+  ResidentKind kind;
   int bf16;
   int NTL;    // state width / 64 (padded)
   int trace;  // normalising flow with the trace row
