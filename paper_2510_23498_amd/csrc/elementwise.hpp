@@ -150,36 +150,21 @@ __global__ void combine_store(float* __restrict__ y, const uint16_t* __restrict_
 // ------------------------------------------------------------------------- backward
 // also marks every step "not accepted yet" (scale 0): a step's parameter-gradient kernel runs
 // only once the step's scale has been recorded
-__global__ void ctl_reset(Ctl* ctl, float* scale_hist, int N) {
-  for (int i = 0; i < N; ++i) scale_hist[i] = 0.f;
+__device__ __forceinline__ void ctl_start(Ctl* ctl) {
   ctl->S = 1.f; ctl->attempt = 1; ctl->poison = 0; ctl->failed_step = -1; ctl->nonfinite = 0;
   ctl->amax_bits = 0; ctl->retries = 0; ctl->s_min = 1.f; ctl->s_max = 1.f; ctl->done = 0; ctl->S_step = 1.f;
   ctl->stalled = 0; ctl->cluster_stalled = 0;
 }
-
-// a <- dL/dy_N (+ running-cost cotangent), max|a|   (paper Alg. 2, initialisation)
-// naive_low: 0, or the low precision (1 fp16, 2 bf16) in which the naive baseline keeps the adjoint
-__global__ void init_adjoint(const float* __restrict__ gyN, const float* __restrict__ gys_last,
-                             float* __restrict__ a, int64_t n, Ctl* ctl, int copy, int naive_low) {
-  unsigned bits = 0;  // (grid-stride: one atomic per workgroup, and few workgroups)
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    float v = gyN[i];
-    if (gys_last) v += gys_last[i];
-    if (naive_low == 1) v = Low<F16>::to_f32(Low<F16>::from_f32(v));
-    if (naive_low == 2) v = Low<BF16>::to_f32(Low<BF16>::from_f32(v));
-    if (copy || gys_last || naive_low) a[i] = v;
-    const unsigned bb = __builtin_bit_cast(unsigned, fabsf(v));
-    bits = bb > bits ? bb : bits;
-  }
-  block_amax(bits, &ctl->amax_bits);
+__global__ void ctl_reset(Ctl* ctl, float* scale_hist, int N) {
+  for (int i = threadIdx.x; i < N; i += blockDim.x) scale_hist[i] = 0.f;
+  if (threadIdx.x == 0) ctl_start(ctl);
 }
 
 // S_N = 2^floor(-log2(u_L * max|a|)) from the exponent of max|a|; exact in integers.
 // A non-finite dL/dy_N is a range event only for the variants that check for them (detect: dynamic
 // scaling reports a failure at step N, unscaled-safe returns infinite gradients); the plain unscaled
 // variant has no checks (paper Sec. 5) and lets the NaN / inf run through the ordinary arithmetic.
-__global__ void scale_init(Ctl* ctl, float* scale_hist, int N, int p_bits, int dynamic, int detect) {
-  unsigned bits = ctl->amax_bits;
+__device__ __forceinline__ void scale_init(Ctl* ctl, unsigned bits, float* scale_hist, int N, int p_bits, int dynamic, int detect) {
   float S = 1.f;
   if (bits >= 0x7F800000u) {  // non-finite dL/dy_N
     if (detect) {
@@ -198,6 +183,31 @@ __global__ void scale_init(Ctl* ctl, float* scale_hist, int N, int p_bits, int d
   ctl->s_max = S;
   ctl->amax_bits = 0;
   scale_hist[N] = S;
+}
+
+// a <- dL/dy_N (+ running-cost cotangent), max|a|, and by the last workgroup to finish S_N   (paper Alg. 2, initialisation)
+// naive_low: 0, or the low precision (1 fp16, 2 bf16) in which the naive baseline keeps the adjoint
+__global__ void init_adjoint(const float* __restrict__ gyN, const float* __restrict__ gys_last,
+                             float* __restrict__ a, int64_t n, Ctl* ctl, int copy, int naive_low, float* scale_hist, int N,
+                             int p_bits, int dynamic, int detect) {
+  unsigned bits = 0;  // (grid-stride: one atomic per workgroup, and few workgroups)
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    float v = gyN[i];
+    if (gys_last) v += gys_last[i];
+    if (naive_low == 1) v = Low<F16>::to_f32(Low<F16>::from_f32(v));
+    if (naive_low == 2) v = Low<BF16>::to_f32(Low<BF16>::from_f32(v));
+    if (copy || gys_last || naive_low) a[i] = v;
+    const unsigned bb = __builtin_bit_cast(unsigned, fabsf(v));
+    bits = bb > bits ? bb : bits;
+  }
+  block_amax(bits, &ctl->amax_bits);
+  if (threadIdx.x == 0) {  // (the thread that has posted the workgroup's maximum)
+    __threadfence();
+    if (atomicAdd(&ctl->done, 1) == (int)gridDim.x - 1) {
+      ctl->done = 0;
+      scale_init(ctl, atomicMax(&ctl->amax_bits, 0u), scale_hist, N, p_bits, dynamic, detect);
+    }
+  }
 }
 
 // kbar_j = Q( b_j * Q(S a) + h * sum_{l>j} a_lj zbar_l )   (paper eq. (vjp): the cotangent

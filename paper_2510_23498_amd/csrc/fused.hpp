@@ -148,11 +148,9 @@ struct CastArgs {
   const int* only_if;  // as in FusedArgs
 };
 
+// one wavefront: fragment `frag` of all layers' fragments
 template <class T>
-__global__ void cast_dense_fragments(CastArgs c) {
-  if (c.only_if && !*c.only_if) return;
-  const int lane = threadIdx.x & 63;
-  int frag = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+__device__ __forceinline__ void cast_fragment(const CastArgs& c, int frag, int lane) {
   if (frag >= c.nfrag) return;
   CastLayer y = c.layer[0];
 #pragma unroll
@@ -186,6 +184,11 @@ __global__ void cast_dense_fragments(CastArgs c) {
     }
     y.WTf[(size_t)f * 64 + lane] = v;
   }
+}
+template <class T>
+__global__ void cast_dense_fragments(CastArgs c) {
+  if (c.only_if && !*c.only_if) return;
+  cast_fragment<T>(c, blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), threadIdx.x & 63);
 }
 
 // tanh of an fp32 pre-activation:  1 - 2 / (exp(2x) + 1)  with the hardware exp2 and reciprocal

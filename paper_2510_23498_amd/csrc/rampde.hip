@@ -720,15 +720,6 @@ __global__ void fill_zero_u32(uint32_t* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
-// Rows R .. Rp of every (feature group, stage) run of Rp 8-byte words to zero: one wavefront per run.  Writes only the
-// padding (at most 63 words a run): clearing the whole buffer sets took 290 us at 2000 rows (32 sets of 512-wide
-// activations), this 9 us.
-__global__ __launch_bounds__(256) void fill_pad_rows(uint2* p, size_t runs, int R, int Rp) {
-  const int lane = threadIdx.x & 63;
-  for (size_t q = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); q < runs; q += (size_t)gridDim.x * 4)
-    if (R + lane < Rp) p[q * Rp + R + lane] = make_uint2(0u, 0u);
-}
-
 // ---------------------------------------------------------------- optional per-kernel timing
 // When enabled, launches of the kernel classes below are bracketed by HIP events on the
 // caller's stream; rampde_timing_read sums the elapsed times.  Process-global, not thread safe:
@@ -769,6 +760,64 @@ struct FloatChunk {
 };
 __global__ void write_floats(FloatChunk c, float* dst, int count) {
   for (int i = threadIdx.x; i < count; i += blockDim.x) dst[i] = c.v[i];
+}
+
+// What a pass on the row-tile kernels needs before its first launch, in one launch (on small networks every launch is a
+// visible part of the pass: 2-32-32-2, 256 rows, 8 RK4 steps f16 took 207 us with one launch each): weight
+// fragments, the trace row's coefficients, the head of the step table, and for a backward pass the control block, the
+// arrays that are added to and the padding rows of the gradient operands (rows R .. Rp of every
+// run of Rp 8-byte words, one wavefront per run: clearing the whole buffer sets took 290 us at 2000 rows).  Workgroups by
+// role.
+constexpr int kPrologueFloats = 512;
+struct Prologue {
+  CastArgs cast;
+  TraceCoef trace;
+  int cast_blocks, trace_blocks, zero_blocks, pad_blocks;
+  uint32_t* zero[4];
+  size_t zero_words[4];
+  uint2* pad;
+  size_t pad_runs;
+  int R, Rp;
+  Ctl* ctl;  // null: a forward pass
+  float* scale_hist;
+  int N;
+  float* steptab;
+  int floats;
+  float v[kPrologueFloats];
+};
+template <class T, bool WIDE>
+__global__ __launch_bounds__(256) void pass_prologue(Prologue a) {
+  int b = blockIdx.x;
+  if (b < a.cast_blocks) {
+    if constexpr (WIDE) cast_fragment_wide<T>(a.cast, b * 4 + (threadIdx.x >> 6), threadIdx.x & 63);
+    else cast_fragment<T>(a.cast, b * 4 + (threadIdx.x >> 6), threadIdx.x & 63);
+    return;
+  }
+  b -= a.cast_blocks;
+  if (b < a.trace_blocks) {
+    trace_coefficient<T>(a.trace, b * 256 + threadIdx.x);
+    return;
+  }
+  b -= a.trace_blocks;
+  if (b == 0) {
+    for (int i = threadIdx.x; i < a.floats; i += 256) a.steptab[i] = a.v[i];
+    if (a.ctl) {
+      for (int i = threadIdx.x; i < a.N; i += 256) a.scale_hist[i] = 0.f;
+      if (threadIdx.x == 0) ctl_start(a.ctl);
+    }
+    return;
+  }
+  b -= 1;
+  if (b < a.zero_blocks) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      for (size_t i = (size_t)b * 256 + threadIdx.x; i < a.zero_words[q]; i += (size_t)a.zero_blocks * 256) a.zero[q][i] = 0u;
+    return;
+  }
+  b -= a.zero_blocks;
+  const int lane = threadIdx.x & 63;
+  for (size_t q = (size_t)b * 4 + (threadIdx.x >> 6); q < a.pad_runs; q += (size_t)a.pad_blocks * 4)
+    if (a.R + lane < a.Rp) a.pad[q * a.Rp + a.R + lane] = make_uint2(0u, 0u);
 }
 
 // Helper stream on which the parameter-gradient kernel of step i runs while the adjoint kernel
@@ -1053,10 +1102,9 @@ struct Runner {
   bool use_fused = false;
   unsigned long long wait_ticks = kWaitTicks;
 
-  void cast_fragments(const float* theta, const int* only_if = nullptr) {
+  CastArgs cast_args(const float* theta) const {
     CastArgs c{};
     c.L = p.L;
-    c.only_if = only_if;
     int nfrag = 0;
     for (int l = 0; l < p.L; ++l) {
       const Layer& y = p.layers[l];
@@ -1075,14 +1123,67 @@ struct Runner {
       nfrag += (y.Kpad / 32) * (y.Npad / 16) + (y.Npad / 32) * (y.Kpad / 16);
     }
     c.nfrag = nfrag;
-    if (p.wide)
-      cast_dense_fragments_wide<T><<<blocks_for(nfrag, 4), 256, 0, st>>>(c);
-    else
-      cast_dense_fragments<T><<<blocks_for(nfrag, 4), 256, 0, st>>>(c);
+    return c;
+  }
+
+  // (a cluster kernel's forward pass casts its own fragments: cast = false)
+  void prologue(const float* theta, const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low, bool cast, bool backward,
+                bool time_sums) {
+    Prologue a{};
+    if (cast) {
+      a.cast = cast_args(theta);
+      a.cast_blocks = blocks_for(a.cast.nfrag, 4);
+    }
+    if (p.cnf) {
+      const Layer &y0 = p.layers[0], &y1 = p.layers[1];
+      a.trace = TraceCoef{theta + y0.theta_w, theta + y1.theta_w, f32(p.cnf_c), y0.in_full, y0.in, y0.out, y0.Npad};
+      a.trace_blocks = blocks_for(y0.Npad, 256);
+    }
+    const std::vector<float> t = step_table(tgrid, N, tab, low);
+    a.steptab = f32(p.steptab);
+    a.floats = (int)std::min<size_t>(kPrologueFloats, t.size());
+    memcpy(a.v, t.data(), sizeof(float) * a.floats);
+    if (backward) {
+      a.ctl = ctl;
+      a.scale_hist = f32(p.scale_hist);
+      a.N = N;
+      int q = 0;
+      auto zero = [&](size_t off, size_t words) {
+        a.zero[q] = (uint32_t*)(ws + off);
+        a.zero_words[q++] = words;
+      };
+      zero(p.gpart, (size_t)p.ksplits * p.P);
+      if (p.slots) zero(p.slots, 2 * (size_t)N * (p.cluster ? p.cl_n * (p.cluster / 64) : (int)blocks_for(p.R, 16 * p.MT)));
+      if (time_sums) {
+        zero(p.tpart, 2 * (size_t)N);
+        zero(p.tslots, 2 * kTimeSlotPairs);
+      }
+      size_t most = 0;
+      for (int i = 0; i < q; ++i) most = std::max(most, a.zero_words[i]);
+      a.zero_blocks = (int)std::max<size_t>(1, std::min<size_t>((most + 1023) / 1024, 1024));
+      if (p.Rp != p.R) {
+        // rows R..Rp of every stage are padding of the contraction: they must read as zero
+        // (the sets are one array of feature groups x stages of Rp 8-byte words each)
+        a.pad = (uint2*)(ws + p.ZT);
+        a.pad_runs = (size_t)p.nsets * p.fm_stride / 8 / p.Rp;
+        a.pad_blocks = (int)std::min<size_t>((a.pad_runs + 3) / 4, 8192);
+        a.R = (int)p.R;
+        a.Rp = (int)p.Rp;
+      }
+    }
+    const unsigned grid = a.cast_blocks + a.trace_blocks + 1 + a.zero_blocks + a.pad_blocks;
+    if (p.wide) pass_prologue<T, true><<<grid, 256, 0, st>>>(a);
+    else pass_prologue<T, false><<<grid, 256, 0, st>>>(a);
+    for (size_t off = a.floats; off < t.size(); off += 768) {
+      FloatChunk c;
+      const int cnt = (int)std::min<size_t>(768, t.size() - off);
+      memcpy(c.v, t.data() + off, sizeof(float) * cnt);
+      write_floats<<<1, 256, 0, st>>>(c, f32(p.steptab) + off, cnt);
+    }
   }
 
   // per step: h_i, then the stage times rounded to low precision
-  void write_steptab(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low) {
+  std::vector<float> step_table(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low) const {
     std::vector<float> tabv((size_t)N * (1 + p.s));
     for (int i = 0; i < N; ++i) {
       const float h = (float)(tgrid[i + 1] - tgrid[i]);
@@ -1090,12 +1191,7 @@ struct Runner {
       for (int j = 0; j < p.s; ++j)
         tabv[(size_t)i * (1 + p.s) + 1 + j] = round_low_host((float)(tgrid[i] + tab->c[j] * (double)h), low);
     }
-    for (size_t off = 0; off < tabv.size(); off += 768) {
-      FloatChunk c;
-      const int cnt = (int)std::min<size_t>(768, tabv.size() - off);
-      memcpy(c.v, tabv.data() + off, sizeof(float) * cnt);
-      write_floats<<<1, 256, 0, st>>>(c, f32(p.steptab) + off, cnt);
-    }
+    return tabv;
   }
 
   FusedArgs fused_args(const rampde_tableau* tab, int N) const {
@@ -1193,13 +1289,6 @@ struct Runner {
       return RAMPDE_OK;
     }
     return launch_fused_width(l, a);
-  }
-
-  // c_h of the trace row from theta (shallow flows)
-  void trace_coefficients(const float* theta) {
-    const Layer &y0 = p.layers[0], &y1 = p.layers[1];
-    cnf_trace_coef_theta<T><<<blocks_for(y0.Npad, 64), 64, 0, st>>>(theta + y0.theta_w, y0.in_full, theta + y1.theta_w, y0.in,
-                                                                   y0.out, y0.Npad, f32(p.cnf_c));
   }
 
   // Groups of steps of the register-resident kernels: recomputed ahead, except where one kernel holds both directions'
@@ -1306,9 +1395,7 @@ struct Runner {
   int forward_fused(const float* theta, const float* y0, const double* tgrid, int N, const rampde_tableau* tab,
                     const rampde_policy* pol, uint16_t* ckpt, float* yN) {
     if (p.cluster) cast_cluster(theta, false);
-    else cast_fragments(theta);
-    if (p.cnf) trace_coefficients(theta);
-    write_steptab(tgrid, N, tab, pol->low);
+    prologue(theta, tgrid, N, tab, pol->low, !p.cluster, false, false);
     FusedArgs a = fused_args(tab, N);
     if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
     a.y0 = y0;
@@ -1327,7 +1414,9 @@ struct Runner {
         }
         // (two launches that do nothing unless a wait of that one ran out)
         a.only_if = &ctl->cluster_stalled;
-        cast_fragments(theta, a.only_if);
+        CastArgs again = cast_args(theta);
+        again.only_if = a.only_if;
+        cast_dense_fragments<T><<<blocks_for(again.nfrag, 4), 256, 0, st>>>(again);
       }
       rc = p.resident ? launch_resident(kResidentForward, a) : launch_fused(false, a);
     }
@@ -1728,8 +1817,10 @@ struct Runner {
                float* grad_y0, float* grad_theta, float* grad_t, float* scale_hist, rampde_stats* stats) {
     const int dynamic = scaling == RAMPDE_SCALE_DYNAMIC;
     if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
-    if (grad_t) fill_zero_u32<<<1, 256, 0, st>>>((uint32_t*)(ws + p.tpart), 2 * (size_t)N);
-    if (grad_t) fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.tslots), 2 * kTimeSlotPairs);
+    if (grad_t && !use_fused) {
+      fill_zero_u32<<<1, 256, 0, st>>>((uint32_t*)(ws + p.tpart), 2 * (size_t)N);
+      fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.tslots), 2 * kTimeSlotPairs);
+    }
     const int detect = dynamic || scaling == RAMPDE_SCALE_NONE_SAFE;
     const int k_max = pol->k_max > 0 ? pol->k_max : 16;
     if (p.conv) HIP_TRY(allow_conv_tile_lds());
@@ -1758,7 +1849,7 @@ struct Runner {
       HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad<T, true, CW_MAXI_HI>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     }
-    ctl_reset<<<1, 1, 0, st>>>(ctl, f32(p.scale_hist), N);
+    if (!use_fused) ctl_reset<<<1, 256, 0, st>>>(ctl, f32(p.scale_hist), N);
     if (conv_wgrad_applies(p))
       for (auto& y : p.layers)
         if (y.cw_floats) fill_zero_u32<<<1024, 256, 0, st>>>((uint32_t*)(ws + y.cw_part), y.cw_floats);
@@ -1783,9 +1874,6 @@ struct Runner {
     };
     if (!use_fused && !p.parabolic) cast_weights(theta);
     SideStream& side = SideStream::get();
-    if (p.slots)
-      fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.slots),
-                                         2 * (size_t)N * (p.cluster ? p.cl_n * (p.cluster / 64) : (int)blocks_for(p.R, 16 * p.MT)));
     if (use_fused && p.overlap_wgrad) {
       int rc = side.prepare(N);
       if (rc) return rc;
@@ -1795,10 +1883,8 @@ struct Runner {
     auto a_buf = [&](int i) -> float* { return (i % 2 == 0) ? grad_y0 : f32(p.a_alt); };
     FusedArgs fa{};
     if (use_fused) {
-      cast_fragments(theta);
+      prologue(theta, tgrid, N, tab, pol->low, true, true, grad_t != nullptr);
       if (p.cluster) cast_cluster(theta, true);
-      if (p.cnf) trace_coefficients(theta);
-      write_steptab(tgrid, N, tab, pol->low);
       fa = fused_args(tab, N);
       fa.ckpt = const_cast<uint16_t*>(ckpt);
       fa.ckpt_stride = step_elems;
@@ -1817,13 +1903,6 @@ struct Runner {
       fa.nsteps = 1;
       fa.tpart = grad_t ? f32(p.tslots) : nullptr;
       fa.round_incr = (pol->flags & RAMPDE_NAIVE_STATE) ? 2 : 0;
-      fill_zero_u32<<<1024, 256, 0, st>>>((uint32_t*)(ws + p.gpart), (size_t)p.ksplits * p.P);
-      if (p.Rp != p.R) {
-        // rows R..Rp of every stage are padding of the contraction: they must read as zero
-        // (the sets are one array of feature groups x stages of Rp 8-byte words each)
-        const size_t runs = (size_t)p.nsets * p.fm_stride / 8 / p.Rp;
-        fill_pad_rows<<<(unsigned)std::min<size_t>((runs + 3) / 4, 8192), 256, 0, st>>>((uint2*)(ws + p.ZT), runs, (int)p.R, (int)p.Rp);
-      }
       fa.ctl = ctl;
       fa.scale_hist = f32(p.scale_hist);
       fa.detect = detect;
@@ -1849,14 +1928,18 @@ struct Runner {
       a = f32(p.a_rows);
       gys_rows = f32(p.gys_rows);
       to_rows(grad_yN, a);
-      init_adjoint<<<stream_blocks(p.n, 512), 256, 0, st>>>(a, gys_at(N), a, p.n, ctl, 0, naive_low);
+      init_adjoint<<<stream_blocks(p.n, 512), 256, 0, st>>>(a, gys_at(N), a, p.n, ctl, 0, naive_low, f32(p.scale_hist), N,
+                                                           Low<T>::p_bits, dynamic, detect);
     } else {
-      init_adjoint<<<stream_blocks(p.n, 512), 256, 0, st>>>(grad_yN, gys_at(N), a, p.n, ctl, 1, naive_low);
+      init_adjoint<<<stream_blocks(p.n, 512), 256, 0, st>>>(grad_yN, gys_at(N), a, p.n, ctl, 1, naive_low, f32(p.scale_hist), N,
+                                                           Low<T>::p_bits, dynamic, detect);
     }
-    scale_init<<<1, 1, 0, st>>>(ctl, f32(p.scale_hist), N, Low<T>::p_bits, dynamic, detect);
 
+    // (the control block and the scale history behind it come back in one copy)
     Ctl hctl;
     memset(&hctl, 0, sizeof hctl);
+    std::vector<char> back(p.scale_hist - p.ctl + sizeof(float) * (size_t)(N + 1));
+    const float* hist = (const float*)(back.data() + (p.scale_hist - p.ctl));
     int from = N - 1;
     bool recompute_first = true;
     int status = RAMPDE_OK;
@@ -2009,8 +2092,9 @@ struct Runner {
         }
       HIP_TRY(hipGetLastError());
       if (!must_sync) break;
-      HIP_TRY(hipMemcpyAsync(&hctl, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipMemcpyAsync(back.data(), ctl, back.size(), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
+      memcpy(&hctl, back.data(), sizeof hctl);
       if (hctl.stalled) return kStalled;
       if (!hctl.poison) break;
       if (!dynamic) break;  // NONE_SAFE: handled below
@@ -2043,13 +2127,8 @@ struct Runner {
     }
     if (p.conv) to_nchw(a, grad_y0);
     HIP_TRY(hipGetLastError());
-    std::vector<float> hist;
-    if (scale_hist || stats) {
-      hist.resize((size_t)N + 1);
-      HIP_TRY(hipMemcpyAsync(hist.data(), f32(p.scale_hist), sizeof(float) * (size_t)(N + 1), hipMemcpyDeviceToHost, st));
-    }
-    if (must_sync) HIP_TRY(hipStreamSynchronize(st));
-    if (scale_hist) memcpy(scale_hist, hist.data(), sizeof(float) * (size_t)(N + 1));
+    if (must_sync && (p.conv || hctl.poison)) HIP_TRY(hipStreamSynchronize(st));
+    if (scale_hist) memcpy(scale_hist, hist, sizeof(float) * (size_t)(N + 1));
     if (stats) {
       stats->status = st_code;
       stats->failed_step = hctl.poison ? hctl.failed_step : -1;

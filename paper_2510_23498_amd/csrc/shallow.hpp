@@ -892,18 +892,21 @@ __global__ __launch_bounds__(256) void cnf_trace_fold(const float* __restrict__ 
 }
 
 // c_h = sum_i W2[i][h] W1[h][i] from the rounded weights, fp32, in the order of i (zero past H); one thread per h
+struct TraceCoef {
+  const float *W1, *W2;
+  float* c;
+  int ld1, d, H, HP;  // HP = 0: none
+};
 template <class T>
-__global__ __launch_bounds__(64) void cnf_trace_coef_theta(const float* __restrict__ W1, int ld1, const float* __restrict__ W2, int d,
-                                                           int H, int HP, float* __restrict__ c) {
-  const int h = blockIdx.x * 64 + threadIdx.x;
-  if (h >= HP) return;
+__device__ __forceinline__ void trace_coefficient(const TraceCoef& t, int h) {
+  if (h >= t.HP) return;
   float acc = 0.f;
-  if (h < H) {
+  if (h < t.H) {
 #pragma unroll 8
-    for (int i = 0; i < d; ++i)
-      acc = fmaf(Low<T>::to_f32(Low<T>::from_f32(W2[(size_t)i * H + h])), Low<T>::to_f32(Low<T>::from_f32(W1[(size_t)h * ld1 + i])), acc);
+    for (int i = 0; i < t.d; ++i)
+      acc = fmaf(Low<T>::to_f32(Low<T>::from_f32(t.W2[(size_t)i * t.H + h])), Low<T>::to_f32(Low<T>::from_f32(t.W1[(size_t)h * t.ld1 + i])), acc);
   }
-  c[h] = acc;
+  t.c[h] = acc;
 }
 
 }  // namespace rampde

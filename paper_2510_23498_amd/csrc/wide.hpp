@@ -98,9 +98,7 @@ __device__ __forceinline__ void st_f4(float* p, float4 v) { *reinterpret_cast<fl
 
 // theta (fp32) -> the two fragment-major copies above + rounded biases / time column (fp32)
 template <class T>
-__global__ void cast_dense_fragments_wide(CastArgs c) {
-  const int lane = threadIdx.x & 63;
-  int frag = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+__device__ __forceinline__ void cast_fragment_wide(const CastArgs& c, int frag, int lane) {
   if (frag >= c.nfrag) return;
   CastLayer y = c.layer[0];
 #pragma unroll
