@@ -381,8 +381,17 @@ __global__ void conv_wgrad_tr_reduce(float* __restrict__ G, int ldg, const float
 // against gemm_tn (a read of both operands per tap, one block of 64 x 64 out of its 128 x 128) and column_sums: 20 images
 // of 28 x 28, 24 channels, 8 steps of two stages: 4.72 -> 2.99 ms per pass.
 __device__ __align__(16) uint16_t kZeroPage[64];
+// The layers of one launch: workgroups splits0 and up of the grid's third axis are the second layer's.  (A launch of a
+// small image set is latency from end to end, 20 us at 24 channels, 20 images of 28 x 28: one instead of two per step.)
+struct ConvWgradLayers {
+  ConvWgrad layer[2];
+  int splits0;
+};
+
 template <class T, bool TS, int W16>
-__global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
+__global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
+  const int layer = (int)blockIdx.z >= a.splits0 ? 1 : 0, split = (int)blockIdx.z - layer * a.splits0;
+  const ConvWgrad& g = a.layer[layer];
   if (g.ctl->poison) return;
   const int Wr = g.Wd;                                         // pixels per image line
   constexpr int W = 16 * W16, LPS = 4 / W16, NL = 32 / W16;   // lines per step, lines in the ring
@@ -399,7 +408,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
   const int wm = wave >> 1, wn = wave & 1;
   const int64_t total_lines = g.rows / Wr;
   const int lines_per_split = g.rows_per_split / Wr;
-  const int64_t c0 = (int64_t)blockIdx.z * lines_per_split;
+  const int64_t c0 = (int64_t)split * lines_per_split;
   int64_t c1 = c0 + lines_per_split;
   if (c1 > total_lines) c1 = total_lines;
   if (c0 >= c1) return;
@@ -659,7 +668,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgrad g) {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the requests past the chunk's end
 
   const float scale = g.h / g.ctl->S_step;
-  float* slotf = g.part + (size_t)blockIdx.z * CW_SLOT;
+  float* slotf = g.part + (size_t)split * CW_SLOT;
   if (g.want_sums) {
     float p0 = 0.f, p1 = 0.f;
     if (sums) {

@@ -129,10 +129,11 @@ __global__ void stage_input(const uint16_t* __restrict__ ck, int d, const uint16
 }
 
 // y <- y + h * sum_j b_j k_j  in fp32;  ckpt[i+1] <- Q(y)     (paper Alg. 1, accumulate + store)
+// z: null, or the next step's first stage input (the same values in the padded layout, whose pad columns are zero already)
 template <class T>
 __global__ void combine_store(float* __restrict__ y, const uint16_t* __restrict__ K, int64_t stage_stride, int s,
                               Coefs b, float h, int round_incr, uint16_t* __restrict__ ck_next, int d, int ld,
-                              int64_t R) {
+                              int64_t R, uint16_t* __restrict__ z) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= R * d) return;
   int64_t r = i / d;
@@ -144,6 +145,7 @@ __global__ void combine_store(float* __restrict__ y, const uint16_t* __restrict_
   const uint16_t q = Low<T>::from_f32(v);
   if (round_incr & 2) v = Low<T>::to_f32(q);  // naive baseline: the state is kept in low precision
   y[i] = v;
+  if (z) z[r * ld + c] = q;
   ck_next[i] = q;
 }
 
@@ -164,7 +166,8 @@ __global__ void ctl_reset(Ctl* ctl, float* scale_hist, int N) {
 // A non-finite dL/dy_N is a range event only for the variants that check for them (detect: dynamic
 // scaling reports a failure at step N, unscaled-safe returns infinite gradients); the plain unscaled
 // variant has no checks (paper Sec. 5) and lets the NaN / inf run through the ordinary arithmetic.
-__device__ __forceinline__ void scale_init(Ctl* ctl, unsigned bits, float* scale_hist, int N, int p_bits, int dynamic, int detect) {
+__device__ __forceinline__ void scale_init(Ctl* ctl, unsigned bits, float* scale_hist, int N, int p_bits, int dynamic, int detect,
+                                           int settled) {
   float S = 1.f;
   if (bits >= 0x7F800000u) {  // non-finite dL/dy_N
     if (detect) {
@@ -183,13 +186,17 @@ __device__ __forceinline__ void scale_init(Ctl* ctl, unsigned bits, float* scale
   ctl->s_max = S;
   ctl->amax_bits = 0;
   scale_hist[N] = S;
+  if (settled) {  // nothing is decided between the steps: every step has this scale
+    ctl->S_step = S;
+    for (int i = 0; i < N; ++i) scale_hist[i] = S;
+  }
 }
 
 // a <- dL/dy_N (+ running-cost cotangent), max|a|, and by the last workgroup to finish S_N   (paper Alg. 2, initialisation)
 // naive_low: 0, or the low precision (1 fp16, 2 bf16) in which the naive baseline keeps the adjoint
 __global__ void init_adjoint(const float* __restrict__ gyN, const float* __restrict__ gys_last,
                              float* __restrict__ a, int64_t n, Ctl* ctl, int copy, int naive_low, float* scale_hist, int N,
-                             int p_bits, int dynamic, int detect) {
+                             int p_bits, int dynamic, int detect, int settled) {
   unsigned bits = 0;  // (grid-stride: one atomic per workgroup, and few workgroups)
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     float v = gyN[i];
@@ -205,7 +212,7 @@ __global__ void init_adjoint(const float* __restrict__ gyN, const float* __restr
     __threadfence();
     if (atomicAdd(&ctl->done, 1) == (int)gridDim.x - 1) {
       ctl->done = 0;
-      scale_init(ctl, atomicMax(&ctl->amax_bits, 0u), scale_hist, N, p_bits, dynamic, detect);
+      scale_init(ctl, atomicMax(&ctl->amax_bits, 0u), scale_hist, N, p_bits, dynamic, detect, settled);
     }
   }
 }
@@ -559,7 +566,8 @@ __global__ __launch_bounds__(256) void stage_input_v8(const uint16_t* __restrict
 template <class T>
 __global__ __launch_bounds__(256) void combine_store_v8(float* __restrict__ y, const uint16_t* __restrict__ K,
                                                         int64_t stage_stride, int s, Coefs b, float h, int round_incr,
-                                                        uint16_t* __restrict__ ck_next, int d, int ld, int64_t R) {
+                                                        uint16_t* __restrict__ ck_next, int d, int ld, int64_t R,
+                                                        uint16_t* __restrict__ z) {
   const int gpr = d >> 3;
   const int64_t G = R * gpr;
   for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < G; g += (int64_t)gridDim.x * blockDim.x) {
@@ -581,6 +589,7 @@ __global__ __launch_bounds__(256) void combine_store_v8(float* __restrict__ y, c
     if (round_incr & 2) unpack8<T>(q, yv);  // naive baseline: the state is kept in low precision
     store8f(y + r * d + c, yv);
     *reinterpret_cast<u16x8*>(ck_next + r * d + c) = q;
+    if (z) *reinterpret_cast<u16x8*>(z + r * ld + c) = q;
   }
 }
 
