@@ -30,7 +30,11 @@ hipError_t pick_kernel(const ResidentLaunch& l, const ResidentArgs& a) {
   // forward and transposed weight slices together: 384 of 512 registers at three layers of 256, 640 at four; 192 of
   // 256 at four layers of 128
   constexpr bool phased = (HP == 256 && (L == 4 || MT == 2)) || (HP == 128 && L == 4);
-  if (l.kind == kResidentForward) return launch_kernel(mlp_forward_resident<T, L, HP, MT>, l, a);
+  if (l.kind == kResidentForward) {
+    if constexpr (MT == 1 && HP >= 128)
+      if (a.f.R <= 4) return launch_kernel(mlp_forward_resident<T, L, HP, MT, true>, l, a);
+    return launch_kernel(mlp_forward_resident<T, L, HP, MT, false>, l, a);
+  }
   if (l.kind == kResidentRecompute)
     return a.f.KT ? launch_kernel(mlp_recompute_resident<T, L, HP, MT, true>, l, a) : launch_kernel(mlp_recompute_resident<T, L, HP, MT, false>, l, a);
   if (l.kind == kResidentChain)
