@@ -62,12 +62,17 @@ inline ConvTileShape conv_tile_shape(int NA, int KC, int H, int Wd, int64_t imag
 // all loads in flight beside the multiplication / as here: 13.1 / 12.4 / 12.3, 13.6 / 13.9 / 13.0, 13.7 / 14.1 / 13.2,
 // 14.2 / 14.8 / 13.7.
 constexpr int kOutside = 0x40000000;  // (a byte offset past every window)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const uint16_t* p, int elements) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, elements * 2, 0x00020000);
+template <class E>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const E* p, int elements) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<E*>(p), 0, elements * (int)sizeof(E), 0x00020000);
 }
 
 // 8 wavefronts: pixel block (wave / AW), output blocks (wave % AW) * NB ...
-enum ConvEpilogue { kConvPlain, kConvTanh, kConvFactor };  // nothing, tanh, tanh' of the stored activation
+// nothing, tanh, tanh' of the stored activation, nothing and the next stage input, nothing and the next slope cotangent.
+// The last two read 2 or 4 bytes and write 2 per element that a pass of their own would have read and written again
+// (us per training pass without / with: 24 x 28 x 28, 20 images, 8 Heun steps 1064 / 955; 64 x 32 x 32, 128 images, 16
+// RK4 steps, as shares of the same pass before on the same card: 0.961 / 0.943)
+enum ConvEpilogue { kConvPlain, kConvTanh, kConvFactor, kConvStage, kConvCotangent };
 template <class T, int NA, int KC, int AW, int EPI>
 __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) {
   constexpr int NT = 512;
@@ -186,6 +191,7 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
   const int n0 = a0 * 32 + 4 * (lane >> 5);           // this lane's first output channel
 
   bool bad = false;
+  const float S = EPI == kConvCotangent ? g.ctl->S : 0.f;
   settle();
   for (int t = blockIdx.x; t < sh.tiles; t += gridDim.x) {
     __syncthreads();  // the previous tile's fragments have been read (and the tables are written)
@@ -204,6 +210,28 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
           dv[a][q4] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(act, (p * g.ldd + n0 + a * 32 + 8 * q4) * 2, 0, 0));
+    }
+    // ... the stored state or the adjoint at them
+    float4 av4[NB][4];
+    if constexpr (EPI == kConvStage) {
+      const auto base = window(g.base + row0 * g.d, pixels * g.d);
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int n = n0 + a * 32 + 8 * q4;
+          dv[a][q4] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(base, n < g.d ? (p * g.d + n) * 2 : kOutside, 0, 0));
+        }
+    }
+    if constexpr (EPI == kConvCotangent) {
+      const auto adj = window(g.adj + row0 * g.d, pixels * g.d);
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int n = n0 + a * 32 + 8 * q4;
+          av4[a][q4] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(adj, n < g.d ? (p * g.d + n) * 4 : kOutside, 0, 0));
+        }
     }
     if (pb * 32 >= PR * W) {  // (uniform: no pixel block for this wavefront)
       if (t + (int)gridDim.x < sh.tiles) load_tile(t + gridDim.x);
@@ -227,11 +255,17 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
         fa[a] = *reinterpret_cast<const u16x8*>(&sW[(tap * NCH + a * 32) * PITCH + w_base + kk * 16]);
       fb = *reinterpret_cast<const u16x8*>(&sIn[in_base + shift + kk * 16]);
     };
-    if constexpr (EPI == kConvFactor) {  // (wait for them)
+    if constexpr (EPI == kConvFactor || EPI == kConvStage) {  // (wait for them)
 #pragma unroll
       for (int a = 0; a < NB; ++a)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) asm volatile("" : "+v"(dv[a][q4].x), "+v"(dv[a][q4].y));
+    }
+    if constexpr (EPI == kConvCotangent) {
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) asm volatile("" : "+v"(av4[a][q4].x), "+v"(av4[a][q4].y), "+v"(av4[a][q4].z), "+v"(av4[a][q4].w));
     }
     u16x8 fa[2][NB], fb[2];
     load_frags(0, fa[0], fb[0]);
@@ -249,6 +283,8 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
     // ---- epilogue: accumulator row = output channel 8 (q / 4) + 4 (lane / 32) + q % 4 of block a,
     //      column = pixel lane % 32
     const auto out = window(g.C + row0 * g.ldc, pixels * g.ldc);
+    __amdgpu_buffer_rsrc_t next;
+    if constexpr (EPI >= kConvStage) next = window(g.next + row0 * g.ldc, pixels * g.ldc);
     int combo = 0;
     if (g.wt) combo = ((y > 0) << 3) | ((y < H - 1) << 2) | ((x > 0) << 1) | (x < W - 1 ? 1 : 0);
     float4 tv[NB][4];
@@ -277,7 +313,31 @@ __global__ __launch_bounds__(512) void conv3x3_tile(GemmNT g, ConvTileShape sh) 
         }
         const uint2 q = pack4<T>(v);
         bad |= live & any_nonfinite4<T>(q);
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, q), out, (p * g.ldc + n0 + a * 32 + 8 * q4) * 2, 0, 0);
+        const int n = n0 + a * 32 + 8 * q4;
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, q), out, (p * g.ldc + n) * 2, 0, 0);
+        if constexpr (EPI >= kConvStage) {
+          float f[4], x[4];
+          unpack4<T>(q, f);
+          if constexpr (EPI == kConvStage) {
+            float yh[4];
+            unpack4<T>(dv[a][q4], yh);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = fmaf(g.h, g.coef * f[r], yh[r]);
+          } else {
+            const float4 av = av4[a][q4];
+            const float sa[4] = {S * av.x, S * av.y, S * av.z, S * av.w};
+            const uint2 lq = pack4<T>(sa);
+            bad |= live & any_nonfinite4<T>(lq);
+            float lam[4];
+            unpack4<T>(lq, lam);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = fmaf(g.h, g.coef * f[r], g.bw * lam[r]);
+          }
+          uint2 xq = pack4<T>(x);
+          if (n >= g.d) xq = make_uint2(0u, 0u);
+          if constexpr (EPI == kConvCotangent) bad |= live & any_nonfinite4<T>(xq);
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, xq), next, (p * g.ldc + n) * 2, 0, 0);
+        }
       }
   }
   if (g.detect) raise_if_any(bad, g.ctl);

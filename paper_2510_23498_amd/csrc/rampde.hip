@@ -906,14 +906,19 @@ struct Runner {
   // conv3x3_tile by shape (32 channels; 64 channels with two, with one wavefront per pixel block) and epilogue
   using ConvTileKernel = void (*)(GemmNT, ConvTileShape);
   template <int NA, int KC, int AW>
-  static constexpr std::array<ConvTileKernel, 3> conv_tile_epilogues() {
-    return {&conv3x3_tile<T, NA, KC, AW, kConvPlain>, &conv3x3_tile<T, NA, KC, AW, kConvTanh>, &conv3x3_tile<T, NA, KC, AW, kConvFactor>};
+  static constexpr std::array<ConvTileKernel, 5> conv_tile_epilogues() {
+    return {&conv3x3_tile<T, NA, KC, AW, kConvPlain>, &conv3x3_tile<T, NA, KC, AW, kConvTanh>, &conv3x3_tile<T, NA, KC, AW, kConvFactor>,
+            &conv3x3_tile<T, NA, KC, AW, kConvStage>, &conv3x3_tile<T, NA, KC, AW, kConvCotangent>};
+  }
+  // whether conv3x3_tile also forms what the next stage's convolution reads: stages that are a chain, 16-byte rows
+  bool conv_fuses_stages(const rampde_tableau* tab) const {
+    return p.conv && !p.parabolic && conv_tile_applies(p.layers[0].Kpad, p.layers[0].Npad, p.Wd) && vec8() && !dense_stages(tab);
   }
   bool few_channels() const { return p.d <= 32; }
   ConvTileShape conv_tile() const {
     return conv_tile_shape(few_channels() ? 1 : 2, few_channels() ? 2 : 4, p.H, p.Wd, p.R / ((int64_t)p.H * p.Wd), device_compute_units());
   }
-  std::array<ConvTileKernel, 3> conv_tile_kernels(const ConvTileShape& sh) const {
+  std::array<ConvTileKernel, 5> conv_tile_kernels(const ConvTileShape& sh) const {
     return few_channels() ? conv_tile_epilogues<1, 2, 1>() : sh.aw == 2 ? conv_tile_epilogues<2, 4, 2>() : conv_tile_epilogues<2, 4, 1>();
   }
 
@@ -923,7 +928,7 @@ struct Runner {
       // persistent: one workgroup per CU (its LDS holds the layer's weights), tiles of whole image lines
       const ConvTileShape sh = conv_tile();
       const size_t lds = conv_tile_lds_bytes(few_channels() ? 1 : 2, few_channels() ? 2 : 4, sh.lines, g.Wd);
-      conv_tile_kernels(sh)[g.dact ? kConvFactor : g.act_tanh ? kConvTanh : kConvPlain]<<<sh.blocks, 512, lds, st>>>(g, sh);
+      conv_tile_kernels(sh)[g.base ? kConvStage : g.adj ? kConvCotangent : g.dact ? kConvFactor : g.act_tanh ? kConvTanh : kConvPlain]<<<sh.blocks, 512, lds, st>>>(g, sh);
     } else if (p.conv && !p.cw_blocks && conv_nt_lines_applies(g)) {
       // ... with the input staged by image lines: a block of input channels serves all nine taps from LDS
       dim3 grid(g.M / 512, g.N / 128);
@@ -1041,12 +1046,13 @@ struct Runner {
   void stages(const uint16_t* ck, double t_i, float h, const rampde_tableau* tab, rampde_dtype low, int keep,
               float* taus_out, Ctl* c, bool first_ready, bool last_slope) {
     const int s = p.s;
+    const bool fuses = conv_fuses_stages(tab);
     for (int j = 0; j < s; ++j) {
       const int jb = keep ? j : 0;
       uint16_t* z = u16(p.Z) + (size_t)jb * p.stage_stride;
       Coefs arow{};
       for (int l = 0; l < j; ++l) arow.v[l] = (float)tab->A[j * s + l];
-      const bool ready = j == 0 && first_ready;
+      const bool ready = j == 0 ? first_ready : fuses;
       if (ready) {
       } else if (vec8())
         stage_input_v8<T><<<stream_blocks(p.R * (p.dpad / 8)), 256, 0, st>>>(ck, p.d, u16(p.K), p.stage_stride, j, arow,
@@ -1056,7 +1062,7 @@ struct Runner {
                                                                      p.dpad, p.R, c);
       const float tau = round_low_host((float)(t_i + tab->c[j] * (double)h), low);
       if (taus_out) taus_out[j] = tau;
-      const uint16_t* in = ready && p.d == p.dpad ? ck : z;
+      const uint16_t* in = j == 0 && ready && p.d == p.dpad ? ck : z;
       const bool slope = last_slope || j + 1 < s;
       if (p.parabolic) {
         parabolic_eval(in, j, jb, c, slope);
@@ -1089,6 +1095,13 @@ struct Runner {
         g.H = p.H;
         g.Wd = p.Wd;
         g.Cpad = y.Kpad;
+        if (fuses && last && j + 1 < s) {
+          g.base = ck;
+          g.next = u16(p.Z) + (size_t)(keep ? j + 1 : 0) * p.stage_stride;
+          g.d = p.d;
+          g.h = h;
+          g.coef = (float)tab->A[(j + 1) * s + j];
+        }
         launch_nt(g);
         in = out;
       }
@@ -1517,11 +1530,13 @@ struct Runner {
       for (int j = 0; j < s; ++j) taus.v[j] = round_low_host((float)(tgrid[i] + tab->c[j] * (double)h), pol->low);
     }
     // cotangent chain, stages in reverse
+    const bool fuses = conv_fuses_stages(tab);
     for (int j = s - 1; j >= 0; --j) {
       Coefs acol{};
       for (int l = j + 1; l < s; ++l) acol.v[l] = (float)tab->A[l * s + j];
       uint16_t* kbar = u16(p.KBAR) + (size_t)j * p.stage_stride;
-      if (vec8())
+      if (fuses && j + 1 < s) {
+      } else if (vec8())
         stage_cotangent_v8<T><<<stream_blocks(p.R * (p.dpad / 8)), 256, 0, st>>>(
             a, p.d, u16(p.ZBAR), p.stage_stride, j, s, (float)tab->b[j], acol, h, kbar, p.dpad, p.R, ctl, detect);
       else
@@ -1565,6 +1580,14 @@ struct Runner {
         g.H = p.H;
         g.Wd = p.Wd;
         g.Cpad = y.Npad;
+        if (fuses && l == 0 && j > 0) {
+          g.adj = a;
+          g.next = u16(p.KBAR) + (size_t)(j - 1) * p.stage_stride;
+          g.d = p.d;
+          g.h = h;
+          g.coef = (float)tab->A[j * s + j - 1];
+          g.bw = (float)tab->b[j - 1];
+        }
         launch_nt(g);
         delta = out;
       }

@@ -596,3 +596,33 @@ def test_cluster_launches_that_were_given_up(widths, B):
             for key in ("yN", "ckpt", "grad_y0"):
                 np.testing.assert_array_equal(got[key], rows[key])
             assert np.any(got["yN"] != clusters["yN"])
+
+
+@pytest.mark.parametrize("widths,B,low,tab", [
+    ((64, 256, 256, 64), 1, "f16", "rk4"), ((30, 200, 130, 256, 30), 4, "bf16", "heun"), ((7, 100, 7), 3, "f16", "euler"),
+    ((64, 256, 256, 64), 5, "f16", "rk4"),  # one row more: the ordinary tile
+])
+def test_forward_of_a_handful_of_rows(widths, B, low, tab):
+    # every row by itself gives the same bits as the batch (samples are independent, the order of sums does not depend on B)
+    cfg = wl.CONFIGS["cfg1"].with_(name="few", B=B, N=5, widths=widths, low=low, tableau=tab, loss="mse")
+    _both(cfg, bias_std=0.1)
+    from paper_2510_23498_amd import binding as rb
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    vel, t, pol = par.gpu_descriptors(cfg)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    wide = torch.cat([y] * 5)[:17].contiguous()  # (17 rows: two ordinary tiles)
+    ref, ref_ck = rb.rampde_odeint_fwd(vel, th, wide, cfg.tgrid(), t, pol)
+    yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), t, pol)
+    # (fp16: see test_stages_recomputed_ahead_equal_those_recomputed_inside)
+    assert par.rel_err(yN.cpu().numpy(), ref[:B].cpu().numpy()) <= (1e-4 if low == "f16" else 0.0)
+    assert par.rel_err(ck.float().cpu().numpy(), ref_ck[:, :B].float().cpu().numpy()) <= (2e-3 if low == "f16" else 0.0)
+
+
+@pytest.mark.parametrize("C,H,W,B,low,tab", [(8, 9, 13, 3, "f16", "rk4"), (24, 28, 28, 2, "bf16", "heun"), (64, 7, 64, 2, "f16", "rk4"),
+                                             (40, 16, 16, 3, "bf16", "rk4"), (20, 8, 8, 2, "f16", "rk4"), (16, 8, 16, 2, "f16", "kutta3")])
+def test_stage_inputs_formed_by_the_convolution(C, H, W, B, low, tab):
+    # pad channels, tiles cut short and full, rows that are not whole 16-byte groups (20 channels) and stages that are not a
+    # chain (kutta3: kernels of their own form the stage inputs there); two steps, so that the update forms one too
+    cfg = wl.CONFIGS["cfg4"].with_(name="stagein", C=C, H=H, W=W, B=B, N=2, t1=0.25, low=low, tableau=tab)
+    _both(cfg, bias_std=0.1, scaling="dynamic" if low == "f16" else "none")
