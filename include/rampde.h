@@ -38,8 +38,8 @@
  *     workspace: same results within rounding, a few ms later, and decided anew by every call.
  *     rampde_odeint_bwd in place (grad_y0 = grad_yN) takes those kernels from the start.
  *   - Dense networks whose hidden layers are all 257 to 512 wide (two or three of them, state up to
- *     128) with up to 2048 rows, or 769 to 1024 wide (one or two, state of 65 to 256) with up to 1024
- *     rows: workgroups share row tiles and exchange activations within a launch, in forward and
+ *     128) with up to 2048 rows, or all 513 to 768 or 769 to 1024 wide (one or two, state of 65 to 256)
+ *     with up to 1024 rows (one) or 2048 (two): workgroups share row tiles and exchange activations within a launch, in forward and
  *     backward passes alike.  Where some of them are kept from running for 2 ms, the launch gives up,
  *     and kernels that do not wait do its work: behind it on the stream (forward passes and a fixed
  *     scale; nothing synchronises), or as above under overflow detection.  An explicit row_tile
@@ -141,7 +141,8 @@ typedef struct {
                              wide, hidden layers up to 256 wide), networks with one hidden layer (state up to 64 wide
                              and hidden layer up to 1024, or 128 and 512) and flows (up to 64 state columns), which
                              run as many as about 1 GiB holds, at most 64, and for wide networks, whose stages are
-                             recomputed for as many steps at once as fill the device (and 4 GiB hold).  A smaller value is the way to a smaller
+                             recomputed for as many steps at once as fill the device (and 4 GiB hold; where
+                             workgroups share row tiles, see above, as 1 GiB holds).  A smaller value is the way to a smaller
                              workspace.  Where wgrad_tile = 256 applies this is the number of accepted steps
                              whose parameter gradients one launch forms (default: as many as keep their buffers in
                              the memory-side cache) */

@@ -27,7 +27,7 @@ def hipcc_path() -> str:
 FUSED_HIDDEN_WIDTHS = (0, 256, 512, 1024)  # translation units of fused_inst.hip: one per width and precision
 RESIDENT_HIDDEN_WIDTHS = (64, 128, 256)    # ... of resident_inst.hip
 SHALLOW_HIDDEN_WIDTHS = (128, 256, 512, 1024)  # ... of shallow_inst.hip
-CLUSTER_HIDDEN_WIDTHS = (512, 1024)        # ... of cluster_inst.hip
+CLUSTER_HIDDEN_WIDTHS = (512, 768, 1024)   # ... of cluster_inst.hip
 
 COMPILE_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Wno-pass-failed",
                  "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

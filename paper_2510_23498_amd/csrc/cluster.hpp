@@ -48,7 +48,8 @@ struct ClusterShape {
   static constexpr int KS1 = NTL, KSH = HP / 64;  // contraction steps of 16 per wavefront: over the state, over a hidden layer
   static constexpr int MIDS = L - 2;
   static constexpr int CTS = 2 * NTL;           // column tiles of 32 of the state
-  static constexpr int APC = C / CTS < RTN ? C / CTS : RTN;  // row tiles whose state-shaped passes run side by side
+  // row tiles whose state-shaped passes run side by side (a power of two)
+  static constexpr int APC = C / CTS >= 4 && RTN >= 4 ? 4 : C / CTS >= 2 && RTN >= 2 ? 2 : 1;
   static constexpr int NU = RTN / APC;          // ... one after the other in one member
   static_assert(APC >= 1 && RTN % APC == 0, "every state tile has a member");
   static constexpr int FRAGS = 2 * KS1 + MIDS * 2 * KSH + KSH;  // weight fragments of a wavefront
@@ -519,7 +520,6 @@ __global__ __launch_bounds__(256, 1) void mlp_chain_cluster(ClusterArgs a) {
   __shared__ int sh_[4];
   using Eng = ClusterEngine<T, HP, L, NTL, RTN>;
   constexpr int NU = Eng::Sh::NU, APC = Eng::Sh::APC;
-  static_assert(RTN <= 2, "a cluster's rows lie within the padded batch");
   const FusedArgs& g = a.r.f;
   if (g.ctl->poison) return;
   Eng c;
@@ -552,6 +552,8 @@ __global__ __launch_bounds__(256, 1) void mlp_chain_cluster(ClusterArgs a) {
     mask_u[u] = row < g.R ? 0xFFFFFFFFu : 0u;
     load4f(g.a_in, row, g.R, ns, g.d, av[u]);
   }
+  // row tiles past the padded batch (64-row units; clusters have 32, 64 or 128 rows): nothing to read or write there
+  auto inside = [&](int rt) __attribute__((always_inline)) { return RTN <= 2 || row0 + rt * 32 < g.Rp; };
   // lane offsets (bytes) into the feature-group-major arrays
   const uint32_t off_h = (uint32_t)(((size_t)(nh >> 2) * g.ldk + row0 + c.lr) * 8);
   const uint32_t off_s = (uint32_t)(((size_t)(ns >> 2) * g.ldk + row0 + c.lr) * 8);
@@ -565,7 +567,7 @@ __global__ __launch_bounds__(256, 1) void mlp_chain_cluster(ClusterArgs a) {
 #pragma unroll
       for (int rt = 0; rt < RTN; ++rt)
 #pragma unroll
-        for (int p = 0; p < 2; ++p) q[l][rt][p] = *reinterpret_cast<const uint2*>(base + p * two_groups + (off_h + rt * 256));
+        for (int p = 0; p < 2; ++p) q[l][rt][p] = *reinterpret_cast<const uint2*>(base + p * two_groups + (off_h + (inside(rt) ? rt * 256 : 0)));
     }
   };
   fetch_act(act, g.step, s - 1);
@@ -605,7 +607,7 @@ __global__ __launch_bounds__(256, 1) void mlp_chain_cluster(ClusterArgs a) {
       q.y &= mask_u[u];
       track(big, q);
       c.publish_z(ev, rt, q);
-      *reinterpret_cast<uint2*>(KBART + j * stage_bytes + (off_s + rt * 256)) = q;
+      if (inside(rt)) *reinterpret_cast<uint2*>(KBART + j * stage_bytes + (off_s + rt * 256)) = q;
     };
     if (owner) {
 #pragma unroll
@@ -632,8 +634,10 @@ __global__ __launch_bounds__(256, 1) void mlp_chain_cluster(ClusterArgs a) {
         track(big, lo);
         track(big, hi);
         char* out = (char*)(g.DELTAT[l] + set_off) + j * stage_bytes;
-        *reinterpret_cast<uint2*>(out + (off_h + rt * 256)) = lo;
-        *reinterpret_cast<uint2*>(out + two_groups + (off_h + rt * 256)) = hi;
+        if (inside(rt)) {
+          *reinterpret_cast<uint2*>(out + (off_h + rt * 256)) = lo;
+          *reinterpret_cast<uint2*>(out + two_groups + (off_h + rt * 256)) = hi;
+        }
       };
       auto st = [&](int u, int rt, float (&v)[4]) __attribute__((always_inline)) {
         uint2 q = pack4<T>(v);

@@ -1,5 +1,5 @@
 // One translation unit per hidden width and precision: compile with
-// -DRAMPDE_INST_HP={512,1024} -DRAMPDE_INST_BF16={0,1}.
+// -DRAMPDE_INST_HP={512,768,1024} -DRAMPDE_INST_BF16={0,1}.
 #include "cluster_launch.hpp"
 
 #if !defined(RAMPDE_INST_HP) || !defined(RAMPDE_INST_BF16)
@@ -27,6 +27,8 @@ hipError_t launch_kernel(const ClusterLaunch& l, const ClusterArgs& a) {
 
 template <class T, int L, int NTL>
 hipError_t pick_rows(const ClusterLaunch& l, const ClusterArgs& a) {
+  if constexpr (RAMPDE_INST_HP > 512)
+    if (l.RTN == 4) return launch_kernel<T, L, NTL, 4>(l, a);
   return l.RTN == 1 ? launch_kernel<T, L, NTL, 1>(l, a) : l.RTN == 2 ? launch_kernel<T, L, NTL, 2>(l, a) : hipErrorInvalidValue;
 }
 

@@ -126,7 +126,7 @@ struct Plan {
   int nsets = 2;                    // sets: step i uses set i % nsets
   int ahead_MT = 0;                 // > 0: the stages of a group of steps are recomputed in a launch of their own, in tiles of 16 ahead_MT rows
   size_t ahead_lds = 0;
-  int cluster = 0;                  // hidden width of the kernels of cluster.hpp (512, 1024), 0: not those
+  int cluster = 0;                  // hidden width of the kernels of cluster.hpp (512, 768, 1024), 0: not those
   int cl_RTN = 0, cl_n = 0;         // their row tiles of 32 per cluster, and clusters
   size_t cl_W = 0, cl_x = 0, cl_tickets = 0;
   int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, or kernels that decide inside a launch)
@@ -300,22 +300,29 @@ static bool resident_takes_rows(const rampde_velocity* vel, const rampde_tableau
 
 constexpr int kClusterEvaluations = 384;  // of the velocity per launch of a forward pass: about 3 ms
 
-// The kernels of cluster.hpp: networks that they are built for, batches of at most one cluster of 64 rows per HP / 64
-// compute units, and a whole device (its eight XCDs; a partition of it has fewer).  32 rows per cluster while those run
-// at once.  Forward pass of 16 RK4 steps, us with row tiles / clusters: 256 -> 2 x 1024 -> 256, f16, 16 rows 1493 / 360,
-// 512 rows 1552 / 380, 520 rows (64 per cluster) 1575 / 516, 1024 rows 1545 / 522; 128 -> 3 x 512 -> 128, bf16, 16 rows
+// The kernels of cluster.hpp: networks that they are built for, batches whose clusters run at once, and a whole device (its
+// eight XCDs; a partition of it has fewer).  32 rows per cluster while those run at once, then 64, and 128 with two hidden
+// layers of more than 512.  Forward pass of 16 RK4 steps, us with row tiles / clusters: 256 -> 2 x 1024 -> 256, f16, 16
+// rows 1493 / 360, 512 rows 1552 / 380, 520 rows (64 per cluster) 1575 / 516, 1024 rows 1545 / 522, 2048 rows (128) 1612 /
+// 874; 2 x 768 128 rows 1054 / 318, 1024 rows 1058 / 475, 2048 rows 1073 / 916; 128 -> 3 x 512 -> 128, bf16, 16 rows
 // 718 / 358, 1024 rows 719 / 373, 2048 rows 725 / 509; 100 -> 2 x 400 -> 100, f16, Heun, 2000 rows 244 / 197;
-// 200 -> 1000 -> 200, bf16, Euler, 128 rows 158 / 77, 1024 rows 158 / 99.
+// 200 -> 1000 -> 200, bf16, Euler, 128 rows 158 / 77, 1024 rows 158 / 99, but 128 -> 1000 -> 128, RK4, 2048 rows (128)
+// 330 / 366 and 100 -> 600 -> 100, Euler, 1500 rows 101 / 122.
 static void choose_clusters(Plan& p) {
   const int hp = p.L >= 2 ? p.layers[0].Npad : 0;
   for (int l = 0; l + 1 < p.L; ++l)
     if (p.layers[l].Npad != hp) return;
   if (!cluster_shape(hp, p.L, p.dpad) || device_compute_units() != 256) return;
-  const int64_t most = 256 / (hp / 64), n32 = (p.R + 31) / 32, n64 = (p.R + 63) / 64;
-  if (n64 > most) return;
-  p.cluster = hp;
-  p.cl_RTN = n32 <= most ? 1 : 2;
-  p.cl_n = (int)(n32 <= most ? n32 : n64);
+  // (clusters that run at once: whole ones on each of the eight XCDs of 32 compute units)
+  const int64_t most = 8 * (32 / (hp / 64));
+  for (int rtn = 1; rtn <= (hp > 512 && p.L > 2 ? 4 : 2); rtn *= 2) {
+    const int64_t n = (p.R + 32 * rtn - 1) / (32 * rtn);
+    if (n > most) continue;
+    p.cluster = hp;
+    p.cl_RTN = rtn;
+    p.cl_n = (int)n;
+    return;
+  }
 }
 
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
@@ -538,6 +545,14 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
           const int64_t cus = device_compute_units(), t = (p.R + 16 * p.ahead_MT - 1) / (16 * p.ahead_MT);
           ahead = cus / t;
           if (ahead == 2 && 40 * t < 17 * cus) ahead = 1;
+          // (clusters: every launch of a group loads the weights and starts the exchange anew, and a group is one pass over
+          // the gradient copies: as many steps as about 1 GiB holds, in whole rounds of the recomputation.  256 -> 2 x 1024 -> 256,
+          // f16, 1024 rows, 256 steps with groups of 8 / 16 steps 29.3 / 28.5 ms; 128 -> 3 x 512 -> 128, bf16, 2000
+          // rows, 32 steps in groups of 8 / 16 / 32 3.57 / 3.52 / 3.45 ms)
+          if (p.cluster && ahead >= 2) {
+            const int64_t most = std::min<int64_t>((int64_t)((size_t(1) << 30) / per_set), kMaxWgradSteps);
+            ahead = std::max(ahead, most / ahead * ahead);
+          }
         }
         const int64_t want = (pol && pol->step_group > 0) ? pol->step_group : std::max(cached, ahead);
         const int64_t group = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, fit), std::min<int64_t>(N, kMaxWgradSteps)));
@@ -1427,7 +1442,7 @@ struct Runner {
     {
       TimeScope ts(RAMPDE_K_FUSED_FORWARD, step_flops() * p.s * N, st);
       if (p.cluster) {
-        const int per = std::max(1, kClusterEvaluations / p.s), launches = (N + per - 1) / per, even = (N + launches - 1) / launches;
+        const int per = std::max(1, kClusterEvaluations / p.s / std::max(1, p.cl_RTN / 2)), launches = (N + per - 1) / per, even = (N + launches - 1) / launches;
         for (a.step = 0; a.step < N; a.step += even) {
           a.nsteps = std::min(even, N - a.step);
           rc = launch_cluster(false, a, a.step == 0);

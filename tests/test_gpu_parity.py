@@ -573,6 +573,11 @@ def test_time_grid_gradient_of_more_row_tiles_than_slots():
     ((128, 512, 400, 300, 128), 2048, "bf16", "none", "euler"),  # ... at the largest batch
     ((50, 300, 512, 50), 41, "f16", "dynamic", "rk4"),
     ((64, 512, 512, 512, 64), 1025, "bf16", "none", "euler"),
+    ((256, 1024, 1024, 256), 1100, "f16", "dynamic", "euler"),   # 128 rows per cluster, the last one ends past the padding
+    ((128, 1000, 1024, 128), 2048, "bf16", "none", "euler"),
+    ((200, 600, 768, 200), 1025, "bf16", "none", "heun"),        # 12 workgroups per cluster
+    ((128, 700, 128), 35, "f16", "dynamic", "rk4"),
+    ((100, 768, 700, 100), 513, "f16", "dynamic", "euler"),
 ])
 def test_cluster_kernels(widths, B, low, scaling, tab):
     cfg = wl.CONFIGS["cfg1"].with_(name="cl" + "_".join(map(str, widths)), B=B, N=4, widths=widths, low=low, tableau=tab, loss="mse")
