@@ -808,6 +808,7 @@ struct WgradArgs {
   int nsteps, nsets;
   int64_t set_stride;
   const float* steptab;
+  int step_splits;      // ... dealt out to this many workgroups per K-chunk (ksplits counts them all)
 };
 constexpr int kMaxWgradSteps = 64;  // steps per launch of wgrad_feature_major_steps
 
@@ -1007,7 +1008,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_feature_major_steps(WgradArgs g)
   const int r = t - y.tile0;
   const int ta = r % y.tiles_a, tb = r / y.tiles_a;
   const int a0 = ta * 128, b0 = tb * 128;
-  const int64_t k_begin = (int64_t)split * g.kchunk;
+  const int64_t k_begin = (int64_t)(split / g.step_splits) * g.kchunk;
   int64_t k_end = k_begin + g.kchunk;
   if (k_end > g.ldk) k_end = g.ldk;
   if (k_begin >= k_end) return;
@@ -1026,8 +1027,12 @@ __global__ __launch_bounds__(256, 2) void wgrad_feature_major_steps(WgradArgs g)
     s_accepted = n;
   }
   __syncthreads();
-  g.nsteps = s_accepted;
-  if (g.nsteps == 0) return;
+  {  // this workgroup's share of them
+    const int per = (g.nsteps + g.step_splits - 1) / g.step_splits, first = split % g.step_splits * per;
+    g.step -= first;
+    g.nsteps = min(s_accepted - first, per);
+  }
+  if (g.nsteps <= 0) return;
   // s_scale[i] = c_i / c_{i+1} with c_i = h / S of the launch's i-th step (the last: c_i itself):
   // multiplying the running sums by it when step i is complete leaves, at the end,
   // sum_i c_i * (partial sum of step i) without a second set of accumulators
@@ -1181,14 +1186,22 @@ __global__ __launch_bounds__(256, 2) void wgrad_feature_major_steps(WgradArgs g)
 }
 
 // g[i] += sum_c part[c][i]   (end of the backward pass: fold the per-K-chunk copies)
-__global__ void reduce_partial_gradients(float* __restrict__ g, const float* __restrict__ part, int64_t P, int copies,
-                                         const Ctl* ctl) {
+// (four threads of a workgroup per parameter, a quarter of the copies each, folded in a fixed order: the loads of one thread
+// are a chain of memory latencies on a small network)
+__global__ __launch_bounds__(256) void reduce_partial_gradients(float* __restrict__ g, const float* __restrict__ part, int64_t P, int copies,
+                                                               const Ctl* ctl) {
   if (ctl->poison) return;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P) return;
+  __shared__ float s[4][64];
+  const int e = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + e;
   float acc = 0.f;
-  for (int c = 0; c < copies; ++c) acc += part[(size_t)c * P + i];
-  g[i] += acc;
+  if (i < P) {
+#pragma unroll 8
+    for (int c = q; c < copies; c += 4) acc += part[(size_t)c * P + i];
+  }
+  s[q][e] = acc;
+  __syncthreads();
+  if (q == 0 && i < P) g[i] += (s[0][e] + s[1][e]) + (s[2][e] + s[3][e]);
 }
 
 }  // namespace rampde

@@ -116,6 +116,7 @@ struct Plan {
   bool overlap_wgrad = false;       // narrow nets: 4-wave adjoint kernel + parameter gradients on a helper stream
   int64_t Rp = 0, ldk = 0;          // feature-major buffers: k = stage * Rp + row
   int ksplits = 1, kchunk = 64;     // K-chunks of the parameter-gradient contraction
+  int step_splits = 1;              // ... times the parts into which a launch's steps are cut
   bool cw_blocks = false;           // convolutions: keep the weight-gradient kernel with 64 x 64 channel blocks (policy.wgrad_tile = 64)
   bool wgrad_slab = false;          // per-step parameter gradients by the 128 x 128-per-wavefront kernel
   int wgrad_group = 1;              // ... of this many adjoint steps per launch (each step has a buffer set of its own)
@@ -579,11 +580,22 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         const int resident = device_compute_units() * ((p.overlap_wgrad || p.wgrad_slab) ? 1 : 2);
         int64_t ks = std::max(1, resident / tiles);
         // (a group of steps multiplies a workgroup's k-steps: chunks can be shorter)
-        const int64_t min_chunk = p.step_group > 1 ? 128 : 256;
+        const int64_t min_chunk = p.step_group > 1 ? 64 : 256;
         ks = std::max<int64_t>(1, std::min<int64_t>(ks, p.ldk / min_chunk > 0 ? p.ldk / min_chunk : 1));
         const int64_t kc = ((p.ldk + ks - 1) / ks + 63) / 64 * 64;
         p.kchunk = (int)kc;
         p.ksplits = (int)((p.ldk + kc - 1) / kc);
+        // (and the steps of a group are dealt out where that still leaves compute units without one: as far as the copies
+        // stay below 32 MB.  us per pass with chunks of 128, with chunks of 64, with the steps dealt out too (and the copies
+        // folded by four threads per parameter: 128 copies by one thread took 20 us): 2-32-32-2, 256 rows, 8 steps
+        // 180 / 176 / 161; 50-200-200-50, 1003 rows, 20 Heun steps, dL/dt 330 / 316 / 306; flow of 10 features, width 100,
+        // 500 rows 352 / 310 / 285)
+        if (p.step_group > 1) {
+          const int64_t spare = resident / ((int64_t)tiles * p.ksplits), room = ((int64_t)32 << 20) / ((int64_t)p.ksplits * p.P * 4);
+          const int64_t parts = p.step_group * (kc / 64) / 4;  // (at least four k-steps of 64 each)
+          p.step_splits = (int)std::max<int64_t>(1, std::min(std::min(spare, room), parts));
+          p.ksplits *= p.step_splits;
+        }
         p.gpart = take(sizeof(float) * (size_t)p.ksplits * p.P);
       }
       // two sets of the per-step buffers: the parameter-gradient kernel of step i reads set i % 2
@@ -1809,6 +1821,7 @@ struct Runner {
     WgradArgs w{};
     w.L = p.L;
     w.ksplits = p.ksplits;
+    w.step_splits = p.step_splits;
     w.kchunk = p.kchunk;
     w.P = p.P;
     w.ldk = p.ldk;
@@ -2134,7 +2147,7 @@ struct Runner {
       if (use_fused) {
         a = grad_y0;
         if (p.overlap_wgrad) HIP_TRY(hipStreamWaitEvent(st, side.wgrad_done(0), 0));  // helper stream is in order: joins all
-        reduce_partial_gradients<<<blocks_for(p.P, 256), 256, 0, st>>>(grad_theta, f32(p.gpart), p.P, p.ksplits, ctl);
+        reduce_partial_gradients<<<blocks_for(p.P, 64), 256, 0, st>>>(grad_theta, f32(p.gpart), p.P, p.ksplits, ctl);
         if (p.cnf) {
           const Layer &y0 = p.layers[0], &y1 = p.layers[1];
           cnf_trace_fold<T><<<blocks_for(y0.out, 4), 256, 0, st>>>(f32(p.trace_slots), N, p.resident, theta + y0.theta_w,
