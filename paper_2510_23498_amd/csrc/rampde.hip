@@ -328,10 +328,11 @@ static void choose_clusters(Plan& p) {
 
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
 // gradient runs on the other row-tile kernels).  small: no choice of the streaming kernels, which keep slopes in the
-// workspace, where the register-resident ones can run
+// workspace, where the register-resident ones can run, and no clusters.  allow_clusters = false: no clusters, every other
+// choice as it is
 static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab,
                       const rampde_policy* pol, int is_backward, bool allow_wide = true, bool allow_resident = true,
-                      bool small = false) {
+                      bool small = false, bool allow_clusters = true) {
   Plan p;
   const bool allow_fused = fused_candidate(vel, pol);
   int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
@@ -465,7 +466,8 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
               p.ahead_lds = lds_need(m, false);
             }
       }
-      if (allow_resident && allow_wide && !small && want_rows == 0 && !p.wide && (p.ahead_MT || !is_backward) && !dense_stages(tab))
+      if (allow_resident && allow_wide && allow_clusters && !small && want_rows == 0 && !p.wide && (p.ahead_MT || !is_backward) &&
+          !dense_stages(tab))
         choose_clusters(p);
       for (auto& y : p.layers) {
         y.Wf = take((size_t)y.Npad * y.Kpad * 2);
@@ -2295,7 +2297,7 @@ static int forward_call(const rampde_velocity* vel, const float* theta, const fl
   if (!theta || !y0 || !ckpt || !yN || !workspace || B < 1) return RAMPDE_EINVAL;
   if (!aligned16(theta) || !aligned16(y0) || !aligned16(ckpt) || !aligned16(yN)) return RAMPDE_EINVAL;
   // (a launch of the cluster kernels that is given up may have written yN: not where that is y0 as well)
-  Plan p = make_plan(vel, B, N, tab, pol, 0, true, true, small || y0 == yN);
+  Plan p = make_plan(vel, B, N, tab, pol, 0, true, true, small, y0 != yN);
   if (!p.ok) return RAMPDE_EINVAL;
   if (workspace_bytes < p.total || ((uintptr_t)workspace & 255)) return RAMPDE_EWORKSPACE;
   const bool fused = p.fused;

@@ -631,3 +631,25 @@ def test_stage_inputs_formed_by_the_convolution(C, H, W, B, low, tab):
     # chain (kutta3: kernels of their own form the stage inputs there); two steps, so that the update forms one too
     cfg = wl.CONFIGS["cfg4"].with_(name="stagein", C=C, H=H, W=W, B=B, N=2, t1=0.25, low=low, tableau=tab)
     _both(cfg, bias_std=0.1, scaling="dynamic" if low == "f16" else "none")
+
+
+@pytest.mark.parametrize("widths,B,row_tile", [
+    ((64, 600, 64), 100, 32), ((128, 256, 128), 16384, 0), ((64, 256, 256, 64), 70, 64), ((140, 300, 140), 33, 0),
+    ((256, 1024, 1024, 256), 70, 0), ((128, 512, 512, 512, 128), 300, 0),  # (not by the clusters in place)
+])
+def test_forward_pass_in_place(widths, B, row_tile):
+    # yN = y0, on exactly the queried workspace: the bits of the call out of place, on the same kernels (for the cluster
+    # networks those of row tiles, which agree bit for bit among themselves in bf16)
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg1"].with_(name="in_place", B=B, N=3, widths=widths, low="bf16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    vel, tab, pol = par.gpu_descriptors(cfg, row_tile=row_tile)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    if widths[1] >= 512 and len(widths) > 3:
+        ref_pol = par.gpu_descriptors(cfg, row_tile=16)[2]
+    else:
+        ref_pol = pol
+    ref, ref_ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, ref_pol)
+    got, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol, yN=y)
+    assert got.data_ptr() == y.data_ptr() and torch.equal(got, ref) and torch.equal(ck, ref_ck)

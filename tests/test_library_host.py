@@ -168,6 +168,35 @@ def test_forward_rejects_bad_arguments_without_touching_the_device():
     assert rb.rampde_workspace_bytes(bad_vel, 4, 3, tab, pol, True) == 0
 
 
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="the pointers are dummies: only where no device can follow them")
+def test_queried_workspace_is_enough_for_every_call_in_place_too():
+    # the size that the query names is never refused: forward and backward, with yN = y0 and grad_y0 = grad_yN, over
+    # widths on both sides of every choice of kernels (there is no device here: the calls end at their first launch)
+    lib = rb.load_library()
+    p = lambda x: C.c_void_p(0x100000 * x)
+    N = 4
+    tg = np.linspace(0.0, 1.0, N + 1)
+    tgp = tg.ctypes.data_as(C.POINTER(C.c_double))
+    for widths in ((64, 600, 64), (30, 768, 30), (2, 1024, 2), (64, 256, 64), (128, 256, 128), (128, 512, 128), (128, 1000, 128),
+                   (64, 256, 256, 64), (50, 300, 512, 50), (128, 512, 512, 512, 128), (256, 1024, 1024, 256), (140, 300, 140)):
+        for row_tile in (0, 16, 32, 64):
+            for low, tabname in (("f16", "rk4"), ("bf16", "euler"), ("bf16", "kutta3")):
+                cfg = wl.CONFIGS["cfg1"].with_(widths=widths, tableau=tabname)
+                vel, tab, _ = _descr(cfg)
+                pol = rb.Policy(low=low, row_tile=row_tile)
+                pc = pol.c
+                for B in (1, 100, 1000, 4096, 16384, 60000):
+                    qf = rb.rampde_workspace_bytes(vel, B, N, tab, pol, False)
+                    qb = rb.rampde_workspace_bytes(vel, B, N, tab, pol, True)
+                    for yN in (4, 2):
+                        rc = lib.rampde_odeint_fwd(C.byref(vel.c), p(1), p(2), B, tgp, N, C.byref(tab.c), C.byref(pc), p(3), p(yN),
+                                                   p(5), qf, None)
+                        assert rc == rb.EHIP, (widths, row_tile, low, tabname, B, yN, rc)
+                        rc = lib.rampde_odeint_bwd(C.byref(vel.c), p(1), B, tgp, N, C.byref(tab.c), C.byref(pc), p(3), p(2), None,
+                                                   p(yN), p(7), None, None, p(5), qb, None)
+                        assert rc == rb.EHIP, (widths, row_tile, low, tabname, B, yN, rc)
+
+
 def test_backward_rejects_bad_arguments_without_touching_the_device():
     lib = rb.load_library()
     cfg = wl.CONFIGS["cfg1"]
