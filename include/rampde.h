@@ -40,8 +40,8 @@
  *   - Dense networks whose hidden layers are all 257 to 512 wide (two or three of them, state up to
  *     128) with up to 2048 rows, or all 513 to 768 or 769 to 1024 wide (one or two, state of 65 to 256)
  *     with up to 1024 rows (one) or 2048 (two): workgroups share row tiles and exchange activations within a launch, in forward and
- *     backward passes alike.  Where some of them are kept from running for 2 ms, the launch gives up,
- *     and kernels that do not wait do its work: behind it on the stream (forward passes and a fixed
+ *     backward passes alike.  Where some of them are kept from running for 2 ms, or an XCD is given
+ *     more of them than its share, the launch gives up, and kernels that do not wait do its work: behind it on the stream (forward passes and a fixed
  *     scale; nothing synchronises), or as above under overflow detection.  An explicit row_tile
  *     selects those kernels from the start.
  *   - theta layout (flat fp32, also the layout of grad_theta):
@@ -108,6 +108,8 @@ typedef enum {
 #define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale or activations within a launch (see
                                      the notes on concurrency above) give up at the first exchange, and the pass is
                                      redone by the kernels that do not.  Same results */
+#define RAMPDE_SKEWED_CLUSTERS 32u  /* test aid: workgroups that share row tiles (same notes) take their places as if one XCD had
+                                     been given a cluster's worth of them too many: the launch is given up and redone */
 
 /* Explicit Butcher tableau, host memory, fp64.  A is s*s row-major; only the strictly
  * lower triangle may be non-zero (checked).  Consistency (sum b = 1, ...) is not checked. */

@@ -30,9 +30,10 @@
 // instead of 2.2.
 //
 // Members find each other at run time: a workgroup takes a ticket of the XCD that it runs on.  Waits end after
-// kWaitTicks (the workgroups of a launch did not run at the same time, or not C to an XCD): the launch then writes
-// `stalled` and no result that is not overwritten, and the row-tile kernels redo its work: behind it on the stream, as
-// launches that do nothing otherwise (forward, fixed scale), or by way of the host (under overflow detection).
+// kWaitTicks (the workgroups of a launch did not run at the same time), and a workgroup that finds its XCD's share of the
+// launch taken gives up at once (the workgroups were not spread evenly over the XCDs): the launch then writes `stalled`
+// and no result that is not overwritten, and the row-tile kernels redo its work: behind it on the stream, as launches that
+// do nothing otherwise (forward, fixed scale), or by way of the host (under overflow detection).
 #pragma once
 #include "resident.hpp"
 
@@ -129,10 +130,11 @@ __global__ __launch_bounds__(256) void cast_cluster_fragments(ClusterCast c) {
 
 typedef uint32_t u32x4c __attribute__((ext_vector_type(4)));
 
-// before a launch: nothing has been written, no ticket taken
-__global__ __launch_bounds__(256) inline void cluster_reset(u32x4c* x, size_t n, unsigned* tickets, int* stalled) {
+// before a launch: nothing has been written, no ticket taken (skew: the first XCD's tickets start there, as if it had been
+// given that many workgroups more)
+__global__ __launch_bounds__(256) inline void cluster_reset(u32x4c* x, size_t n, unsigned* tickets, int* stalled, unsigned skew) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) x[i] = u32x4c{kUnwritten, kUnwritten, kUnwritten, kUnwritten};
-  if (blockIdx.x == 0 && threadIdx.x < 8) tickets[threadIdx.x] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x < 8) tickets[threadIdx.x] = threadIdx.x == 0 ? skew : 0u;
   if (stalled && blockIdx.x == 0 && threadIdx.x == 0) *stalled = 0;
 }
 
@@ -148,6 +150,7 @@ struct ClusterEngine {
   unsigned long long ticks;
   lds_f32* red;   // [2][4 destinations][3][2][64 lanes] x 16 B: partial sums
   RAMPDE_LDS int* dead;
+  bool lost = false;  // setup gave the launch up
   int par = 0;    // half of `red` in use
   u16x8 w1[2][KS1];
   u16x8 wm[MIDS > 0 ? MIDS : 1][2][KSH];
@@ -174,11 +177,11 @@ struct ClusterEngine {
     const int rank = __builtin_amdgcn_readfirstlane(sh[2]);
     cl = __builtin_amdgcn_readfirstlane(sh[1]) + 8 * (rank / Sh::C);
     me = rank % Sh::C;
-    if (sh[0] || cl >= a.clusters) return false;
-    if (ticks == 0) {
-      give_up();
-      return false;
-    }
+    if (sh[0]) return false;
+    // (more workgroups here than an XCD's share: others have fewer, and a cluster that nobody joins has nobody to notice)
+    lost = ticks == 0 || rank >= (a.clusters + 7) / 8 * Sh::C;
+    if (lost) give_up();
+    if (lost || cl >= a.clusters) return false;
     unit_ct = me % Sh::CTS;
     unit_rt = me / Sh::CTS < Sh::APC ? me / Sh::CTS : -1;
     xr = __builtin_amdgcn_make_buffer_rsrc((char*)a.exchange + (size_t)cl * Sh::exchange_bytes, 0, (int)Sh::exchange_bytes, 0x00020000);
@@ -533,7 +536,7 @@ __global__ __launch_bounds__(256, 1) void mlp_chain_cluster(ClusterArgs a) {
     }
   };
   if (!part) {
-    if (c.ticks == 0) lost();
+    if (c.lost) lost();
     return;
   }
   const int s = g.s;

@@ -1151,6 +1151,7 @@ struct Runner {
   // ------------------------------------------------ row-tile-persistent path (dense networks)
   bool use_fused = false;
   unsigned long long wait_ticks = kWaitTicks;
+  bool skewed_clusters = false;  // (see RAMPDE_SKEWED_CLUSTERS)
 
   CastArgs cast_args(const float* theta) const {
     CastArgs c{};
@@ -1424,7 +1425,8 @@ struct Runner {
     ca.clusters = p.cl_n;
     const size_t words = (size_t)p.cl_n * cluster_exchange_bytes(p.cluster, p.L, p.dpad, p.cl_RTN) / 16;
     cluster_reset<<<(unsigned)std::min<size_t>((words + 255) / 256, 2048), 256, 0, st>>>((u32x4c*)ca.exchange, words, ca.tickets,
-                                                                                       reset_stalled ? ca.stalled : nullptr);
+                                                                                       reset_stalled ? ca.stalled : nullptr,
+                                                                                       skewed_clusters ? p.cluster / 64 : 0);
     ClusterLaunch l{};
     l.chain = chain ? 1 : 0;
     l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
@@ -1448,6 +1450,7 @@ struct Runner {
     prologue(theta, tgrid, N, tab, pol->low, !p.cluster, false, false);
     FusedArgs a = fused_args(tab, N);
     if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
+    skewed_clusters = (pol->flags & RAMPDE_SKEWED_CLUSTERS) != 0;
     a.y0 = y0;
     a.y = yN;
     a.ckpt = ckpt;
@@ -1895,6 +1898,7 @@ struct Runner {
                float* grad_y0, float* grad_theta, float* grad_t, float* scale_hist, rampde_stats* stats) {
     const int dynamic = scaling == RAMPDE_SCALE_DYNAMIC;
     if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
+    skewed_clusters = (pol->flags & RAMPDE_SKEWED_CLUSTERS) != 0;
     if (grad_t && !use_fused) {
       fill_zero_u32<<<1, 256, 0, st>>>((uint32_t*)(ws + p.tpart), 2 * (size_t)N);
       fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.tslots), 2 * kTimeSlotPairs);

@@ -603,6 +603,23 @@ def test_cluster_launches_that_were_given_up(widths, B):
             assert np.any(got["yN"] != clusters["yN"])
 
 
+@pytest.mark.parametrize("widths,B", [((256, 1024, 1024, 256), 70), ((256, 1024, 1024, 256), 300), ((128, 512, 512, 512, 128), 1030)])
+def test_workgroups_that_are_not_spread_evenly_over_the_dies(widths, B):
+    # one XCD has more workgroups of a launch than its share, so that a cluster elsewhere has none and nobody waits for it
+    # (70 rows: 3 clusters on 8 XCDs, 300 rows: 10): its rows are computed all the same, by the row-tile kernels
+    from paper_2510_23498_amd import binding as rb
+    for low, scaling in (("bf16", "none"), ("f16", "dynamic")):
+        cfg = wl.CONFIGS["cfg1"].with_(name="skewed", B=B, N=3, widths=widths, low=low, loss="mse")
+        theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+        got = par.run_gpu(cfg, theta, y0, target, scaling=scaling, flags=rb.SKEWED_CLUSTERS)
+        rows = par.run_gpu(cfg, theta, y0, target, scaling=scaling, row_tile=16)
+        par.compare(cfg, got, rows, par.TOL_EMUL, "the row-tile kernels")
+        np.testing.assert_array_equal(got["scale_hist"], rows["scale_hist"])
+        if low == "bf16":
+            for key in ("yN", "ckpt", "grad_y0"):
+                np.testing.assert_array_equal(got[key], rows[key])
+
+
 @pytest.mark.parametrize("widths,B,low,tab", [
     ((64, 256, 256, 64), 1, "f16", "rk4"), ((30, 200, 130, 256, 30), 4, "bf16", "heun"), ((7, 100, 7), 3, "f16", "euler"),
     ((64, 256, 256, 64), 5, "f16", "rk4"),  # one row more: the ordinary tile
