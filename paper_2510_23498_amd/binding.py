@@ -31,6 +31,11 @@ K_VELOCITY_GEMM, K_WGRAD_GEMM, K_COMBINE_STORE, K_ADJOINT_UPDATE, K_FUSED_FORWAR
 ROUND_INCREMENT, GROW_RAW_NORM, PER_LAYER_KERNELS, NAIVE_STATE, NO_WAITS, SKEWED_CLUSTERS = 1, 2, 4, 8, 16, 32
 
 
+def no_waits_after(n: int) -> int:
+    """RAMPDE_NO_WAITS_AFTER(n)"""
+    return NO_WAITS | n << 16
+
+
 class _Tableau(C.Structure):
     _fields_ = [("s", C.c_int), ("A", C.POINTER(C.c_double)), ("b", C.POINTER(C.c_double)),
                 ("c", C.POINTER(C.c_double))]

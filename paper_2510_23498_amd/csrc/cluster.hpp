@@ -66,6 +66,7 @@ struct ClusterArgs {
   unsigned* tickets;       // [8], zero at the start of the launch
   int* stalled;            // raised when a wait ran out; raised before the launch: nothing is done
   int clusters;
+  int budget;              // evaluations of this launch after which it is given up (see RAMPDE_NO_WAITS_AFTER)
 };
 
 // theta (fp32) -> the wavefronts' weight fragments (transposed: as the cotangent chain multiplies by them)
@@ -179,7 +180,7 @@ struct ClusterEngine {
     me = rank % Sh::C;
     if (sh[0]) return false;
     // (more workgroups here than an XCD's share: others have fewer, and a cluster that nobody joins has nobody to notice)
-    lost = ticks == 0 || rank >= (a.clusters + 7) / 8 * Sh::C;
+    lost = a.budget <= 0 || rank >= (a.clusters + 7) / 8 * Sh::C;
     if (lost) give_up();
     if (lost || cl >= a.clusters) return false;
     unit_ct = me % Sh::CTS;
@@ -503,7 +504,7 @@ __global__ __launch_bounds__(256, 1) void mlp_forward_cluster(ClusterArgs a) {
         c.publish_z(e + 1, rt, zq);
         if (last_stage) store4h(g.ckpt + (size_t)(i + 1) * n_state, row, g.R, ns, g.d, zq);
       };
-      if (!c.evaluate(e, hid, st, []() {})) {
+      if (e == a.budget || !c.evaluate(e, hid, st, []() {})) {
         c.give_up();
         return;
       }
@@ -652,7 +653,7 @@ __global__ __launch_bounds__(256, 1) void mlp_chain_cluster(ClusterArgs a) {
         for (int r = 0; r < 4; ++r) da[u][r] += zf[u][r];
         if (j > 0) make_kbar(e + 1, u, rt, j - 1);
       };
-      if (!c.evaluate(e, hid, st, [&]() { fetch_act(act_next, step_next, j_next); })) {
+      if (e == a.budget || !c.evaluate(e, hid, st, [&]() { fetch_act(act_next, step_next, j_next); })) {
         lost();
         return;
       }

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <array>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -1151,7 +1152,15 @@ struct Runner {
   // ------------------------------------------------ row-tile-persistent path (dense networks)
   bool use_fused = false;
   unsigned long long wait_ticks = kWaitTicks;
-  bool skewed_clusters = false;  // (see RAMPDE_SKEWED_CLUSTERS)
+  bool skewed_clusters = false;      // (see RAMPDE_SKEWED_CLUSTERS)
+  int64_t cluster_budget = INT_MAX;  // evaluations that the pass's cluster launches may still run (see RAMPDE_NO_WAITS_AFTER)
+
+  void test_aids(unsigned flags) {
+    skewed_clusters = (flags & RAMPDE_SKEWED_CLUSTERS) != 0;
+    if (!(flags & RAMPDE_NO_WAITS)) return;
+    if (p.cluster) cluster_budget = flags >> 16;
+    else wait_ticks = 0;
+  }
 
   CastArgs cast_args(const float* theta) const {
     CastArgs c{};
@@ -1423,6 +1432,8 @@ struct Runner {
     ca.tickets = (unsigned*)(ws + p.cl_tickets);
     ca.stalled = &ctl->cluster_stalled;
     ca.clusters = p.cl_n;
+    ca.budget = (int)std::max<int64_t>(0, std::min<int64_t>(cluster_budget, INT_MAX));
+    if (cluster_budget < INT_MAX) cluster_budget -= (int64_t)a.nsteps * p.s;
     const size_t words = (size_t)p.cl_n * cluster_exchange_bytes(p.cluster, p.L, p.dpad, p.cl_RTN) / 16;
     cluster_reset<<<(unsigned)std::min<size_t>((words + 255) / 256, 2048), 256, 0, st>>>((u32x4c*)ca.exchange, words, ca.tickets,
                                                                                        reset_stalled ? ca.stalled : nullptr,
@@ -1449,8 +1460,7 @@ struct Runner {
     if (p.cluster) cast_cluster(theta, false);
     prologue(theta, tgrid, N, tab, pol->low, !p.cluster, false, false);
     FusedArgs a = fused_args(tab, N);
-    if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
-    skewed_clusters = (pol->flags & RAMPDE_SKEWED_CLUSTERS) != 0;
+    test_aids(pol->flags);
     a.y0 = y0;
     a.y = yN;
     a.ckpt = ckpt;
@@ -1897,8 +1907,7 @@ struct Runner {
                rampde_scaling scaling, const uint16_t* ckpt, const float* grad_yN, const float* grad_ys,
                float* grad_y0, float* grad_theta, float* grad_t, float* scale_hist, rampde_stats* stats) {
     const int dynamic = scaling == RAMPDE_SCALE_DYNAMIC;
-    if (pol->flags & RAMPDE_NO_WAITS) wait_ticks = 0;
-    skewed_clusters = (pol->flags & RAMPDE_SKEWED_CLUSTERS) != 0;
+    test_aids(pol->flags);
     if (grad_t && !use_fused) {
       fill_zero_u32<<<1, 256, 0, st>>>((uint32_t*)(ws + p.tpart), 2 * (size_t)N);
       fill_zero_u32<<<256, 256, 0, st>>>((uint32_t*)(ws + p.tslots), 2 * kTimeSlotPairs);

@@ -603,6 +603,65 @@ def test_cluster_launches_that_were_given_up(widths, B):
             assert np.any(got["yN"] != clusters["yN"])
 
 
+@pytest.mark.parametrize("widths,B", [((128, 512, 512, 128), 70), ((128, 700, 128), 600), ((256, 1024, 1024, 256), 1100)])
+@pytest.mark.parametrize("after", [3, 10, 26])
+def test_cluster_launches_given_up_in_mid_pass(widths, B, after):
+    # with part of the results written: the one forward launch (28 evaluations), and of four groups of adjoint steps
+    # (8, 8, 8 and 4 evaluations) the first, the second and the last one.  The forward pass is redone from y0; under a fixed
+    # scale the group is redone from the adjoint that its predecessor left, under detection the whole pass
+    from paper_2510_23498_amd import binding as rb
+    for low, scaling in (("bf16", "none"), ("f16", "dynamic")):
+        cfg = wl.CONFIGS["cfg1"].with_(name="mid_pass", B=B, N=7, widths=widths, low=low, loss="mse")
+        theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+        gys = (np.random.default_rng(5).standard_normal((cfg.N + 1,) + cfg.state_shape) * 0.01 / y0.size).astype(np.float32)
+        got = par.run_gpu(cfg, theta, y0, target, scaling=scaling, flags=rb.no_waits_after(after), step_group=2, grad_ys=gys)
+        rows = par.run_gpu(cfg, theta, y0, target, scaling=scaling, row_tile=16, grad_ys=gys)
+        par.compare(cfg, got, rows, par.TOL_EMUL, "the row-tile kernels")
+        np.testing.assert_array_equal(got["scale_hist"], rows["scale_hist"])
+        if low == "bf16":
+            for key in ("yN", "ckpt"):
+                np.testing.assert_array_equal(got[key], rows[key])
+
+
+@pytest.mark.parametrize("after", [5, 300, 799])
+def test_later_launch_of_a_forward_pass_on_clusters_is_given_up(after):
+    # 200 RK4 steps are three launches of 268 evaluations; yN holds the state between them
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg1"].with_(name="pieces", B=40, N=200, widths=(128, 512, 512, 128), low="bf16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    out = []
+    for kw in (dict(flags=rb.no_waits_after(after)), dict(row_tile=16), {}):
+        vel, tab, pol = par.gpu_descriptors(cfg, **kw)
+        out.append(rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert not torch.equal(out[2][1], out[1][1])  # (undisturbed: another order of sums)
+
+
+@pytest.mark.parametrize("widths,B", [((128, 512, 512, 128), 65), ((200, 1000, 200), 33)])
+@pytest.mark.parametrize("N,in_place", [(7, False), (8, False), (7, True), (8, True)])
+def test_groups_of_steps_on_clusters_under_a_fixed_scale(widths, B, N, in_place):
+    # the adjoint goes from group to group through two buffers in turn, an even and an odd number of them, the last group
+    # short or full; running cost; dL/dy_0 in the place of dL/dy_N
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg1"].with_(name="clgroups", B=B, N=N, widths=widths, low="bf16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    gys = torch.randn(N + 1, B, widths[0], generator=torch.Generator().manual_seed(3)).to(dev)
+    out = []
+    for kw in (dict(step_group=2), dict(row_tile=16)):
+        vel, tab, pol = par.gpu_descriptors(cfg, **kw)
+        yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
+        g = yN.clone()
+        gy0, gth, _ = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, g, grad_ys=gys,
+                                           grad_y0=g if in_place and "step_group" in kw else None)
+        out.append((gy0.cpu().numpy(), gth.cpu().numpy()))
+    for a, b in zip(*out):
+        assert par.rel_err(a, b) <= par.TOL_EMUL
+
+
 @pytest.mark.parametrize("widths,B", [((256, 1024, 1024, 256), 70), ((256, 1024, 1024, 256), 300), ((128, 512, 512, 512, 128), 1030)])
 def test_workgroups_that_are_not_spread_evenly_over_the_dies(widths, B):
     # one XCD has more workgroups of a launch than its share, so that a cluster elsewhere has none and nobody waits for it

@@ -263,6 +263,9 @@ GROUPED = [
     ("cfg2", dict(name="retry1h2", B=40, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(128, 512, 128))),
     ("cnf", dict(name="retrycnf", B=100, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(20, 200, 20))),
     ("cnf", dict(name="retrycnfw", B=40, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(15, 600, 15))),
+    # workgroups that share row tiles (groups of two steps and up; one step per group and dL/dt: the row-tile kernels)
+    ("cfg2", dict(name="retrycl512", B=70, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(128, 512, 512, 128))),
+    ("cfg2", dict(name="retrycl768", B=40, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(128, 700, 128))),
 ]
 
 
