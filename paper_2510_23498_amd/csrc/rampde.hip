@@ -327,6 +327,23 @@ static void choose_clusters(Plan& p) {
   }
 }
 
+// Groups of steps under a fixed scale on the streaming kernels: whether their stages are recomputed in a launch of their
+// own.  That spares the adjoint kernel the weight stream of its smaller tiles, and costs the activations' way through
+// memory.  Not where its own 32-row tiles fill three quarters of their rounds and the network is shallow, nor with one
+// 1024-wide layer (16-row tiles), whose activations are the larger part.  bf16, 8 RK4 steps, inside / ahead, us:
+// 64 -> 2 x 512 -> 64 B = 6000 (73 % of a round) 1421 / 1417, B = 6900 1490 / 1552, B = 8192 1569 / 1663, B = 10000
+// 2492 / 2365, B = 16384 2904 / 3076; 200 -> 2 x 256 -> 200 B = 8192 1019 / 1068, B = 10000 1708 / 1613; 256 -> 256 -> 256
+// B = 4096 509 / 497, B = 6000 730 / 718, B = 6900 769 / 796, B = 8192 794 / 831; 128 -> 2 x 300 -> 128 B = 8192 1650 / 1682, B = 16384 2791 / 2759; but three layers 64 -> 3 x 512 -> 64
+// B = 8192 2545 / 2527, 128 -> 3 x 256 -> 128 1132 / 1091, wider ones 64 -> 2 x 1024 -> 64 4794 / 4692, 100 -> 600 -> 100
+// 1371 / 1339.  128 -> 1000 -> 128 B = 2100 792 / 772, B = 2560 833 / 856, B = 4096 914 / 1018, B = 16384 3097 / 3489
+static bool group_recomputes_ahead(const Plan& p) {
+  const int64_t cus = device_compute_units(), tiles = (p.R + 16 * p.MT - 1) / (16 * p.MT), rounds = (tiles + cus - 1) / cus;
+  int widest = 0;
+  for (int l = 0; l + 1 < p.L; ++l) widest = std::max(widest, p.layers[l].Npad);
+  if (p.L == 2 && widest == 1024 && p.dpad <= 128) return 16 * tiles <= 9 * cus;
+  return !(p.MT == 2 && p.L <= 3 && widest <= 512 && 4 * tiles >= 3 * rounds * cus);
+}
+
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
 // gradient runs on the other row-tile kernels).  small: no choice of the streaming kernels, which keep slopes in the
 // workspace, where the register-resident ones can run, and no clusters.  allow_clusters = false: no clusters, every other
@@ -545,10 +562,17 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // inside / ahead, us: B = 4096 (4 steps) 4171 / 3731, B = 8192 (2 steps, a full round) 5934 / 5540, B = 6000
         // (2 steps, 0.7 rounds) 4949 / 5026, 2 x 300 with B = 12000 7247 / 7533)
         int64_t ahead = 1;
+        if (p.ahead_MT && p.step_group > 1 && !group_recomputes_ahead(p)) p.ahead_MT = 0;
         if (p.ahead_MT) {
           const int64_t cus = device_compute_units(), t = (p.R + 16 * p.ahead_MT - 1) / (16 * p.ahead_MT);
           ahead = cus / t;
-          if (ahead == 2 && 40 * t < 17 * cus) ahead = 1;
+          // (nor one or two 512-wide layers between narrow states, whose own 32-row tiles are at their best there, and
+          // three only close to a full round: f16, 8 RK4 steps, inside / ahead, us: 64 -> 2 x 512 -> 64 B = 7000 1708 / 1786,
+          // B = 8192 1776 / 1885; 128 -> 2 x 300 -> 128 B = 8192 1824 / 1898; 64 -> 3 x 512 -> 64 B = 7000 2540 / 2620,
+          // B = 8192 2782 / 2740; but 128 -> 3 x 512 -> 128 B = 8192 2983 / 2858, 200 -> 2 x 256 -> 200 1450 / 1356,
+          // 256 -> 2 x 512 -> 256 2498 / 2442)
+          const bool narrow512 = p.dpad <= 128 && p.layers[0].Npad == 512;
+          if (ahead == 2 && (40 * t < (narrow512 && p.dpad == 64 ? 19 : 17) * cus || (p.L <= 3 && narrow512))) ahead = 1;
           // (clusters: every launch of a group loads the weights and starts the exchange anew, and a group is one pass over
           // the gradient copies: as many steps as about 1 GiB holds, in whole rounds of the recomputation.  256 -> 2 x 1024 -> 256,
           // f16, 1024 rows, 256 steps with groups of 8 / 16 steps 29.3 / 28.5 ms; 128 -> 3 x 512 -> 128, bf16, 2000

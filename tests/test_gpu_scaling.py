@@ -523,6 +523,15 @@ def test_backward_pass_beside_a_long_forward_pass_on_another_stream():
     ((70, 300, 190, 70), 130, 6, "f16", "rk4", 1.0),            # run-time widths
     ((128, 512, 512, 512, 128), 300, 6, "f16", "rk4", 256.0),   # rejected steps inside a group
     ((128, 512, 512, 128), 4096, 3, "f16", "rk4", 1.0),         # several groups of whole rounds
+    # both sides of the line where groups under a fixed scale recompute inside instead: 32-row tiles that fill three quarters
+    # of a round, 16-row tiles of one 1024-wide layer past nine sixteenths
+    ((64, 512, 512, 64), 6112, 3, "bf16", "euler", 1.0),
+    ((64, 512, 512, 64), 6113, 3, "bf16", "euler", 1.0),
+    ((128, 1000, 128), 2304, 3, "bf16", "heun", 1.0),
+    ((128, 1000, 128), 2305, 3, "bf16", "heun", 1.0),
+    # and under detection: groups of two steps from 6913 rows on, of none with two 512-wide layers
+    ((128, 512, 512, 512, 128), 6913, 4, "f16", "euler", 1.0),
+    ((64, 512, 512, 64), 8192, 4, "f16", "euler", 1.0),
 ])
 def test_stages_recomputed_ahead_equal_those_recomputed_inside(widths, B, N, low, tab, gain):
     # one step per group recomputes inside the adjoint kernel.  The contractions sum in the same order in both: in bf16
@@ -535,9 +544,10 @@ def test_stages_recomputed_ahead_equal_those_recomputed_inside(widths, B, N, low
     cfg, theta, y0, target = _gain_case("cfg3", name="ahead", widths=widths, B=B, N=N, t1=0.015 * N, low=low, tableau=tab,
                                         gain=gain, scaling="dynamic" if low == "f16" else "none")
     # (row_tile: the row-tile kernels, not the clusters of cluster.hpp)
-    one = par.run_gpu(cfg, theta, y0, target, step_group=1, row_tile=16)
+    row_tile = 16 if B <= 2048 else 0
+    one = par.run_gpu(cfg, theta, y0, target, step_group=1, row_tile=row_tile)
     for group in (0, 2):
-        got = par.run_gpu(cfg, theta, y0, target, step_group=group, row_tile=16)
+        got = par.run_gpu(cfg, theta, y0, target, step_group=group, row_tile=row_tile)
         assert got["retries"] == one["retries"] and (gain == 1.0 or one["retries"] > 0)
         np.testing.assert_array_equal(got["scale_hist"], one["scale_hist"])
         if low == "bf16":

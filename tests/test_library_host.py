@@ -121,6 +121,19 @@ def test_forward_rule_of_one_hidden_layer_at_the_edges_of_a_round():
         assert (rb.rampde_workspace_bytes(vel, B, cfg.N, tab, pol, False) > 4 * B * 128 * 2) == streaming, B
 
 
+@pytest.mark.parametrize("widths,B,ahead", [
+    ((64, 512, 512, 64), 4096, True), ((64, 512, 512, 64), 7000, False), ((64, 512, 512, 64), 8192, False),
+    ((128, 300, 300, 128), 8192, False), ((64, 512, 512, 512, 64), 7400, False), ((64, 512, 512, 512, 64), 8192, True),
+    ((128, 512, 512, 512, 128), 6912, False), ((128, 512, 512, 512, 128), 6913, True), ((200, 256, 256, 200), 8192, True),
+])
+def test_recomputation_ahead_under_detection(widths, B, ahead):
+    # as many buffer sets as steps are recomputed ahead: more than the one of a plan with one step per group
+    cfg = wl.CONFIGS["cfg2"].with_(widths=widths, low="f16")
+    vel, tab, _ = _descr(cfg)
+    size = [rb.rampde_workspace_bytes(vel, B, 8, tab, rb.Policy(low="f16", step_group=g, wgrad_tile=256), True) for g in (0, 1)]
+    assert (size[0] > size[1]) == ahead
+
+
 def test_checkpoint_store_is_half_of_fp32():
     # only the low-precision states are kept (paper Sec. 3): (N+1) * n * 2 bytes
     for cfg in wl.CONFIGS.values():
