@@ -327,6 +327,21 @@ static void choose_clusters(Plan& p) {
   }
 }
 
+// Groups of steps of the register-resident kernels: recomputed ahead, except where one kernel holds both directions'
+// slices (up to three layers, 16-row tiles) and its tiles already fill the device.  64 -> 256 -> 256 -> 64, 32 RK4 steps,
+// us per pass with one kernel / recomputed ahead: bf16 4096 rows 1084 / 1095, 3000 rows 991 / 946, 2000 rows 889 / 818,
+// 8192 rows (32-row tiles) 1072 / 1040 with 16 steps; 40 -> 100 -> 100 -> 40, 8000 rows (two workgroups per compute
+// unit) 561 / 579; four layers of 256, 4000 rows 886 / 808; 2 -> 32 -> 32 -> 2, f16, 256 rows, 8 steps 237 / 222;
+// 50 -> 200 -> 200 -> 50 with the time-grid gradient, 1003 rows, Heun 414 / 347.
+static bool resident_ahead(const Plan& p, int step_group) {
+  if (!p.resident || step_group < 2) return false;
+  // (one hidden layer: flow of 63 features, width 1024, f16, 512 rows 793 / 584, 4096 rows 1462 / 1411; 128 -> 512 -> 128,
+  // bf16, 1000 rows 550 / 399, 16000 rows 2578 / 2308; flow of 10 features, width 100, 8000 rows 705 / 710)
+  if (p.shallow) return p.resident > 128 || 8 * ((p.R + 15) / 16) <= 7 * 2 * (int64_t)device_compute_units();
+  const int64_t slots = (int64_t)device_compute_units() * (p.resident == 256 ? 1 : 2), tiles = (p.R + 16 * p.MT - 1) / (16 * p.MT);
+  return p.MT == 2 || p.L == 4 || 8 * tiles <= 7 * slots;
+}
+
 // Groups of steps under a fixed scale on the streaming kernels: whether their stages are recomputed in a launch of their
 // own.  That spares the adjoint kernel the weight stream of its smaller tiles, and costs the activations' way through
 // memory.  Not where its own 32-row tiles fill three quarters of their rounds and the network is shallow, nor with one
@@ -524,6 +539,9 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       p.ldk = (int64_t)p.s * p.Rp;
       size_t per_set = 2 * (size_t)p.dpad * p.ldk * 2;
       for (int l = 0; l + 1 < p.L; ++l) per_set += 2 * (size_t)p.layers[l].Npad * p.ldk * 2;
+      // (register-resident kernels, time-grid gradient: the slopes too where stages are recomputed ahead)
+      const size_t slopes = resident_ahead(p, kMaxWgradSteps) && !p.shallow && !allow_wide ? (size_t)p.dpad * p.ldk * 2 : 0;
+      per_set += slopes;
       // buffer sets in about 4 GiB, or in 1 GiB under overflow detection (at most 75 MB a set there: its tiles run at
       // once).  64 -> 256 -> 256 -> 64, 4096 rows, f16, 32 RK4 steps under detection, us per pass with groups of 1 / 2 /
       // 4 / 8 / 16 / 32 steps (37 MB each): 2397 / 1715 / 1363 / 1353 / 1279 / 1218.  Without it a set can be larger and
@@ -630,7 +648,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       const size_t fm_begin = off;
       p.ZT = take((size_t)p.dpad * p.ldk * 2);
       p.KBART = take((size_t)p.dpad * p.ldk * 2);
-      if (p.resident && !p.shallow && !allow_wide) p.KT = take((size_t)p.dpad * p.ldk * 2);
+      if (slopes && resident_ahead(p, p.step_group)) p.KT = take(slopes);
       for (int l = 0; l + 1 < p.L; ++l) {
         p.ACTT.push_back(take((size_t)p.layers[l].Npad * p.ldk * 2));
         p.DELTAT.push_back(take((size_t)p.layers[l].Npad * p.ldk * 2));
@@ -1375,21 +1393,6 @@ struct Runner {
     return launch_fused_width(l, a);
   }
 
-  // Groups of steps of the register-resident kernels: recomputed ahead, except where one kernel holds both directions'
-  // slices (up to three layers, 16-row tiles) and its tiles already fill the device.  64 -> 256 -> 256 -> 64, 32 RK4 steps,
-  // us per pass with one kernel / recomputed ahead: bf16 4096 rows 1084 / 1095, 3000 rows 991 / 946, 2000 rows 889 / 818,
-  // 8192 rows (32-row tiles) 1072 / 1040 with 16 steps; 40 -> 100 -> 100 -> 40, 8000 rows (two workgroups per compute
-  // unit) 561 / 579; four layers of 256, 4000 rows 886 / 808; 2 -> 32 -> 32 -> 2, f16, 256 rows, 8 steps 237 / 222;
-  // 50 -> 200 -> 200 -> 50 with the time-grid gradient, 1003 rows, Heun 414 / 347.
-  bool resident_ahead() const {
-    if (!p.resident || p.step_group < 2) return false;
-    // (one hidden layer: flow of 63 features, width 1024, f16, 512 rows 793 / 584, 4096 rows 1462 / 1411; 128 -> 512 -> 128,
-    // bf16, 1000 rows 550 / 399, 16000 rows 2578 / 2308; flow of 10 features, width 100, 8000 rows 705 / 710)
-    if (p.shallow) return p.resident > 128 || 8 * (int64_t)blocks_for(p.R, 16) <= 7 * 2 * (int64_t)device_compute_units();
-    const int64_t slots = (int64_t)device_compute_units() * (p.resident == 256 ? 1 : 2), tiles = blocks_for(p.R, 16 * p.MT);
-    return p.MT == 2 || p.L == 4 || 8 * tiles <= 7 * slots;
-  }
-
   int launch_resident(ResidentKind kind, const FusedArgs& a) {
     ResidentArgs ra{};
     ra.f = a;
@@ -1526,7 +1529,7 @@ struct Runner {
           again.only_if = &ctl->cluster_stalled;
           rc = launch_fused(true, again);
         }
-      } else if (!rc && resident_ahead()) {
+      } else if (!rc && resident_ahead(p, p.step_group)) {
         rc = launch_resident(kResidentRecompute, a);
         if (!rc) rc = launch_resident(kResidentChain, a);
       } else if (!rc) rc = p.resident ? launch_resident(kResidentAdjoint, a) : launch_fused(true, a);

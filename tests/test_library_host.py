@@ -82,6 +82,7 @@ def test_weight_gradient_of_eight_pixel_lines_pads_only_short_contractions(C):
     ("cfg2", dict(low="f16", B=4096, N=64)),
     ("cfg2", dict(low="f16", B=4096, N=64, widths=(128, 512, 128))),
     ("cnf", dict(B=4000, N=64)),
+    ("cfg2", dict(low="f16", B=8192, N=64, widths=(64, 64, 64))),  # (the slopes that dL/dt needs are part of a step's buffers)
 ])
 def test_workspace_of_grouped_steps_under_detection(base, kw):
     # include/rampde.h: about 1 GiB of per-step buffers (and what else a pass keeps); fewer with a smaller step_group
