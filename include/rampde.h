@@ -147,7 +147,7 @@ typedef struct {
                              and hidden layer up to 1024, or 128 and 512) and flows (up to 64 state columns), which
                              run as many as about 1 GiB holds, at most 64, and for wide networks, whose stages are
                              recomputed for as many steps at once as fill the device (and 4 GiB hold; where
-                             workgroups share row tiles, see above, as 1 GiB holds).  A smaller value is the way to a smaller
+                             workgroups share row tiles, see above, more of them, as about 640 MiB hold).  A smaller value is the way to a smaller
                              workspace.  Where wgrad_tile = 256 applies this is the number of accepted steps
                              whose parameter gradients one launch forms (default: as many as keep their buffers in
                              the memory-side cache) */

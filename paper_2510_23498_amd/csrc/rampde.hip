@@ -592,11 +592,14 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
           const bool narrow512 = p.dpad <= 128 && p.layers[0].Npad == 512;
           if (ahead == 2 && (40 * t < (narrow512 && p.dpad == 64 ? 19 : 17) * cus || (p.L <= 3 && narrow512))) ahead = 1;
           // (clusters: every launch of a group loads the weights and starts the exchange anew, and a group is one pass over
-          // the gradient copies: as many steps as about 1 GiB holds, in whole rounds of the recomputation.  256 -> 2 x 1024 -> 256,
-          // f16, 1024 rows, 256 steps with groups of 8 / 16 steps 29.3 / 28.5 ms; 128 -> 3 x 512 -> 128, bf16, 2000
-          // rows, 32 steps in groups of 8 / 16 / 32 3.57 / 3.52 / 3.45 ms)
+          // the gradient copies: as many steps as about 640 MiB hold, 1 GiB under a fixed scale, where groups of steps take
+          // up to 4 GiB otherwise, in whole rounds of the recomputation.  f16, ms per pass / MiB of workspace with groups of
+          // 4 / 8 / 16 / 24 steps: 256 -> 2 x 1024 -> 256, 64 steps, 1024 rows 8.64 / 242, 7.43 / 386, 7.18 / 674, 7.11 / 962;
+          // 512 rows 6.82 / 149, 5.41 / 221, 4.87 / 365, 4.92 / 509; 128 -> 3 x 512 -> 128, 32 steps, 2000 rows 4.48 / 298,
+          // 3.84 / 506, 3.70 / 922, 3.69 / 1338)
           if (p.cluster && ahead >= 2) {
-            const int64_t most = std::min<int64_t>((int64_t)((size_t(1) << 30) / per_set), kMaxWgradSteps);
+            const size_t room = size_t(pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE ? 640 : 1024) << 20;
+            const int64_t most = std::min<int64_t>((int64_t)(room / per_set), kMaxWgradSteps);
             ahead = std::max(ahead, most / ahead * ahead);
           }
         }

@@ -94,6 +94,15 @@ def test_workspace_of_grouped_steps_under_detection(base, kw):
     assert small <= 200 << 20
 
 
+@pytest.mark.parametrize("widths,B", [((256, 1024, 1024, 256), 1024), ((256, 1024, 1024, 256), 512), ((100, 1000, 1000, 100), 941),
+                                      ((128, 512, 512, 512, 128), 2000), ((128, 512, 512, 128), 2048), ((100, 600, 100), 1024)])
+def test_workspace_of_clusters_under_detection(widths, B):
+    # include/rampde.h: about 640 MiB of per-step buffers, and what else a pass keeps
+    cfg = wl.CONFIGS["cfg5"].with_(widths=widths, low="f16", B=B, N=256)
+    vel, tab, pol = _descr(cfg)
+    assert rb.rampde_workspace_bytes(vel, B, cfg.N, tab, pol, True) <= (640 << 20) + (120 << 20)
+
+
 def test_row_tile_that_only_the_streaming_kernels_have_selects_them():
     # what tells the plans apart: the 64-row kernels keep sum_j b_j k_j of every row in the forward workspace, the
     # streaming kernels their slopes, the kernels for narrow networks and one hidden layer neither
