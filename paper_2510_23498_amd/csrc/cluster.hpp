@@ -13,8 +13,11 @@
 // to the XCD's L2, and read back by loads that bypass the compute unit's own cache.  There are no flags: a buffer is
 // filled with a word that no result has (all ones; results are kept off it) and a reader repeats its loads until none is
 // left.  So a layer costs one trip through L2 instead of three (store, arrival counter, gather).  Every buffer exists
-// kClusterRing times: a member clears its part of the buffer of evaluation e once evaluation e + 1's stage input is
-// complete (which nobody publishes before everybody has read evaluation e), three evaluations before it is used again.
+// kClusterRing times: a member clears its part of the buffers of evaluation e during evaluation e + 1, once that one's
+// stage input is complete (which nobody publishes before everybody has read evaluation e), two evaluations before they are
+// used again.  The clear lands in time: a wavefront's loads and stores complete in the order of issue, so that its wait
+// for the stage input of e + 2 has retired the clear before it publishes anything of e + 2, and nobody looks into the
+// buffers of e + 3 before all of e + 2 has been published.
 // With several row tiles of 32 per cluster, one tile's exchange runs beside the next one's contraction.
 //
 //   mlp_forward_cluster : Algorithm 1, as many steps per launch as take about 3 ms (a launch holds the whole device; other

@@ -27,7 +27,7 @@ hipError_t launch_kernel(const ClusterLaunch& l, const ClusterArgs& a) {
 
 template <class T, int L, int NTL>
 hipError_t pick_rows(const ClusterLaunch& l, const ClusterArgs& a) {
-  if constexpr (RAMPDE_INST_HP > 512)
+  if constexpr (RAMPDE_INST_HP > 512 && L > 2)  // (128 rows: see choose_clusters)
     if (l.RTN == 4) return launch_kernel<T, L, NTL, 4>(l, a);
   return l.RTN == 1 ? launch_kernel<T, L, NTL, 1>(l, a) : l.RTN == 2 ? launch_kernel<T, L, NTL, 2>(l, a) : hipErrorInvalidValue;
 }

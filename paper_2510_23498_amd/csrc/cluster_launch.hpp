@@ -8,7 +8,7 @@ struct ClusterLaunch {
   int chain;    // 0: mlp_forward_cluster, 1: mlp_chain_cluster
   int bf16;
   int L, NTL;   // layers; dpad / 64
-  int RTN;      // row tiles of 32 per cluster: 1, 2, or 4 (hidden widths above 512)
+  int RTN;      // row tiles of 32 per cluster: 1, 2, or 4 (two hidden layers of more than 512)
   hipStream_t stream;
 };
 
