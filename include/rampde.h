@@ -38,12 +38,18 @@
  *     workspace: same results within rounding, a few ms later, and decided anew by every call.
  *     rampde_odeint_bwd in place (grad_y0 = grad_yN) takes those kernels from the start.
  *   - Dense networks whose hidden layers are all 257 to 512 wide (two or three of them, state up to
- *     128) with up to 2048 rows, or all 513 to 768 or 769 to 1024 wide (one or two, state of 65 to 256)
- *     with up to 1024 rows (one) or 2048 (two): workgroups share row tiles and exchange activations within a launch, in forward and
- *     backward passes alike.  Where some of them are kept from running for 2 ms, or an XCD is given
- *     more of them than its share, the launch gives up, and kernels that do not wait do its work: behind it on the stream (forward passes and a fixed
- *     scale; nothing synchronises), or as above under overflow detection.  An explicit row_tile
- *     selects those kernels from the start.
+ *     128) with up to 2048 rows, or all 513 to 768 or 769 to 1024 wide (one or two, state of 65 to 128
+ *     or 193 to 256) with up to 1024 rows (one) or 2048 (two): workgroups share row tiles and exchange
+ *     activations within a launch, in forward and backward passes alike.  Such a launch holds the whole
+ *     device, for up to about 3 ms in a forward pass and for a group of steps in a backward pass: other
+ *     streams' kernels run between two of them.  Where some of its workgroups are kept from running for
+ *     2 ms, or an XCD is given more of them than its share, the launch gives up, and kernels that do not
+ *     wait do its work: behind it on the stream (forward passes, all of it, and a fixed scale; nothing
+ *     synchronises), or as above under overflow detection.  They take three to four times as long.  They
+ *     sum in another order, so that results change within rounding (single roundings to 16 bits: about
+ *     4e-4 relative in bf16, 5e-5 in fp16, no nearer to or farther from the exact ones), as they do at
+ *     the batch sizes above.  An explicit row_tile selects those kernels from the start, and so does
+ *     rampde_odeint_fwd in place (yN = y0).
  *   - theta layout (flat fp32, also the layout of grad_theta):
  *       MLP  : for each layer l: W_l[out_l][in_l] row-major, then b_l[out_l];
  *              layer 1 has in_1 = d + 1 when time_input is set (time column LAST).

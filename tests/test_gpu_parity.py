@@ -567,7 +567,12 @@ def test_time_grid_gradient_of_more_row_tiles_than_slots():
     ((256, 1024, 1024, 256), 70, "f16", "dynamic", "rk4"),       # 32 rows per cluster, the last one ragged
     ((200, 1024, 900, 200), 513, "bf16", "none", "heun"),        # 64 rows per cluster, the last one holds one row
     ((128, 1000, 128), 33, "f16", "dynamic", "rk4"),             # one hidden layer
-    ((140, 1024, 140), 1024, "bf16", "none", "euler"),           # ... at the largest batch
+    ((128, 1000, 128), 1024, "bf16", "none", "euler"),           # ... at the largest batch: 64 rows per cluster
+    ((200, 900, 200), 1024, "f16", "dynamic", "euler"),
+    ((200, 1000, 200), 513, "f16", "dynamic", "heun"),           # ... the last cluster holds one row
+    ((128, 700, 128), 700, "bf16", "none", "heun"),              # 12 workgroups per cluster; 21 row tiles of 32 run at once
+    ((200, 768, 200), 1001, "f16", "dynamic", "euler"),
+    ((140, 1024, 140), 1024, "bf16", "none", "euler"),           # (a state that pads to 192 columns: no cluster kernels)
     ((100, 1024, 800, 100), 1, "f16", "none_safe", "heun"),      # one row
     ((128, 512, 512, 512, 128), 1030, "f16", "dynamic", "heun"),
     ((128, 512, 400, 300, 128), 2048, "bf16", "none", "euler"),  # ... at the largest batch
@@ -581,6 +586,13 @@ def test_time_grid_gradient_of_more_row_tiles_than_slots():
 ])
 def test_cluster_kernels(widths, B, low, scaling, tab):
     cfg = wl.CONFIGS["cfg1"].with_(name="cl" + "_".join(map(str, widths)), B=B, N=4, widths=widths, low=low, tableau=tab, loss="mse")
+    # (the exchange buffers of the clusters are part of the forward workspace, and row_tile keeps to the row-tile kernels)
+    from paper_2510_23498_amd import binding as rb
+    size = []
+    for row_tile in (0, 16):
+        vel, t, pol = par.gpu_descriptors(cfg, scaling=scaling, row_tile=row_tile)
+        size.append(rb.rampde_workspace_bytes(vel, cfg.B, cfg.N, t, pol, False))
+    assert (size[0] > size[1]) == (not 128 < widths[0] <= 192)
     _both(cfg, bias_std=0.1, scaling=scaling)
 
 

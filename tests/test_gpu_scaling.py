@@ -473,10 +473,13 @@ def test_scale_group_sizes_that_cover_the_batch_are_the_default_path():
         np.testing.assert_array_equal(got["grad_y0"], base["grad_y0"])
 
 
-def test_backward_pass_beside_a_long_forward_pass_on_another_stream():
-    # the forward pass (about 100 ms) holds a quarter of the compute units, so that the 256 workgroups of the backward
-    # launch, which exchange the adjoint scale, cannot all run: the launch gives up and the pass is redone step by step
-    # long before the forward pass ends
+@pytest.mark.parametrize("row_tile", [16, 0], ids=["row-tiles", "clusters"])
+def test_backward_pass_beside_a_long_forward_pass_on_another_stream(row_tile):
+    # row tiles: the forward pass (about 100 ms) holds a quarter of the compute units, so that the 256 workgroups of the
+    # backward launch, which exchange the adjoint scale, cannot all run: the launch gives up and the pass is redone step by
+    # step long before the forward pass ends.  Clusters: the forward pass holds the whole device in launches of about 3 ms,
+    # the backward kernels run between them or beside one whose workgroups then cannot all run, so that it is redone by row
+    # tiles: its results are those of the pass alone, or of the row tiles
     long = wl.CONFIGS["cfg5"].with_(name="beside", N=1024)
     cfg = wl.CONFIGS["cfg2"].with_(name="beside", low="f16", N=8)
     dev = torch.device("cuda:0")
@@ -485,7 +488,7 @@ def test_backward_pass_beside_a_long_forward_pass_on_another_stream():
         theta, y0, _ = par.make_inputs(c)
         return torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
 
-    lvel, ltab, lpol = par.gpu_descriptors(long)
+    lvel, ltab, lpol = par.gpu_descriptors(long, row_tile=row_tile)
     lth, ly0 = tensors(long)
     lws = rb.alloc_workspace(lvel, long.B, long.N, ltab, lpol, False)
     lyN, lck = torch.empty_like(ly0), torch.empty(lvel.ckpt_shape(long.B, long.N), dtype=torch.float16, device=dev)
@@ -494,6 +497,7 @@ def test_backward_pass_beside_a_long_forward_pass_on_another_stream():
     yN, ck = rb.rampde_odeint_fwd(vel, th, y0, cfg.tgrid(), tab, pol)
     ws = rb.alloc_workspace(vel, cfg.B, cfg.N, tab, pol, True)
     alone = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, yN, workspace=ws)
+    undisturbed = [rb.rampde_odeint_fwd(lvel, lth, ly0, long.tgrid(), ltab, q)[0] for q in (lpol, par.gpu_descriptors(long, row_tile=16)[2])]
     mark = torch.zeros(1, device=dev)
     for _ in range(8):  # (a stream may share its hardware queue with the current one: nothing runs side by side then)
         side = torch.cuda.Stream()
@@ -510,10 +514,11 @@ def test_backward_pass_beside_a_long_forward_pass_on_another_stream():
     beside = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, yN, workspace=ws)
     waited = ended.query()
     torch.cuda.synchronize()
-    assert not waited, "the backward pass must not wait for the other stream's forward pass"
+    assert not waited or row_tile == 0, "the backward pass must not wait for the other stream's forward pass"
     np.testing.assert_array_equal(beside[2].scale_hist, alone[2].scale_hist)
     for a, b in zip(beside[:2], alone[:2]):
         assert par.rel_err(a.cpu().numpy(), b.cpu().numpy()) <= par.TOL_EMUL
+    assert any(torch.equal(lyN, ref) for ref in undisturbed)
 
 
 @pytest.mark.parametrize("widths,B,N,low,tab,gain", [
