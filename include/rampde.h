@@ -47,7 +47,7 @@
  *     wait do its work: behind it on the stream (forward passes, all of it, and a fixed scale; nothing
  *     synchronises), or as above under overflow detection.  They take three to four times as long.  They
  *     sum in another order, so that results change within rounding (single roundings to 16 bits: about
- *     4e-4 relative in bf16, 5e-5 in fp16, no nearer to or farther from the exact ones), as they do at
+ *     4e-4 relative in bf16, 1e-4 in fp16, no nearer to or farther from the exact ones), as they do at
  *     the batch sizes above.  An explicit row_tile selects those kernels from the start, and so does
  *     rampde_odeint_fwd in place (yN = y0).
  *   - theta layout (flat fp32, also the layout of grad_theta):

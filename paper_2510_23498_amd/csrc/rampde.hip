@@ -611,6 +611,10 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         p.wgrad_slab = !p.overlap_wgrad && !p.resident && p.step_group <= 1 && offsets_fit &&
                        (want_tile == 256 || (want_tile != 128 && group * p.ldk >= kSlabMinK));
         if (p.step_group <= 1 && std::min(group, ahead) < 2) p.ahead_MT = p.cluster = 0;
+        if (p.ahead_MT && p.act_lds_off) {  // (the chain alone reads the activations from memory)
+          p.lds_bytes = 2 * (size_t)p.act_lds_off;
+          p.act_lds_off = 0;
+        }
         if (p.wgrad_slab) p.wgrad_group = (int)group;
         if (p.wgrad_slab || (p.ahead_MT && p.step_group <= 1)) p.nsets = (int)group;
         int tiles = 0;
