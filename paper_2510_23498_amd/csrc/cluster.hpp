@@ -25,8 +25,8 @@
 //   mlp_chain_cluster   : Algorithm 2 for a group of steps whose stages have been recomputed (mlp_recompute_fused): the
 //                         cotangent chain, the fp32 adjoint and the scale decisions (StepExchange of resident.hpp)
 //
-// Measured, 256 -> 1024 -> 1024 -> 256, f16, 1024 rows, 256 RK4 steps: forward 24.2 -> 7.8 ms (7.6 us per evaluation of 64
-// rows, 5.7 of 32), cotangent chain 48 -> 10.7 ms, pass 95.6 -> 29.6 ms (72.3 with the recomputation ahead alone).  A phase
+// Measured, 256 -> 1024 -> 1024 -> 256, f16, 1024 rows, 256 RK4 steps: forward 24.2 -> 7.7 ms (7.6 us per evaluation of 64
+// rows, 5.7 of 32), cotangent chain 48 -> 10.3 ms, pass 95.6 -> 28.6 ms (72.3 with the recomputation ahead alone).  A phase
 // (gather, contraction, fold, epilogue) of 64 rows takes 2 to 3 us: 128 KB from L2 per compute unit in 1.6 us, 0.85 us of
 // matrix instructions, two LDS folds, and a trip through L2 of about 1 us that the other row tile hides in part.  Stores
 // that go through to memory instead of the XCD's own L2 (workgroups anywhere on the device) made an exchange 3.8 us

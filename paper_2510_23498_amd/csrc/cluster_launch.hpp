@@ -12,7 +12,9 @@ struct ClusterLaunch {
   hipStream_t stream;
 };
 
-// networks that have kernels: hidden width (all hidden layers padded to it), layers, padded state width
+// networks that have kernels: hidden width (all hidden layers padded to it), layers, padded state width.  (Two 1024-wide
+// layers between 256-wide states are 224 registers of weight fragments per lane, three would be 352; the other shapes
+// that are left out would fit and have not been built)
 inline bool cluster_shape(int hp, int L, int dpad) {
   return (hp == 512 && (L == 3 || L == 4) && (dpad == 64 || dpad == 128)) ||
          ((hp == 768 || hp == 1024) && (L == 2 || L == 3) && (dpad == 128 || dpad == 256));
