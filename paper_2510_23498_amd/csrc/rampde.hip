@@ -132,6 +132,7 @@ struct Plan {
   int cl_RTN = 0, cl_n = 0;         // their row tiles of 32 per cluster, and clusters
   size_t cl_W = 0, cl_x = 0, cl_tickets = 0;
   int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, or kernels that decide inside a launch)
+  bool lean = false;                // no choice of kernels for which the workspace alone is larger (see plan_within)
   std::vector<size_t> ACTT, DELTAT;
 };
 
@@ -334,7 +335,7 @@ static void choose_clusters(Plan& p) {
 // unit) 561 / 579; four layers of 256, 4000 rows 886 / 808; 2 -> 32 -> 32 -> 2, f16, 256 rows, 8 steps 237 / 222;
 // 50 -> 200 -> 200 -> 50 with the time-grid gradient, 1003 rows, Heun 414 / 347.
 static bool resident_ahead(const Plan& p, int step_group) {
-  if (!p.resident || step_group < 2) return false;
+  if (!p.resident || step_group < 2 || p.lean) return false;
   // (one hidden layer: flow of 63 features, width 1024, f16, 512 rows 793 / 584, 4096 rows 1462 / 1411; 128 -> 512 -> 128,
   // bf16, 1000 rows 550 / 399, 16000 rows 2578 / 2308; flow of 10 features, width 100, 8000 rows 705 / 710)
   if (p.shallow) return p.resident > 128 || 8 * ((p.R + 15) / 16) <= 7 * 2 * (int64_t)device_compute_units();
@@ -362,11 +363,12 @@ static bool group_recomputes_ahead(const Plan& p) {
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
 // gradient runs on the other row-tile kernels).  small: no choice of the streaming kernels, which keep slopes in the
 // workspace, where the register-resident ones can run, and no clusters.  allow_clusters = false: no clusters, every other
-// choice as it is
+// choice as it is.  lean: see plan_within
 static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab,
                       const rampde_policy* pol, int is_backward, bool allow_wide = true, bool allow_resident = true,
-                      bool small = false, bool allow_clusters = true) {
+                      bool small = false, bool allow_clusters = true, bool lean = false) {
   Plan p;
+  p.lean = lean;
   const bool allow_fused = fused_candidate(vel, pol);
   int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
   if (rhp == 0 && allow_resident && allow_wide) {  // (the time-grid gradient is formed by the other kernels)
@@ -416,7 +418,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     // (and with the time-grid gradient every workgroup of a launch writes a slot; the 32-row tiles below need half as many)
     const bool slots_fit = allow_wide || !is_backward || (size_t)tiles <= kTimeSlotPairs;
     if (lds > lds_limit || !offsets_fit || !slots_fit || (detects && tiles > cus * (p.shallow ? 1 : resident_per_cu(rhp, lds))))
-      return make_plan(vel, B, N, tab, pol, is_backward, allow_wide, false);
+      return make_plan(vel, B, N, tab, pol, is_backward, allow_wide, false, small, allow_clusters, lean);
     p.resident = rhp;
     p.fused = true;
     p.MT = mt;
@@ -492,14 +494,14 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
           p.lds_bytes += act_bytes;
         }
         // stages recomputed ahead for several steps at once (not for the time-grid gradient, whose sums need the slopes)
-        if (allow_wide && !p.overlap_wgrad && !dense_stages(tab))
+        if (allow_wide && !lean && !p.overlap_wgrad && !dense_stages(tab))
           for (int m = 4; m >= 2 && !p.ahead_MT; m >>= 1)
             if (lds_need(m, false) <= lds_limit) {
               p.ahead_MT = m;
               p.ahead_lds = lds_need(m, false);
             }
       }
-      if (allow_resident && allow_wide && allow_clusters && !small && want_rows == 0 && !p.wide && (p.ahead_MT || !is_backward) &&
+      if (allow_resident && allow_wide && allow_clusters && !small && !lean && want_rows == 0 && !p.wide && (p.ahead_MT || !is_backward) &&
           !dense_stages(tab))
         choose_clusters(p);
       for (auto& y : p.layers) {
@@ -632,7 +634,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         const int resident = device_compute_units() * ((p.overlap_wgrad || p.wgrad_slab) ? 1 : 2);
         int64_t ks = std::max(1, resident / tiles);
         // (a group of steps multiplies a workgroup's k-steps: chunks can be shorter)
-        const int64_t min_chunk = p.step_group > 1 ? 64 : 256;
+        const int64_t min_chunk = p.step_group > 1 ? (lean ? 128 : 64) : 256;
         ks = std::max<int64_t>(1, std::min<int64_t>(ks, p.ldk / min_chunk > 0 ? p.ldk / min_chunk : 1));
         const int64_t kc = ((p.ldk + ks - 1) / ks + 63) / 64 * 64;
         p.kchunk = (int)kc;
@@ -642,7 +644,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // folded by four threads per parameter: 128 copies by one thread took 20 us): 2-32-32-2, 256 rows, 8 steps
         // 180 / 176 / 161; 50-200-200-50, 1003 rows, 20 Heun steps, dL/dt 330 / 316 / 306; flow of 10 features, width 100,
         // 500 rows 352 / 310 / 285)
-        if (p.step_group > 1) {
+        if (p.step_group > 1 && !lean) {
           const int64_t spare = resident / ((int64_t)tiles * p.ksplits), room = ((int64_t)32 << 20) / ((int64_t)p.ksplits * p.P * 4);
           const int64_t parts = p.step_group * (kc / 64) / 4;  // (at least four k-steps of 64 each)
           p.step_splits = (int)std::max<int64_t>(1, std::min(std::min(spare, room), parts));
@@ -2336,6 +2338,17 @@ size_t rampde_workspace_bytes(const rampde_velocity* vel, int64_t B, int N, cons
   return total;
 }
 
+// The plan of a call on `bytes` of workspace.  Exchange buffers of clusters, stages of more steps at once, slopes beside them
+// and more copies of the gradients grow the workspace of some batches past that of larger ones (256 -> 2 x 1024 -> 256, f16, 32
+// RK4 steps, 1024 / 4096 rows: backward 674 / 384 MiB, forward 31 / 20): a workspace made for the largest batch of a
+// program does not hold them for a smaller one, and that runs on the kernels that need less.
+static Plan plan_within(size_t bytes, const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab, const rampde_policy* pol,
+                        int is_backward, bool allow_wide, bool allow_resident, bool small = false, bool allow_clusters = true) {
+  Plan p = make_plan(vel, B, N, tab, pol, is_backward, allow_wide, allow_resident, small, allow_clusters);
+  if (p.ok && p.total > bytes) p = make_plan(vel, B, N, tab, pol, is_backward, allow_wide, allow_resident, small, allow_clusters, true);
+  return p;
+}
+
 static int forward_call(const rampde_velocity* vel, const float* theta, const float* y0, int64_t B, const double* tgrid, int N,
                         const rampde_tableau* tab, const rampde_policy* pol, void* ckpt, float* yN, void* workspace,
                         size_t workspace_bytes, hipStream_t st, bool small) {
@@ -2344,7 +2357,7 @@ static int forward_call(const rampde_velocity* vel, const float* theta, const fl
   if (!theta || !y0 || !ckpt || !yN || !workspace || B < 1) return RAMPDE_EINVAL;
   if (!aligned16(theta) || !aligned16(y0) || !aligned16(ckpt) || !aligned16(yN)) return RAMPDE_EINVAL;
   // (a launch of the cluster kernels that is given up may have written yN: not where that is y0 as well)
-  Plan p = make_plan(vel, B, N, tab, pol, 0, true, true, small, y0 != yN);
+  Plan p = plan_within(workspace_bytes, vel, B, N, tab, pol, 0, true, true, small, y0 != yN);
   if (!p.ok) return RAMPDE_EINVAL;
   if (workspace_bytes < p.total || ((uintptr_t)workspace & 255)) return RAMPDE_EWORKSPACE;
   const bool fused = p.fused;
@@ -2405,7 +2418,7 @@ static int backward_rows(const rampde_velocity* vel, const float* theta, int64_t
                          size_t workspace_bytes, hipStream_t st, bool allow_resident = true) {
   // (a pass that has to be redone starts from grad_yN again: not possible when grad_y0 is the same buffer)
   const bool in_place = grad_yN == grad_y0 && resolve_scaling(pol) != RAMPDE_SCALE_NONE;
-  Plan p = make_plan(vel, B, N, tab, pol, 1, grad_t == nullptr, allow_resident && !in_place);
+  Plan p = plan_within(workspace_bytes, vel, B, N, tab, pol, 1, grad_t == nullptr, allow_resident && !in_place);
   if (!p.ok) return RAMPDE_EINVAL;
   if (workspace_bytes < p.total || ((uintptr_t)workspace & 255)) return RAMPDE_EWORKSPACE;
   const rampde_scaling sc = resolve_scaling(pol);

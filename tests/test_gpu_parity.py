@@ -741,3 +741,35 @@ def test_forward_pass_in_place(widths, B, row_tile):
     ref, ref_ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, ref_pol)
     got, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol, yN=y)
     assert got.data_ptr() == y.data_ptr() and torch.equal(got, ref) and torch.equal(ck, ref_ck)
+
+
+@pytest.mark.parametrize("base,widths,low,tabname,N,large,B", [
+    ("cfg1", (64, 512, 512, 64), "bf16", "heun", 16, 654, 588),           # no clusters; groups of steps under a fixed scale
+    ("cfg1", (128, 300, 300, 300, 128), "f16", "heun", 64, 2247, 1123),   # ... under detection: a step per launch
+    ("cfg1", (2, 1000, 1000, 2), "f16", "rk4", 64, 1071, 535),            # stages not recomputed ahead
+    ("cfg1", (2, 128, 128, 128, 2), "f16", "heun", 64, 7558, 3779),       # adjoint of a group in one launch, slopes not kept
+    ("cnf", (63, 1024, 63), "bf16", "heun", 4, 1109, 998),                # ... of a flow
+])
+def test_smaller_batch_on_the_workspace_of_a_larger_one(base, widths, low, tabname, N, large, B):
+    # it is smaller than what the batch would take of its own: the same results (32-bit sums in another order) by the
+    # kernels that need less
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS[base].with_(name="last_batch", B=B, N=N, widths=widths, low=low, tableau=tabname, loss="mse")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    vel, tab, pol = par.gpu_descriptors(cfg, scaling="dynamic" if low == "f16" else "none")
+    own = [rb.alloc_workspace(vel, B, N, tab, pol, b) for b in (False, True)]
+    less = [rb.alloc_workspace(vel, large, N, tab, pol, b) for b in (False, True)]
+    assert less[1].numel() < own[1].numel()
+    out = []
+    for ws in (own, less):
+        yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol, workspace=ws[0])
+        for want_t in (False, True):
+            gt = torch.zeros(N + 1, device=dev) if want_t else None
+            kw = {"grad_t": gt} if want_t else {}
+            gy0, gth, info = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, yN, workspace=ws[1], **kw)
+            out.append([yN, ck, gy0, gth] + ([gt] if want_t else []))
+    for k in (0, 1):
+        for a, b in zip(out[k], out[k + 2]):
+            assert par.rel_err(a.float().cpu().numpy(), b.float().cpu().numpy()) <= par.TOL_EMUL

@@ -307,6 +307,45 @@ def test_retry_inside_and_across_groups_of_steps(base, kw, step_group, want_grad
     _compare_amplifying(cfg, theta, y0, target, gpu, emu, want_grad_t=want_grad_t)
 
 
+LEAST = GROUPED + [("cfg2", dict(name="retry4l", B=300, N=6, t1=0.09, gain=256.0, scaling="dynamic", widths=(64, 256, 256, 256, 64)))]
+
+
+@pytest.mark.parametrize("base,kw", LEAST, ids=[k["name"] for _, k in LEAST])
+@pytest.mark.parametrize("want_grad_t", [False, True])
+def test_retries_on_the_least_workspace(base, kw, want_grad_t):
+    # the smallest workspace that the pass accepts (kernels that need less than those of the queried size): the same
+    # decisions, and nothing written behind it
+    cfg, theta, y0, target = _gain_case(base, **dict(kw))
+    emu = par.run_oracle(cfg, theta, y0, target, "emul")
+    vel, tab, pol = par.gpu_descriptors(cfg)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
+    gyN = torch.from_numpy(np.ascontiguousarray(wl.loss_and_grad(cfg, yN.cpu().numpy(), target)[1])).to(dev)
+    ws = rb.alloc_workspace(vel, cfg.B, cfg.N, tab, pol, True)
+
+    def run(size):
+        gt = torch.zeros(cfg.N + 1, device=dev) if want_grad_t else None
+        ws[size:] = 77
+        gy0, gth, info = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, gyN, workspace=ws[:size], grad_t=gt)
+        assert bool((ws[size:] == 77).all())
+        return dict(yN=yN.cpu().numpy(), grad_y0=gy0.cpu().numpy(), grad_theta=gth.cpu().numpy(), retries=info.retries,
+                    scale_hist=info.scale_hist, grad_t=gt.cpu().numpy() if want_grad_t else None)
+
+    refused, size, gpu = 0, ws.numel(), run(ws.numel())
+    while size - refused > 256:
+        mid = (refused + size) // 512 * 256
+        try:
+            gpu, size = run(mid), mid
+        except rb.RampdeError as e:
+            assert e.code == rb.EWORKSPACE
+            refused = mid
+    print(f"[case] {cfg.name}: {size} of {ws.numel()} bytes", flush=True)
+    assert gpu["retries"] == emu["retries"]
+    np.testing.assert_array_equal(gpu["scale_hist"].astype(np.float64), emu["scale_hist"])
+    _compare_amplifying(cfg, theta, y0, target, gpu, emu, want_grad_t=want_grad_t)
+
+
 @pytest.mark.parametrize("base,kw", GROUPED[1:], ids=[k["name"] for _, k in GROUPED[1:]])
 def test_failure_overflow_and_scale_groups_with_grouped_steps(base, kw):
     cfg, theta, y0, target = _gain_case(base, **dict(kw))

@@ -220,6 +220,46 @@ def test_queried_workspace_is_enough_for_every_call_in_place_too():
                         assert rc == rb.EHIP, (widths, row_tile, low, tabname, B, yN, rc)
 
 
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="the pointers are dummies: only where no device can follow them")
+def test_workspace_of_a_larger_batch_serves_smaller_ones():
+    # the last batch of an epoch, or inference on fewer samples: kernels that would need more than the larger batch's
+    # workspace (clusters and their exchange buffers, stages of more steps at once, slopes, gradient copies) give way
+    lib = rb.load_library()
+    p = lambda x: C.c_void_p(0x100000 * x)
+
+    def codes(cfg, low, N, size_f, size_b, B):
+        vel, tab, _ = _descr(cfg)
+        pc = rb.Policy(low=low).c
+        tgp = np.linspace(0.0, 1.0, N + 1).ctypes.data_as(C.POINTER(C.c_double))
+        out = [lib.rampde_odeint_fwd(C.byref(vel.c), p(1), p(2), B, tgp, N, C.byref(tab.c), C.byref(pc), p(3), p(4), p(5), size_f, None)]
+        for grad_t in (None, p(9)):
+            out.append(lib.rampde_odeint_bwd_tgrid(C.byref(vel.c), p(1), B, tgp, N, C.byref(tab.c), C.byref(pc), p(3), p(2), None, p(4),
+                                                   p(7), grad_t, None, None, p(5), size_b, None))
+        return out
+
+    def sizes(cfg, low, N, B):
+        vel, tab, _ = _descr(cfg)
+        return [rb.rampde_workspace_bytes(vel, B, N, tab, rb.Policy(low=low), b) for b in (False, True)]
+
+    for widths in ((2, 32, 2), (64, 600, 64), (128, 1000, 128), (64, 256, 256, 64), (100, 300, 300, 100),
+                   (128, 512, 512, 512, 128), (200, 700, 700, 200), (256, 1024, 1024, 256)):
+        for low, tabname in (("f16", "rk4"), ("bf16", "heun")):
+            cfg = wl.CONFIGS["cfg1"].with_(widths=widths, tableau=tabname)
+            for B in (100, 1024, 1025, 2049, 4096, 6000, 20000):
+                size_f, _ = sizes(cfg, low, 16, B)
+                for part in (0.95, 0.7, 0.5, 0.3, 0.1, 0.02):
+                    small = max(1, int(B * part))
+                    assert codes(cfg, low, 16, size_f, 1 << 40, small) == [rb.EHIP] * 3, (widths, low, B, small)
+    for base, widths, low, tabname, N, B, small in (
+            ("cfg1", (64, 512, 512, 64), "bf16", "heun", 16, 654, 588), ("cfg1", (128, 300, 300, 300, 128), "f16", "heun", 64, 2247, 1123),
+            ("cfg1", (2, 1000, 1000, 2), "f16", "rk4", 64, 1071, 535), ("cfg1", (2, 128, 128, 128, 2), "f16", "heun", 64, 7558, 3779),
+            ("cfg1", (256, 1000, 1000, 256), "f16", "heun", 16, 15439, 1543), ("cnf", (63, 1024, 63), "bf16", "heun", 4, 1109, 998)):
+        cfg = wl.CONFIGS[base].with_(widths=widths, tableau=tabname)
+        size_f, size_b = sizes(cfg, low, N, B)
+        assert size_b < sizes(cfg, low, N, small)[1]  # (what the smaller batch would take of a workspace of its own)
+        assert codes(cfg, low, N, size_f, size_b, small) == [rb.EHIP] * 3, (widths, low, B, small)
+
+
 def test_backward_rejects_bad_arguments_without_touching_the_device():
     lib = rb.load_library()
     cfg = wl.CONFIGS["cfg1"]
