@@ -610,9 +610,17 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         // (the kernel addresses a lane's part of an operand tensor by a 32-bit byte offset)
         bool offsets_fit = (size_t)p.dpad * p.ldk * 2 < (size_t(1) << 32);
         for (auto& y : p.layers) offsets_fit = offsets_fit && (size_t)std::max(y.Npad, y.Kpad) * p.ldk * 2 < (size_t(1) << 32);
-        p.wgrad_slab = !p.overlap_wgrad && !p.resident && p.step_group <= 1 && offsets_fit &&
-                       (want_tile == 256 || (want_tile != 128 && group * p.ldk >= kSlabMinK));
         if (p.step_group <= 1 && std::min(group, ahead) < 2) p.ahead_MT = p.cluster = 0;
+        // (a long group of clusters can have a short contraction per step, which the other kernel folds faster: from 3e9
+        // multiplications a step on.  Backward pass, us with the slab kernel / the other, f16 under detection:
+        // 64 -> 2 x 512 -> 64, 64 Euler steps, 300 rows (0.1e9) 1405 / 1003, 2048 rows (0.7e9) 1808 / 1407; 128 -> 700 -> 128,
+        // 16 RK4 steps, 1024 rows (0.8e9) 662 / 556; 128 -> 3 x 512 -> 128, 32 Heun steps, 2048 rows (2.7e9) 1662 / 1563;
+        // 256 -> 2 x 700 -> 256, 16 RK4 steps, 1024 rows (4e9) 1120 / 1131; 256 -> 2 x 1000 -> 256 (6.4e9) 1395 / 1445)
+        int64_t macs = 0;
+        for (auto& y : p.layers) macs += (int64_t)y.Npad * y.Kpad * p.ldk;
+        const bool short_steps = p.cluster && macs < 3000000000;
+        p.wgrad_slab = !p.overlap_wgrad && !p.resident && p.step_group <= 1 && offsets_fit &&
+                       (want_tile == 256 || (want_tile != 128 && group * p.ldk >= kSlabMinK && !short_steps));
         if (p.ahead_MT && p.act_lds_off) {  // (the chain alone reads the activations from memory)
           p.lds_bytes = 2 * (size_t)p.act_lds_off;
           p.act_lds_off = 0;

@@ -651,6 +651,25 @@ def test_later_launch_of_a_forward_pass_on_clusters_is_given_up(after):
     assert not torch.equal(out[2][1], out[1][1])  # (undisturbed: another order of sums)
 
 
+@pytest.mark.parametrize("widths,B,tab,N", [
+    ((64, 512, 512, 64), 300, "euler", 40),      # one contraction over a long group of short steps
+    ((100, 300, 300, 100), 2048, "heun", 9),     # ... of longer ones
+    ((256, 700, 700, 256), 760, "rk4", 3),       # on both sides of 3e9 multiplications a step: 760 rows pad to 768, 3.02e9
+    ((256, 700, 700, 256), 700, "rk4", 3),       # 704, 2.77e9
+])
+def test_parameter_gradients_of_groups_on_clusters(widths, B, tab, N):
+    # by either kernel the same sums, in another order in 32 bits
+    for low, scaling in (("bf16", "none"), ("f16", "dynamic")):
+        cfg = wl.CONFIGS["cfg1"].with_(name="clgrads", B=B, N=N, widths=widths, low=low, tableau=tab, loss="mse")
+        theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+        got = [par.run_gpu(cfg, theta, y0, target, scaling=scaling, wgrad_tile=t) for t in (0, 128, 256)]
+        for other in got[1:]:
+            np.testing.assert_array_equal(got[0]["grad_y0"], other["grad_y0"])
+            assert par.rel_err(got[0]["grad_theta"], other["grad_theta"]) <= 1e-5
+        rows = par.run_gpu(cfg, theta, y0, target, scaling=scaling, row_tile=16)
+        par.compare(cfg, got[0], rows, par.TOL_EMUL, "the row-tile kernels")
+
+
 @pytest.mark.parametrize("widths,B", [((128, 512, 512, 128), 65), ((200, 1000, 200), 33)])
 @pytest.mark.parametrize("N,in_place", [(7, False), (8, False), (7, True), (8, True)])
 def test_groups_of_steps_on_clusters_under_a_fixed_scale(widths, B, N, in_place):
