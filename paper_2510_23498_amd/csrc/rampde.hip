@@ -311,7 +311,28 @@ constexpr int kClusterEvaluations = 384;  // of the velocity per launch of a for
 // 718 / 358, 1024 rows 719 / 373, 2048 rows 725 / 509; 100 -> 2 x 400 -> 100, f16, Heun, 2000 rows 244 / 197;
 // 200 -> 1000 -> 200, bf16, Euler, 128 rows 158 / 77, 1024 rows 158 / 99, but 128 -> 1000 -> 128, RK4, 2048 rows (128)
 // 330 / 366 and 100 -> 600 -> 100, Euler, 1500 rows 101 / 122.
-static void choose_clusters(Plan& p) {
+//
+// A pass has four launches more than on row tiles, and a launch fills its members' registers first: a forward pass of few
+// evaluations is faster on row tiles.  From how many on it is not, with few clusters and with as many as run at once (32 rows
+// each), with 64 and with 128 rows each, up to the evaluation where both were first equal; by hidden width, layers and state.
+// Forward, us, row tiles / clusters: 128 -> 2 x 512 -> 128, 40 rows, 2 evaluations 28 / 26; 1024 rows 1 / 4 / 8
+// evaluations 21 / 26, 42 / 40, 69 / 55; 2048 rows 8 / 12 / 24 69 / 72, 97 / 93, 181 / 157; 128 -> 1000 -> 128, 1024 rows 4 /
+// 16 / 48 30 / 40, 86 / 86, 238 / 207; 128 -> 2 x 700 -> 128, 2048 rows 2 / 8 / 48 44 / 54, 128 / 124, 692 / 571;
+// 256 -> 2 x 1000 -> 256 2 / 8 70 / 69, 208 / 151.
+static bool enough_evaluations(int64_t evaluations, int hp, int L, int dpad, int rtn, int64_t clusters, int64_t most) {
+  struct Line { int hp, L, dpad; double few, full, two, four; };
+  static constexpr Line lines[] = {
+      {512, 3, 64, 3, 6, 16, 0}, {512, 3, 128, 2, 4, 11, 0}, {512, 4, 64, 2, 3, 7, 0},  {512, 4, 128, 1, 2, 6, 0},
+      {768, 2, 128, 4, 4, 7, 0}, {768, 2, 256, 2, 2, 4, 0},  {768, 3, 128, 1, 1, 2, 7}, {768, 3, 256, 1, 1, 1, 11},
+      {1024, 2, 128, 6, 8, 16, 0}, {1024, 2, 256, 2, 2, 3, 0}, {1024, 3, 128, 1, 1, 1, 4}, {1024, 3, 256, 1, 1, 1, 2}};
+  for (const Line& l : lines)
+    if (l.hp == hp && l.L == L && l.dpad == dpad)
+      return evaluations >= (rtn == 4 ? l.four : rtn == 2 ? l.two : l.few + (l.full - l.few) * clusters / most);
+  return true;
+}
+
+// forward_evaluations: of the velocity in a forward pass; 0: a backward pass
+static void choose_clusters(Plan& p, int64_t forward_evaluations) {
   const int hp = p.L >= 2 ? p.layers[0].Npad : 0;
   for (int l = 0; l + 1 < p.L; ++l)
     if (p.layers[l].Npad != hp) return;
@@ -321,6 +342,7 @@ static void choose_clusters(Plan& p) {
   for (int rtn = 1; rtn <= (hp > 512 && p.L > 2 ? 4 : 2); rtn *= 2) {
     const int64_t n = (p.R + 32 * rtn - 1) / (32 * rtn);
     if (n > most) continue;
+    if (forward_evaluations && !enough_evaluations(forward_evaluations, hp, p.L, p.dpad, rtn, n, most)) return;
     p.cluster = hp;
     p.cl_RTN = rtn;
     p.cl_n = (int)n;
@@ -503,7 +525,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       }
       if (allow_resident && allow_wide && allow_clusters && !small && !lean && want_rows == 0 && !p.wide && (p.ahead_MT || !is_backward) &&
           !dense_stages(tab))
-        choose_clusters(p);
+        choose_clusters(p, is_backward ? 0 : (int64_t)N * p.s);
       for (auto& y : p.layers) {
         y.Wf = take((size_t)y.Npad * y.Kpad * 2);
         y.WTf = take((size_t)y.Npad * y.Kpad * 2);

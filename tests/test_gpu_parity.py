@@ -585,7 +585,9 @@ def test_time_grid_gradient_of_more_row_tiles_than_slots():
     ((100, 768, 700, 100), 513, "f16", "dynamic", "euler"),
 ])
 def test_cluster_kernels(widths, B, low, scaling, tab):
-    cfg = wl.CONFIGS["cfg1"].with_(name="cl" + "_".join(map(str, widths)), B=B, N=4, widths=widths, low=low, tableau=tab, loss="mse")
+    # (as many steps as a forward pass on clusters takes at least)
+    cfg = wl.CONFIGS["cfg1"].with_(name="cl" + "_".join(map(str, widths)), B=B, N={"euler": 16, "heun": 8, "rk4": 4}[tab], widths=widths,
+                                   low=low, tableau=tab, loss="mse")
     # (the exchange buffers of the clusters are part of the forward workspace, and row_tile keeps to the row-tile kernels)
     from paper_2510_23498_amd import binding as rb
     size = []

@@ -144,6 +144,22 @@ def test_recomputation_ahead_under_detection(widths, B, ahead):
     assert (size[0] > size[1]) == ahead
 
 
+@pytest.mark.parametrize("widths,B,least", [
+    ((64, 512, 512, 64), 20, 4), ((64, 512, 512, 64), 1024, 6), ((64, 512, 512, 64), 1025, 16), ((128, 300, 300, 128), 2048, 11),
+    ((128, 512, 512, 512, 128), 1024, 2), ((128, 512, 512, 512, 128), 2048, 6), ((128, 700, 128), 500, 4), ((128, 700, 128), 1024, 7),
+    ((100, 700, 700, 100), 2048, 7), ((128, 1000, 128), 1024, 16), ((256, 1024, 1024, 256), 1024, 1), ((256, 1024, 1024, 256), 2048, 2),
+])
+def test_forward_passes_of_few_evaluations_are_not_on_clusters(widths, B, least):
+    # the exchange buffers are part of the forward workspace; row_tile keeps to the row-tile kernels
+    cfg = wl.CONFIGS["cfg1"].with_(widths=widths, tableau="euler")
+    vel, tab, _ = _descr(cfg)
+    for N in (1, least - 1, least, 100):
+        if N < 1:
+            continue
+        size = [rb.rampde_workspace_bytes(vel, B, N, tab, rb.Policy(low="f16", row_tile=r), False) for r in (0, 16)]
+        assert (size[0] > size[1]) == (N >= least), N
+
+
 def test_checkpoint_store_is_half_of_fp32():
     # only the low-precision states are kept (paper Sec. 3): (N+1) * n * 2 bytes
     for cfg in wl.CONFIGS.values():
