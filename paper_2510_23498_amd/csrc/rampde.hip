@@ -1021,8 +1021,11 @@ struct Runner {
     return {&conv3x3_tile<T, NA, KC, AW, kConvPlain>, &conv3x3_tile<T, NA, KC, AW, kConvTanh>, &conv3x3_tile<T, NA, KC, AW, kConvFactor>,
             &conv3x3_tile<T, NA, KC, AW, kConvStage>, &conv3x3_tile<T, NA, KC, AW, kConvCotangent>};
   }
-  // whether conv3x3_tile also forms what the next stage's convolution reads: stages that are a chain, 16-byte rows
+  // whether conv3x3_tile also forms what the next stage's convolution reads: stages that are a chain, 16-byte rows.  (A slope
+  // that the next stage does not use at all stays out of it, also where it is infinite: 0 times it would be NaN)
   bool conv_fuses_stages(const rampde_tableau* tab) const {
+    for (int j = 1; j < p.s; ++j)
+      if ((float)tab->A[j * p.s + j - 1] == 0.f) return false;
     return p.conv && !p.parabolic && conv_tile_applies(p.layers[0].Kpad, p.layers[0].Npad, p.Wd) && vec8() && !dense_stages(tab);
   }
   bool few_channels() const { return p.d <= 32; }

@@ -794,3 +794,18 @@ def test_smaller_batch_on_the_workspace_of_a_larger_one(base, widths, low, tabna
     for k in (0, 1):
         for a, b in zip(out[k], out[k + 2]):
             assert par.rel_err(a.float().cpu().numpy(), b.float().cpu().numpy()) <= par.TOL_EMUL
+
+
+def test_infinite_slope_that_no_stage_uses():
+    # stages that do not build on one another: the second one starts from the stored state although the first one's slope
+    # has left the range of 16 bits
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name="apart", C=16, H=8, W=8, B=2, N=1, low="f16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    name, shape, off = [x for x in wl.theta_layout(cfg) if x[0].startswith("b")][-1]
+    theta[off:off + int(np.prod(shape))] = 7e4
+    vel, _, pol = par.gpu_descriptors(cfg)
+    tab = rb.Tableau([[0.0, 0.0], [0.0, 0.0]], [0.5, 0.5], [0.0, 0.5])
+    dev = torch.device("cuda:0")
+    yN, _ = rb.rampde_odeint_fwd(vel, torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev), cfg.tgrid(), tab, pol)
+    assert bool(torch.isposinf(yN).all())
