@@ -132,6 +132,7 @@ struct Plan {
   int cl_RTN = 0, cl_n = 0;         // their row tiles of 32 per cluster, and clusters
   size_t cl_W = 0, cl_x = 0, cl_tickets = 0;
   int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, or kernels that decide inside a launch)
+  bool time_grid = false;           // a backward pass that forms dL/dt
   bool lean = false;                // no choice of kernels for which the workspace alone is larger (see plan_within)
   std::vector<size_t> ACTT, DELTAT;
 };
@@ -351,18 +352,23 @@ static void choose_clusters(Plan& p, int64_t forward_evaluations) {
 }
 
 // Groups of steps of the register-resident kernels: recomputed ahead, except where one kernel holds both directions'
-// slices (up to three layers, 16-row tiles) and its tiles already fill the device.  64 -> 256 -> 256 -> 64, 32 RK4 steps,
-// us per pass with one kernel / recomputed ahead: bf16 4096 rows 1084 / 1095, 3000 rows 991 / 946, 2000 rows 889 / 818,
-// 8192 rows (32-row tiles) 1072 / 1040 with 16 steps; 40 -> 100 -> 100 -> 40, 8000 rows (two workgroups per compute
-// unit) 561 / 579; four layers of 256, 4000 rows 886 / 808; 2 -> 32 -> 32 -> 2, f16, 256 rows, 8 steps 237 / 222;
-// 50 -> 200 -> 200 -> 50 with the time-grid gradient, 1003 rows, Heun 414 / 347.
+// slices (up to three layers, 16-row tiles) and its tiles fill more than a share of the slots (one or, up to 128 wide, two
+// workgroups per compute unit).  us per backward pass of 64 RK4 steps, f16 under detection, with one kernel / recomputed
+// ahead: 64 -> 100 -> 64, 50 % of the slots 768 / 837, 75 % 1026 / 1147, with the time-grid gradient 907 / 998, 1140 / 1321;
+// 16 -> 100 -> 100 -> 16, 85 % 1580 / 1701, with it 1741 / 1963; 64 -> 256 -> 64, 85 % 1091 / 1138, with it 75 % 1140 / 1242.
+// 30 % of 64 -> 100 -> 64 were 849 / 691, some 95 of the former for launches that neither needs now.
+// bf16, 32 steps: 64 -> 256 -> 256 -> 64, 4096 rows (all slots) 1084 / 1095, 3000 rows 991 / 946, 8192 rows (32-row tiles, 16
+// steps) 1072 / 1040; four layers of 256, 4000 rows 886 / 808.
 static bool resident_ahead(const Plan& p, int step_group) {
   if (!p.resident || step_group < 2 || p.lean) return false;
   // (one hidden layer: flow of 63 features, width 1024, f16, 512 rows 793 / 584, 4096 rows 1462 / 1411; 128 -> 512 -> 128,
   // bf16, 1000 rows 550 / 399, 16000 rows 2578 / 2308; flow of 10 features, width 100, 8000 rows 705 / 710)
   if (p.shallow) return p.resident > 128 || 8 * ((p.R + 15) / 16) <= 7 * 2 * (int64_t)device_compute_units();
   const int64_t slots = (int64_t)device_compute_units() * (p.resident == 256 ? 1 : 2), tiles = (p.R + 16 * p.MT - 1) / (16 * p.MT);
-  return p.MT == 2 || p.L == 4 || 8 * tiles <= 7 * slots;
+  if (p.MT == 2 || p.L == 4) return true;
+  // (in fortieths of the slots)
+  const int part = p.resident <= 128 ? 18 : p.L == 2 ? (p.time_grid ? 24 : 30) : 35;
+  return 40 * tiles <= part * slots;
 }
 
 // Groups of steps under a fixed scale on the streaming kernels: whether their stages are recomputed in a launch of their
@@ -391,6 +397,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
                       bool small = false, bool allow_clusters = true, bool lean = false) {
   Plan p;
   p.lean = lean;
+  p.time_grid = is_backward && !allow_wide;
   const bool allow_fused = fused_candidate(vel, pol);
   int rhp = allow_resident ? resident_width(vel, tab, pol) : 0;
   if (rhp == 0 && allow_resident && allow_wide) {  // (the time-grid gradient is formed by the other kernels)
