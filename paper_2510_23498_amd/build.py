@@ -29,6 +29,8 @@ RESIDENT_HIDDEN_WIDTHS = (64, 128, 256)    # ... of resident_inst.hip
 SHALLOW_HIDDEN_WIDTHS = (128, 256, 512, 1024)  # ... of shallow_inst.hip
 CLUSTER_HIDDEN_WIDTHS = (512, 768, 1024)   # ... of cluster_inst.hip
 
+CONV_PAIR_BLOCKS = (1, 2)                  # ... of conv_pair_inst.hip: one per number of 32-channel blocks
+
 COMPILE_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Wno-pass-failed",
                  "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
@@ -42,12 +44,13 @@ def _compile(args):
 
 # headers each translation unit includes (directly or not), for the incremental mode
 _DEPS = {
-    "rampde.hip": ("common.hpp", "elementwise.hpp", "fused.hpp", "fused_launch.hpp", "cluster.hpp", "cluster_launch.hpp", "resident.hpp", "resident_launch.hpp", "shallow.hpp", "shallow_launch.hpp", "wide.hpp", "gemm.hpp", "wgrad_slab.hpp", "gemm_slab.hpp", "conv_wgrad_tr.hpp", "conv.hpp", "norm.hpp",
+    "rampde.hip": ("common.hpp", "elementwise.hpp", "fused.hpp", "fused_launch.hpp", "cluster.hpp", "cluster_launch.hpp", "resident.hpp", "resident_launch.hpp", "shallow.hpp", "shallow_launch.hpp", "wide.hpp", "gemm.hpp", "wgrad_slab.hpp", "gemm_slab.hpp", "conv_wgrad_tr.hpp", "conv_pair.hpp", "conv_pair_launch.hpp", "norm.hpp",
                    os.path.join("..", "..", "include", "rampde.h")),
     "fused_inst.hip": ("common.hpp", "fused.hpp", "fused_launch.hpp"),
     "resident_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "resident_launch.hpp"),
     "shallow_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "resident_launch.hpp", "shallow.hpp", "shallow_launch.hpp"),
     "cluster_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "cluster.hpp", "cluster_launch.hpp"),
+    "conv_pair_inst.hip": ("common.hpp", "fused.hpp", "conv_pair.hpp", "conv_pair_launch.hpp"),
     "wide_inst.hip": ("common.hpp", "fused.hpp", "fused_launch.hpp", "wide.hpp"),
 }
 
@@ -85,6 +88,10 @@ def build_library(verbose: bool = False, jobs: int = 0, incremental: bool = Fals
         for bf16 in (0, 1):
             units.append((os.path.join(CSRC, "cluster_inst.hip"), os.path.join(objdir, f"cluster_hp{hp}_{bf16}.o"),
                           [f"-DRAMPDE_INST_HP={hp}", f"-DRAMPDE_INST_BF16={bf16}"]))
+    for c32 in CONV_PAIR_BLOCKS:
+        for bf16 in (0, 1):
+            units.append((os.path.join(CSRC, "conv_pair_inst.hip"), os.path.join(objdir, f"conv_pair_{c32}_{bf16}.o"),
+                          [f"-DRAMPDE_INST_C32={c32}", f"-DRAMPDE_INST_BF16={bf16}"]))
     # (longest first: the widest instantiations take the longest to compile)
     units.sort(key=lambda u: -int(u[2][0].split("=")[1]) if u[2] else 1)
     jobs = jobs or min(len(units), os.cpu_count() or 1, 16)

@@ -39,17 +39,25 @@ __global__ void cast_dense_layer(const float* __restrict__ W, const float* __res
 //   WTp [Cpad][9*Cpad] : WTp[ci][tap*Cpad + co] = Q(W[co][ci][8 - tap])      (input cotangent:
 //         the transposed convolution is a convolution with the flipped kernel)
 //   wt_f [9][Cpad] time-channel weights per tap, bias_f[Cpad].
+// frags (Cpad = 64): Wp and WTp in the order in which conv_pair.hpp multiplies them, a fragment of v_mfma_f32_16x16x32 (16
+// output channels, 32 inputs of a tap; lane l: output l % 16, inputs 8 (l / 16) ..) as 1 KB, [tap][input block][output block].
 template <class T>
 __global__ void cast_conv_layer(const float* __restrict__ W, const float* __restrict__ b, int C, int Cin,
-                                int has_time, uint16_t* Wp, uint16_t* WTp, float* bias_f, float* wt_f, int Cpad) {
+                                int has_time, uint16_t* Wp, uint16_t* WTp, float* bias_f, float* wt_f, int Cpad, int frags) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;  // over Cpad * 9 * Cpad
   int total = Cpad * 9 * Cpad;
   if (idx >= total) return;
   int ci = idx % Cpad, tap = (idx / Cpad) % 9, co = idx / (9 * Cpad);
   uint16_t q = 0;
   if (co < C && ci < C) q = Low<T>::from_f32(W[((size_t)co * Cin + ci) * 9 + tap]);
-  Wp[(size_t)co * 9 * Cpad + tap * Cpad + ci] = q;
-  WTp[(size_t)ci * 9 * Cpad + (8 - tap) * Cpad + co] = q;
+  if (frags) {
+    auto at = [](int row, int t, int k) { return ((((t * 2 + k / 32) * 4 + row / 16) * 64 + row % 16 + 16 * (k % 32 / 8)) * 8) + k % 8; };
+    Wp[at(co, tap, ci)] = q;
+    WTp[at(ci, 8 - tap, co)] = q;
+  } else {
+    Wp[(size_t)co * 9 * Cpad + tap * Cpad + ci] = q;
+    WTp[(size_t)ci * 9 * Cpad + (8 - tap) * Cpad + co] = q;
+  }
   if (ci == 0) {
     float w = 0.f;
     if (co < C && has_time) w = Low<T>::to_f32(Low<T>::from_f32(W[((size_t)co * Cin + C) * 9 + tap]));

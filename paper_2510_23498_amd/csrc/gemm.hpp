@@ -39,13 +39,6 @@ struct GemmNT {
   int detect;                  // raise ctl->nonfinite if any output is inf/nan
   // conv geometry (CONV only)
   int H, Wd, Cpad;
-  // conv3x3_tile only: what the next convolution of a chained tableau reads is formed where its input is written.
-  // With base: C is the slope k of a stage, next = Q(base + h coef k) its successor's stage input (base: the stored state).
-  // With adj: C is the cotangent zbar of a stage input, next = Q(bw Q(S adj) + h coef zbar) the slope cotangent of the
-  // stage before (adj: the fp32 adjoint).  d columns; base and adj have pitch d, next has C's; pad columns are zeroed.
-  const uint16_t* base; const float* adj; uint16_t* next;
-  int d;
-  float h, coef, bw;
 };
 
 template <class T, int MI, int NI, bool CONV>

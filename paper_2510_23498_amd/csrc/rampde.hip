@@ -29,7 +29,7 @@
 #include "wgrad_slab.hpp"
 #include "gemm_slab.hpp"
 #include "conv_wgrad_tr.hpp"
-#include "conv.hpp"
+#include "conv_pair_launch.hpp"
 #include "norm.hpp"
 #include "cnf.hpp"
 
@@ -989,7 +989,7 @@ struct Runner {
         int total = y.Npad * 9 * y.Kpad;
         cast_conv_layer<T><<<blocks_for(total, 256), 256, 0, st>>>(theta + y.theta_w, theta + y.theta_b, y.out, y.in_full,
                                                                    y.has_time, u16(y.Wp), u16(y.WTp), f32(y.bias_f),
-                                                                   f32(y.wt_f), y.Kpad);
+                                                                   f32(y.wt_f), y.Kpad, conv_pairs() ? 1 : 0);
       } else {
         dim3 grid(blocks_for(y.Kpad, 64), y.Npad);
         cast_dense_layer<T><<<grid, 64, 0, st>>>(theta + y.theta_w, theta + y.theta_b, y.out, y.in, y.in_full, y.has_time,
@@ -1003,8 +1003,8 @@ struct Runner {
     }
   }
 
-  // the convolution tile kernel keeps a layer's weights in LDS: more than the default limit
-  hipError_t allow_conv_tile_lds() {
+  // the kernels for convolutions of many channels take more LDS than the default limit
+  hipError_t allow_conv_lds() {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_nt_slab<T, true>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kNtSlabLdsBytes);
     if (e != hipSuccess) return e;
@@ -1013,44 +1013,31 @@ struct Runner {
       e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, NtLines<4>::LDS);
       if (e != hipSuccess) return e;
     }
-    if (p.parabolic || !conv_tile_applies(p.layers[0].Kpad, p.layers[0].Npad, p.Wd)) return hipSuccess;
-    for (ConvTileKernel f : conv_tile_kernels(conv_tile())) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
-      if (e != hipSuccess) return e;
-    }
     return hipSuccess;
   }
 
-  // conv3x3_tile by shape (32 channels; 64 channels with two, with one wavefront per pixel block) and epilogue
-  using ConvTileKernel = void (*)(GemmNT, ConvTileShape);
-  template <int NA, int KC, int AW>
-  static constexpr std::array<ConvTileKernel, 5> conv_tile_epilogues() {
-    return {&conv3x3_tile<T, NA, KC, AW, kConvPlain>, &conv3x3_tile<T, NA, KC, AW, kConvTanh>, &conv3x3_tile<T, NA, KC, AW, kConvFactor>,
-            &conv3x3_tile<T, NA, KC, AW, kConvStage>, &conv3x3_tile<T, NA, KC, AW, kConvCotangent>};
-  }
-  // whether conv3x3_tile also forms what the next stage's convolution reads: stages that are a chain, 16-byte rows.  (A slope
+  // the velocity of two convolutions with at most 64 channels: both in one launch (conv_pair.hpp)
+  bool conv_pairs() const { return p.conv && !p.parabolic && conv_pair_applies(p.layers[0].Kpad, p.Wd); }
+  // whether that launch also forms what the next evaluation reads: stages that are a chain, 16-byte rows.  (A slope
   // that the next stage does not use at all stays out of it, also where it is infinite: 0 times it would be NaN)
   bool conv_fuses_stages(const rampde_tableau* tab) const {
     for (int j = 1; j < p.s; ++j)
       if ((float)tab->A[j * p.s + j - 1] == 0.f) return false;
-    return p.conv && !p.parabolic && conv_tile_applies(p.layers[0].Kpad, p.layers[0].Npad, p.Wd) && vec8() && !dense_stages(tab);
+    return conv_pairs() && vec8() && !dense_stages(tab);
   }
-  bool few_channels() const { return p.d <= 32; }
-  ConvTileShape conv_tile() const {
-    return conv_tile_shape(few_channels() ? 1 : 2, few_channels() ? 2 : 4, p.H, p.Wd, p.R / ((int64_t)p.H * p.Wd), device_compute_units());
-  }
-  std::array<ConvTileKernel, 5> conv_tile_kernels(const ConvTileShape& sh) const {
-    return few_channels() ? conv_tile_epilogues<1, 2, 1>() : sh.aw == 2 ? conv_tile_epilogues<2, 4, 2>() : conv_tile_epilogues<2, 4, 1>();
+  int launch_pair(ConvPair& g, bool vjp) {
+    const int C32 = p.d <= 32 ? 1 : 2;
+    g.H = p.H;
+    g.Wd = p.Wd;
+    TimeScope ts(RAMPDE_K_VELOCITY_GEMM, (g.C ? 2 : 1) * 2.0 * p.R * 64.0 * 9 * 64, st);
+    const ConvPairShape sh = conv_pair_shape(C32, p.H, p.Wd, p.R / ((int64_t)p.H * p.Wd), device_compute_units());
+    HIP_TRY(conv_pair_launch(C32, std::is_same<T, BF16>::value, g, sh, vjp, st));
+    return RAMPDE_OK;
   }
 
   void launch_nt(const GemmNT& g) {
     TimeScope ts(RAMPDE_K_VELOCITY_GEMM, 2.0 * g.M * (double)g.N * g.K, st);
-    if (p.conv && !p.parabolic && conv_tile_applies(g.Cpad, g.N, g.Wd)) {
-      // persistent: one workgroup per CU (its LDS holds the layer's weights), tiles of whole image lines
-      const ConvTileShape sh = conv_tile();
-      const size_t lds = conv_tile_lds_bytes(few_channels() ? 1 : 2, few_channels() ? 2 : 4, sh.lines, g.Wd);
-      conv_tile_kernels(sh)[g.base ? kConvStage : g.adj ? kConvCotangent : g.dact ? kConvFactor : g.act_tanh ? kConvTanh : kConvPlain]<<<sh.blocks, 512, lds, st>>>(g, sh);
-    } else if (p.conv && !p.cw_blocks && conv_nt_lines_applies(g)) {
+    if (p.conv && !p.cw_blocks && conv_nt_lines_applies(g)) {
       // ... with the input staged by image lines: a block of input channels serves all nine taps from LDS
       dim3 grid(g.M / 512, g.N / 128);
       if (g.Wd == 16) conv_nt_lines<T, 1><<<grid, 256, NtLines<1>::LDS, st>>>(g);
@@ -1164,8 +1151,8 @@ struct Runner {
   // first_ready: the first stage's input is there already (in Z, or, with no pad columns, the stored state itself);
   // last_slope: the last stage's slope is wanted (the recomputation needs it for the time-grid gradient only).
   // (64 x 32 x 32, 128 images, 16 RK4 steps: 144 us of copies and 16 convolutions of 19 us less per pass of 13.6 ms)
-  void stages(const uint16_t* ck, double t_i, float h, const rampde_tableau* tab, rampde_dtype low, int keep,
-              float* taus_out, Ctl* c, bool first_ready, bool last_slope) {
+  int stages(const uint16_t* ck, double t_i, float h, const rampde_tableau* tab, rampde_dtype low, int keep,
+             float* taus_out, Ctl* c, bool first_ready, bool last_slope) {
     const int s = p.s;
     const bool fuses = conv_fuses_stages(tab);
     for (int j = 0; j < s; ++j) {
@@ -1187,6 +1174,31 @@ struct Runner {
       const bool slope = last_slope || j + 1 < s;
       if (p.parabolic) {
         parabolic_eval(in, j, jb, c, slope);
+        continue;
+      }
+      if (conv_pairs()) {
+        const Layer &y0 = p.layers[0], &y1 = p.layers[1];
+        ConvPair g{};
+        g.A = in;
+        g.W1 = u16(y0.Wp);
+        g.W2 = u16(y1.Wp);
+        g.bias1 = f32(y0.bias_f);
+        g.bias2 = f32(y1.bias_f);
+        g.wt1 = y0.has_time ? f32(y0.wt_f) : nullptr;
+        g.wt2 = y1.has_time ? f32(y1.wt_f) : nullptr;
+        g.tau = tau;
+        if (keep) g.mid = u16(p.ACT[0]) + (size_t)jb * p.R * y0.Npad;
+        if (slope) g.C = u16(p.K) + (size_t)j * p.stage_stride;
+        g.ctl = c;
+        if (fuses && j + 1 < s) {
+          g.base = ck;
+          g.next = u16(p.Z) + (size_t)(keep ? j + 1 : 0) * p.stage_stride;
+          g.d = p.d;
+          g.h = h;
+          g.coef = (float)tab->A[(j + 1) * s + j];
+        }
+        const int rc = launch_pair(g, false);
+        if (rc) return rc;
         continue;
       }
       for (int l = 0; l < p.L; ++l) {
@@ -1216,13 +1228,6 @@ struct Runner {
         g.H = p.H;
         g.Wd = p.Wd;
         g.Cpad = y.Kpad;
-        if (fuses && last && j + 1 < s) {
-          g.base = ck;
-          g.next = u16(p.Z) + (size_t)(keep ? j + 1 : 0) * p.stage_stride;
-          g.d = p.d;
-          g.h = h;
-          g.coef = (float)tab->A[(j + 1) * s + j];
-        }
         launch_nt(g);
         in = out;
       }
@@ -1231,6 +1236,7 @@ struct Runner {
                                                              p.layers[0].Npad, f32(p.cnf_c), p.R,
                                                              u16(p.K) + (size_t)j * p.stage_stride, p.dpad, p.d - 1, c);
     }
+    return RAMPDE_OK;
   }
 
   // streaming kernels: 8-wide variants when the state width allows 16-byte accesses
@@ -1596,7 +1602,7 @@ struct Runner {
   int forward(const float* theta, const float* y0, const double* tgrid, int N, const rampde_tableau* tab,
               const rampde_policy* pol, uint16_t* ckpt, float* yN) {
     if (use_fused) return forward_fused(theta, y0, tgrid, N, tab, pol, ckpt, yN);
-    if (p.conv) HIP_TRY(allow_conv_tile_lds());
+    if (p.conv) HIP_TRY(allow_conv_lds());
     cast_weights(theta);
     const int naive = (pol->flags & RAMPDE_NAIVE_STATE) ? 1 : 0;
     const int incr_mode = ((pol->flags & RAMPDE_ROUND_INCREMENT) ? 1 : 0) | (naive ? 2 : 0);
@@ -1618,7 +1624,7 @@ struct Runner {
         piece = piece_of(i, N);
         cast_weights(theta + (size_t)piece * p.Pblk);
       }
-      stages(ck, tgrid[i], h, tab, pol->low, 0, nullptr, nullptr, p.d == p.dpad || i > 0, true);
+      if (const int rc = stages(ck, tgrid[i], h, tab, pol->low, 0, nullptr, nullptr, p.d == p.dpad || i > 0, true)) return rc;
       uint16_t* z = p.d != p.dpad && i + 1 < N ? u16(p.Z) : nullptr;
       // bytes per state element: read y (4) + s slopes (2 each) + write y (4) + write checkpoint (2)
       TimeScope ts(RAMPDE_K_COMBINE_STORE, (double)p.n * (10.0 + 2.0 * p.s), st);
@@ -1635,15 +1641,15 @@ struct Runner {
   }
 
   // one step of the adjoint recursion: recompute, cotangent chain, decision, fp32 updates
-  void backward_step(int i, const double* tgrid, const rampde_tableau* tab, const rampde_policy* pol,
-                     const uint16_t* ckpt, float* a, const float* gys_i, float* grad_theta, int dynamic, int detect,
-                     bool recompute, float* tpart_i) {
+  int backward_step(int i, const double* tgrid, const rampde_tableau* tab, const rampde_policy* pol,
+                    const uint16_t* ckpt, float* a, const float* gys_i, float* grad_theta, int dynamic, int detect,
+                    bool recompute, float* tpart_i) {
     const int s = p.s;
     const int naive = (pol->flags & RAMPDE_NAIVE_STATE) ? 1 : 0;
     const float h = (float)(tgrid[i + 1] - tgrid[i]);
     Coefs taus{};
     if (recompute) {
-      stages(ckpt + (size_t)i * step_elems, tgrid[i], h, tab, pol->low, 1, taus.v, ctl, false, tpart_i != nullptr);
+      if (const int rc = stages(ckpt + (size_t)i * step_elems, tgrid[i], h, tab, pol->low, 1, taus.v, ctl, false, tpart_i != nullptr)) return rc;
     } else {
       for (int j = 0; j < s; ++j) taus.v[j] = round_low_host((float)(tgrid[i] + tab->c[j] * (double)h), pol->low);
     }
@@ -1664,6 +1670,28 @@ struct Runner {
       const uint16_t* delta = kbar;
       if (p.parabolic) {
         parabolic_vjp(kbar, j, detect);
+        continue;
+      }
+      if (conv_pairs()) {
+        ConvPair g{};
+        g.A = kbar;
+        g.W1 = u16(p.layers[1].WTp);
+        g.W2 = u16(p.layers[0].WTp);
+        g.act = u16(p.ACT[0]) + (size_t)j * p.R * p.layers[0].Npad;
+        g.mid = u16(p.DELTA[0]) + (size_t)j * p.R * p.layers[0].Npad;
+        g.C = u16(p.ZBAR) + (size_t)j * p.stage_stride;
+        g.ctl = ctl;
+        g.detect = detect;
+        if (fuses && j > 0) {
+          g.adj = a;
+          g.next = u16(p.KBAR) + (size_t)(j - 1) * p.stage_stride;
+          g.d = p.d;
+          g.h = h;
+          g.coef = (float)tab->A[j * s + j - 1];
+          g.bw = (float)tab->b[j - 1];
+        }
+        const int rc = launch_pair(g, true);
+        if (rc) return rc;
         continue;
       }
       for (int l = p.L - 1; l >= 0; --l) {
@@ -1698,14 +1726,6 @@ struct Runner {
         g.H = p.H;
         g.Wd = p.Wd;
         g.Cpad = y.Npad;
-        if (fuses && l == 0 && j > 0) {
-          g.adj = a;
-          g.next = u16(p.KBAR) + (size_t)(j - 1) * p.stage_stride;
-          g.d = p.d;
-          g.h = h;
-          g.coef = (float)tab->A[j * s + j - 1];
-          g.bw = (float)tab->b[j - 1];
-        }
         launch_nt(g);
         delta = out;
       }
@@ -1743,6 +1763,7 @@ struct Runner {
     if (detect) scale_grow<<<1, 256, 0, st>>>(ctl, f32(p.scale_hist), i, Low<T>::p_bits, dynamic,
                                   (pol->flags & RAMPDE_GROW_RAW_NORM) ? 1 : 0, (const unsigned*)(ws + p.amax_slots), nslots);
     param_grads(h, taus, grad_theta, cs, tpart_i);
+    return RAMPDE_OK;
   }
 
   // parameter gradient of one accepted step: contraction over all stages and rows at once,
@@ -1990,7 +2011,7 @@ struct Runner {
     }
     const int detect = dynamic || scaling == RAMPDE_SCALE_NONE_SAFE;
     const int k_max = pol->k_max > 0 ? pol->k_max : 16;
-    if (p.conv) HIP_TRY(allow_conv_tile_lds());
+    if (p.conv) HIP_TRY(allow_conv_lds());
     if (p.wgrad_slab)  // (its ring of operand slabs takes most of a CU's LDS)
       for (const void* f : {reinterpret_cast<const void*>(&wgrad_slab<T, false>), reinterpret_cast<const void*>(&wgrad_slab<T, true>)})
         HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsBytes));
@@ -2231,8 +2252,9 @@ struct Runner {
             }
             g_i = grad_theta + (size_t)q * p.Pblk;
           }
-          backward_step(i, tgrid, tab, pol, ckpt, a, gys_at(i), g_i, dynamic, detect,
-                        i == from ? recompute_first : true, grad_t ? f32(p.tpart) + 2 * (size_t)i : nullptr);
+          const int rc = backward_step(i, tgrid, tab, pol, ckpt, a, gys_at(i), g_i, dynamic, detect,
+                                       i == from ? recompute_first : true, grad_t ? f32(p.tpart) + 2 * (size_t)i : nullptr);
+          if (rc) return rc;
         }
       }
       if (use_fused) {

@@ -242,6 +242,20 @@ def test_conv_tiles_of_whole_lines(C, H, W, B):
     _both(wl.CONFIGS["cfg4"].with_(name=f"convtile{C}x{H}x{W}", B=B, N=1, C=C, H=H, W=W, tableau="heun"), bias_std=0.1)
 
 
+@pytest.mark.parametrize("C,H,W,few,many", [(64, 32, 32, 2, 128), (24, 28, 28, 1, 128), (64, 14, 14, 2, 256), (64, 9, 64, 1, 60),
+                                            (32, 33, 30, 1, 90), (64, 40, 13, 2, 100)])
+def test_conv_tiles_of_other_heights_give_the_same_bits(C, H, W, few, many):
+    # the height of a tile follows from the number of images: from one or two lines to the most that a workgroup
+    # multiplies.  A pixel's sums are the same ones in every tile, so an image's trajectory and adjoint are too
+    cfg = wl.CONFIGS["cfg4"].with_(name=f"convheight{C}x{H}x{W}", B=many, N=1, C=C, H=H, W=W, tableau="heun", low="bf16", loss="half_sse")
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    a = par.run_gpu(cfg, theta, y0, target)
+    b = par.run_gpu(cfg.with_(B=few), theta, y0[-few:].copy(), target[-few:].copy())
+    np.testing.assert_array_equal(a["yN"][-few:], b["yN"])
+    np.testing.assert_array_equal(a["ckpt"][:, -few:], b["ckpt"])
+    np.testing.assert_array_equal(a["grad_y0"][-few:], b["grad_y0"])
+
+
 def test_conv_small_odd_geometry():
     cfg = wl.CONFIGS["cfg4"].with_(name="convodd", B=2, N=2, C=5, H=7, W=6, tableau="kutta3")
     _both(cfg, bias_std=0.1)
