@@ -37,6 +37,7 @@ static_assert(sizeof(Ctl) == 64, "control block layout");
 
 struct F16 {};
 struct BF16 {};
+constexpr uint32_t kNonfiniteBits = 0x80008000u;  // (see nonfinite2)
 
 template <class T>
 struct Low;
@@ -58,6 +59,8 @@ struct Low<F16> {
     return __builtin_bit_cast(uint32_t, v);
   }
   __device__ static inline bool nonfinite(uint16_t u) { return (u & 0x7C00u) == 0x7C00u; }
+  // two packed values: a bit of kNonfiniteBits where one is not finite (its exponent, all ones, carries into the sign)
+  __device__ static inline uint32_t nonfinite2(uint32_t u) { return (u & 0x7C007C00u) + 0x04000400u; }
   __device__ static inline f32x16 mfma32(u16x8 a, u16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
   }
@@ -85,6 +88,7 @@ struct Low<BF16> {
     return __builtin_bit_cast(uint32_t, v);
   }
   __device__ static inline bool nonfinite(uint16_t u) { return (u & 0x7F80u) == 0x7F80u; }
+  __device__ static inline uint32_t nonfinite2(uint32_t u) { return (u & 0x7F807F80u) + 0x00800080u; }
   __device__ static inline f32x16 mfma32(u16x8 a, u16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }

@@ -14,6 +14,8 @@
 // of one tap NCT weight fragments, which come from memory in the order in which they are used (1 KB each, four blocks
 // ahead), and MT pixel fragments from LDS (a tap is a shifted pixel address) for NCT MT matrix instructions.
 #pragma once
+#include <type_traits>
+
 #include "fused.hpp"
 
 namespace rampde {
@@ -26,8 +28,8 @@ struct ConvPairShape {
 struct ConvPair {
   const uint16_t* A;                 // [rows][64] stage input / slope cotangent
   const uint16_t *W1, *W2;           // weight fragments of the first and the second convolution (see cast_conv_layer)
-  const float *bias1, *wt1, *bias2, *wt2;  // fp32 (rounded) biases [64], time-channel weights [9][64] (null: none)
-  float tau;                         // stage time, already rounded to low
+  const uint16_t *T1, *T2;           // their time-channel weights and biases: [2][64][8], contraction index 0-8: tap, 9: bias
+  uint32_t tau;                      // stage time, low-precision bits
   const uint16_t* act;               // VJP: [rows][64] stored hidden activation
   uint16_t* mid;                     // [rows][64] hidden activation / its cotangent, or null: not kept
   uint16_t* C;                       // [rows][64] slope / cotangent of the stage input, or null: the hidden activation alone
@@ -46,7 +48,7 @@ struct ConvPair {
 
 constexpr int conv_pair_pitch(int C32) { return 32 * C32 + 8; }  // elements per LDS row of one pixel's channels
 inline size_t conv_pair_lds_bytes(int C32, int lines, int Wd) {
-  return (size_t)(lines + 4) * (Wd + 2) * conv_pair_pitch(C32) * 2 + 2 * (16 + 10) * 32 * C32 * 4;
+  return (size_t)(lines + 4) * (Wd + 2) * conv_pair_pitch(C32) * 2;
 }
 inline bool conv_pair_applies(int Cpad, int Wd) { return Cpad == 64 && Wd >= 1 && Wd <= 64; }
 typedef uint32_t u32x4p __attribute__((ext_vector_type(4)));
@@ -58,62 +60,93 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t pair_window(const E* p, int el
 }
 
 // The contraction: acc[m][t] += weights of output channels 16 t .. x pixels of block m.  base: LDS element of the block's
-// pixel (this lane's) and channel chunk.
+// pixel (this lane's) and channel chunk.  The first two lines of taps are one loop body: unrolled over all nine taps, a
+// launch fetched more instructions that it executes once.
 template <class T, int C32, int MT>
 struct PairGemm {
-  static constexpr int NCT = 2 * C32, NB = 9 * C32, PITCH = conv_pair_pitch(C32);
+  static constexpr int NCT = 2 * C32, U = 3 * C32, PITCH = conv_pair_pitch(C32), FR = U % 2 ? 3 : 2;
   u16x8 w[kPairLookahead][NCT];
-  const uint16_t* Wf;
-  __device__ __forceinline__ void load_w(int it, u16x8 (&dst)[NCT]) {
-    const int tap = it / C32, kk = it % C32;
+  __amdgpu_buffer_rsrc_t frags;
+  int at;  // bytes into the fragments
+  __device__ __forceinline__ void load_w(int u, u16x8 (&dst)[NCT]) {
 #pragma unroll
-    for (int t = 0; t < NCT; ++t) dst[t] = *reinterpret_cast<const u16x8*>(Wf + ((tap * 2 + kk) * 4 + t) * 512);
+    for (int t = 0; t < NCT; ++t)
+      dst[t] = __builtin_bit_cast(u16x8, __builtin_amdgcn_raw_buffer_load_b128(frags, (threadIdx.x & 63) * 16 + t * 1024, at + (u / C32 * 8 + u % C32 * 4) * 1024, 0));
   }
-  __device__ __forceinline__ void start(const uint16_t* frags) {
-    Wf = frags + (threadIdx.x & 63) * 8;
+  __device__ __forceinline__ void start(const uint16_t* W) {
+    frags = pair_window(W, 64 * 576);
+    at = 0;
 #pragma unroll
     for (int i = 0; i < kPairLookahead; ++i) load_w(i, w[i]);
   }
-  __device__ __forceinline__ void run(const uint16_t* in, const int (&base)[MT], int LW, f32x4 (&acc)[MT][NCT]) {
-    auto load_b = [&](int it, u16x8 (&fb)[MT]) __attribute__((always_inline)) {
-      const int tap = it / C32, kk = it % C32;
-      const int shift = ((tap / 3 - 1) * LW + (tap % 3 - 1)) * PITCH;
+  // between: issues what the epilogue needs from memory, before the last line of taps (loads return in order: issued
+  // earlier, the first weights behind them would wait for them)
+  template <class Between>
+  __device__ __forceinline__ void run(const uint16_t* in, const int (&base)[MT], int LW, f32x4 (&acc)[MT][NCT], const Between& between) {
+    int b[MT];
 #pragma unroll
-      for (int m = 0; m < MT; ++m) fb[m] = *reinterpret_cast<const u16x8*>(&in[base[m] + shift + kk * 32]);
+    for (int m = 0; m < MT; ++m) b[m] = base[m] - (LW + 1) * PITCH;
+    auto load_b = [&](int u, u16x8 (&fb)[MT]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) fb[m] = *reinterpret_cast<const u16x8*>(&in[b[m] + u / C32 * PITCH + u % C32 * 32]);
     };
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-      for (int t = 0; t < NCT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u16x8 fb[2][MT];
+    u16x8 fb[FR][MT];
     load_b(0, fb[0]);
+    auto line = [&](auto last) __attribute__((always_inline)) {
 #pragma unroll
-    for (int it = 0; it < NB; ++it) {
-      u16x8 cur[NCT];
+      for (int u = 0; u < U; ++u) {
+        if (!last && u + 1 == U) {
 #pragma unroll
-      for (int t = 0; t < NCT; ++t) cur[t] = w[it % kPairLookahead][t];
-      if (it + 1 < NB) load_b(it + 1, fb[(it + 1) & 1]);
-      __builtin_amdgcn_sched_barrier(0);
+          for (int m = 0; m < MT; ++m) b[m] += LW * PITCH;
+        }
+        if (!last || u + 1 < U) load_b((u + 1) % U, fb[(u + 1) % FR]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int m = 0; m < MT; ++m)
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int t = 0; t < NCT; ++t) acc[m][t] = Low<T>::mfma16(cur[t], fb[it & 1][m], acc[m][t]);
-      if (it + kPairLookahead < NB) load_w(it + kPairLookahead, w[it % kPairLookahead]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+          for (int t = 0; t < NCT; ++t) acc[m][t] = Low<T>::mfma16(w[u % kPairLookahead][t], fb[u % FR][m], acc[m][t]);
+        if (u + kPairLookahead == U) at += 3 * 8 * 1024;
+        if (!last || u + kPairLookahead < U) load_w((u + kPairLookahead) % U, w[u % kPairLookahead]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+#pragma unroll 1
+    for (int dy = 0; dy < 2; ++dy) line(std::false_type{});
+    between();
+    __builtin_amdgcn_sched_barrier(0);
+    line(std::true_type{});
+  }
+};
+
+// One more contraction block in front: the time channel (the stage time where the tap is inside the image) and the bias.
+template <class T, int NCT>
+struct PairTime {
+  u16x8 w[NCT];
+  __device__ __forceinline__ void start(const uint16_t* W) {
+    const auto win = pair_window(W, 2 * 64 * 8);  // (contraction indices 16 and up: zeros)
+#pragma unroll
+    for (int t = 0; t < NCT; ++t)
+      w[t] = __builtin_bit_cast(u16x8, __builtin_amdgcn_raw_buffer_load_b128(win, ((threadIdx.x & 63) / 16 * 64 + t * 16 + (threadIdx.x & 15)) * 16, 0, 0));
+  }
+  __device__ __forceinline__ void run(uint32_t tau, int y, int x, int H, int W, f32x4 (&acc)[NCT]) {
+    constexpr uint32_t one = std::is_same<T, BF16>::value ? 0x3f80u : 0x3c00u;
+    const bool t = y > 0, b = y < H - 1, l = x > 0, r = x < W - 1;
+    auto two = [&](bool lo, bool hi) __attribute__((always_inline)) { return (lo ? tau : 0u) | (hi ? tau << 16 : 0u); };
+    uint4 q = make_uint4(two(t & l, t), two(t & r, l), two(true, r), two(b & l, b));
+    if (threadIdx.x & 16) q.x = two(b & r, false) | one << 16;  // (lanes of contraction indices 8 to 15)
+#pragma unroll
+    for (int o = 0; o < NCT; ++o) acc[o] = Low<T>::mfma16(w[o], __builtin_bit_cast(u16x8, q), f32x4{0.f, 0.f, 0.f, 0.f});
   }
 };
 
 template <class T, int C32, int MT1, int MT2, bool VJP>
 __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, ConvPairShape sh) {
-  constexpr int NT = 256, NCT = 2 * C32, C8 = 4 * C32, NCH = 32 * C32, PITCH = conv_pair_pitch(C32);
+  constexpr int NT = 256, NCT = 2 * C32, C8 = 4 * C32, PITCH = conv_pair_pitch(C32);
   constexpr int MAXC = ((64 * MT1 + 128) * C8 + NT - 1) / NT;  // staged chunks of a thread: at most 2 lines of 64 more than the hidden tile
   constexpr int MAXO = (64 * MT2 * C8 + NT - 1) / NT;          // ... of the tile's own lines
   extern __shared__ __attribute__((aligned(16))) uint16_t cp_smem[];
   const int W = g.Wd, H = g.H, PR = sh.lines, LW = W + 2;
   uint16_t* sIn = cp_smem;                                               // [PR + 4][W + 2][PITCH]
-  float* s_tt = reinterpret_cast<float*>(sIn + (PR + 4) * LW * PITCH);   // [2][16][NCH]: bias + time term by border class
-  float* s_wt = s_tt + 2 * 16 * NCH;                                     // [2][10][NCH]: time-channel weights, bias
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fl = lane & 15, fg = lane >> 4;
 
@@ -143,14 +176,10 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
   PairGemm<T, C32, MT1> first;
   first.start(g.W1);
 
-  // ---- time terms, zero columns and lines
-  if constexpr (!VJP) {
-    for (int i = tid; i < 2 * 10 * NCH; i += NT) {
-      const int layer = i / (10 * NCH), t = i / NCH % 10, n = i % NCH;
-      const float* wt = layer ? g.wt2 : g.wt1;
-      s_wt[i] = t == 9 ? (layer ? g.bias2 : g.bias1)[n] : wt ? wt[t * 64 + n] : 0.f;
-    }
-  }
+  PairTime<T, NCT> time;
+  if constexpr (!VJP) time.start(g.T1);
+
+  // ---- zero columns and lines
   const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int id = tid; id < (PR + 4) * 2 * C8; id += NT) {
     const int c8 = id % C8, side = (id / C8) & 1, l = id / (2 * C8);
@@ -168,36 +197,26 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
     if (px < staged) *reinterpret_cast<u16x8*>(&sIn[lds_at(px, f0) + (id % C8) * 8]) = reg[i];
   }
   __syncthreads();
-  if constexpr (!VJP) {
-    for (int i = tid; i < 2 * 16 * NCH; i += NT) {
-      const int layer = i / (16 * NCH), combo = i / NCH % 16, n = i % NCH;
-      const float* wt = s_wt + layer * 10 * NCH;
-      float sum = 0.f;
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const int dy = t / 3 - 1, dx = t % 3 - 1;
-        const bool ok = (dy >= 0 || (combo & 8)) && (dy <= 0 || (combo & 4)) && (dx >= 0 || (combo & 2)) && (dx <= 0 || (combo & 1));
-        sum += ok ? wt[t * NCH + n] * g.tau : 0.f;
-      }
-      s_tt[i] = wt[9 * NCH + n] + sum;
-    }
-  }
-  auto border = [&](int y, int x) __attribute__((always_inline)) {
-    return ((y > 0) << 3) | ((y < H - 1) << 2) | ((x > 0) << 1) | (x < W - 1 ? 1 : 0);
-  };
-
-  bool bad = false;
+  uint32_t bad = 0u;  // (kNonfiniteBits of it)
+  auto watch = [&](uint2 q) __attribute__((always_inline)) { return Low<T>::nonfinite2(q.x) | Low<T>::nonfinite2(q.y); };
   // ---- first convolution
   {
-    int base[MT1], combo[MT1];
+    int base[MT1];
+    f32x4 acc[MT1][NCT];
     uint2 dv[VJP ? MT1 : 1][NCT];
 #pragma unroll
     for (int m = 0; m < MT1; ++m) {
       const int p = (wave * MT1 + m) * 16 + fl, pc = p < n1 ? p : 0, l = line_of(pc);
       base[m] = lds_at(pc, h0) + fg * 8;
-      if constexpr (!VJP) combo[m] = border(h0 + l, pc - l * W);
+      if constexpr (!VJP) {
+        time.run(g.tau, h0 + l, pc - l * W, H, W, acc[m]);
+      } else {
+#pragma unroll
+        for (int t = 0; t < NCT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
     }
-    if constexpr (VJP) {  // the stored activations for the tanh' factor
+    first.run(sIn, base, LW, acc, []() {});
+    if constexpr (VJP) {  // the stored activations for the tanh' factor (requested any earlier, beside the multiplication, they slow it down by more)
       const auto act = pair_window(g.act + (line0 + h0) * W * 64, n1 * 64);
 #pragma unroll
       for (int m = 0; m < MT1; ++m)
@@ -205,9 +224,7 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
         for (int t = 0; t < NCT; ++t)
           dv[m][t] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(act, ((wave * MT1 + m) * 16 + fl) * 128 + t * 32 + fg * 8, 0, 0));
     }
-    f32x4 acc[MT1][NCT];
-    first.run(sIn, base, LW, acc);
-    __syncthreads();  // the input has been read (and the time terms are written)
+    __syncthreads();  // the input has been read
 #pragma unroll
     for (int m = 0; m < MT1; ++m) {
       const bool on = (wave * MT1 + m) * 16 + fl < n1;
@@ -223,18 +240,20 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = v[r] * (1.f - av[r] * av[r]);
         } else {
-          const float4 tv = *reinterpret_cast<const float4*>(&s_tt[combo[m] * NCH + n]);
-          v[0] = tanh_fast(v[0] + tv.x); v[1] = tanh_fast(v[1] + tv.y);
-          v[2] = tanh_fast(v[2] + tv.z); v[3] = tanh_fast(v[3] + tv.w);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = tanh_fast(v[r]);
         }
         const uint2 q = pack4<T>(v);
-        if constexpr (VJP) bad |= on & any_nonfinite4<T>(q);
+        if constexpr (VJP) bad |= on ? watch(q) : 0u;
         if (on) *reinterpret_cast<uint2*>(&sIn[base[m] - fg * 8 + n]) = q;
       }
     }
   }
   PairGemm<T, C32, MT2> second;
-  if (g.C) second.start(g.W2);
+  if (g.C) {
+    second.start(g.W2);
+    if constexpr (!VJP) time.start(g.T2);
+  }
   __syncthreads();
   if (g.mid) {
     const auto out = pair_window(g.mid + (line0 + y0) * W * 64, n2 * 64);
@@ -247,49 +266,67 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
   }
   // ---- second convolution
   if (g.C) {
-    int base[MT2], combo[MT2];
+    int base[MT2];
+    f32x4 acc[MT2][NCT];
 #pragma unroll
     for (int m = 0; m < MT2; ++m) {
       const int p = (wave * MT2 + m) * 16 + fl, pc = p < n2 ? p : 0, l = line_of(pc);
       base[m] = lds_at(pc, y0) + fg * 8;
-      if constexpr (!VJP) combo[m] = border(y0 + l, pc - l * W);
+      if constexpr (!VJP) {
+        time.run(g.tau, y0 + l, pc - l * W, H, W, acc[m]);
+      } else {
+#pragma unroll
+        for (int t = 0; t < NCT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
     }
-    f32x4 acc[MT2][NCT];
-    second.run(sIn, base, LW, acc);
+    // what the next evaluation's input is formed from: the stored state in flight beside the multiplication, the adjoint
+    // behind it (without `next` nothing is read; a chunk past the d columns reads zeros)
+    const int dst0 = tid % C8 * 16, n = tid % C8 * 8, outside = n < g.d ? 0 : 0x40000000;
+    uint4 ahead[MAXO][VJP ? 2 : 1];
+    auto fetch = [&]() __attribute__((always_inline)) {
+      const int live = g.next ? n2 * g.d : 0;
+      if constexpr (VJP) {
+        const auto adj = pair_window(g.adj + (g.next ? (line0 + y0) * W * g.d : 0), live);
+#pragma unroll
+        for (int i = 0; i < MAXO; ++i)
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+            ahead[i][e] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(adj, ((tid + NT * i) / C8 * g.d + n + 4 * e) * 4 | outside, 0, 0));
+      } else {
+        const auto ybase = pair_window(g.base + (g.next ? (line0 + y0) * W * g.d : 0), live);
+#pragma unroll
+        for (int i = 0; i < MAXO; ++i)
+          ahead[i][0] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ybase, ((tid + NT * i) / C8 * g.d + n) * 2 | outside, 0, 0));
+      }
+    };
+    if constexpr (VJP) {
+      second.run(sIn, base, LW, acc, []() {});
+      fetch();
+    } else {
+      second.run(sIn, base, LW, acc, fetch);
+    }
     __syncthreads();
 #pragma unroll
     for (int m = 0; m < MT2; ++m) {
       const bool on = (wave * MT2 + m) * 16 + fl < n2;
 #pragma unroll
       for (int t = 0; t < NCT; ++t) {
-        const int n = t * 16 + fg * 4;
-        float v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = acc[m][t][r];
-        if constexpr (!VJP) {
-          const float4 tv = *reinterpret_cast<const float4*>(&s_tt[(16 + combo[m]) * NCH + n]);
-          v[0] += tv.x; v[1] += tv.y; v[2] += tv.z; v[3] += tv.w;
-        }
-        if (on) *reinterpret_cast<uint2*>(&sIn[base[m] - fg * 8 + n]) = pack4<T>(v);
+        const float v[4] = {acc[m][t][0], acc[m][t][1], acc[m][t][2], acc[m][t][3]};
+        if (on) *reinterpret_cast<uint2*>(&sIn[base[m] - fg * 8 + t * 16 + fg * 4]) = pack4<T>(v);
       }
     }
     __syncthreads();
     const auto out = pair_window(g.C + (line0 + y0) * W * 64, n2 * 64);
-    const int dst0 = tid % C8 * 16, n = tid % C8 * 8;
     if (!g.next) {
 #pragma unroll
       for (int i = 0; i < MAXO; ++i) {
         const int id = tid + NT * i, px = id / C8;
         const uint4 q = *reinterpret_cast<const uint4*>(&sIn[lds_at(px < n2 ? px : 0, y0) + n]);
-        if constexpr (VJP) bad |= px < n2 & (any_nonfinite4<T>(make_uint2(q.x, q.y)) | any_nonfinite4<T>(make_uint2(q.z, q.w)));
+        if constexpr (VJP) bad |= watch(make_uint2(q.x, q.y)) | watch(make_uint2(q.z, q.w));  // (past the tile: its first pixel)
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4p, q), out, px * 128 + dst0, 0, 0);
       }
     } else {
       const auto next = pair_window(g.next + (line0 + y0) * W * 64, n2 * 64);
-      // (a chunk past the d columns reads and keeps zeros)
-      const int outside = n < g.d ? 0 : 0x40000000;
-      const auto ybase = pair_window(g.base + (VJP ? 0 : (line0 + y0) * W * g.d), VJP ? 0 : n2 * g.d);
-      const auto adj = pair_window(g.adj + (VJP ? (line0 + y0) * W * g.d : 0), VJP ? n2 * g.d : 0);
       const float S = VJP ? g.ctl->S : 0.f;
 #pragma unroll
       for (int i = 0; i < MAXO; ++i) {
@@ -299,16 +336,11 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
         const uint2 half[2] = {make_uint2(q.x, q.y), make_uint2(q.z, q.w)};
         uint4 xq;
         if constexpr (VJP) {
-          float a[8];
-#pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const float4 v = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(adj, (px * g.d + n + 4 * e) * 4 | outside, 0, 0));
-            a[4 * e] = v.x; a[4 * e + 1] = v.y; a[4 * e + 2] = v.z; a[4 * e + 3] = v.w;
-          }
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
             float fe[4], lam[4], xe[4];
-            const float sa[4] = {S * a[4 * e], S * a[4 * e + 1], S * a[4 * e + 2], S * a[4 * e + 3]};
+            const float4 a = __builtin_bit_cast(float4, ahead[i][e]);
+            const float sa[4] = {S * a.x, S * a.y, S * a.z, S * a.w};
             const uint2 lq = pack4<T>(sa);
             unpack4<T>(half[e], fe);
             unpack4<T>(lq, lam);
@@ -316,11 +348,11 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
             for (int r = 0; r < 4; ++r) xe[r] = fmaf(g.h, g.coef * fe[r], g.bw * lam[r]);
             uint2 z = pack4<T>(xe);
             if (n >= g.d) z = make_uint2(0u, 0u);
-            bad |= px < n2 & (any_nonfinite4<T>(half[e]) | any_nonfinite4<T>(lq) | any_nonfinite4<T>(z));
+            bad |= px < n2 ? watch(half[e]) | watch(lq) | watch(z) : 0u;
             if (e == 0) { xq.x = z.x; xq.y = z.y; } else { xq.z = z.x; xq.w = z.y; }
           }
         } else {
-          const uint4 yq = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ybase, (px * g.d + n) * 2 | outside, 0, 0));
+          const uint4 yq = ahead[i][0];
           const uint2 yh[2] = {make_uint2(yq.x, yq.y), make_uint2(yq.z, yq.w)};
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
@@ -338,7 +370,7 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
       }
     }
   }
-  if (g.detect) raise_if_any(bad, g.ctl);
+  if (g.detect) raise_if_any((bad & kNonfiniteBits) != 0u, g.ctl);
 }
 
 }  // namespace rampde

@@ -40,10 +40,12 @@ __global__ void cast_dense_layer(const float* __restrict__ W, const float* __res
 //         the transposed convolution is a convolution with the flipped kernel)
 //   wt_f [9][Cpad] time-channel weights per tap, bias_f[Cpad].
 // frags (Cpad = 64): Wp and WTp in the order in which conv_pair.hpp multiplies them, a fragment of v_mfma_f32_16x16x32 (16
-// output channels, 32 inputs of a tap; lane l: output l % 16, inputs 8 (l / 16) ..) as 1 KB, [tap][input block][output block].
+// output channels, 32 inputs of a tap; lane l: output l % 16, inputs 8 (l / 16) ..) as 1 KB, [tap][input block][output block];
+// WTp may be null.  And the time-channel weights and the bias likewise, as a block of their own: frags [2][64][8], element
+// (k / 8, output, k % 8), k = 0-8: tap, 9: bias.
 template <class T>
 __global__ void cast_conv_layer(const float* __restrict__ W, const float* __restrict__ b, int C, int Cin,
-                                int has_time, uint16_t* Wp, uint16_t* WTp, float* bias_f, float* wt_f, int Cpad, int frags) {
+                                int has_time, uint16_t* Wp, uint16_t* WTp, float* bias_f, float* wt_f, int Cpad, uint16_t* frags) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;  // over Cpad * 9 * Cpad
   int total = Cpad * 9 * Cpad;
   if (idx >= total) return;
@@ -53,7 +55,7 @@ __global__ void cast_conv_layer(const float* __restrict__ W, const float* __rest
   if (frags) {
     auto at = [](int row, int t, int k) { return ((((t * 2 + k / 32) * 4 + row / 16) * 64 + row % 16 + 16 * (k % 32 / 8)) * 8) + k % 8; };
     Wp[at(co, tap, ci)] = q;
-    WTp[at(ci, 8 - tap, co)] = q;
+    if (WTp) WTp[at(ci, 8 - tap, co)] = q;
   } else {
     Wp[(size_t)co * 9 * Cpad + tap * Cpad + ci] = q;
     WTp[(size_t)ci * 9 * Cpad + (8 - tap) * Cpad + co] = q;
@@ -62,7 +64,12 @@ __global__ void cast_conv_layer(const float* __restrict__ W, const float* __rest
     float w = 0.f;
     if (co < C && has_time) w = Low<T>::to_f32(Low<T>::from_f32(W[((size_t)co * Cin + C) * 9 + tap]));
     wt_f[tap * Cpad + co] = w;
-    if (tap == 0) bias_f[co] = (co < C) ? Low<T>::to_f32(Low<T>::from_f32(b[co])) : 0.f;
+    const uint16_t bq = co < C ? Low<T>::from_f32(b[co]) : 0;
+    if (tap == 0) bias_f[co] = Low<T>::to_f32(bq);
+    if (frags) {
+      frags[((tap / 8) * 64 + co) * 8 + tap % 8] = Low<T>::from_f32(w);
+      if (tap < 7) frags[(64 + co) * 8 + tap + 1] = tap == 0 ? bq : 0;
+    }
   }
 }
 

@@ -54,6 +54,19 @@ static float round_low_host(float x, rampde_dtype low) {
   return r;
 }
 
+// the bits of a value that is exact in the low-precision format
+static uint32_t low_bits_host(float x, rampde_dtype low) {
+  if (low == RAMPDE_F16) {
+    const _Float16 h = (_Float16)x;
+    uint16_t b;
+    memcpy(&b, &h, 2);
+    return b;
+  }
+  uint32_t u;
+  memcpy(&u, &x, 4);
+  return u >> 16;
+}
+
 struct Layer {
   int out, in, in_full;  // in: state/activation inputs; in_full: + time column (dense layer 1)
   int Npad, Kpad;        // padded out / in
@@ -62,6 +75,7 @@ struct Layer {
   // workspace offsets (bytes)
   size_t Wp, WTp, bias_f, wt_f;
   size_t Wf, WTf;  // fragment-major copies (row-tile-persistent kernels)
+  size_t tf;       // conv_pair.hpp: time-channel weights and bias (no WTp in a forward pass there)
   int ldw;  // K extent of the forward GEMM (dense: Kpad; conv: 9 * Cpad)
   // all-taps convolution weight gradient: K-chunk length, chunk count, the chunks' private copies
   int cw_per = 0, cw_splits = 0;
@@ -133,6 +147,8 @@ struct Plan {
   size_t cl_W = 0, cl_x = 0, cl_tickets = 0;
   int step_group = 1;               // adjoint steps per kernel launch (> 1: fixed scale, or kernels that decide inside a launch)
   bool time_grid = false;           // a backward pass that forms dL/dt
+  // the velocity of two convolutions with at most 64 channels: both in one launch (conv_pair.hpp)
+  bool conv_pairs() const { return conv && !parabolic && conv_pair_applies(layers[0].Kpad, Wd); }
   bool lean = false;                // no choice of kernels for which the workspace alone is larger (see plan_within)
   std::vector<size_t> ACTT, DELTAT;
 };
@@ -427,7 +443,8 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
   for (auto& y : p.layers) {
     size_t wel = (size_t)y.Npad * (p.conv ? 9 * y.Kpad : y.Kpad);
     y.Wp = take(wel * 2);
-    y.WTp = take(wel * 2);
+    if (is_backward || !p.conv_pairs()) y.WTp = take(wel * 2);
+    if (p.conv_pairs()) y.tf = take(2 * 64 * 8 * sizeof(uint16_t));
     y.bias_f = take(sizeof(float) * y.Npad);
     y.wt_f = take(sizeof(float) * y.Npad * (p.conv ? 9 : 1));
   }
@@ -988,8 +1005,8 @@ struct Runner {
       if (p.conv) {
         int total = y.Npad * 9 * y.Kpad;
         cast_conv_layer<T><<<blocks_for(total, 256), 256, 0, st>>>(theta + y.theta_w, theta + y.theta_b, y.out, y.in_full,
-                                                                   y.has_time, u16(y.Wp), u16(y.WTp), f32(y.bias_f),
-                                                                   f32(y.wt_f), y.Kpad, conv_pairs() ? 1 : 0);
+                                                                   y.has_time, u16(y.Wp), y.WTp ? u16(y.WTp) : nullptr, f32(y.bias_f),
+                                                                   f32(y.wt_f), y.Kpad, y.tf ? u16(y.tf) : nullptr);
       } else {
         dim3 grid(blocks_for(y.Kpad, 64), y.Npad);
         cast_dense_layer<T><<<grid, 64, 0, st>>>(theta + y.theta_w, theta + y.theta_b, y.out, y.in, y.in_full, y.has_time,
@@ -1016,14 +1033,12 @@ struct Runner {
     return hipSuccess;
   }
 
-  // the velocity of two convolutions with at most 64 channels: both in one launch (conv_pair.hpp)
-  bool conv_pairs() const { return p.conv && !p.parabolic && conv_pair_applies(p.layers[0].Kpad, p.Wd); }
-  // whether that launch also forms what the next evaluation reads: stages that are a chain, 16-byte rows.  (A slope
+  // whether conv_pair also forms what the next evaluation reads: stages that are a chain, 16-byte rows.  (A slope
   // that the next stage does not use at all stays out of it, also where it is infinite: 0 times it would be NaN)
   bool conv_fuses_stages(const rampde_tableau* tab) const {
     for (int j = 1; j < p.s; ++j)
       if ((float)tab->A[j * p.s + j - 1] == 0.f) return false;
-    return conv_pairs() && vec8() && !dense_stages(tab);
+    return p.conv_pairs() && vec8() && !dense_stages(tab);
   }
   int launch_pair(ConvPair& g, bool vjp) {
     const int C32 = p.d <= 32 ? 1 : 2;
@@ -1157,7 +1172,10 @@ struct Runner {
     const bool fuses = conv_fuses_stages(tab);
     for (int j = 0; j < s; ++j) {
       const int jb = keep ? j : 0;
-      uint16_t* z = u16(p.Z) + (size_t)jb * p.stage_stride;
+      // (conv_pair: a tile writes its lines of the next stage's input while others still read theirs with a halo, so that
+      // is never the same buffer; a forward pass keeps no hidden activation and alternates with that one's)
+      auto stage_z = [&](int q) { return !keep && fuses && q % 2 ? u16(p.ACT[0]) : u16(p.Z) + (size_t)(keep ? q : 0) * p.stage_stride; };
+      uint16_t* z = stage_z(j);
       Coefs arow{};
       for (int l = 0; l < j; ++l) arow.v[l] = (float)tab->A[j * s + l];
       const bool ready = j == 0 ? first_ready : fuses;
@@ -1176,23 +1194,21 @@ struct Runner {
         parabolic_eval(in, j, jb, c, slope);
         continue;
       }
-      if (conv_pairs()) {
+      if (p.conv_pairs()) {
         const Layer &y0 = p.layers[0], &y1 = p.layers[1];
         ConvPair g{};
         g.A = in;
         g.W1 = u16(y0.Wp);
         g.W2 = u16(y1.Wp);
-        g.bias1 = f32(y0.bias_f);
-        g.bias2 = f32(y1.bias_f);
-        g.wt1 = y0.has_time ? f32(y0.wt_f) : nullptr;
-        g.wt2 = y1.has_time ? f32(y1.wt_f) : nullptr;
-        g.tau = tau;
+        g.T1 = u16(y0.tf);
+        g.T2 = u16(y1.tf);
+        g.tau = low_bits_host(tau, low);
         if (keep) g.mid = u16(p.ACT[0]) + (size_t)jb * p.R * y0.Npad;
         if (slope) g.C = u16(p.K) + (size_t)j * p.stage_stride;
         g.ctl = c;
         if (fuses && j + 1 < s) {
           g.base = ck;
-          g.next = u16(p.Z) + (size_t)(keep ? j + 1 : 0) * p.stage_stride;
+          g.next = stage_z(j + 1);
           g.d = p.d;
           g.h = h;
           g.coef = (float)tab->A[(j + 1) * s + j];
@@ -1672,7 +1688,7 @@ struct Runner {
         parabolic_vjp(kbar, j, detect);
         continue;
       }
-      if (conv_pairs()) {
+      if (p.conv_pairs()) {
         ConvPair g{};
         g.A = kbar;
         g.W1 = u16(p.layers[1].WTp);

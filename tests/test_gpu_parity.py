@@ -242,11 +242,12 @@ def test_conv_tiles_of_whole_lines(C, H, W, B):
     _both(wl.CONFIGS["cfg4"].with_(name=f"convtile{C}x{H}x{W}", B=B, N=1, C=C, H=H, W=W, tableau="heun"), bias_std=0.1)
 
 
-@pytest.mark.parametrize("C,H,W,few,many", [(64, 32, 32, 2, 128), (24, 28, 28, 1, 128), (64, 14, 14, 2, 256), (64, 9, 64, 1, 60),
+@pytest.mark.parametrize("C,H,W,few,many", [(64, 32, 32, 2, 128), (24, 28, 28, 1, 128), (64, 14, 14, 2, 256), (64, 9, 64, 1, 60), (64, 32, 32, 2, 400),
                                             (32, 33, 30, 1, 90), (64, 40, 13, 2, 100)])
 def test_conv_tiles_of_other_heights_give_the_same_bits(C, H, W, few, many):
     # the height of a tile follows from the number of images: from one or two lines to the most that a workgroup
-    # multiplies.  A pixel's sums are the same ones in every tile, so an image's trajectory and adjoint are too
+    # multiplies, in one round of workgroups and in several.  A pixel's sums are the same ones in every tile, so an image's
+    # trajectory and adjoint are too
     cfg = wl.CONFIGS["cfg4"].with_(name=f"convheight{C}x{H}x{W}", B=many, N=1, C=C, H=H, W=W, tableau="heun", low="bf16", loss="half_sse")
     theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
     a = par.run_gpu(cfg, theta, y0, target)
