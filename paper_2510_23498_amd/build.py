@@ -44,13 +44,13 @@ def _compile(args):
 
 # headers each translation unit includes (directly or not), for the incremental mode
 _DEPS = {
-    "rampde.hip": ("common.hpp", "elementwise.hpp", "fused.hpp", "fused_launch.hpp", "cluster.hpp", "cluster_launch.hpp", "resident.hpp", "resident_launch.hpp", "shallow.hpp", "shallow_launch.hpp", "wide.hpp", "gemm.hpp", "wgrad_slab.hpp", "gemm_slab.hpp", "conv_wgrad_tr.hpp", "conv_pair.hpp", "conv_pair_launch.hpp", "norm.hpp",
+    "rampde.hip": ("common.hpp", "elementwise.hpp", "fused.hpp", "fused_launch.hpp", "cluster.hpp", "cluster_launch.hpp", "resident.hpp", "resident_launch.hpp", "shallow.hpp", "shallow_launch.hpp", "wide.hpp", "gemm.hpp", "wgrad_slab.hpp", "gemm_slab.hpp", "conv_wgrad_tr.hpp", "conv_pair.hpp", "conv_pass.hpp", "conv_pair_launch.hpp", "norm.hpp",
                    os.path.join("..", "..", "include", "rampde.h")),
     "fused_inst.hip": ("common.hpp", "fused.hpp", "fused_launch.hpp"),
     "resident_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "resident_launch.hpp"),
     "shallow_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "resident_launch.hpp", "shallow.hpp", "shallow_launch.hpp"),
     "cluster_inst.hip": ("common.hpp", "fused.hpp", "resident.hpp", "cluster.hpp", "cluster_launch.hpp"),
-    "conv_pair_inst.hip": ("common.hpp", "fused.hpp", "conv_pair.hpp", "conv_pair_launch.hpp"),
+    "conv_pair_inst.hip": ("common.hpp", "fused.hpp", "conv_pair.hpp", "conv_pass.hpp", "conv_pair_launch.hpp"),
     "wide_inst.hip": ("common.hpp", "fused.hpp", "fused_launch.hpp", "wide.hpp"),
 }
 

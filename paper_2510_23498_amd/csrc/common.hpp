@@ -97,6 +97,12 @@ struct Low<BF16> {
   }
 };
 
+// Host floats -> device memory by way of kernel arguments (copied at launch: no host buffer has
+// to outlive the call, and the write is an ordinary kernel node for a caller capturing a graph).
+struct FloatChunk {
+  float v[768];
+};
+
 // tanh of an fp32 pre-activation; the result is rounded to low precision by the caller.
 __device__ inline float act_tanh(float x) { return tanhf(x); }
 

@@ -52,7 +52,6 @@ inline size_t conv_pair_lds_bytes(int C32, int lines, int Wd) {
 }
 inline bool conv_pair_applies(int Cpad, int Wd) { return Cpad == 64 && Wd >= 1 && Wd <= 64; }
 typedef uint32_t u32x4p __attribute__((ext_vector_type(4)));
-constexpr int kPairLookahead = 3;  // contraction blocks of weights in flight
 
 template <class E>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t pair_window(const E* p, int elements) {
@@ -62,10 +61,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t pair_window(const E* p, int el
 // The contraction: acc[m][t] += weights of output channels 16 t .. x pixels of block m.  base: LDS element of the block's
 // pixel (this lane's) and channel chunk.  The first two lines of taps are one loop body: unrolled over all nine taps, a
 // launch fetched more instructions that it executes once.
-template <class T, int C32, int MT>
+// LA: contraction blocks of weights in flight.
+template <class T, int C32, int MT, int LA = 3>
 struct PairGemm {
   static constexpr int NCT = 2 * C32, U = 3 * C32, PITCH = conv_pair_pitch(C32), FR = U % 2 ? 3 : 2;
-  u16x8 w[kPairLookahead][NCT];
+  u16x8 w[LA][NCT];
   __amdgpu_buffer_rsrc_t frags;
   int at;  // bytes into the fragments
   __device__ __forceinline__ void load_w(int u, u16x8 (&dst)[NCT]) {
@@ -77,7 +77,33 @@ struct PairGemm {
     frags = pair_window(W, 64 * 576);
     at = 0;
 #pragma unroll
-    for (int i = 0; i < kPairLookahead; ++i) load_w(i, w[i]);
+    for (int i = 0; i < LA; ++i) load_w(i, w[i]);
+  }
+  // One line of taps.  The lines are multiplied in the order dy = 0, -1, 1, in which the weights lie.  b: LDS element of
+  // the blocks' pixels at the line's first tap; fb[0]: the pixels' first fragments.  AHEAD: those of the next line, `shift`
+  // elements on, are read too.  LAST: no weights follow.
+  template <bool AHEAD, bool LAST>
+  __device__ __forceinline__ void line(const uint16_t* in, int (&b)[MT], int shift, u16x8 (&fb)[FR][MT], f32x4 (&acc)[MT][NCT]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (AHEAD && u + 1 == U) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) b[m] += shift;
+      }
+      if (AHEAD || u + 1 < U) load_b(in, b, (u + 1) % U, fb[(u + 1) % FR]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int t = 0; t < NCT; ++t) acc[m][t] = Low<T>::mfma16(w[u % LA][t], fb[u % FR][m], acc[m][t]);
+      if (u + LA == U) at += 3 * 8 * 1024;
+      if (!LAST || u + LA < U) load_w((u + LA) % U, w[u % LA]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  __device__ __forceinline__ void load_b(const uint16_t* in, const int (&b)[MT], int u, u16x8 (&fb)[MT]) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m) fb[m] = *reinterpret_cast<const u16x8*>(&in[b[m] + u / C32 * PITCH + u % C32 * 32]);
   }
   // between: issues what the epilogue needs from memory, before the last line of taps (loads return in order: issued
   // earlier, the first weights behind them would wait for them)
@@ -85,36 +111,14 @@ struct PairGemm {
   __device__ __forceinline__ void run(const uint16_t* in, const int (&base)[MT], int LW, f32x4 (&acc)[MT][NCT], const Between& between) {
     int b[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) b[m] = base[m] - (LW + 1) * PITCH;
-    auto load_b = [&](int u, u16x8 (&fb)[MT]) __attribute__((always_inline)) {
-#pragma unroll
-      for (int m = 0; m < MT; ++m) fb[m] = *reinterpret_cast<const u16x8*>(&in[b[m] + u / C32 * PITCH + u % C32 * 32]);
-    };
+    for (int m = 0; m < MT; ++m) b[m] = base[m] - PITCH;
     u16x8 fb[FR][MT];
-    load_b(0, fb[0]);
-    auto line = [&](auto last) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (!last && u + 1 == U) {
-#pragma unroll
-          for (int m = 0; m < MT; ++m) b[m] += LW * PITCH;
-        }
-        if (!last || u + 1 < U) load_b((u + 1) % U, fb[(u + 1) % FR]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-          for (int t = 0; t < NCT; ++t) acc[m][t] = Low<T>::mfma16(w[u % kPairLookahead][t], fb[u % FR][m], acc[m][t]);
-        if (u + kPairLookahead == U) at += 3 * 8 * 1024;
-        if (!last || u + kPairLookahead < U) load_w((u + kPairLookahead) % U, w[u % kPairLookahead]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
+    load_b(in, b, 0, fb[0]);
 #pragma unroll 1
-    for (int dy = 0; dy < 2; ++dy) line(std::false_type{});
+    for (int i = 0; i < 2; ++i) line<true, false>(in, b, (3 * i - 1) * LW * PITCH, fb, acc);
     between();
     __builtin_amdgcn_sched_barrier(0);
-    line(std::true_type{});
+    line<false, true>(in, b, 0, fb, acc);
   }
 };
 
@@ -128,9 +132,10 @@ struct PairTime {
     for (int t = 0; t < NCT; ++t)
       w[t] = __builtin_bit_cast(u16x8, __builtin_amdgcn_raw_buffer_load_b128(win, ((threadIdx.x & 63) / 16 * 64 + t * 16 + (threadIdx.x & 15)) * 16, 0, 0));
   }
-  __device__ __forceinline__ void run(uint32_t tau, int y, int x, int H, int W, f32x4 (&acc)[NCT]) {
+  // edges: bits 0 to 3, the pixel is not in the image's first line, last line, first column, last column
+  __device__ __forceinline__ void run(uint32_t tau, unsigned edges, f32x4 (&acc)[NCT]) {
     constexpr uint32_t one = std::is_same<T, BF16>::value ? 0x3f80u : 0x3c00u;
-    const bool t = y > 0, b = y < H - 1, l = x > 0, r = x < W - 1;
+    const bool t = edges & 1, b = edges & 2, l = edges & 4, r = edges & 8;
     auto two = [&](bool lo, bool hi) __attribute__((always_inline)) { return (lo ? tau : 0u) | (hi ? tau << 16 : 0u); };
     uint4 q = make_uint4(two(t & l, t), two(t & r, l), two(true, r), two(b & l, b));
     if (threadIdx.x & 16) q.x = two(b & r, false) | one << 16;  // (lanes of contraction indices 8 to 15)
@@ -139,23 +144,25 @@ struct PairTime {
   }
 };
 
+// One tile.  With a control block nothing is done once a cotangent chain has been rejected.
 template <class T, int C32, int MT1, int MT2, bool VJP>
-__global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, ConvPairShape sh) {
+__device__ __forceinline__ void pair_tile(const ConvPair& g, const ConvPairShape& sh, int tile, uint16_t* sIn) {
   constexpr int NT = 256, NCT = 2 * C32, C8 = 4 * C32, PITCH = conv_pair_pitch(C32);
   constexpr int MAXC = ((64 * MT1 + 128) * C8 + NT - 1) / NT;  // staged chunks of a thread: at most 2 lines of 64 more than the hidden tile
   constexpr int MAXO = (64 * MT2 * C8 + NT - 1) / NT;          // ... of the tile's own lines
-  extern __shared__ __attribute__((aligned(16))) uint16_t cp_smem[];
-  const int W = g.Wd, H = g.H, PR = sh.lines, LW = W + 2;
-  uint16_t* sIn = cp_smem;                                               // [PR + 4][W + 2][PITCH]
+  const int W = g.Wd, H = g.H, PR = sh.lines, LW = W + 2;              // sIn: [PR + 4][W + 2][PITCH]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fl = lane & 15, fg = lane >> 4;
 
-  const int img = blockIdx.x / sh.per_image, y0 = (blockIdx.x - img * sh.per_image) * PR;
+  const int img = tile / sh.per_image, y0 = (tile - img * sh.per_image) * PR;
   const int rows = min(PR, H - y0);
   const int f0 = max(y0 - 2, 0), f1 = min(y0 + rows + 2, H);  // staged image lines
   const int h0 = max(y0 - 1, 0), h1 = min(y0 + rows + 1, H);  // lines of the first convolution
   const size_t line0 = (size_t)img * H;
   const int staged = (f1 - f0) * W, n1 = (h1 - h0) * W, n2 = rows * W;
+  auto edges_of = [&](int y, int x) __attribute__((always_inline)) {
+    return (unsigned)((y > 0) | (y < H - 1) << 1 | (x > 0) << 2 | (x < W - 1) << 3);
+  };
   auto line_of = [&](int p) __attribute__((always_inline)) { return (p * sh.magic) >> 16; };
   auto lds_at = [&](int p, int first) __attribute__((always_inline)) {  // pixel p of the lines from image line `first` on
     const int l = line_of(p);
@@ -209,7 +216,7 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
       const int p = (wave * MT1 + m) * 16 + fl, pc = p < n1 ? p : 0, l = line_of(pc);
       base[m] = lds_at(pc, h0) + fg * 8;
       if constexpr (!VJP) {
-        time.run(g.tau, h0 + l, pc - l * W, H, W, acc[m]);
+        time.run(g.tau, edges_of(h0 + l, pc - l * W), acc[m]);
       } else {
 #pragma unroll
         for (int t = 0; t < NCT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -273,7 +280,7 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
       const int p = (wave * MT2 + m) * 16 + fl, pc = p < n2 ? p : 0, l = line_of(pc);
       base[m] = lds_at(pc, y0) + fg * 8;
       if constexpr (!VJP) {
-        time.run(g.tau, y0 + l, pc - l * W, H, W, acc[m]);
+        time.run(g.tau, edges_of(y0 + l, pc - l * W), acc[m]);
       } else {
 #pragma unroll
         for (int t = 0; t < NCT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -371,6 +378,12 @@ __global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, C
     }
   }
   if (g.detect) raise_if_any((bad & kNonfiniteBits) != 0u, g.ctl);
+}
+
+template <class T, int C32, int MT1, int MT2, bool VJP>
+__global__ __launch_bounds__(256, MT1 <= 5 ? 2 : 1) void conv_pair(ConvPair g, ConvPairShape sh) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t cp_smem[];
+  pair_tile<T, C32, MT1, MT2, VJP>(g, sh, blockIdx.x, cp_smem);
 }
 
 }  // namespace rampde

@@ -14,39 +14,56 @@ namespace {
 
 constexpr int C32 = RAMPDE_INST_C32;
 
-template <class T, int MT1, int MT2>
-hipError_t launch_tiles(const ConvPair& g, const ConvPairShape& sh, bool vjp, hipStream_t st) {
-  const size_t lds = conv_pair_lds_bytes(C32, sh.lines, g.Wd);
-  auto kern = vjp ? &conv_pair<T, C32, MT1, MT2, true> : &conv_pair<T, C32, MT1, MT2, false>;
+template <class Kern, class... Args>
+hipError_t launch_kernel(Kern kern, size_t lds, const ConvLaunch& l, Args... args) {
   if (lds > 48 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  kern<<<sh.tiles, 256, lds, st>>>(g, sh);
+  kern<<<l.grid, 256, lds, l.st>>>(args...);
   return hipGetLastError();
 }
 
 template <class T, int I = 0>
-hipError_t pick(const ConvPair& g, const ConvPairShape& sh, bool vjp, hipStream_t st) {
+hipError_t pick_pair(const ConvPair& g, const ConvPairShape& sh, const ConvLaunch& l) {
   if constexpr (I < (int)(sizeof(kPairTiles) / sizeof(kPairTiles[0]))) {
-    if (sh.mt1 == kPairTiles[I][0] && sh.mt2 == kPairTiles[I][1])
-      return launch_tiles<T, kPairTiles[I][0], kPairTiles[I][1]>(g, sh, vjp, st);
-    return pick<T, I + 1>(g, sh, vjp, st);
+    constexpr int MT1 = kPairTiles[I][0], MT2 = kPairTiles[I][1];
+    if (sh.mt1 != MT1 || sh.mt2 != MT2) return pick_pair<T, I + 1>(g, sh, l);
+    return launch_kernel(l.vjp ? &conv_pair<T, C32, MT1, MT2, true> : &conv_pair<T, C32, MT1, MT2, false>,
+                         conv_pair_lds_bytes(C32, sh.lines, g.Wd), l, g, sh);
   } else {
     return hipErrorInvalidValue;
   }
 }
 
+template <class T, int MT = 1>
+hipError_t pick_pass(const ConvPass& g, const PassShape& sh, const ConvLaunch& l) {
+  if constexpr (MT <= kPassTiles) {
+    if (sh.mt != MT) return pick_pass<T, MT + 1>(g, sh, l);
+    return launch_kernel(l.kind == kPassForward ? &conv_pass_forward<T, C32, MT>
+                         : l.kind == kPassRecompute ? &conv_pass_recompute<T, C32, MT> : &conv_pass_chain<T, C32, MT>,
+                         pass_lds_bytes(C32, sh.lines, g.Wd), l, g, sh);
+  } else {
+    return hipErrorInvalidValue;
+  }
+}
+
+template <class T>
+hipError_t pick_redo(const ConvRedo& a, const ConvLaunch& l) {
+  return launch_kernel(l.backward ? &conv_redo_backward<T, C32> : &conv_redo_forward<T, C32>, conv_pair_lds_bytes(C32, a.sh.lines, a.g.Wd), l, a);
+}
+
 }  // namespace
 
 #if RAMPDE_INST_BF16
-hipError_t RAMPDE_CAT(RAMPDE_CAT(conv_pair_launch_, RAMPDE_INST_C32), _bf16)(const ConvPair& g, const ConvPairShape& sh, bool vjp, hipStream_t st) {
-  return pick<BF16>(g, sh, vjp, st);
-}
+#define RAMPDE_LOW BF16
+#define RAMPDE_NAME(f) RAMPDE_CAT(RAMPDE_CAT(f, RAMPDE_INST_C32), _bf16)
 #else
-hipError_t RAMPDE_CAT(RAMPDE_CAT(conv_pair_launch_, RAMPDE_INST_C32), _f16)(const ConvPair& g, const ConvPairShape& sh, bool vjp, hipStream_t st) {
-  return pick<F16>(g, sh, vjp, st);
-}
+#define RAMPDE_LOW F16
+#define RAMPDE_NAME(f) RAMPDE_CAT(RAMPDE_CAT(f, RAMPDE_INST_C32), _f16)
 #endif
+hipError_t RAMPDE_NAME(conv_pair_launch_)(const ConvPair& g, const ConvPairShape& sh, const ConvLaunch& l) { return pick_pair<RAMPDE_LOW>(g, sh, l); }
+hipError_t RAMPDE_NAME(conv_pass_launch_)(const ConvPass& g, const PassShape& sh, const ConvLaunch& l) { return pick_pass<RAMPDE_LOW>(g, sh, l); }
+hipError_t RAMPDE_NAME(conv_redo_launch_)(const ConvRedo& a, const ConvLaunch& l) { return pick_redo<RAMPDE_LOW>(a, l); }
 
 }  // namespace rampde

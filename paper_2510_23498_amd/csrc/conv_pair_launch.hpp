@@ -1,10 +1,10 @@
-// Launchers of conv_pair.hpp, one per number of channel blocks and precision, each in a translation unit of its own.
+// Launchers of conv_pair.hpp and conv_pass.hpp, one per number of channel blocks and precision, each in a translation unit of its own.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
-#include "conv_pair.hpp"
+#include "conv_pass.hpp"
 
 namespace rampde {
 
@@ -51,16 +51,69 @@ inline ConvPairShape conv_pair_shape(int C32, int H, int Wd, int64_t images, int
   return best;
 }
 
-#define RAMPDE_DECLARE_CONV_PAIR(c32)                                                                                          \
-  hipError_t conv_pair_launch_##c32##_f16(const ConvPair& g, const ConvPairShape& sh, bool vjp, hipStream_t st);               \
-  hipError_t conv_pair_launch_##c32##_bf16(const ConvPair& g, const ConvPairShape& sh, bool vjp, hipStream_t st);
-RAMPDE_DECLARE_CONV_PAIR(1)
-RAMPDE_DECLARE_CONV_PAIR(2)
-#undef RAMPDE_DECLARE_CONV_PAIR
+constexpr int kPassTiles = 4;  // blocks of 16 pixels per wavefront, at most
+// Tiles for the launches of conv_pass.hpp: all workgroups of a launch run at once, two on a compute unit.
+inline PassShape conv_pass_tiles(int C32, int lines, int H, int Wd, int64_t images, int cus) {
+  PassShape t{};
+  t.mt = (std::min(lines, H) * Wd + 63) / 64;
+  t.lines = lines;
+  t.per_image = (H + lines - 1) / lines;
+  t.magic = (65536 + Wd - 1) / Wd;
+  if (t.mt > kPassTiles || t.per_image > 2 * cus || pass_lds_bytes(C32, lines, Wd) > 79 * 1024) return PassShape{};
+  const int64_t most = 2 * cus / t.per_image, rounds = (images + most - 1) / most;
+  t.slots = (int)((images + rounds - 1) / rounds);
+  return t;
+}
+// The least estimated time of an evaluation, from (us, forward / recomputation; workgroups):
+// 64 channels, 128 x 32 x 32, tiles of 4 lines (2 rounds of 512) 36.9 / 36.8, of 6 (2 of 384) 40.4 / 35.5, of 8 (512)
+// 30.6 / 23.3; 64 x 16 x 16, 4 lines (256) 9.6 / 9.9, 8 (128) 10.5 / 10.6, 16 (64) 14.8 / 11.9; 32 channels, 20 x 28 x 28,
+// 2 lines (280) 6.8 / 8.3, 4 (140) 6.2 / 7.3, 7 (80) 7.5 / 8.5; 128 x 32 x 32, 4 lines (2 of 512) 15.6 / 15.5, 8 (512) 10.2 / 11.1.
+inline double conv_pass_cost(const PassShape& t, int C32, int64_t images, int cus) {
+  const double rounds = (double)((images + t.slots - 1) / t.slots), shared = t.slots * t.per_image > cus ? (C32 == 1 ? 1.35 : 1.75) : 1.0;
+  return rounds * shared * (C32 == 1 ? 5.3 + 0.6 * t.mt : 8.2 + 1.4 * t.mt);
+}
+inline PassShape conv_pass_shape(int C32, int H, int Wd, int64_t images, int cus) {
+  PassShape best{};
+  for (int lines = 1; lines <= std::min(H, 64 * kPassTiles / Wd); ++lines) {
+    const PassShape t = conv_pass_tiles(C32, lines, H, Wd, images, cus);
+    if (t.lines && (!best.lines || conv_pass_cost(t, C32, images, cus) < conv_pass_cost(best, C32, images, cus))) best = t;
+  }
+  return best;
+}
+
+enum ConvPassKind { kPassForward, kPassRecompute, kPassChain };
+struct ConvLaunch {
+  bool vjp;             // conv_pair
+  ConvPassKind kind;    // conv_pass
+  bool backward;        // conv_redo
+  unsigned grid;
+  hipStream_t st;
+};
+
+#define RAMPDE_DECLARE_CONV(c32, low)                                                                        \
+  hipError_t conv_pair_launch_##c32##_##low(const ConvPair& g, const ConvPairShape& sh, const ConvLaunch& l); \
+  hipError_t conv_pass_launch_##c32##_##low(const ConvPass& g, const PassShape& sh, const ConvLaunch& l);     \
+  hipError_t conv_redo_launch_##c32##_##low(const ConvRedo& g, const ConvLaunch& l);
+RAMPDE_DECLARE_CONV(1, f16)
+RAMPDE_DECLARE_CONV(1, bf16)
+RAMPDE_DECLARE_CONV(2, f16)
+RAMPDE_DECLARE_CONV(2, bf16)
+#undef RAMPDE_DECLARE_CONV
 
 inline hipError_t conv_pair_launch(int C32, bool bf16, const ConvPair& g, const ConvPairShape& sh, bool vjp, hipStream_t st) {
-  if (C32 == 1) return bf16 ? conv_pair_launch_1_bf16(g, sh, vjp, st) : conv_pair_launch_1_f16(g, sh, vjp, st);
-  return bf16 ? conv_pair_launch_2_bf16(g, sh, vjp, st) : conv_pair_launch_2_f16(g, sh, vjp, st);
+  const ConvLaunch l{vjp, kPassForward, false, (unsigned)sh.tiles, st};
+  if (C32 == 1) return bf16 ? conv_pair_launch_1_bf16(g, sh, l) : conv_pair_launch_1_f16(g, sh, l);
+  return bf16 ? conv_pair_launch_2_bf16(g, sh, l) : conv_pair_launch_2_f16(g, sh, l);
+}
+inline hipError_t conv_pass_launch(int C32, bool bf16, const ConvPass& g, const PassShape& sh, ConvPassKind kind, hipStream_t st) {
+  const ConvLaunch l{false, kind, false, (unsigned)(sh.slots * sh.per_image), st};
+  if (C32 == 1) return bf16 ? conv_pass_launch_1_bf16(g, sh, l) : conv_pass_launch_1_f16(g, sh, l);
+  return bf16 ? conv_pass_launch_2_bf16(g, sh, l) : conv_pass_launch_2_f16(g, sh, l);
+}
+inline hipError_t conv_redo_launch(int C32, bool bf16, const ConvRedo& g, bool backward, unsigned grid, hipStream_t st) {
+  const ConvLaunch l{false, kPassForward, backward, grid, st};
+  if (C32 == 1) return bf16 ? conv_redo_launch_1_bf16(g, l) : conv_redo_launch_1_f16(g, l);
+  return bf16 ? conv_redo_launch_2_bf16(g, l) : conv_redo_launch_2_f16(g, l);
 }
 
 }  // namespace rampde

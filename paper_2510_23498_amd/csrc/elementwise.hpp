@@ -40,7 +40,7 @@ __global__ void cast_dense_layer(const float* __restrict__ W, const float* __res
 //         the transposed convolution is a convolution with the flipped kernel)
 //   wt_f [9][Cpad] time-channel weights per tap, bias_f[Cpad].
 // frags (Cpad = 64): Wp and WTp in the order in which conv_pair.hpp multiplies them, a fragment of v_mfma_f32_16x16x32 (16
-// output channels, 32 inputs of a tap; lane l: output l % 16, inputs 8 (l / 16) ..) as 1 KB, [tap][input block][output block];
+// output channels, 32 inputs of a tap; lane l: output l % 16, inputs 8 (l / 16) ..) as 1 KB, [tap][input block][output block], taps of the middle line first;
 // WTp may be null.  And the time-channel weights and the bias likewise, as a block of their own: frags [2][64][8], element
 // (k / 8, output, k % 8), k = 0-8: tap, 9: bias.
 template <class T>
@@ -53,7 +53,11 @@ __global__ void cast_conv_layer(const float* __restrict__ W, const float* __rest
   uint16_t q = 0;
   if (co < C && ci < C) q = Low<T>::from_f32(W[((size_t)co * Cin + ci) * 9 + tap]);
   if (frags) {
-    auto at = [](int row, int t, int k) { return ((((t * 2 + k / 32) * 4 + row / 16) * 64 + row % 16 + 16 * (k % 32 / 8)) * 8) + k % 8; };
+    // (taps in the order of the lines 0, -1, 1 of the neighbourhood)
+    auto at = [](int row, int t, int k) {
+      t += t / 3 == 0 ? 3 : t / 3 == 1 ? -3 : 0;
+      return ((((t * 2 + k / 32) * 4 + row / 16) * 64 + row % 16 + 16 * (k % 32 / 8)) * 8) + k % 8;
+    };
     Wp[at(co, tap, ci)] = q;
     if (WTp) WTp[at(ci, 8 - tap, co)] = q;
   } else {

@@ -149,6 +149,10 @@ struct Plan {
   bool time_grid = false;           // a backward pass that forms dL/dt
   // the velocity of two convolutions with at most 64 channels: both in one launch (conv_pair.hpp)
   bool conv_pairs() const { return conv && !parabolic && conv_pair_applies(layers[0].Kpad, Wd); }
+  PassShape pass{};                 // conv_pass.hpp: its tiles (lines = 0: not those kernels)
+  int64_t images() const { return R / ((int64_t)H * Wd); }
+  int c32() const { return d <= 32 ? 1 : 2; }
+  size_t words = 0, word_bytes = 0; // its exchange
   bool lean = false;                // no choice of kernels for which the workspace alone is larger (see plan_within)
   std::vector<size_t> ACTT, DELTAT;
 };
@@ -279,6 +283,11 @@ static bool dense_stages(const rampde_tableau* tab) {  // some stage is built fr
     for (int j = 0; j + 1 < i; ++j)
       if (tab->A[i * tab->s + j] != 0.0) return true;
   return false;
+}
+static bool linked_stages(const rampde_tableau* tab) {  // every stage uses the slope of the one before it
+  for (int j = 1; j < tab->s; ++j)
+    if ((float)tab->A[j * tab->s + j - 1] == 0.f) return false;
+  return true;
 }
 static bool chained_stages(const rampde_tableau* tab) { return tab && tab->s >= 1 && tab->s <= kResidentStages && !dense_stages(tab); }
 static int resident_width(const rampde_velocity* vel, const rampde_tableau* tab, const rampde_policy* pol) {
@@ -563,7 +572,24 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       return make_plan(vel, B, N, tab, &pl, is_backward, allow_wide);
     }
   }
-  const int sbuf = is_backward ? p.s : 1;  // forward keeps one stage of inputs/activations
+  // Whole steps per launch (conv_pass.hpp): 16-byte rows, stages that are a chain, the state kept in 32 bits between the steps.
+  // Not for dL/dt, whose sums need the slopes.
+  if (p.conv_pairs() && allow_resident && allow_clusters && !small && !lean && !p.time_grid && p.d % 8 == 0 && chained_stages(tab) &&
+      tab->s <= kPassStages && linked_stages(tab) && !(pol && (pol->flags & (RAMPDE_NAIVE_STATE | RAMPDE_ROUND_INCREMENT))))
+    p.pass = conv_pass_shape(p.c32(), p.H, p.Wd, p.images(), device_compute_units());
+  int sbuf = is_backward ? p.s : 1;  // forward keeps one stage of inputs/activations
+  if (p.pass.lines) {
+    p.word_bytes = (size_t)p.pass.slots * p.pass.per_image * pass_words(p.c32(), p.Wd) * 8;
+    p.words = take(p.word_bytes);
+    p.steptab = take(sizeof(float) * (size_t)N * (1 + p.s));
+    if (is_backward) {
+      // buffer sets: the stages of as many steps as 128 MiB hold are recomputed in one launch, at most 32
+      p.a_alt = take(sizeof(float) * (size_t)p.n);
+      const int64_t fit = std::min<int64_t>(32, ((int64_t)128 << 20) / (4 * p.s * p.R * 64 * 2));
+      p.nsets = (int)std::max<int64_t>(1, std::min<int64_t>(fit, pol && pol->step_group > 0 ? std::min(N, pol->step_group) : N));
+      sbuf *= p.nsets;
+    }
+  }
   if (p.conv) {
     p.y_rows = take(sizeof(float) * (size_t)p.n);
     if (is_backward) {
@@ -739,9 +765,9 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       p.npart = take(sizeof(float) * 2 * (size_t)p.norm_chunks * Bn * y.Npad);
     }
     if (is_backward) {
-      p.KBAR = take((size_t)p.s * p.R * p.dpad * 2);
+      p.KBAR = take((size_t)sbuf * p.R * p.dpad * 2);
       p.ZBAR = take((size_t)p.s * p.R * p.dpad * 2);
-      for (int l = 0; l + 1 < p.L; ++l) p.DELTA.push_back(take((size_t)p.s * p.R * p.layers[l].Npad * 2));
+      for (int l = 0; l + 1 < p.L; ++l) p.DELTA.push_back(take((size_t)sbuf * p.R * p.layers[l].Npad * 2));
       if (p.parabolic)  // DELTA[0] = cotangent of n, DELTA[1] = cotangent of the pre-activation
         for (int q = 0; q < 2; ++q) p.DELTA.push_back(take((size_t)p.s * p.R * p.layers[0].Npad * 2));
       if (conv_wgrad_applies(p)) {
@@ -888,11 +914,6 @@ struct TimeScope {
   }
 };
 
-// Host floats -> device memory by way of kernel arguments (copied at launch: no host buffer has
-// to outlive the call, and the write is an ordinary kernel node for a caller capturing a graph).
-struct FloatChunk {
-  float v[768];
-};
 __global__ void write_floats(FloatChunk c, float* dst, int count) {
   for (int i = threadIdx.x; i < count; i += blockDim.x) dst[i] = c.v[i];
 }
@@ -1036,17 +1057,138 @@ struct Runner {
   // whether conv_pair also forms what the next evaluation reads: stages that are a chain, 16-byte rows.  (A slope
   // that the next stage does not use at all stays out of it, also where it is infinite: 0 times it would be NaN)
   bool conv_fuses_stages(const rampde_tableau* tab) const {
-    for (int j = 1; j < p.s; ++j)
-      if ((float)tab->A[j * p.s + j - 1] == 0.f) return false;
-    return p.conv_pairs() && vec8() && !dense_stages(tab);
+    return p.conv_pairs() && vec8() && !dense_stages(tab) && linked_stages(tab);
   }
   int launch_pair(ConvPair& g, bool vjp) {
-    const int C32 = p.d <= 32 ? 1 : 2;
+    const int C32 = p.c32();
     g.H = p.H;
     g.Wd = p.Wd;
     TimeScope ts(RAMPDE_K_VELOCITY_GEMM, (g.C ? 2 : 1) * 2.0 * p.R * 64.0 * 9 * 64, st);
-    const ConvPairShape sh = conv_pair_shape(C32, p.H, p.Wd, p.R / ((int64_t)p.H * p.Wd), device_compute_units());
+    const ConvPairShape sh = conv_pair_shape(C32, p.H, p.Wd, p.images(), device_compute_units());
     HIP_TRY(conv_pair_launch(C32, std::is_same<T, BF16>::value, g, sh, vjp, st));
+    return RAMPDE_OK;
+  }
+
+  // ---- whole steps per launch (conv_pass.hpp)
+  static constexpr bool kBf16 = std::is_same<T, BF16>::value;
+  uint32_t exchanges = 1;  // number of the next launch's first exchange
+  ConvPass conv_pass(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low, int* stalled) {
+    const std::vector<float> t = step_table(tgrid, N, tab, low);
+    for (size_t off = 0; off < t.size(); off += 768) {
+      FloatChunk c;
+      const int cnt = (int)std::min<size_t>(768, t.size() - off);
+      memcpy(c.v, t.data() + off, sizeof(float) * cnt);
+      if (off == 0) pass_reset<<<256, 256, 0, st>>>((uint4*)(ws + p.words), p.word_bytes / 16, stalled, c, f32(p.steptab), cnt);
+      else write_floats<<<1, 256, 0, st>>>(c, f32(p.steptab) + off, cnt);
+    }
+    const Layer &y0 = p.layers[0], &y1 = p.layers[1];
+    ConvPass g{};
+    g.W1 = u16(y0.Wp);
+    g.W2 = u16(y1.Wp);
+    g.T1 = u16(y0.tf);
+    g.T2 = u16(y1.tf);
+    g.steptab = f32(p.steptab);
+    g.words = (unsigned long long*)(ws + p.words);
+    g.ticks = wait_ticks ? kPassWaitTicks : 0;
+    g.stalled = &ctl->cluster_stalled;
+    g.H = p.H; g.Wd = p.Wd; g.d = p.d; g.s = p.s; g.images = (int)p.images();
+    g.n = step_elems;
+    g.stage_stride = p.stage_stride;
+    for (int j = 0; j < p.s; ++j) {
+      g.b[j] = (float)tab->b[j];
+      g.sub[j] = j + 1 < p.s ? (float)tab->A[(j + 1) * p.s + j] : 0.f;
+    }
+    g.Z = u16(p.Z);
+    return g;
+  }
+  // items: images, or images times steps, that the launch works on; convolutions of one of them; evaluations of the whole batch
+  int launch_pass(ConvPass& g, ConvPassKind kind, int64_t items, int convolutions, double evaluations) {
+    TimeScope ts(RAMPDE_K_VELOCITY_GEMM, evaluations * 4.0 * p.R * 64.0 * 9 * 64, st);
+    g.first = exchanges;
+    exchanges += (uint32_t)((items + p.pass.slots - 1) / p.pass.slots * convolutions);
+    HIP_TRY(conv_pass_launch(p.c32(), kBf16, g, p.pass, kind, st));
+    return RAMPDE_OK;
+  }
+  int launch_redo(const ConvPass& g, bool backward) {
+    ConvRedo a{};
+    a.g = g;
+    a.sh = conv_pair_tiles(p.c32(), 1, p.H, p.Wd, p.images());
+    a.K = u16(p.K);
+    if (backward) {
+      const Layer &y0 = p.layers[0], &y1 = p.layers[1];
+      a.g.W1 = u16(y0.Wp);
+      a.g.W2 = u16(y1.Wp);
+      a.V1 = u16(y1.WTp);
+      a.V2 = u16(y0.WTp);
+      a.ZBAR = u16(p.ZBAR);
+    } else {
+      a.Z2 = u16(p.ACT[0]);
+    }
+    HIP_TRY(conv_redo_launch(p.c32(), kBf16, a, backward, (unsigned)std::min<int64_t>(p.images(), device_compute_units()), st));
+    return RAMPDE_OK;
+  }
+  int forward_pass(const float* theta, const float* y0, const double* tgrid, int N, const rampde_tableau* tab, const rampde_policy* pol,
+                   uint16_t* ckpt, float* yN) {
+    test_aids(pol->flags);
+    cast_weights(theta);
+    ConvPass g = conv_pass(tgrid, N, tab, pol->low, &ctl->cluster_stalled);
+    g.N = N;
+    g.ckpt = ckpt;
+    g.y0 = y0;
+    g.y = f32(p.y_rows);
+    g.yN = yN;
+    // (a launch holds the device: pieces of about 3 ms, so that other streams' kernels get in between)
+    const int64_t rounds = (p.images() + p.pass.slots - 1) / p.pass.slots;
+    const int piece = (int)std::max<int64_t>(1, kPassEvaluations / (p.s * rounds));
+    for (g.step = 0; g.step < N; g.step += g.nsteps) {
+      g.nsteps = std::min(piece, N - g.step);
+      if (const int rc = launch_pass(g, kPassForward, p.images(), 2 * p.s * g.nsteps, (double)p.s * g.nsteps)) return rc;
+    }
+    return p.pass.per_image > 1 ? launch_redo(g, false) : RAMPDE_OK;
+  }
+  // the adjoint of the steps hi, hi - 1, ... hi - n + 1, from a to a_out; g as conv_pass leaves it
+  int backward_steps(ConvPass g, int hi, int n, const rampde_tableau* tab, const rampde_policy* pol, const uint16_t* ckpt, const double* tgrid,
+                     float* (&buf)[2], const float* gys, float* grad_theta, int dynamic, int detect) {
+    const Layer &y0 = p.layers[0], &y1 = p.layers[1];
+    g.ckpt = const_cast<uint16_t*>(ckpt);
+    g.ACT = u16(p.ACT[0]);
+    g.KBAR = u16(p.KBAR);
+    g.DELTA = u16(p.DELTA[0]);
+    g.gys = gys;
+    g.amax = (unsigned*)(ws + p.amax_slots);
+    g.ctl = ctl;
+    g.detect = detect;
+    g.step = hi;
+    g.nsteps = n;
+    if (const int rc = launch_pass(g, kPassRecompute, p.images() * n, 2 * p.s, p.s * n)) return rc;
+    g.W1 = u16(y1.WTp);
+    g.W2 = u16(y0.WTp);
+    const int per_launch = detect ? 1 : n;
+    for (int q = 0; q < n; q += per_launch) {
+      g.step = hi - q;
+      g.set0 = q;
+      g.nsteps = per_launch;
+      g.a_in = buf[0];
+      g.a_out = buf[1];
+      if (const int rc = launch_pass(g, kPassChain, p.images(), 2 * p.s * per_launch, p.s * per_launch)) return rc;
+      std::swap(buf[0], buf[1]);
+      if (detect)
+        pass_decide<<<1, 256, 0, st>>>(ctl, f32(p.scale_hist), g.step, Low<T>::p_bits, dynamic, (pol->flags & RAMPDE_GROW_RAW_NORM) ? 1 : 0,
+                                       g.amax, p.pass.slots * p.pass.per_image);
+      else if (p.pass.per_image > 1) {
+        if (const int rc = launch_redo(g, true)) return rc;
+      }
+      for (int r = q; r < q + per_launch; ++r) {
+        const int i = hi - r;
+        const float h = (float)(tgrid[i + 1] - tgrid[i]);
+        Coefs taus{}, cs{};
+        for (int j = 0; j < p.s; ++j) {
+          taus.v[j] = round_low_host((float)(tgrid[i] + tab->c[j] * (double)h), pol->low);
+          cs.v[j] = (float)tab->c[j];
+        }
+        param_grads(h, taus, grad_theta, cs, nullptr, r);
+      }
+    }
     return RAMPDE_OK;
   }
 
@@ -1618,6 +1760,7 @@ struct Runner {
   int forward(const float* theta, const float* y0, const double* tgrid, int N, const rampde_tableau* tab,
               const rampde_policy* pol, uint16_t* ckpt, float* yN) {
     if (use_fused) return forward_fused(theta, y0, tgrid, N, tab, pol, ckpt, yN);
+    if (p.pass.lines) return forward_pass(theta, y0, tgrid, N, tab, pol, ckpt, yN);
     if (p.conv) HIP_TRY(allow_conv_lds());
     cast_weights(theta);
     const int naive = (pol->flags & RAMPDE_NAIVE_STATE) ? 1 : 0;
@@ -1784,7 +1927,8 @@ struct Runner {
 
   // parameter gradient of one accepted step: contraction over all stages and rows at once,
   // scaled by h / S_step and accumulated in fp32 (paper Sec. 3, update of g)
-  void param_grads(float h, const Coefs& taus, float* grad_theta, const Coefs& cs, float* tpart_i) {
+  // (set: the buffer set that holds the step's stages)
+  void param_grads(float h, const Coefs& taus, float* grad_theta, const Coefs& cs, float* tpart_i, int set = 0) {
     // (grad_theta: the gradient of the parameters this step used -- the step's piece when they are piecewise constant)
     const int s = p.s;
     const int64_t rows = (int64_t)s * p.R;
@@ -1795,9 +1939,9 @@ struct Runner {
     for (int l = 0; l < passes; ++l) {
       const Layer& y = p.layers[p.parabolic ? 0 : l];
       GemmTN g{};
-      g.A = (l == p.L - 1) ? u16(p.KBAR) : u16(p.DELTA[l]);
+      g.A = ((l == p.L - 1) ? u16(p.KBAR) : u16(p.DELTA[l])) + (size_t)set * s * p.R * y.Npad;
       g.lda = y.Npad;
-      g.B = (l == 0) ? u16(p.Z) : u16(p.ACT[l - 1]);
+      g.B = ((l == 0) ? u16(p.Z) : u16(p.ACT[l - 1])) + (size_t)set * s * p.R * y.Kpad;
       g.ldb = y.Kpad;
       if (p.parabolic) {
         g.A = l == 0 ? u16(p.DELTA[1]) : u16(p.ACT[1]);
@@ -2128,8 +2272,21 @@ struct Runner {
       to_rows(src, gys_rows);
       return gys_rows;
     };
+    // (whole steps per launch: step i reads buffer (i + 1) % 2 under overflow detection; without it the launches alternate)
+    float* pass_buf[2] = {f32(p.a_rows), f32(p.a_alt)};
+    auto pass_start = [&](int next) {  // the adjoint behind step `next` is in its buffer
+      float* even = f32(p.a_rows);
+      float* odd = f32(p.a_alt);
+      pass_buf[0] = next % 2 == 0 ? odd : even;
+      pass_buf[1] = next % 2 == 0 ? even : odd;
+    };
+    ConvPass pass{};
+    if (p.pass.lines) {
+      pass = conv_pass(tgrid, N, tab, pol->low, nullptr);
+      pass_start(N - 1);
+    }
     if (p.conv) {
-      a = f32(p.a_rows);
+      a = p.pass.lines ? pass_buf[0] : f32(p.a_rows);
       gys_rows = f32(p.gys_rows);
       to_rows(grad_yN, a);
       init_adjoint<<<stream_blocks(p.n, 512), 256, 0, st>>>(a, gys_at(N), a, p.n, ctl, 0, naive_low, f32(p.scale_hist), N,
@@ -2220,8 +2377,17 @@ struct Runner {
           hi -= n;
         }
       }
+      if (p.pass.lines) {
+        pass_start(from);
+        for (int hi = from; hi >= 0;) {
+          const int n = std::min(grad_ys ? 1 : p.nsets, hi + 1);
+          if (const int rc = backward_steps(pass, hi, n, tab, pol, ckpt, tgrid, pass_buf, gys_at(hi), grad_theta, dynamic, detect)) return rc;
+          hi -= n;
+        }
+        a = pass_buf[0];
+      }
       int pending_hi = -1, pending_n = 0;  // steps whose parameter gradients wait for their group's launch
-      for (int i = (p.resident || p.cluster || (use_fused && p.step_group > 1)) ? -1 : from; i >= 0; --i) {
+      for (int i = (p.resident || p.cluster || p.pass.lines || (use_fused && p.step_group > 1)) ? -1 : from; i >= 0; --i) {
         if (use_fused) {
           // this set was last read by the parameter-gradient kernel of step i + 2
           if (p.overlap_wgrad && i + 2 <= N - 1) HIP_TRY(hipStreamWaitEvent(st, side.wgrad_done(i + 2), 0));
@@ -2404,7 +2570,7 @@ size_t rampde_workspace_bytes(const rampde_velocity* vel, int64_t B, int N, cons
   Plan p = make_plan(vel, B, N, tab, pol, is_backward);
   if (!p.ok) return 0;
   size_t total = p.total;
-  if (is_backward && (p.wide || p.resident || p.cluster)) {
+  if (is_backward && (p.wide || p.resident || p.cluster || p.pass.lines)) {
     // the backward pass with the time-grid gradient (neither wide nor shallow) or redone step by step (not resident, no clusters)
     // uses the other row-tile kernels: room for any of them
     for (const bool wide : {false, true})

@@ -257,6 +257,41 @@ def test_conv_tiles_of_other_heights_give_the_same_bits(C, H, W, few, many):
     np.testing.assert_array_equal(a["grad_y0"][-few:], b["grad_y0"])
 
 
+@pytest.mark.parametrize("C,H,W,B,N,low,tab,group", [(64, 24, 32, 2, 3, "bf16", "rk4", 2), (16, 13, 12, 3, 5, "f16", "heun", 0),
+                                                     (40, 9, 17, 2, 4, "bf16", "euler", 3), (8, 7, 64, 1, 3, "f16", "rk4", 1),
+                                                     (64, 5, 5, 2, 7, "bf16", "heun", 0)])
+def test_conv_steps_in_one_launch(C, H, W, B, N, low, tab, group):
+    # tiles that exchange lines (whole and cut short) and images of one tile; groups of steps that do not divide N, a group of
+    # one; unequal steps; the running cost's cotangents, which go step by step
+    cfg = wl.CONFIGS["cfg4"].with_(name=f"convsteps{C}x{H}x{W}", B=B, N=N, C=C, H=H, W=W, tableau=tab, low=low)
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    tgrid = _nonuniform_grid(N, seed=6)
+    tol = 2e-3 if low == "bf16" else par.TOL_EMUL  # (bf16: see test_conv_weight_gradient_64_channels_transposing_reads_bf16)
+    for gys in (None, wl.normals(7, "convsteps.gys", (N + 1,) + tuple(cfg.state_shape), 0.1)):
+        gpu = par.run_gpu(cfg, theta, y0, target, tgrid=tgrid, step_group=group, grad_ys=gys)
+        emu = par.run_oracle(cfg, theta, y0, target, "emul", tgrid=tgrid, grad_ys=None if gys is None else gys.astype(np.float64))
+        par.compare(cfg, gpu, emu, tol, "emulation oracle", tol_max=par.TOL_EMUL_MAX[low])
+        np.testing.assert_array_equal(gpu["scale_hist"].astype(np.float64), emu["scale_hist"])
+
+
+@pytest.mark.parametrize("low,scaling", [("bf16", "none"), ("f16", "dynamic")])
+def test_conv_launches_that_are_given_up(low, scaling):
+    # no workgroup waits for its neighbours: the launches behind do the work again, under overflow detection the host does.
+    # The same sums in the same order; in bf16 that gives the same bits.  (In f16 the compiler may round a fused
+    # multiply-add to 16 bits directly in one kernel and by way of 32 bits in the other: a flipped rounding here and there,
+    # 2^-11 of a value, as between the library and the oracle.)
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name="convredo", B=3, N=3, C=40, H=19, W=20, tableau="rk4", low=low)
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    a = par.run_gpu(cfg, theta, y0, target, scaling=scaling)
+    b = par.run_gpu(cfg, theta, y0, target, scaling=scaling, flags=rb.NO_WAITS)
+    np.testing.assert_array_equal(a["scale_hist"], b["scale_hist"])
+    for k in ("yN", "ckpt", "grad_y0", "grad_theta"):
+        if low == "bf16":
+            np.testing.assert_array_equal(a[k], b[k])
+        assert par.rel_err(b[k], a[k]) <= par.TOL_EMUL
+
+
 def test_conv_small_odd_geometry():
     cfg = wl.CONFIGS["cfg4"].with_(name="convodd", B=2, N=2, C=5, H=7, W=6, tableau="kutta3")
     _both(cfg, bias_std=0.1)
