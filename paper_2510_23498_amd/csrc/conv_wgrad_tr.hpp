@@ -409,7 +409,11 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
   const int wm = wave >> 1, wn = wave & 1;
   const int64_t total_lines = g.rows / Wr;
   const int lines_per_split = g.rows_per_split / Wr;
-  const int64_t c0 = (int64_t)split * lines_per_split;
+  const int group = g.steptab ? split / g.per_step : 0;        // step of a group
+  const float* times = g.steptab ? g.steptab + (size_t)(g.step - group) * (1 + g.s) : nullptr;
+  const uint16_t* gA = g.A + (size_t)group * g.rows * g.lda;
+  const uint16_t* gB = g.B + (size_t)group * g.rows * g.ldb;
+  const int64_t c0 = (int64_t)(split - group * g.per_step) * lines_per_split;
   int64_t c1 = c0 + lines_per_split;
   if (c1 > total_lines) c1 = total_lines;
   if (c0 >= c1) return;
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
     const int prow = op ? ld_px[i] + 1 : ld_px[i];                    // LDS row of the lane's pixel
     const int piece = sp ^ (((prow >> 1) & 1) << 2);
     const bool off = ld_px[i] >= Wr;
-    ld_src[i] = (off ? kZeroPage : op ? g.B : g.A) + piece * 8;
+    ld_src[i] = (off ? kZeroPage : op ? gB : gA) + piece * 8;
     ld_ldx[i] = off ? 0 : op ? g.ldb : g.lda;
     ld_linelen[i] = ld_ldx[i] * Wr;
     ld_dst[i] = (op ? GB + 128 : 0) + (8 * (u & 7) % W) * 128;        // (+ the line's slot)
@@ -532,6 +536,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
       tau = (q == cur_stage) ? g.taus[q] : tau;
       cj = (q == cur_stage) ? g.cs[q] : cj;
     }
+    if (times) tau = times[1 + cur_stage];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       s_tau[q] = fmaf(tau, am[q], s_tau[q]);
@@ -668,7 +673,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the requests past the chunk's end
 
-  const float scale = g.h / g.ctl->S_step;
+  const float scale = (times ? times[0] : g.h) / g.ctl->S_step;
   float* slotf = g.part + (size_t)split * CW_SLOT;
   if (g.want_sums) {
     float p0 = 0.f, p1 = 0.f;

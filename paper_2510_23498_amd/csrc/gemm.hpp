@@ -385,6 +385,9 @@ struct ConvWgrad {
   //   tpart[0] += scale * sum_j (1 - c_j) taubar_j,   tpart[1] += scale * sum_j c_j taubar_j
   const float* wt; int ldwt;    // rounded time-channel weights [9][ldwt], or null
   float* tpart;                 // or null: the launch's table of per-workgroup slots (fold_time_slots)
+  // conv_wgrad_tr64 under a fixed scale: a group of steps, `per_step` K-chunks each; step `step` - q is rows q * rows and on.
+  // steptab: [N][1 + stages] step sizes and stage times, or null: one step
+  const float* steptab; int step, per_step, s;
   float cs[kMaxStages];         // c_j
 };
 
@@ -698,32 +701,52 @@ __global__ __launch_bounds__(256) void conv_wgrad(ConvWgrad g) {
 
 // dW[co][ci][tap], db[co] and dwt[co][tap] += sum over K-chunks of the private accumulators (end of the
 // backward pass).  gb / gwt null: no bias / no time channel; element (co, tap) of dwt at co * wt_stride + tap.
-__global__ void conv_wgrad_reduce(float* __restrict__ G, int ldg, const float* __restrict__ part, int splits,
-                                  int tiles_a, int tiles_b, int Na, int Nb, float* __restrict__ gb,
-                                  float* __restrict__ gwt, int wt_stride, const Ctl* ctl) {
+// The copies are read as they lie, 16 bytes per lane, the K-chunks dealt out to four wavefronts whose sums are added in
+// order (a thread per gradient element and all chunks one after the other, in the gradient's order: 64 channels, 256
+// chunks 70 us, 24 channels, 70 chunks 20 us).  Grid: kReduceBlocks x channel blocks.
+constexpr int kReduceBlocks = CW_SLOT / 4 / 64;
+__global__ __launch_bounds__(256) void conv_wgrad_reduce(float* __restrict__ G, int ldg, const float* __restrict__ part, int splits,
+                                                         int tiles_a, int tiles_b, int Na, int Nb, float* __restrict__ gb,
+                                                         float* __restrict__ gwt, int wt_stride, const Ctl* ctl) {
   if (ctl->poison) return;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nW = (int64_t)Na * Nb * 9;
-  if (i >= nW + (int64_t)Na * 10) return;
-  if (i >= nW) {
-    const int na = (int)((i - nW) / 10), e = (int)((i - nW) % 10);
-    float* dst = e == 0 ? (gb ? gb + na : nullptr) : (gwt ? gwt + (size_t)na * wt_stride + (e - 1) : nullptr);
-    if (!dst) return;
-    const size_t off = (size_t)(na >> 6) * tiles_b * CW_SLOT + 9 * 4096 + (na & 63) * 16 + e;
-    float acc = 0.f;
-    for (int c = 0; c < splits; ++c) acc += part[(size_t)c * tiles_a * tiles_b * CW_SLOT + off];
-    *dst += acc;
-    return;
-  }
-  const int nb = (int)(i % Nb), t = (int)((i / Nb) % 9), na = (int)(i / ((int64_t)Nb * 9));
+  __shared__ float4 sums[3][64];
+  const int tile = blockIdx.x / kReduceBlocks, pos = (blockIdx.x % kReduceBlocks) * 64 + (threadIdx.x & 63), wave = threadIdx.x >> 6;
+  const int tiles = tiles_a * tiles_b;
   // (position of element (tap, co, ci) in a workgroup's copy: see the epilogue of conv_wgrad)
-  const int r = na & 31, c = nb & 31;
-  const int thread = (((na >> 5) & 1) * 2 + ((nb >> 5) & 1)) * 64 + ((r >> 2) & 1) * 32 + c;
-  const size_t in_tile = ((size_t)(t * 4 + (r >> 3)) * 256 + thread) * 4 + (r & 3);
-  const size_t tile = (size_t)(na >> 6) * tiles_b + (nb >> 6);
-  float acc = 0.f;
-  for (int c2 = 0; c2 < splits; ++c2) acc += part[((size_t)c2 * tiles_a * tiles_b + tile) * CW_SLOT + in_tile];
-  G[(size_t)na * ldg + (size_t)nb * 9 + t] += acc;
+  const int t4 = pos >> 8, thread = pos & 255, lane = thread & 63;
+  const int na = (tile / tiles_b) * 64 + (thread >> 7) * 32 + (t4 & 3) * 8 + (lane >> 5) * 4;
+  const int nb = (tile % tiles_b) * 64 + ((thread >> 6) & 1) * 32 + (lane & 31);
+  const bool tail = pos >= 9 * 1024;
+  const int sn = (tile / tiles_b) * 64 + ((pos - 9 * 1024) >> 2), se = ((pos - 9 * 1024) & 3) * 4;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (tail ? tile % tiles_b == 0 && sn < Na && se < 10 : na < Na && nb < Nb) {
+    const float4* src = reinterpret_cast<const float4*>(part) + (size_t)tile * (CW_SLOT / 4) + pos;
+#pragma unroll 8
+    for (int c = wave; c < splits; c += 4) {
+      const float4 v = src[(size_t)c * tiles * (CW_SLOT / 4)];
+      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    }
+  }
+  if (wave) sums[wave - 1][threadIdx.x & 63] = acc;
+  __syncthreads();
+  if (wave) return;
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    const float4 v = sums[w][threadIdx.x];
+    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  }
+  const float a[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (tail) {
+      const int e = se + r;
+      if (tile % tiles_b != 0 || sn >= Na || e >= 10) continue;
+      float* dst = e == 0 ? (gb ? gb + sn : nullptr) : (gwt ? gwt + (size_t)sn * wt_stride + (e - 1) : nullptr);
+      if (dst) *dst += a[r];
+    } else if (na + r < Na && nb < Nb) {
+      G[(size_t)(na + r) * ldg + (size_t)nb * 9 + (t4 >> 2)] += a[r];
+    }
+  }
 }
 
 // The MFMAs of one k-step of 64 on a wavefront's 64 x 64 output block: operand fragments of k-block

@@ -79,6 +79,7 @@ struct Layer {
   int ldw;  // K extent of the forward GEMM (dense: Kpad; conv: 9 * Cpad)
   // all-taps convolution weight gradient: K-chunk length, chunk count, the chunks' private copies
   int cw_per = 0, cw_splits = 0;
+  int cw_step = 0;       // chunks of a step where a launch takes a group of steps, 0: one step per launch
   size_t cw_part = 0;
   size_t cw_floats = 0;  // fp32 elements of all the copies
 };
@@ -794,12 +795,19 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
         } else
         for (auto& y : p.layers) {
           const int tiles = (y.Npad / 64) * (y.Kpad / 64);
-          const int64_t want = std::max<int64_t>(1, device_compute_units() / tiles);
+          // (the launch of conv_wgrad_tr64 that takes both convolutions has the compute units once, not once per layer: 64
+          // channels, 128 images of 32 x 32, us per launch with 256 / 128 chunks per layer 143 / 123)
+          const bool pair = !p.parabolic && conv_wgrad_tr64_applies(p, y);
+          const int cus = device_compute_units() / (pair ? 2 : 1);
+          // (under a fixed scale the steps of a buffer set's group are one launch)
+          const int group = pair && p.pass.lines && pol && resolve_scaling(pol) == RAMPDE_SCALE_NONE ? p.nsets : 1;
+          const int64_t want = std::max<int64_t>(1, cus / tiles / group);
           const int64_t unit = conv_wgrad_tr64_applies(p, y) ? (int64_t)2 * tr64_step_lines(p.Wd) * p.Wd : CW_KS;
           int64_t per = ((rows + want - 1) / want + unit - 1) / unit * unit;
           if (per < 4 * unit) per = 4 * unit;
           y.cw_per = (int)per;
-          y.cw_splits = (int)((rows + per - 1) / per);
+          y.cw_splits = (int)((rows + per - 1) / per) * group;
+          y.cw_step = group > 1 ? y.cw_splits / group : 0;
           y.cw_floats = (size_t)y.cw_splits * tiles * CW_SLOT;
           y.cw_part = take(sizeof(float) * y.cw_floats);
         }
@@ -1177,6 +1185,10 @@ struct Runner {
                                        g.amax, p.pass.slots * p.pass.per_image);
       else if (p.pass.per_image > 1) {
         if (const int rc = launch_redo(g, true)) return rc;
+      }
+      if (y0.cw_step && !detect) {
+        param_grads(0.f, Coefs{}, grad_theta, Coefs{}, nullptr, 0, n, hi);
+        continue;
       }
       for (int r = q; r < q + per_launch; ++r) {
         const int i = hi - r;
@@ -1927,8 +1939,8 @@ struct Runner {
 
   // parameter gradient of one accepted step: contraction over all stages and rows at once,
   // scaled by h / S_step and accumulated in fp32 (paper Sec. 3, update of g)
-  // (set: the buffer set that holds the step's stages)
-  void param_grads(float h, const Coefs& taus, float* grad_theta, const Coefs& cs, float* tpart_i, int set = 0) {
+  // (set: the buffer set that holds the step's stages; group: the steps first, first - 1, ... of the sets from 0 on instead)
+  void param_grads(float h, const Coefs& taus, float* grad_theta, const Coefs& cs, float* tpart_i, int set = 0, int group = 0, int first = 0) {
     // (grad_theta: the gradient of the parameters this step used -- the step's piece when they are piecewise constant)
     const int s = p.s;
     const int64_t rows = (int64_t)s * p.R;
@@ -1984,19 +1996,25 @@ struct Runner {
         c.wt = y.has_time ? f32(y.wt_f) : nullptr;
         c.ldwt = y.Npad;
         c.tpart = tpart_i ? f32(p.tslots) : nullptr;
-        dim3 cgrid(y.Npad / 64, y.Kpad / 64, y.cw_splits);
+        dim3 cgrid(y.Npad / 64, y.Kpad / 64, group ? group * y.cw_step : y.cw_splits);
+        if (group) {
+          c.steptab = f32(p.steptab);
+          c.step = first;
+          c.per_step = y.cw_step;
+          c.s = s;
+        }
         // 64 x 64 channels: both convolutions of the velocity in one launch (the parabolic block's two terms share their
         // private copies: one after the other)
         const bool pair = !p.parabolic && conv_wgrad_tr64_applies(p, y);
         if (pair) {
           both.layer[l] = c;
           if (l == 0) {
-            both.splits0 = y.cw_splits;
+            both.splits0 = cgrid.z;
             continue;
           }
           cgrid.z += both.splits0;
         }
-        TimeScope ts(RAMPDE_K_WGRAD_GEMM, (pair ? 2 : 1) * 2.0 * rows * (double)y.Npad * y.Kpad * 9, st);
+        TimeScope ts(RAMPDE_K_WGRAD_GEMM, (group ? group : 1) * (pair ? 2 : 1) * 2.0 * rows * (double)y.Npad * y.Kpad * 9, st);
         const bool tsum = c.tpart && c.wt;
         if (conv_wgrad_tr64_applies(p, y)) {
           // the kernel built on transposing LDS reads (same private copies)
@@ -2215,7 +2233,7 @@ struct Runner {
         conv_wgrad_tr_reduce<<<blocks_for(n, 256), 256, 0, st>>>(gq + y.theta_w, y.in_full * 9, f32(y.cw_part), y.cw_splits,
                                                                  y.Npad / 128, y.Kpad / 128, y.out, y.in, gq + y.theta_b, ctl);
       else
-        conv_wgrad_reduce<<<blocks_for(n, 256), 256, 0, st>>>(gq + y.theta_w, y.in_full * 9, f32(y.cw_part), y.cw_splits,
+        conv_wgrad_reduce<<<kReduceBlocks * (y.Npad / 64) * (y.Kpad / 64), 256, 0, st>>>(gq + y.theta_w, y.in_full * 9, f32(y.cw_part), y.cw_splits,
                                                               y.Npad / 64, y.Kpad / 64, y.out, y.in, gq + y.theta_b, nullptr,
                                                               y.in_full * 9, ctl);
       fill_zero_unless_poisoned<<<1024, 256, 0, st>>>((uint32_t*)(ws + y.cw_part), y.cw_floats, ctl);
@@ -2456,8 +2474,7 @@ struct Runner {
         piece = -1;  // (a retry starts by rounding the weights of its piece again)
       } else if (conv_wgrad_applies(p))
         for (auto& y : p.layers) {
-          const int64_t n = (int64_t)y.out * y.in * 9 + (int64_t)y.out * 10;
-          conv_wgrad_reduce<<<blocks_for(n, 256), 256, 0, st>>>(
+          conv_wgrad_reduce<<<kReduceBlocks * (y.Npad / 64) * (y.Kpad / 64), 256, 0, st>>>(
               grad_theta + y.theta_w, y.in_full * 9, f32(y.cw_part), y.cw_splits, y.Npad / 64, y.Kpad / 64, y.out, y.in,
               grad_theta + y.theta_b, y.has_time ? grad_theta + y.theta_w + (size_t)y.in * 9 : nullptr, y.in_full * 9, ctl);
         }
