@@ -1643,7 +1643,10 @@ struct Runner {
     l.kind = kind;
     l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
     l.MT = p.MT;
-    l.grid = blocks_for(p.R, 16 * p.MT);
+    l.copies = 1;
+    if (kind == kResidentForward && p.MT == 1 && p.resident >= 128)  // (as long as those tiles have a compute unit each)
+      while (l.copies < 4 && p.R * 2 * l.copies <= 16 * (int64_t)device_compute_units()) l.copies *= 2;
+    l.grid = blocks_for(p.R, 16 * p.MT / l.copies);
     if (kind == kResidentRecompute) {
       const int64_t cus = device_compute_units();
       if (p.resident == 256 && (int64_t)blocks_for(p.R, 16) * a.nsteps > 2 * cus) l.MT = 2;

@@ -293,20 +293,23 @@ __device__ __forceinline__ void zero_acc(f32x4 (&acc)[NT][MT]) {
 }
 
 // ---------------------------------------------------------------------------------------
-// FEW: at most four rows (inference on a handful of samples).  The tile's 16 rows are then four copies of them, and copy c
-// of a row finishes column tile c of its wavefront: a quarter of the tanh arithmetic per lane.  One row, 64 -> 256 -> 256
-// -> 64, f16, 32 RK4 steps: 203 -> 174 us per pass.
-template <class T, int L, int HP, int MT, bool FEW>
+// COPIES = 2, 4: tiles of 8 or 4 rows, where the 16-row tiles leave half or three quarters of the compute units idle.  The
+// tile's 16 rows are then so many copies of them, and a copy of a row finishes its share of the wavefront's column tiles:
+// half or a quarter of the tanh arithmetic per lane.  One row, 64 -> 256 -> 256 -> 64, f16, 32 RK4 steps: 203 -> 174 us per
+// pass; 300 rows, one hidden layer, bf16 129 -> 111; 1024 rows, 64 -> 3 x 200 -> 64 271 -> 230; 2048 rows (two copies), two
+// of 256 200 -> 182.
+template <class T, int L, int HP, int MT, int COPIES>
 __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_forward_resident(ResidentArgs ra) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   using Sh = ResidentShape<L, HP>;
   const FusedArgs& g = ra.f;
   ResidentLds<L, HP> lds((lds_u16*)smem, MT);
-  static_assert(!FEW || MT == 1, "one tile");
-  const int lane0 = threadIdx.x & 63, wave = threadIdx.x >> 6, copy = FEW ? (lane0 >> 2) & 3 : 0;
-  const int lane = FEW ? lane0 & 0x33 : lane0, lm = lane & 15, lq = lane >> 4;  // (of the copied row)
+  static_assert(COPIES == 1 || MT == 1, "one tile");
+  constexpr int ROWS = 16 / COPIES;               // of a tile of 16
+  const int lane0 = threadIdx.x & 63, wave = threadIdx.x >> 6, copy = (lane0 & 15) / ROWS;
+  const int lane = (lane0 & 0x30) | lane0 % ROWS, lm = lane & 15, lq = lane >> 4;  // (of the copied row)
   constexpr int TPW = Sh::TPW;
-  const int64_t row0 = (int64_t)blockIdx.x * 16 * MT;
+  const int64_t row0 = (int64_t)blockIdx.x * ROWS * MT;
   const int64_t n_state = g.R * g.d;
   const int s = g.s;
   const int ns = wave * 16 + lq * 4;              // the lane's state columns
@@ -332,17 +335,21 @@ __global__ __launch_bounds__(256, HP == 256 ? 1 : 2) void mlp_forward_resident(R
   __syncthreads();
 
   auto store_tanh = [&](const f32x4 (&acc)[TPW][MT], lds_u16* out) __attribute__((always_inline)) {
-    if constexpr (FEW) {
-      const int t = copy % TPW;
-      float v[4];
+    if constexpr (COPIES > 1) {
+      constexpr int C = COPIES < TPW ? COPIES : TPW;  // (fewer column tiles than copies: two finish the same one)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float x = acc[0][0][r];
+      for (int u = 0; u < TPW / C; ++u) {
+        const int t = copy % C;
+        float v[4];
 #pragma unroll
-        for (int q = 1; q < TPW; ++q) x = t == q ? acc[q][0][r] : x;
-        v[r] = tanh_fast(x);
+        for (int r = 0; r < 4; ++r) {
+          float x = acc[u * C][0][r];
+#pragma unroll
+          for (int q = 1; q < C; ++q) x = t == q ? acc[u * C + q][0][r] : x;
+          v[r] = tanh_fast(x);
+        }
+        lds_store_u2(&out[lm * Sh::LDP + nh + (u * C + t) * 16], pack4<T>(v));
       }
-      lds_store_u2(&out[lm * Sh::LDP + nh + t * 16], pack4<T>(v));
       return;
     }
 #pragma unroll

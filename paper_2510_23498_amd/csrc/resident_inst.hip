@@ -31,9 +31,11 @@ hipError_t pick_kernel(const ResidentLaunch& l, const ResidentArgs& a) {
   // 256 at four layers of 128
   constexpr bool phased = (HP == 256 && (L == 4 || MT == 2)) || (HP == 128 && L == 4);
   if (l.kind == kResidentForward) {
-    if constexpr (MT == 1 && HP >= 128)
-      if (a.f.R <= 4) return launch_kernel(mlp_forward_resident<T, L, HP, MT, true>, l, a);
-    return launch_kernel(mlp_forward_resident<T, L, HP, MT, false>, l, a);
+    if constexpr (MT == 1 && HP >= 128) {
+      if (l.copies == 4) return launch_kernel(mlp_forward_resident<T, L, HP, MT, 4>, l, a);
+      if (l.copies == 2) return launch_kernel(mlp_forward_resident<T, L, HP, MT, 2>, l, a);
+    }
+    return l.copies == 1 ? launch_kernel(mlp_forward_resident<T, L, HP, MT, 1>, l, a) : hipErrorInvalidValue;
   }
   if (l.kind == kResidentRecompute)
     return a.f.KT ? launch_kernel(mlp_recompute_resident<T, L, HP, MT, true>, l, a) : launch_kernel(mlp_recompute_resident<T, L, HP, MT, false>, l, a);

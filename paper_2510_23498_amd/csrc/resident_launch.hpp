@@ -12,6 +12,7 @@ struct ResidentLaunch {
   ResidentKind kind;
   int bf16;
   int MT;        // row tile = 16 MT rows; 2 only at hidden width 256
+  int copies;    // forward pass, hidden width 128 or 256, MT = 1: tiles of 16 / copies rows (1, 2, 4)
   unsigned grid;
   hipStream_t stream;
 };

@@ -297,6 +297,22 @@ def test_conv_small_odd_geometry():
     _both(cfg, bias_std=0.1)
 
 
+@pytest.mark.parametrize("widths,low", [((40, 250, 200, 40), "bf16"), ((64, 256, 64), "f16"), ((7, 100, 128, 128, 7), "f16")])
+def test_forward_tiles_of_four_eight_and_sixteen_rows_give_the_same_bits(widths, low):
+    # up to 1024 rows in tiles of 4, up to 2048 in tiles of 8 (256 compute units): the rows' sums are the same ones
+    cfg = wl.CONFIGS["cfg1"].with_(name="fwdcopies", B=2049, N=2, widths=widths, low=low)
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    from paper_2510_23498_amd import binding as rb
+    vel, tab, pol = par.gpu_descriptors(cfg)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    yN, ckpt = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
+    for B in (1, 3, 5, 17, 1023, 1024, 1025, 2047, 2048):
+        print(f"[case] {widths} rows {B}", flush=True)
+        part, ck = rb.rampde_odeint_fwd(vel, th, y[-B:].contiguous(), cfg.tgrid(), tab, pol)
+        assert torch.equal(part, yN[-B:]) and torch.equal(ck, ckpt[:, -B:])
+
+
 @PATHS
 @pytest.mark.parametrize("tab", ["rk4", "heun", "euler"])
 def test_cfg5_shape_reduced(tab, flags):
