@@ -266,6 +266,13 @@ static int device_compute_units() {
   return cus;
 }
 
+// Tiles of 16 / copies rows of the kernels that have them (resident.hpp, shallow.hpp): as long as each has a compute unit
+static int tile_copies(int64_t rows) {
+  int copies = 1;
+  while (copies < 4 && rows * 2 * copies <= 16 * (int64_t)device_compute_units()) copies *= 2;
+  return copies;
+}
+
 constexpr size_t kRowTileLds = 159 * 1024;  // 160 KB per compute unit minus the row-tile kernels' small static arrays
 
 static bool fused_candidate(const rampde_velocity* vel, const rampde_policy* pol) {
@@ -1629,7 +1636,8 @@ struct Runner {
       l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
       l.NTL = p.dpad / 64;
       l.trace = p.cnf ? 1 : 0;
-      l.grid = blocks_for(p.R, 16);
+      l.copies = kind == kResidentForward && l.NTL == 1 && p.resident > 256 ? tile_copies(p.R) : 1;
+      l.grid = blocks_for(p.R, 16 / l.copies);
       // (two wavefronts per SIMD: one workgroup of eight or two of four on a compute unit)
       if (kind == kResidentRecompute) l.grid = (unsigned)std::min<int64_t>((int64_t)l.grid * a.nsteps, (int64_t)device_compute_units() * (p.resident <= 128 ? 2 : 1));
       l.stream = st;
@@ -1643,9 +1651,7 @@ struct Runner {
     l.kind = kind;
     l.bf16 = std::is_same<T, BF16>::value ? 1 : 0;
     l.MT = p.MT;
-    l.copies = 1;
-    if (kind == kResidentForward && p.MT == 1 && p.resident >= 128)  // (as long as those tiles have a compute unit each)
-      while (l.copies < 4 && p.R * 2 * l.copies <= 16 * (int64_t)device_compute_units()) l.copies *= 2;
+    l.copies = kind == kResidentForward && p.MT == 1 && p.resident >= 128 ? tile_copies(p.R) : 1;
     l.grid = blocks_for(p.R, 16 * p.MT / l.copies);
     if (kind == kResidentRecompute) {
       const int64_t cus = device_compute_units();

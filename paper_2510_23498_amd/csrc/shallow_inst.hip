@@ -28,9 +28,14 @@ hipError_t launch_kernel(Kern kern, const ShallowLaunch& l, const ShallowArgs& a
 template <class T, int NTL, bool TRACE>
 hipError_t pick_kind(const ShallowLaunch& l, const ShallowArgs& a) {
   switch (l.kind) {
-    case kResidentForward: return launch_kernel<NTL>(mlp_forward_shallow<T, NTL, HP, TRACE>, l, a);
-    case kResidentRecompute: return launch_kernel<NTL>(mlp_recompute_shallow<T, NTL, HP, TRACE>, l, a);
+    case kResidentForward:
+      if constexpr (NTL == 1 && HP > 256) {
+        if (l.copies == 4) return launch_kernel<NTL>(mlp_forward_shallow<T, NTL, HP, TRACE, 4>, l, a);
+        if (l.copies == 2) return launch_kernel<NTL>(mlp_forward_shallow<T, NTL, HP, TRACE, 2>, l, a);
+      }
+      return l.copies == 1 ? launch_kernel<NTL>(mlp_forward_shallow<T, NTL, HP, TRACE, 1>, l, a) : hipErrorInvalidValue;
     case kResidentChain: return launch_kernel<NTL>(mlp_chain_shallow<T, NTL, HP, TRACE>, l, a);
+    case kResidentRecompute: return launch_kernel<NTL>(mlp_recompute_shallow<T, NTL, HP, TRACE>, l, a);
     default: return launch_kernel<NTL>(mlp_adjoint_shallow<T, NTL, HP, TRACE>, l, a);
   }
 }

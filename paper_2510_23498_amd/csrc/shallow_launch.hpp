@@ -12,6 +12,7 @@ struct ShallowLaunch {
   int bf16;
   int NTL;    // state width / 64 (padded)
   int trace;  // normalising flow with the trace row
+  int copies; // forward pass, NTL = 1, hidden width above 256: tiles of 16 / copies rows (1, 2, 4)
   unsigned grid;
   hipStream_t stream;
 };

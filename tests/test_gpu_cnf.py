@@ -60,9 +60,10 @@ def test_cnf_time_grid_gradient():
     _case(BASE.with_(name="cnft", B=48, N=3, widths=(7, 64, 7), grad_scale=1.0), want_grad_t=True)
 
 
-@pytest.mark.parametrize("H,B,low", [(128, 1, "f16"), (129, 17, "bf16"), (300, 33, "f16"), (513, 100, "f16")])
+@pytest.mark.parametrize("H,B,low", [(128, 1, "f16"), (129, 17, "bf16"), (300, 33, "f16"), (513, 100, "f16"), (600, 1030, "bf16")])
 def test_cnf_hidden_widths_of_every_kernel(H, B, low):
-    # the four compiled hidden widths; one row, a tile and a row, two tiles and a row, a batch that is no tile multiple
+    # the four compiled hidden widths; one row, a tile and a row, two tiles and a row, a batch that is no tile multiple,
+    # forward tiles of four and of eight rows (up to 1024 and 2048 rows of more than 256 hidden units)
     _case(BASE.with_(name=f"cnfw{H}", B=B, N=3, widths=(10, H, 10), low=low, grad_scale=1.0))
 
 

@@ -309,8 +309,14 @@ def test_forward_tiles_of_four_eight_and_sixteen_rows_give_the_same_bits(widths,
     yN, ckpt = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
     for B in (1, 3, 5, 17, 1023, 1024, 1025, 2047, 2048):
         print(f"[case] {widths} rows {B}", flush=True)
-        part, ck = rb.rampde_odeint_fwd(vel, th, y[-B:].contiguous(), cfg.tgrid(), tab, pol)
+        part, ck = rb.rampde_odeint_fwd(vel, th, y[-B:].clone(), cfg.tgrid(), tab, pol)
         assert torch.equal(part, yN[-B:]) and torch.equal(ck, ckpt[:, -B:])
+
+
+@pytest.mark.parametrize("B,low", [(3, "f16"), (1030, "bf16")])
+def test_one_hidden_layer_forward_tiles_of_four_and_eight_rows(B, low):
+    _both(wl.CONFIGS["cfg2"].with_(name=f"shallowrows{B}", B=B, N=2, widths=(30, 600, 30), low=low), bias_std=0.1,
+          tol_emul=2e-3 if low == "bf16" else par.TOL_EMUL)
 
 
 @PATHS
