@@ -333,34 +333,51 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr(ConvWgradTr g) {
 }
 
 // dW[co][ci][tap] and db[co] += sum over K-chunks of the private copies (end of the backward pass, or of a piece of
-// piecewise-constant weights).  tiles_a, tiles_b: 128-channel blocks of the output / input channels.
-__global__ void conv_wgrad_tr_reduce(float* __restrict__ G, int ldg, const float* __restrict__ part, int splits,
-                                     int tiles_a, int tiles_b, int Na, int Nb, float* __restrict__ gb, const Ctl* ctl) {
+// piecewise-constant weights).  tiles_a, tiles_b: 128-channel blocks of the output / input channels.  As conv_wgrad_reduce: the
+// copies as they lie, chunks dealt out to four wavefronts (256 channels, 10 copies of 18 MB in all: a thread per element 44 us,
+// now 23).  Grid: kTrReduceBlocks x 3 tiles_a tiles_b, 256 threads.
+constexpr int kTrReduceBlocks = 12 * 1024 / 64 + 1;  // (the last one: the bias)
+__global__ __launch_bounds__(256) void conv_wgrad_tr_reduce(float* __restrict__ G, int ldg, const float* __restrict__ part, int splits,
+                                                            int tiles_a, int tiles_b, int Na, int Nb, float* __restrict__ gb, const Ctl* ctl) {
   if (ctl->poison) return;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nW = (int64_t)Na * Nb * 9;
-  if (i >= nW + Na) return;
+  __shared__ float4 sums[3][64];
+  const int tile = blockIdx.x / kTrReduceBlocks, block = blockIdx.x % kTrReduceBlocks, wave = threadIdx.x >> 6;
   const size_t per_split = (size_t)tiles_a * tiles_b * 3 * CT_SLOT;
-  if (i >= nW) {
-    if (!gb) return;
-    const int na = (int)(i - nW);
+  const int na0 = tile / (3 * tiles_b) * 128, dy = tile % 3, nb0 = tile / 3 % tiles_b * 128;
+  if (block == kTrReduceBlocks - 1) {
+    // (the sums of the middle line's workgroups, added up by the first input block's)
+    const int na = na0 + threadIdx.x;
+    if (!gb || dy != 1 || nb0 != 0 || threadIdx.x >= 128 || na >= Na) return;
     float acc = 0.f;
     for (int c = 0; c < splits; ++c)
-      for (int b = 0; b < tiles_b; ++b)
-        acc += part[c * per_split + ((size_t)(na >> 7) * tiles_b * 3 + b * 3 + 1) * CT_SLOT + 12 * 4096 + (na & 127)];
+      for (int b = 0; b < tiles_b; ++b) acc += part[c * per_split + (size_t)(tile + 3 * b) * CT_SLOT + 12 * 4096 + threadIdx.x];
     gb[na] += acc;
     return;
   }
-  const int nb = (int)(i % Nb), t = (int)((i / Nb) % 9), na = (int)(i / ((int64_t)Nb * 9));
   // (position of element (co, ci, tap) in a workgroup's copy: see the epilogue of conv_wgrad_tr)
-  const int a = (na & 127) >> 5, r = na & 31, wave = (nb & 127) >> 5, c = nb & 31;
-  const int thread = wave * 64 + ((r >> 2) & 1) * 32 + c;
-  const int j = a * 3 + t % 3;
-  const size_t in_tile = ((size_t)(j * 4 + (r >> 3)) * 256 + thread) * 4 + (r & 3);
-  const size_t tile = ((size_t)(na >> 7) * tiles_b + (nb >> 7)) * 3 + t / 3;
-  float acc = 0.f;
-  for (int c2 = 0; c2 < splits; ++c2) acc += part[c2 * per_split + tile * CT_SLOT + in_tile];
-  G[(size_t)na * ldg + (size_t)nb * 9 + t] += acc;
+  const int pos = block * 64 + (threadIdx.x & 63), jq = pos >> 8, thread = pos & 255, lane = thread & 63;
+  const int na = na0 + jq / 12 * 32 + (jq & 3) * 8 + (lane >> 5) * 4, nb = nb0 + (thread >> 6) * 32 + (lane & 31), t = dy * 3 + jq / 4 % 3;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (na < Na && nb < Nb) {
+    const float4* src = reinterpret_cast<const float4*>(part + (size_t)tile * CT_SLOT) + pos;
+#pragma unroll 8
+    for (int c = wave; c < splits; c += 4) {
+      const float4 v = src[c * (per_split / 4)];
+      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    }
+  }
+  if (wave) sums[wave - 1][threadIdx.x & 63] = acc;
+  __syncthreads();
+  if (wave) return;
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    const float4 v = sums[w][threadIdx.x];
+    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  }
+  const float a[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (na + r < Na && nb < Nb) G[(size_t)(na + r) * ldg + (size_t)nb * 9 + t] += a[r];
 }
 
 

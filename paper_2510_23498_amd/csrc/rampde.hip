@@ -2237,9 +2237,8 @@ struct Runner {
       if (!conv_wgrad_applies(p)) return;
       const Layer& y = p.layers[0];
       float* gq = grad_theta + (size_t)q * p.Pblk;
-      const int64_t n = (int64_t)y.out * y.in * 9 + (int64_t)y.out * 10;
       if (conv_wgrad_tr_applies(p))
-        conv_wgrad_tr_reduce<<<blocks_for(n, 256), 256, 0, st>>>(gq + y.theta_w, y.in_full * 9, f32(y.cw_part), y.cw_splits,
+        conv_wgrad_tr_reduce<<<kTrReduceBlocks * 3 * (y.Npad / 128) * (y.Kpad / 128), 256, 0, st>>>(gq + y.theta_w, y.in_full * 9, f32(y.cw_part), y.cw_splits,
                                                                  y.Npad / 128, y.Kpad / 128, y.out, y.in, gq + y.theta_b, ctl);
       else
         conv_wgrad_reduce<<<kReduceBlocks * (y.Npad / 64) * (y.Kpad / 64), 256, 0, st>>>(gq + y.theta_w, y.in_full * 9, f32(y.cw_part), y.cw_splits,
