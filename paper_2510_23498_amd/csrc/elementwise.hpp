@@ -216,13 +216,35 @@ __device__ __forceinline__ void scale_init(Ctl* ctl, unsigned bits, float* scale
 __global__ void init_adjoint(const float* __restrict__ gyN, const float* __restrict__ gys_last,
                              float* __restrict__ a, int64_t n, Ctl* ctl, int copy, int naive_low, float* scale_hist, int N,
                              int p_bits, int dynamic, int detect, int settled) {
-  unsigned bits = 0;  // (grid-stride: one atomic per workgroup, and few workgroups)
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    float v = gyN[i];
-    if (gys_last) v += gys_last[i];
+  // (16 bytes at a time, and few workgroups: each posts two atomics to the same words.  262144 elements in 512 workgroups
+  // took 14.8 us, now 5.8; 8.4 million 32, now 19.)
+  auto finish = [&](float v) {
     if (naive_low == 1) v = Low<F16>::to_f32(Low<F16>::from_f32(v));
     if (naive_low == 2) v = Low<BF16>::to_f32(Low<BF16>::from_f32(v));
-    if (copy || gys_last || naive_low) a[i] = v;
+    return v;
+  };
+  unsigned bits = 0;
+  const bool store = copy || gys_last || naive_low;
+  const int64_t n4 = n / 4, stride = (int64_t)gridDim.x * blockDim.x;
+#pragma unroll 4
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
+    float4 v = reinterpret_cast<const float4*>(gyN)[i];
+    if (gys_last) {  // (the last of N + 1 arrays of any length: not aligned to 16 bytes)
+      const float* e = gys_last + 4 * i;
+      v.x += e[0]; v.y += e[1]; v.z += e[2]; v.w += e[3];
+    }
+    v = make_float4(finish(v.x), finish(v.y), finish(v.z), finish(v.w));
+    if (store) reinterpret_cast<float4*>(a)[i] = v;
+    const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const unsigned bb = __builtin_bit_cast(unsigned, fabsf(x[r]));
+      bits = bb > bits ? bb : bits;
+    }
+  }
+  for (int64_t i = 4 * n4 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const float v = finish(gys_last ? gyN[i] + gys_last[i] : gyN[i]);
+    if (store) a[i] = v;
     const unsigned bb = __builtin_bit_cast(unsigned, fabsf(v));
     bits = bb > bits ? bb : bits;
   }

@@ -1416,6 +1416,8 @@ struct Runner {
     return RAMPDE_OK;
   }
 
+  // init_adjoint: as few workgroups as read at the device's rate (each posts to the same words)
+  unsigned init_blocks() const { return stream_blocks(p.n / 16, p.n >= (1 << 22) ? 256 : 64); }
   // streaming kernels: 8-wide variants when the state width allows 16-byte accesses
   bool vec8() const { return (p.d & 7) == 0; }
   static unsigned stream_blocks(int64_t groups, int64_t cap = 4096) {  // grid-stride loops
@@ -2315,10 +2317,10 @@ struct Runner {
       a = p.pass.lines ? pass_buf[0] : f32(p.a_rows);
       gys_rows = f32(p.gys_rows);
       to_rows(grad_yN, a);
-      init_adjoint<<<stream_blocks(p.n, 512), 256, 0, st>>>(a, gys_at(N), a, p.n, ctl, 0, naive_low, f32(p.scale_hist), N,
+      init_adjoint<<<init_blocks(), 256, 0, st>>>(a, gys_at(N), a, p.n, ctl, 0, naive_low, f32(p.scale_hist), N,
                                                            Low<T>::p_bits, dynamic, detect, !use_fused && !detect);
     } else {
-      init_adjoint<<<stream_blocks(p.n, 512), 256, 0, st>>>(grad_yN, gys_at(N), a, p.n, ctl, 1, naive_low, f32(p.scale_hist), N,
+      init_adjoint<<<init_blocks(), 256, 0, st>>>(grad_yN, gys_at(N), a, p.n, ctl, 1, naive_low, f32(p.scale_hist), N,
                                                            Low<T>::p_bits, dynamic, detect, !use_fused && !detect);
     }
 
