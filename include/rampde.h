@@ -50,6 +50,13 @@
  *     4e-4 relative in bf16, 1e-4 in fp16, no nearer to or farther from the exact ones), as they do at
  *     the batch sizes above.  An explicit row_tile selects those kernels from the start, and so does
  *     rampde_odeint_fwd in place (yN = y0).
+ *   - Two-convolution networks of at most 64 channels in multiples of 8, image lines of at most 64
+ *     pixels, up to four stages that each use the slope of the one before, without dL/dt: workgroups
+ *     that share an image exchange its lines within a launch, which runs whole steps (a forward pass in
+ *     launches of up to about 3 ms).  Where some of them are kept from running for 20 ms the launch
+ *     gives up and its work is done again as above: behind it on the stream (forward passes and a fixed
+ *     scale), by one workgroup per image and many times as slowly, or on kernels with one launch per
+ *     evaluation under overflow detection.  rampde_odeint_fwd in place takes those from the start.
  *   - theta layout (flat fp32, also the layout of grad_theta):
  *       MLP  : for each layer l: W_l[out_l][in_l] row-major, then b_l[out_l];
  *              layer 1 has in_1 = d + 1 when time_input is set (time column LAST).
@@ -111,7 +118,7 @@ typedef enum {
 #define RAMPDE_NAIVE_STATE 8u       /* comparison baseline, not the paper's scheme: the state y and the adjoint a are
                                      themselves kept in low precision (rounded after every update), i.e. without
                                      the fp32 accumulators of Algorithms 1-2 (the "naive" rows of the paper's Table 5) */
-#define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale or activations within a launch (see
+#define RAMPDE_NO_WAITS 16u         /* test aid: workgroups that exchange the adjoint scale, activations or image lines within a launch (see
                                      the notes on concurrency above) give up at the first exchange, and the pass is
                                      redone by the kernels that do not.  Same results */
 #define RAMPDE_NO_WAITS_AFTER(n) (RAMPDE_NO_WAITS | (unsigned)(n) << 16)  /* test aid, networks whose workgroups share row tiles:

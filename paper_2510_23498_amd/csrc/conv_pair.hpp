@@ -13,6 +13,12 @@
 // A wavefront multiplies all output channels with its MT blocks of 16 pixels: per contraction block of 32 input channels
 // of one tap NCT weight fragments, which come from memory in the order in which they are used (1 KB each, four blocks
 // ahead), and MT pixel fragments from LDS (a tap is a shifted pixel address) for NCT MT matrix instructions.
+//
+// It runs where conv_pass.hpp, which keeps a tile's state on chip over whole steps, does not: channel counts that are no
+// multiple of 8, tableaux whose stages are no chain, dL/dt, calls in place, passes that are redone.  What bounds a launch
+// (64 channels, 16 lines of 32 pixels, cycles of 75000 before the time channel became a block of the contraction): the
+// input's arrival 13000, the two contractions 12700 and 11300 (10400 and 9200 of matrix instructions), tanh 10900, the output
+// 15000: the memory's share moves 75 MB per evaluation of 128 images, 130 MB per vector-Jacobian product.
 #pragma once
 #include <type_traits>
 

@@ -27,13 +27,13 @@ inline ConvPairShape conv_pair_tiles(int C32, int lines, int H, int Wd, int64_t 
   if (t.mt1 && conv_pair_lds_bytes(C32, lines, Wd) <= (t.mt1 <= 5 ? 78 : 156) * 1024) t.tiles = (int)(images * t.per_image);
   return t;
 }
-// The tiles of least estimated time, from launches of every possible height on nine shapes (us per evaluation with the
-// next stage's input; 64 channels unless noted): a launch takes about 8 us (6 with 32 channels), a tile 1.1 (0.5) per
-// block of 16 pixels and wavefront, a little less where two workgroups share a compute unit (up to 5 blocks; the larger
-// tiles have it alone), which also waits less for memory.  128 x 32 x 32 with 4 / 8 / 16 lines 39.1 / 29.7 / 35.2;
-// 128 x 16 x 16 with 2 / 4 / 8 / 16 25.5 / 17.4 / 15.1 / 18.2; 60 x 14 x 14 with 1 / 2 / 4 / 7 / 14 23.3 / 15.6 / 12.6 /
-// 13.2 / 17.3; 16 x 64 x 64 with 1 / 2 / 4 / 7 38.4 / 26.7 / 27.0 / 31.4; 32 channels, 20 x 28 x 28 with 1 / 2 / 4 / 7 / 14
-// 8.2 / 7.6 / 7.9 / 9.5 / 12.7, 128 x 32 x 32 with 2 / 4 / 8 / 16 24.2 / 17.3 / 16.8 / 18.8.
+// The tiles of least estimated time, fitted to launches of every possible height on nine shapes, of which it picks the best
+// or one within 3 %: a fixed part, a part per block of 16 pixels and wavefront, a little less of it where two workgroups
+// share a compute unit (up to 5 blocks; the larger tiles have it alone), which also wait less for memory.  us per
+// evaluation with the next stage's input, 64 channels: 128 x 32 x 32 with 4 / 8 / 16 lines 30.9 / 25.6 / 29.1; 128 x 16 x 16
+// with 2 / 4 / 8 / 16 22.3 / 13.2 / 10.6 / 13.0; 60 x 14 x 14 with 2 / 4 / 7 / 14 11.7 / 8.4 / 9.1 / 12.1; 16 x 64 x 64 with 1 /
+// 2 / 4 / 7 31.5 / 22.3 / 22.4 / 24.8; 32 channels, 20 x 28 x 28 with 1 / 2 / 4 / 7 / 14 7.0 / 5.7 / 5.3 / 6.7 / 9.8, 128 x 32 x 32
+// with 2 / 4 / 8 / 16 20.0 / 14.4 / 13.0 / 15.7.
 inline ConvPairShape conv_pair_shape(int C32, int H, int Wd, int64_t images, int cus) {
   ConvPairShape best{};
   double least = 0;

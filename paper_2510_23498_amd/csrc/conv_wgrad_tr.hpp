@@ -334,8 +334,8 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr(ConvWgradTr g) {
 
 // dW[co][ci][tap] and db[co] += sum over K-chunks of the private copies (end of the backward pass, or of a piece of
 // piecewise-constant weights).  tiles_a, tiles_b: 128-channel blocks of the output / input channels.  As conv_wgrad_reduce: the
-// copies as they lie, chunks dealt out to four wavefronts (256 channels, 10 copies of 18 MB in all: a thread per element 44 us,
-// now 23).  Grid: kTrReduceBlocks x 3 tiles_a tiles_b, 256 threads.
+// copies as they lie, chunks dealt out to four wavefronts (256 channels, 20 copies, 47 MB: a thread per element 44 us, now
+// 23).  Grid: kTrReduceBlocks x 3 tiles_a tiles_b, 256 threads.
 constexpr int kTrReduceBlocks = 12 * 1024 / 64 + 1;  // (the last one: the bias)
 __global__ __launch_bounds__(256) void conv_wgrad_tr_reduce(float* __restrict__ G, int ldg, const float* __restrict__ part, int splits,
                                                             int tiles_a, int tiles_b, int Na, int Nb, float* __restrict__ gb, const Ctl* ctl) {
@@ -400,7 +400,8 @@ __global__ __launch_bounds__(256) void conv_wgrad_tr_reduce(float* __restrict__ 
 __device__ __align__(16) uint16_t kZeroPage[64];
 // The layers of one launch: workgroups splits0 and up of the grid's third axis are the second layer's.  (A launch of a
 // small image set is latency from end to end, 20 us at 24 channels, 20 images of 28 x 28: one instead of two per step.  A
-// large one gains nothing: 64 channels, 128 images of 32 x 32 143 us against two of 71 to 73.)
+// large one gains nothing: 64 channels, 128 images of 32 x 32 143 us against two of 71 to 73; 123 with half the chunks
+// per layer, so that the launch's workgroups run at once.)
 struct ConvWgradLayers {
   ConvWgrad layer[2];
   int splits0;
