@@ -402,6 +402,9 @@ __device__ __align__(16) uint16_t kZeroPage[64];
 // small image set is latency from end to end, 20 us at 24 channels, 20 images of 28 x 28: one instead of two per step.  A
 // large one gains nothing: 64 channels, 128 images of 32 x 32 143 us against two of 71 to 73; 123 with half the chunks
 // per layer, so that the launch's workgroups run at once.)
+// A group of steps is one launch where there are buffer sets for several: their K-chunks share the chip, and the private
+// copies are read and written once for all of them (64 channels, 64 images of 8 x 8, f16, 8 Heun steps, us per pass with a
+// launch per step / per group: 751 / 632; 128 of 16 x 16, 8 RK4 steps 1557 / 1484).
 struct ConvWgradLayers {
   ConvWgrad layer[2];
   int splits0;
@@ -411,7 +414,6 @@ template <class T, bool TS, int W16>
 __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
   const int layer = (int)blockIdx.z >= a.splits0 ? 1 : 0, split = (int)blockIdx.z - layer * a.splits0;
   const ConvWgrad& g = a.layer[layer];
-  if (g.ctl->poison) return;
   const int Wr = g.Wd;                                         // pixels per image line
   constexpr int W = 16 * W16, LPS = 4 / W16, NL = 32 / W16;   // lines per step, lines in the ring
   constexpr int GB = W * 128, LSLOT = (2 * W + 2) * 128;      // cotangent line, then the input line with its zero rows
@@ -429,6 +431,13 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
   const int lines_per_split = g.rows_per_split / Wr;
   const int group = g.steptab ? split / g.per_step : 0;        // step of a group
   const float* times = g.steptab ? g.steptab + (size_t)(g.step - group) * (1 + g.s) : nullptr;
+  float S = 0.f;
+  if (times) {
+    S = g.scale_hist[g.step - group];
+    if (S == 0.f) return;  // (the steps of a group before a rejected one are accepted ones all the same)
+  } else if (g.ctl->poison) {
+    return;
+  }
   const uint16_t* gA = g.A + (size_t)group * g.rows * g.lda;
   const uint16_t* gB = g.B + (size_t)group * g.rows * g.ldb;
   const int64_t c0 = (int64_t)(split - group * g.per_step) * lines_per_split;
@@ -691,7 +700,7 @@ __global__ __launch_bounds__(256, 1) void conv_wgrad_tr64(ConvWgradLayers a) {
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the requests past the chunk's end
 
-  const float scale = (times ? times[0] : g.h) / g.ctl->S_step;
+  const float scale = times ? times[0] / S : g.h / g.ctl->S_step;
   float* slotf = g.part + (size_t)split * CW_SLOT;
   if (g.want_sums) {
     float p0 = 0.f, p1 = 0.f;

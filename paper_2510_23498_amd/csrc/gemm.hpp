@@ -385,8 +385,9 @@ struct ConvWgrad {
   //   tpart[0] += scale * sum_j (1 - c_j) taubar_j,   tpart[1] += scale * sum_j c_j taubar_j
   const float* wt; int ldwt;    // rounded time-channel weights [9][ldwt], or null
   float* tpart;                 // or null: the launch's table of per-workgroup slots (fold_time_slots)
-  // conv_wgrad_tr64 under a fixed scale: a group of steps, `per_step` K-chunks each; step `step` - q is rows q * rows and on.
-  // steptab: [N][1 + stages] step sizes and stage times, or null: one step
+  // conv_wgrad_tr64: a group of steps, `per_step` K-chunks each; step `step` - q is rows q * rows and on.  steptab: [N][1 +
+  // stages] step sizes and stage times, or null: one step.  scale_hist: [N] the steps' scales, 0: not accepted (left out)
+  const float* scale_hist;
   const float* steptab; int step, per_step, s;
   float cs[kMaxStages];         // c_j
 };

@@ -79,7 +79,7 @@ struct Layer {
   int ldw;  // K extent of the forward GEMM (dense: Kpad; conv: 9 * Cpad)
   // all-taps convolution weight gradient: K-chunk length, chunk count, the chunks' private copies
   int cw_per = 0, cw_splits = 0;
-  int cw_step = 0;       // chunks of a step where a launch takes a group of steps, 0: one step per launch
+  int cw_step = 0;       // chunks of a step where a launch takes a group of buffer sets, 0: one step per launch
   size_t cw_part = 0;
   size_t cw_floats = 0;  // fp32 elements of all the copies
 };
@@ -806,8 +806,8 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
           // channels, 128 images of 32 x 32, us per launch with 256 / 128 chunks per layer 143 / 123)
           const bool pair = !p.parabolic && conv_wgrad_tr64_applies(p, y);
           const int cus = device_compute_units() / (pair ? 2 : 1);
-          // (under a fixed scale the steps of a buffer set's group are one launch)
-          const int group = pair && p.pass.lines && pol && resolve_scaling(pol) == RAMPDE_SCALE_NONE ? p.nsets : 1;
+          // (the steps of a group of buffer sets are one launch)
+          const int group = pair && p.pass.lines ? p.nsets : 1;
           const int64_t want = std::max<int64_t>(1, cus / tiles / group);
           const int64_t unit = conv_wgrad_tr64_applies(p, y) ? (int64_t)2 * tr64_step_lines(p.Wd) * p.Wd : CW_KS;
           int64_t per = ((rows + want - 1) / want + unit - 1) / unit * unit;
@@ -1193,10 +1193,7 @@ struct Runner {
       else if (p.pass.per_image > 1) {
         if (const int rc = launch_redo(g, true)) return rc;
       }
-      if (y0.cw_step && !detect) {
-        param_grads(0.f, Coefs{}, grad_theta, Coefs{}, nullptr, 0, n, hi);
-        continue;
-      }
+      if (y0.cw_step) continue;
       for (int r = q; r < q + per_launch; ++r) {
         const int i = hi - r;
         const float h = (float)(tgrid[i + 1] - tgrid[i]);
@@ -1208,6 +1205,7 @@ struct Runner {
         param_grads(h, taus, grad_theta, cs, nullptr, r);
       }
     }
+    if (y0.cw_step) param_grads(0.f, Coefs{}, grad_theta, Coefs{}, nullptr, 0, n, hi);
     return RAMPDE_OK;
   }
 
@@ -2010,6 +2008,7 @@ struct Runner {
         dim3 cgrid(y.Npad / 64, y.Kpad / 64, group ? group * y.cw_step : y.cw_splits);
         if (group) {
           c.steptab = f32(p.steptab);
+          c.scale_hist = f32(p.scale_hist);
           c.step = first;
           c.per_step = y.cw_step;
           c.s = s;

@@ -228,6 +228,19 @@ def test_retry_in_the_middle_of_the_pass_many_workgroups(base, kw, flags, row_ti
     print("  vs emul:", {k: f"{v:.2e}" for k, v in errs.items()}, flush=True)
 
 
+@pytest.mark.parametrize("step_group", [2, 3, 5])
+def test_retry_in_the_middle_of_a_group_of_convolution_steps(step_group):
+    # stages of a group recomputed in one launch, its parameter gradients in one that leaves the rejected step and those
+    # behind it out; tiles that exchange lines
+    cfg, theta, y0, target = _gain_case("cfg4", name="retryconvgroup", B=2, N=5, C=8, H=24, W=20, t1=0.025, gain=256.0, scaling="dynamic")
+    emu = par.run_oracle(cfg, theta, y0, target, "emul")
+    assert emu["status"] == "ok" and emu["retries"] >= 2
+    gpu = par.run_gpu(cfg, theta, y0, target, step_group=step_group)
+    np.testing.assert_array_equal(gpu["scale_hist"].astype(np.float64), emu["scale_hist"])
+    assert gpu["status"] == 0 and gpu["retries"] == emu["retries"]
+    par.compare(cfg, gpu, emu, par.TOL_F64[cfg.low], "emulation oracle (amplifying network)")
+
+
 @pytest.mark.parametrize("base,kw", MULTI_WG, ids=[k["name"] for _, k in MULTI_WG])
 def test_scaling_failure_many_workgroups(base, kw):
     cfg, theta, y0, target = _gain_case(base, **dict(kw))
