@@ -210,7 +210,8 @@ int64_t rampde_num_params(const rampde_velocity *vel);
  * The size depends on the policy: the backward pass of a dense network keeps the low-precision
  * stage inputs, activations and cotangents of all the steps that one launch runs (policy.step_group:
  * up to 64 steps, with a fixed scale at most about 4 GiB, with overflow detection at most about
- * 1 GiB, or, for wide networks, of as many steps as are recomputed at once).  Pass the same policy to the query and to the
+ * 1 GiB, or, for wide networks, of as many steps as are recomputed at once; that of a convolutional network up to
+ * 32 steps and 1 GiB).  Pass the same policy to the query and to the
  * call.  A batch may ask for more than a larger one does (where workgroups share row tiles, or more steps' stages are
  * recomputed at once).  On a workspace without room for that it runs on the kernels that do without, as the
  * last, smaller batch of a program on the workspace of its others: results within rounding. */

@@ -241,6 +241,30 @@ def test_retry_in_the_middle_of_a_group_of_convolution_steps(step_group):
     par.compare(cfg, gpu, emu, par.TOL_F64[cfg.low], "emulation oracle (amplifying network)")
 
 
+@pytest.mark.parametrize("scaling", ["dynamic", "none"])
+def test_fewer_convolution_steps_at_once_on_a_smaller_workspace(scaling):
+    # the queried workspace holds the stages of all five steps; one with room for fewer takes fewer at once: the bits of a
+    # call that asks for as many
+    cfg, theta, y0, _ = _gain_case("cfg4", name="fewersets", B=6, N=5, C=8, H=24, W=20, t1=0.025, gain=1.0, scaling=scaling)
+    vel, tab, pol = par.gpu_descriptors(cfg, scaling)
+    th, y = (torch.from_numpy(x).to("cuda:0") for x in (theta, y0))
+    yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
+    gyN = 2 / yN.numel() * yN
+
+    def backward(policy, size):
+        gy0, gth, info = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, policy, ck, gyN, workspace=ws[:size])
+        assert info.status == 0
+        return gy0, gth
+
+    asked = {g: par.gpu_descriptors(cfg, scaling, step_group=g)[2] for g in (5, 2, 1)}
+    sizes = {g: rb.rampde_workspace_bytes(vel, cfg.B, cfg.N, tab, a, True) for g, a in asked.items()}
+    assert sizes[5] > sizes[2] > sizes[1]
+    ws = rb.alloc_workspace(vel, cfg.B, cfg.N, tab, pol, True)
+    for g, a in asked.items():
+        want, got = backward(a, sizes[5]), backward(pol, sizes[g])
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 @pytest.mark.parametrize("base,kw", MULTI_WG, ids=[k["name"] for _, k in MULTI_WG])
 def test_scaling_failure_many_workgroups(base, kw):
     cfg, theta, y0, target = _gain_case(base, **dict(kw))
