@@ -17,8 +17,6 @@
 // single steps and to tiles of narrow networks that fill the device.  Measured on flows of 63 features, width 1024,
 // fp16, 16 RK4 steps of 512 rows: 793 -> 584 us per pass; one launch per layer, 900 launches, 6456 to 6514 us.
 #pragma once
-#include <type_traits>
-
 #include "resident.hpp"
 
 namespace rampde {
@@ -141,35 +139,25 @@ struct ShallowTile {
   }
   // this wavefront's contributions to the state columns
   template <int COPIES = 1>
-  static __device__ __forceinline__ void put_part(f32x4 (&out)[Sh::NS], const ShallowLds& l, int wave, int lane) {
-    lds_f32* p = l.part + ((size_t)wave * 16 + (lane & 15)) * Sh::LDS_ + (lane >> 4) * 4;
-#pragma unroll
-    for (int n = 0; n < Sh::NS; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) out[n][r] = sum_copies<COPIES>(out[n][r]);
-    if (COPIES == 1 || (lane & 15) < 16 / COPIES)
+  static __device__ __forceinline__ void put_part(const f32x4 (&out)[Sh::NS], const ShallowLds& l, int wave, int lane) {
+    lds_f32* p = l.part + ((size_t)wave * 16 + (lane & 15) / COPIES) * Sh::LDS_ + (lane >> 4) * 4;
+    if (COPIES == 1 || lane % COPIES == 0)
 #pragma unroll
       for (int n = 0; n < Sh::NS; ++n) *(RAMPDE_LDS f32x4*)(p + n * 16) = out[n];
   }
   // ---- COPIES = 2, 4: tiles of 16 / COPIES rows, where those of 16 leave compute units idle.  A tile's 16 rows are copies of
-  // them, and copy c of a row does the arithmetic of a share of the hidden units: of a lane's eight of a block of 32 (the
-  // four words of its operand) those of word c, or words 2c and 2c + 1.  The others are zeros in its operand, so that the
-  // contraction gives each copy a part of the row's sum, added up at the end.  Forward pass, up to 64 state columns and more
-  // than 256 hidden units (16 RK4 steps, us): 63 features, width 1024, 512 rows, trace row 159 -> 128; 40 features, width 700,
-  // 64 rows 165 -> 133; 50 -> 1000 -> 50, 800 rows 134 -> 114.  Not with fewer hidden units or more state columns, where the
-  // sums over the copies cost what the arithmetic saves (training pass, 128 -> 512 -> 128, 1024 rows 391 -> 410; flow of 8
-  // features, width 100, 2048 rows 281 -> 289), and not for the chain, whose exchange of the scale grows with the tiles
-  // (128 -> 512 -> 128, 1024 rows 410 -> 433).
+  // them, in neighbouring lanes, and copy c of a row does the tanh arithmetic of a share of the hidden units: of a lane's
+  // eight of a block of 32 (the four words of its operand) those of word c, or words 2c and 2c + 1.  The other words come
+  // from the lanes beside it (DPP within four lanes), so that every copy has the whole operand and the sums, trace included,
+  // are those of the 16-row tiles, bit for bit.  (With zeros for the other words and the copies' sums added up at the end
+  // the recomputation, which has no copies, summed in another order, and an infinite output weight gave NaN.)  Forward pass,
+  // up to 64 state columns and more than 256 hidden units (16 RK4 steps, us): 40 features, width 700, 64 rows, trace row 165
+  // -> 135 (130 with every copy's share of the trace sum); 50 -> 1000 -> 50, 800 rows 134 -> 109; training pass of 63
+  // features, width 1024, 512 rows 559 -> 527.  Not with fewer hidden units or more state columns, where a version that added
+  // up the copies' sums lost (training pass, 128 -> 512 -> 128, 1024 rows 391 -> 410; flow of 8 features, width 100, 2048 rows
+  // 281 -> 289; this one is not measured there), and not in the chain, where that version lost on shapes outside this range
+  // (128 -> 512 -> 128, 1024 rows 410 -> 433: more tiles exchange the scale) and was not tried by itself within it.
   static constexpr int words(int COPIES) { return 4 / COPIES; }
-  template <int COPIES>
-  static __device__ __forceinline__ float sum_copies(float x) {
-    auto turned = [](float v, auto n) __attribute__((always_inline)) {  // lane l of 16: lane l - n's
-      return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + decltype(n)::value, 0xf, 0xf, false));
-    };
-    if constexpr (COPIES == 4) x += turned(x, std::integral_constant<int, 4>{});
-    if constexpr (COPIES >= 2) x += turned(x, std::integral_constant<int, 8>{});
-    return x;
-  }
   // this copy's of a lane's eight hidden units: pair u of words(COPIES)
   template <int COPIES>
   static __device__ __forceinline__ void own(const f32x4 (&acc)[2], int copy, int u, float (&v)[2]) {
@@ -187,19 +175,19 @@ struct ShallowTile {
       }
     }
   }
-  // first hidden unit of that pair within the block of 32, past the lane's nh
-  template <int COPIES>
-  static __device__ __forceinline__ int own_at(int copy, int u) {
-    const int w = COPIES == 1 ? u : COPIES == 2 ? 2 * copy + u : copy;
-    return (w >> 1) * 16 + 2 * (w & 1);
+  // word K of the operand, from the copy that has it
+  template <int COPIES, int K>
+  static __device__ __forceinline__ uint32_t word(const uint32_t (&w)[words(COPIES)]) {
+    constexpr int owner = K / words(COPIES), other = COPIES == 4 ? owner : owner + 2;  // (lanes 0, 1 and 2, 3 of four)
+    if constexpr (COPIES == 1) return w[K];
+    else return __builtin_amdgcn_update_dpp(0, (int)w[K % words(COPIES)], owner * 5 + other * 0x50, 0xf, 0xf, false);
   }
   template <int COPIES>
-  static __device__ __forceinline__ u16x8 own_operand(const uint32_t (&w)[words(COPIES)], int copy) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 v;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = COPIES == 1 ? w[k % words(COPIES)] : copy == k / words(COPIES) ? w[k % words(COPIES)] : 0u;
-    return __builtin_bit_cast(u16x8, v);
+  static __device__ __forceinline__ void whole(const uint32_t (&w)[words(COPIES)], uint32_t (&v)[4]) {
+    v[0] = word<COPIES, 0>(w);
+    v[1] = word<COPIES, 1>(w);
+    v[2] = word<COPIES, 2>(w);
+    v[3] = word<COPIES, 3>(w);
   }
   static __device__ __forceinline__ void sum_parts(float (&v)[Sh::EPT], const ShallowLds& l, int row, int c) {
 #pragma unroll
@@ -243,10 +231,9 @@ struct ShallowTile {
   // sum of a row's trace terms over the four lanes that share it -> LDS
   template <int COPIES = 1>
   static __device__ __forceinline__ void put_trace(float tr, const ShallowLds& l, int wave, int lane) {
-    tr = sum_copies<COPIES>(tr);
     tr += __shfl_xor(tr, 16);
     tr += __shfl_xor(tr, 32);
-    if (lane < 16) l.tr[wave * 16 + lane] = tr;
+    if (lane < 16 && lane % COPIES == 0) l.tr[wave * 16 + lane / COPIES] = tr;
   }
   static __device__ __forceinline__ float trace_of(const ShallowLds& l, int row) {
     float v = 0.f;
@@ -266,7 +253,7 @@ __global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) v
   ShallowLds l;
   l.carve<NTL, HP>((lds_u16*)smem);
   constexpr int ROWS = 16 / COPIES, WORDS = Tile::words(COPIES);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, copy = (lane & 15) / ROWS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, copy = lane % COPIES;
   const int nh = wave * Sh::TPW * 16 + (lane >> 4) * 4;
   const int er = tid / (Sh::NT / 16), ec = (tid % (Sh::NT / 16)) * EPT;  // this thread's state elements
   const int64_t row = er < ROWS ? (int64_t)blockIdx.x * ROWS + er : g.R;
@@ -303,7 +290,7 @@ __global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) v
       const float row_next = rows.load(g, i_next);
       const float tau = rows.tau(i, j);
       u16x8 a[Sh::KS];
-      Tile::read_z(a, l.z, (lane & 0x30) | lane % ROWS);
+      Tile::read_z(a, l.z, (lane & 0x30) | (lane & 15) / COPIES);
       f32x4 out[Sh::NS];
 #pragma unroll
       for (int n = 0; n < Sh::NS; ++n) out[n] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -313,22 +300,26 @@ __global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) v
         f32x4 acc[2];
         Tile::start(acc, l, tau, nh, p);
         Tile::pre(acc, w, a, p);
-        uint32_t hq[WORDS];
+        uint32_t hq[WORDS], op[4];
 #pragma unroll
         for (int u = 0; u < WORDS; ++u) {
           float v[2];
           Tile::template own<COPIES>(acc, copy, u, v);
           hq[u] = Low<T>::pack2(tanh_fast(v[0]), tanh_fast(v[1]));
-          if constexpr (TRACE) {
-            const lds_f32* c = l.cf + nh + 32 * p + Tile::template own_at<COPIES>(copy, u);
-            const float q0 = Low<T>::to_f32((uint16_t)hq[u]), q1 = Low<T>::to_f32((uint16_t)(hq[u] >> 16));
-            tr = fmaf(c[0], fmaf(-q0, q0, 1.f), tr);
-            tr = fmaf(c[1], fmaf(-q1, q1, 1.f), tr);
+        }
+        Tile::template whole<COPIES>(hq, op);
+        if constexpr (TRACE) {
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh) {
+            const f32x4 c = *(const RAMPDE_LDS f32x4*)(l.cf + nh + (2 * p + hh) * 16);
+            float v[4];
+            unpack4<T>(make_uint2(op[2 * hh], op[2 * hh + 1]), v);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tr = fmaf(c[r], fmaf(-v[r], v[r], 1.f), tr);
           }
         }
-        const u16x8 op = Tile::template own_operand<COPIES>(hq, copy);
 #pragma unroll
-        for (int n = 0; n < Sh::NS; ++n) out[n] = Low<T>::mfma16(w.V[n][p], op, out[n]);
+        for (int n = 0; n < Sh::NS; ++n) out[n] = Low<T>::mfma16(w.V[n][p], Tile::operand(make_uint2(op[0], op[1]), make_uint2(op[2], op[3])), out[n]);
       }
       Tile::template put_part<COPIES>(out, l, wave, lane);
       if constexpr (TRACE) Tile::template put_trace<COPIES>(tr, l, wave, lane);

@@ -313,6 +313,29 @@ def test_forward_tiles_of_four_eight_and_sixteen_rows_give_the_same_bits(widths,
         assert torch.equal(part, yN[-B:]) and torch.equal(ck, ckpt[:, -B:])
 
 
+@pytest.mark.parametrize("base,widths,low,overflow", [("cfg1", (30, 600, 30), "bf16", False), ("cfg1", (64, 300, 64), "f16", False),
+                                                      ("cfg1", (50, 1000, 50), "f16", True), ("cnf", (20, 900, 20), "f16", False)])
+def test_one_hidden_layer_forward_tiles_give_the_same_bits(base, widths, low, overflow):
+    # as above: the copies of a row in a tile share the tanh arithmetic and nothing else, so that the recomputation, which
+    # has tiles of 16 rows only, forms the forward pass's stages.  An output weight that rounds to infinity makes its own
+    # output infinite, at every batch size
+    cfg = wl.CONFIGS[base].with_(name="fwdshallow", B=2049, N=1 if overflow else 2, widths=widths, low=low, tableau="euler" if overflow else "rk4")
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    if overflow:
+        theta[wl.theta_layout(cfg)[2][2] + 37] = 1e6
+    from paper_2510_23498_amd import binding as rb
+    vel, tab, pol = par.gpu_descriptors(cfg)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    yN, ckpt = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
+    assert bool(torch.isinf(ckpt[1, :, 0]).any()) == overflow
+    for B in (1, 5, 1024, 1025, 2048):
+        print(f"[case] {widths} rows {B}", flush=True)
+        part, ck = rb.rampde_odeint_fwd(vel, th, y[-B:].clone(), cfg.tgrid(), tab, pol)
+        np.testing.assert_array_equal(part.cpu().numpy(), yN[-B:].cpu().numpy())
+        np.testing.assert_array_equal(ck.float().cpu().numpy(), ckpt[:, -B:].float().cpu().numpy())
+
+
 @pytest.mark.parametrize("B,low", [(3, "f16"), (1030, "bf16")])
 def test_one_hidden_layer_forward_tiles_of_four_and_eight_rows(B, low):
     _both(wl.CONFIGS["cfg2"].with_(name=f"shallowrows{B}", B=B, N=2, widths=(30, 600, 30), low=low), bias_std=0.1,
