@@ -35,6 +35,8 @@ struct ConvPair {
   const uint16_t* A;                 // [rows][64] stage input / slope cotangent
   const uint16_t *W1, *W2;           // weight fragments of the first and the second convolution (see cast_conv_layer)
   const uint16_t *T1, *T2;           // their time-channel weights and biases: [2][64][8], contraction index 0-8: tap, 9: bias
+  const float *X1, *X2;              // the time-channel weights [9][64] in 32 bits ...
+  const float *F1, *F2;              // ... and which outputs [64] have one that is not finite: 1 or 0 (see PairTime::odd)
   uint32_t tau;                      // stage time, low-precision bits
   const uint16_t* act;               // VJP: [rows][64] stored hidden activation
   uint16_t* mid;                     // [rows][64] hidden activation / its cotangent, or null: not kept
@@ -148,6 +150,24 @@ struct PairTime {
 #pragma unroll
     for (int o = 0; o < NCT; ++o) acc[o] = Low<T>::mfma16(w[o], __builtin_bit_cast(u16x8, q), f32x4{0.f, 0.f, 0.f, 0.f});
   }
+  // Time weights that are not finite once rounded are zeros among the fragments: a tap outside the image leaves its weight
+  // out of the sum, where a product with zero would be NaN.  Whether there are any (uniform; flag: that of output
+  // threadIdx.x % 64), and their terms.
+  static __device__ __forceinline__ bool odd(float flag) { return __builtin_amdgcn_ballot_w64(flag != 0.f) != 0; }
+  static __device__ __forceinline__ void add_odd(const float* X, uint32_t tau, unsigned edges, f32x4 (&acc)[NCT]) {
+    const float time = Low<T>::to_f32((uint16_t)tau);
+#pragma unroll 1
+    for (int tap = 0; tap < 9; ++tap) {
+      const bool inside = (tap / 3 > 0 || edges & 1) && (tap / 3 < 2 || edges & 2) && (tap % 3 > 0 || edges & 4) && (tap % 3 < 2 || edges & 8);
+#pragma unroll
+      for (int o = 0; o < NCT; ++o) {
+        const float4 x = *reinterpret_cast<const float4*>(X + tap * 64 + o * 16 + (threadIdx.x & 63) / 16 * 4);
+        const float v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[o][r] += inside && !__builtin_isfinite(v[r]) ? time * v[r] : 0.f;
+      }
+    }
+  }
 };
 
 // One tile.  With a control block nothing is done once a cotangent chain has been rejected.
@@ -175,6 +195,16 @@ __device__ __forceinline__ void pair_tile(const ConvPair& g, const ConvPairShape
     return ((first - y0 + 2 + l) * LW + p - l * W + 1) * PITCH;
   };
 
+  // (see PairTime::odd; behind the contraction, where registers are free)
+  auto add_odd = [&](const float* X, int n, int first, auto& acc) __attribute__((always_inline)) {
+    constexpr int MT = sizeof(acc) / sizeof(acc[0]);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int p = (wave * MT + m) * 16 + fl, pc = p < n ? p : 0, l = line_of(pc);
+      PairTime<T, NCT>::add_odd(X, g.tau, edges_of(first + l, pc - l * W), acc[m]);
+    }
+  };
+
   // ---- the input lines (past the window: zeros)
   u16x8 reg[MAXC];
   {
@@ -190,7 +220,12 @@ __device__ __forceinline__ void pair_tile(const ConvPair& g, const ConvPairShape
   first.start(g.W1);
 
   PairTime<T, NCT> time;
-  if constexpr (!VJP) time.start(g.T1);
+  float odd1 = 0.f, odd2 = 0.f;
+  if constexpr (!VJP) {
+    time.start(g.T1);
+    odd1 = g.F1[lane];
+    odd2 = g.F2[lane];
+  }
 
   // ---- zero columns and lines
   const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -229,6 +264,7 @@ __device__ __forceinline__ void pair_tile(const ConvPair& g, const ConvPairShape
       }
     }
     first.run(sIn, base, LW, acc, []() {});
+    if (!VJP && time.odd(odd1)) add_odd(g.X1, n1, h0, acc);
     if constexpr (VJP) {  // the stored activations for the tanh' factor (requested any earlier, beside the multiplication, they slow it down by more)
       const auto act = pair_window(g.act + (line0 + h0) * W * 64, n1 * 64);
 #pragma unroll
@@ -318,6 +354,7 @@ __device__ __forceinline__ void pair_tile(const ConvPair& g, const ConvPairShape
     } else {
       second.run(sIn, base, LW, acc, fetch);
     }
+    if (!VJP && time.odd(odd2)) add_odd(g.X2, n2, y0, acc);
     __syncthreads();
 #pragma unroll
     for (int m = 0; m < MT2; ++m) {

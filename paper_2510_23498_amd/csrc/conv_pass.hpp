@@ -17,7 +17,9 @@
 // The tiles of an image have to run at the same time: a launch has at most as many workgroups as the device runs at once.
 // If others hold the device a wait ends after `ticks`; the launch then raises `stalled`, and conv_redo_* behind it do the
 // work again, one workgroup per image (nothing is left of a launch that was given up: they start from its inputs).  A pass
-// under overflow detection is redone by way of the host instead.
+// under overflow detection is redone by way of the host instead.  Time weights that are not finite go the same way from the
+// start (pass_reset): beside the contractions here their terms (PairTime::add_odd) cost registers, 137 spilled instead of 5 in
+// the recomputation of 64 channels.
 //
 // Measured, us per evaluation of 64 x 32 x 32, 128 images (512 workgroups of 8 lines): forward 30.6, recomputation 23.3, chain
 // 38 (conv_pair.hpp with the passes over memory that it needs beside it 31, 28 and 45); 32 channels 10.2, 11.1 and 13.5;
@@ -45,6 +47,7 @@ struct PassShape {
 struct ConvPass {
   const uint16_t *W1, *W2;      // weight fragments in the order of use: forward W_1, W_2, chain W_2^T, W_1^T
   const uint16_t *T1, *T2;      // time-channel weights and biases (forward)
+  const float *X1, *X2, *F1, *F2;  // (see ConvPair)
   const float* steptab;         // [N][1 + s]: step size, stage times rounded to low
   unsigned long long* words;    // [workgroups][2][2][Wd x 16-byte chunks of a pixel x 4]
   uint32_t first;               // number of the launch's first exchange
@@ -662,6 +665,7 @@ __global__ __launch_bounds__(256, 1) void conv_redo_forward(ConvRedo a) {
         ConvPair p{};
         p.A = j % 2 ? a.Z2 : g.Z;
         p.W1 = g.W1; p.W2 = g.W2; p.T1 = g.T1; p.T2 = g.T2;
+        p.X1 = g.X1; p.X2 = g.X2; p.F1 = g.F1; p.F2 = g.F2;
         p.tau = low_bits<T>(tab[1 + j]);
         p.C = a.K + (size_t)j * g.stage_stride;
         if (j + 1 < g.s) {
@@ -717,6 +721,7 @@ __global__ __launch_bounds__(256, 1) void conv_redo_backward(ConvRedo a) {
         ConvPair p{};
         p.A = g.Z + set + (size_t)j * g.stage_stride;
         p.W1 = g.W1; p.W2 = g.W2; p.T1 = g.T1; p.T2 = g.T2;
+        p.X1 = g.X1; p.X2 = g.X2; p.F1 = g.F1; p.F2 = g.F2;
         p.tau = low_bits<T>(tab[1 + j]);
         p.mid = g.ACT + set + (size_t)j * g.stage_stride;
         if (j + 1 < g.s) {
@@ -758,13 +763,18 @@ __global__ __launch_bounds__(256, 1) void conv_redo_backward(ConvRedo a) {
   }
 }
 
-// In front of a pass: no exchange has taken place, nothing is given up (stalled may be null: cleared elsewhere), and the head
-// of the step table.
-__global__ __launch_bounds__(256) inline void pass_reset(uint4* words, size_t n, int* stalled, FloatChunk c, float* table, int count) {
+// In front of a pass: no exchange has taken place, nothing is given up unless the kernels cannot do the work (F1, F2: see
+// ConvPair; ctl: under overflow detection), and the head of the step table.
+__global__ __launch_bounds__(256) inline void pass_reset(uint4* words, size_t n, int* stalled, const float* F1, const float* F2, Ctl* ctl,
+                                                         FloatChunk c, float* table, int count) {
   if (blockIdx.x == 0)
     for (int i = threadIdx.x; i < count; i += 256) table[i] = c.v[i];
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) words[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (stalled && blockIdx.x == 0 && threadIdx.x == 0) *stalled = 0;
+  if (blockIdx.x != 0 || threadIdx.x >= 64) return;
+  const bool odd = __builtin_amdgcn_ballot_w64(F1[threadIdx.x] + F2[threadIdx.x] != 0.f) != 0;
+  if (threadIdx.x != 0) return;
+  *stalled = odd;
+  if (odd && ctl) ctl->stalled = ctl->poison = 1;
 }
 
 // Behind the chain of a step under overflow detection: accept or reject it, the scale of the next (Alg. 2).  256 threads.

@@ -42,7 +42,8 @@ __global__ void cast_dense_layer(const float* __restrict__ W, const float* __res
 // frags (Cpad = 64): Wp and WTp in the order in which conv_pair.hpp multiplies them, a fragment of v_mfma_f32_16x16x32 (16
 // output channels, 32 inputs of a tap; lane l: output l % 16, inputs 8 (l / 16) ..) as 1 KB, [tap][input block][output block], taps of the middle line first;
 // WTp may be null.  And the time-channel weights and the bias likewise, as a block of their own: frags [2][64][8], element
-// (k / 8, output, k % 8), k = 0-8: tap, 9: bias.
+// (k / 8, output, k % 8), k = 0-8: tap, 9: bias.  A time weight that is not finite is zero there and itself in wt_f, and
+// bias_f holds, in place of the bias, 1 for its output and 0 for the others.
 template <class T>
 __global__ void cast_conv_layer(const float* __restrict__ W, const float* __restrict__ b, int C, int Cin,
                                 int has_time, uint16_t* Wp, uint16_t* WTp, float* bias_f, float* wt_f, int Cpad, uint16_t* frags) {
@@ -50,6 +51,11 @@ __global__ void cast_conv_layer(const float* __restrict__ W, const float* __rest
   int total = Cpad * 9 * Cpad;
   if (idx >= total) return;
   int ci = idx % Cpad, tap = (idx / Cpad) % 9, co = idx / (9 * Cpad);
+  float row[9] = {};  // (in flight beside everything else)
+  if (frags && ci == 0 && tap == 0 && co < C && has_time) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t) row[t] = W[((size_t)co * Cin + C) * 9 + t];
+  }
   uint16_t q = 0;
   if (co < C && ci < C) q = Low<T>::from_f32(W[((size_t)co * Cin + ci) * 9 + tap]);
   if (frags) {
@@ -69,9 +75,17 @@ __global__ void cast_conv_layer(const float* __restrict__ W, const float* __rest
     if (co < C && has_time) w = Low<T>::to_f32(Low<T>::from_f32(W[((size_t)co * Cin + C) * 9 + tap]));
     wt_f[tap * Cpad + co] = w;
     const uint16_t bq = co < C ? Low<T>::from_f32(b[co]) : 0;
-    if (tap == 0) bias_f[co] = Low<T>::to_f32(bq);
+    if (tap == 0) {
+      float f = Low<T>::to_f32(bq);
+      if (frags) {
+        f = 0.f;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) f = Low<T>::nonfinite(Low<T>::from_f32(row[t])) ? 1.f : f;
+      }
+      bias_f[co] = f;
+    }
     if (frags) {
-      frags[((tap / 8) * 64 + co) * 8 + tap % 8] = Low<T>::from_f32(w);
+      frags[((tap / 8) * 64 + co) * 8 + tap % 8] = Low<T>::from_f32(__builtin_isfinite(w) ? w : 0.f);
       if (tap < 7) frags[(64 + co) * 8 + tap + 1] = tap == 0 ? bq : 0;
     }
   }

@@ -1089,13 +1089,14 @@ struct Runner {
   // ---- whole steps per launch (conv_pass.hpp)
   static constexpr bool kBf16 = std::is_same<T, BF16>::value;
   uint32_t exchanges = 1;  // number of the next launch's first exchange
-  ConvPass conv_pass(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low, int* stalled) {
+  ConvPass conv_pass(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low, Ctl* detecting) {
     const std::vector<float> t = step_table(tgrid, N, tab, low);
     for (size_t off = 0; off < t.size(); off += 768) {
       FloatChunk c;
       const int cnt = (int)std::min<size_t>(768, t.size() - off);
       memcpy(c.v, t.data() + off, sizeof(float) * cnt);
-      if (off == 0) pass_reset<<<256, 256, 0, st>>>((uint4*)(ws + p.words), p.word_bytes / 16, stalled, c, f32(p.steptab), cnt);
+      if (off == 0) pass_reset<<<256, 256, 0, st>>>((uint4*)(ws + p.words), p.word_bytes / 16, &ctl->cluster_stalled, f32(p.layers[0].bias_f),
+                                                    f32(p.layers[1].bias_f), detecting, c, f32(p.steptab), cnt);
       else write_floats<<<1, 256, 0, st>>>(c, f32(p.steptab) + off, cnt);
     }
     const Layer &y0 = p.layers[0], &y1 = p.layers[1];
@@ -1104,6 +1105,10 @@ struct Runner {
     g.W2 = u16(y1.Wp);
     g.T1 = u16(y0.tf);
     g.T2 = u16(y1.tf);
+    g.X1 = f32(y0.wt_f);
+    g.X2 = f32(y1.wt_f);
+    g.F1 = f32(y0.bias_f);
+    g.F2 = f32(y1.bias_f);
     g.steptab = f32(p.steptab);
     g.words = (unsigned long long*)(ws + p.words);
     g.ticks = wait_ticks ? kPassWaitTicks : 0;
@@ -1148,7 +1153,7 @@ struct Runner {
                    uint16_t* ckpt, float* yN) {
     test_aids(pol->flags);
     cast_weights(theta);
-    ConvPass g = conv_pass(tgrid, N, tab, pol->low, &ctl->cluster_stalled);
+    ConvPass g = conv_pass(tgrid, N, tab, pol->low, nullptr);
     g.N = N;
     g.ckpt = ckpt;
     g.y0 = y0;
@@ -1161,7 +1166,7 @@ struct Runner {
       g.nsteps = std::min(piece, N - g.step);
       if (const int rc = launch_pass(g, kPassForward, p.images(), 2 * p.s * g.nsteps, (double)p.s * g.nsteps)) return rc;
     }
-    return p.pass.per_image > 1 ? launch_redo(g, false) : RAMPDE_OK;
+    return launch_redo(g, false);
   }
   // the adjoint of the steps hi, hi - 1, ... hi - n + 1, from a to a_out; g as conv_pass leaves it
   int backward_steps(ConvPass g, int hi, int n, const rampde_tableau* tab, const rampde_policy* pol, const uint16_t* ckpt, const double* tgrid,
@@ -1192,9 +1197,8 @@ struct Runner {
       if (detect)
         pass_decide<<<1, 256, 0, st>>>(ctl, f32(p.scale_hist), g.step, Low<T>::p_bits, dynamic, (pol->flags & RAMPDE_GROW_RAW_NORM) ? 1 : 0,
                                        g.amax, p.pass.slots * p.pass.per_image);
-      else if (p.pass.per_image > 1) {
-        if (const int rc = launch_redo(g, true)) return rc;
-      }
+      else if (const int rc = launch_redo(g, true))
+        return rc;
       if (y0.cw_step) continue;
       for (int r = q; r < q + per_launch; ++r) {
         const int i = hi - r;
@@ -1363,6 +1367,10 @@ struct Runner {
         g.W2 = u16(y1.Wp);
         g.T1 = u16(y0.tf);
         g.T2 = u16(y1.tf);
+        g.X1 = f32(y0.wt_f);
+        g.X2 = f32(y1.wt_f);
+        g.F1 = f32(y0.bias_f);
+        g.F2 = f32(y1.bias_f);
         g.tau = low_bits_host(tau, low);
         if (keep) g.mid = u16(p.ACT[0]) + (size_t)jb * p.R * y0.Npad;
         if (slope) g.C = u16(p.K) + (size_t)j * p.stage_stride;
@@ -2311,7 +2319,7 @@ struct Runner {
     };
     ConvPass pass{};
     if (p.pass.lines) {
-      pass = conv_pass(tgrid, N, tab, pol->low, nullptr);
+      pass = conv_pass(tgrid, N, tab, pol->low, detect ? ctl : nullptr);
       pass_start(N - 1);
     }
     if (p.conv) {

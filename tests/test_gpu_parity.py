@@ -292,6 +292,41 @@ def test_conv_launches_that_are_given_up(low, scaling):
         assert par.rel_err(b[k], a[k]) <= par.TOL_EMUL
 
 
+@pytest.mark.parametrize("C,H,W,B,low,scaling", [(40, 19, 20, 3, "bf16", "none"), (64, 20, 33, 2, "f16", "dynamic"), (24, 8, 8, 3, "bf16", "dynamic"),
+                                                 (16, 7, 9, 2, "f16", "none"), (21, 12, 10, 2, "bf16", "dynamic")])
+def test_conv_time_weight_that_rounds_to_infinity(C, H, W, B, low, scaling):
+    # a tap outside the image leaves its time weight out of the sum, also an infinite one: images of several tiles and of
+    # one, kernels that run whole steps and (21 channels) single evaluations.  Bits as with a finite weight behind which
+    # tanh is +-1 as well; f16: see test_conv_launches_that_are_given_up
+    cfg = wl.CONFIGS["cfg4"].with_(name=f"convinf{C}x{H}x{W}", B=B, N=2, C=C, H=H, W=W, tableau="heun", low=low)
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    offs = {n: o for n, _, o in wl.theta_layout(cfg)}
+    tgrid = np.linspace(0.5, 1.0, 3)
+    huge, large = (3.4e38, 1e38) if low == "bf16" else (1e6, 6e4)
+
+    def with_weight(layer, value, taps=((1, 0, 0, 1.0), (3, 2, 1, -1.0), (C - 1, 1, 2, 1.0))):
+        th = theta.copy()
+        for co, ky, kx, sign in taps:  # (the last input channel is the time)
+            th[offs[layer] + ((co * (C + 1) + C) * 3 + ky) * 3 + kx] = sign * value
+        return th
+
+    same = np.testing.assert_array_equal if low == "bf16" else lambda a, b: np.testing.assert_array_less(par.rel_err(a, b), par.TOL_EMUL)
+    a, b = (par.run_gpu(cfg, with_weight("W1", v), y0, target, scaling=scaling, tgrid=tgrid) for v in (huge, large))
+    for k in ("yN", "ckpt", "grad_y0", "grad_theta"):
+        assert np.isfinite(b[k]).all()
+        if k != "grad_theta":
+            same(a[k], b[k])
+    # (the redone pass deals the contraction out in other chunks: fp32 sums of about 1000 terms in another order, 2^-24 each)
+    assert par.rel_err(a["grad_theta"], b["grad_theta"]) <= (1e-5 if low == "bf16" else par.TOL_EMUL)
+    # behind the second convolution: +-infinity where the tap is inside, and nothing elsewhere (one step of one evaluation)
+    one = cfg.with_(N=1, tableau="euler")
+    a, b = (par.run_gpu(one, with_weight("W2", v), y0, target, scaling="none", tgrid=tgrid[:2]) for v in (huge, 0.0))
+    inside = np.zeros((C, H, W), dtype=bool)
+    inside[1, 1:, 1:] = inside[3, :-1, :] = inside[C - 1, :, :-1] = True
+    assert (np.isposinf(a["yN"]) | np.isneginf(a["yN"]))[:, inside].all()
+    same(a["yN"][:, ~inside], b["yN"][:, ~inside])
+
+
 def test_conv_small_odd_geometry():
     cfg = wl.CONFIGS["cfg4"].with_(name="convodd", B=2, N=2, C=5, H=7, W=6, tableau="kutta3")
     _both(cfg, bias_std=0.1)
