@@ -566,6 +566,7 @@ __global__ __launch_bounds__(256, MT <= 4 ? 2 : 1) void conv_pass_chain(ConvPass
           return;
         }
         const float coef = j > 0 ? g.sub[j - 1] : 0.f, bw = j > 0 ? g.b[j - 1] : 0.f;
+        const int first = (t.me() >> 4 & 3) * 4;  // this lane's first channel
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -580,7 +581,8 @@ __global__ __launch_bounds__(256, MT <= 4 ? 2 : 1) void conv_pass_chain(ConvPass
               sum[m][c][r] += f[r];
               x[r] = fmaf(h, coef * f[r], bw * l[r]);
             }
-            const uint2 kq = pack4<T>(x);
+            uint2 kq = pack4<T>(x);
+            if (first + 16 * c >= g.d) kq = make_uint2(0u, 0u);  // (an infinite slope cotangent times the zero weights of pad channels: NaN)
             if (t.on(m)) {
               watch(zq);
               if (j > 0) watch(kq);

@@ -265,6 +265,27 @@ def test_fewer_convolution_steps_at_once_on_a_smaller_workspace(scaling):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
+@pytest.mark.parametrize("flags", [0, rb.NO_WAITS])
+@pytest.mark.parametrize("C,H,W", [(40, 20, 16), (24, 9, 12)])
+def test_overflow_of_a_convolution_under_a_fixed_scale_leaves_its_infinity(C, H, W, flags):
+    # a hidden cotangent overflows around one pixel (2e4 / 2 x 10 > 65504) and with it, all weights being positive, the
+    # cotangents of the stage before: db_1 and db_2 are infinite, as sums of +infinity and finite terms.  The pad channels
+    # (infinity times their zero weights) must not make them NaN
+    cfg = wl.CONFIGS["cfg4"].with_(name="convinf", B=1, N=1, C=C, H=H, W=W, tableau="heun", low="f16")
+    theta = np.zeros(cfg.n_params, dtype=np.float32)
+    slices = {n: (slice(o, o + int(np.prod(shp))), shp) for n, shp, o in wl.theta_layout(cfg)}
+    for n in ("W1", "W2"):
+        theta[slices[n][0]].reshape(slices[n][1])[:, :C] = 10.0  # (not the time's)
+    vel, tab, pol = par.gpu_descriptors(cfg, "none", flags=flags)
+    th, y0 = torch.from_numpy(theta).to("cuda:0"), torch.zeros((1, C, H, W), device="cuda:0")
+    _, ckpt = rb.rampde_odeint_fwd(vel, th, y0, cfg.tgrid(), tab, pol)
+    gyN = torch.zeros_like(y0)
+    gyN[0, 3, H // 2, W // 2] = 2e4
+    _, gth, _ = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ckpt, gyN)
+    for n in ("b1", "b2"):
+        assert bool(torch.isposinf(gth[slices[n][0]]).all())
+
+
 @pytest.mark.parametrize("base,kw", MULTI_WG, ids=[k["name"] for _, k in MULTI_WG])
 def test_scaling_failure_many_workgroups(base, kw):
     cfg, theta, y0, target = _gain_case(base, **dict(kw))
