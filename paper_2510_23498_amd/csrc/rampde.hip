@@ -79,7 +79,7 @@ struct Layer {
   int ldw;  // K extent of the forward GEMM (dense: Kpad; conv: 9 * Cpad)
   // all-taps convolution weight gradient: K-chunk length, chunk count, the chunks' private copies
   int cw_per = 0, cw_splits = 0;
-  int cw_step = 0;       // chunks of a step where a launch takes a group of buffer sets, 0: one step per launch
+  bool cw_group = false; // a launch takes a group of buffer sets, not one step
   size_t cw_part = 0;
   size_t cw_floats = 0;  // fp32 elements of all the copies
 };
@@ -421,6 +421,12 @@ static bool group_recomputes_ahead(const Plan& p) {
   return !(p.MT == 2 && p.L <= 3 && widest <= 512 && 4 * tiles >= 3 * rounds * cus);
 }
 
+// rows of a K-chunk of a convolution's weight gradient where at most `want` chunks share `rows`
+static int64_t conv_chunk_rows(const Plan& p, const Layer& y, int64_t rows, int64_t want) {
+  const int64_t unit = conv_wgrad_tr64_applies(p, y) ? (int64_t)2 * tr64_step_lines(p.Wd) * p.Wd : CW_KS;
+  return std::max(4 * unit, ((rows + want - 1) / want + unit - 1) / unit * unit);
+}
+
 // allow_wide = false: never the kernels of wide.hpp (the backward pass that also forms the time-grid
 // gradient runs on the other row-tile kernels).  small: no choice of the streaming kernels, which keep slopes in the
 // workspace, where the register-resident ones can run, and no clusters.  allow_clusters = false: no clusters, every other
@@ -595,8 +601,11 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
       // gradients are one contraction.  128 MiB, which the memory-side cache holds, against 1 GiB, us per pass: 64 channels,
       // 128 images of 32 x 32, f16, 16 RK4 steps 7819 / 7429, 40 of them, bf16, 8 steps 1790 / 1545, 16 of 64 x 64 1568 / 1493
       p.a_alt = take(sizeof(float) * (size_t)p.n);
+      // (evenly: five steps where four fit are groups of three and two)
       const int64_t fit = std::min<int64_t>(32, ((int64_t)1 << 30) / (4 * p.s * p.R * 64 * 2));
-      p.nsets = (int)std::max<int64_t>(1, std::min<int64_t>(fit, pol && pol->step_group > 0 ? std::min(N, pol->step_group) : N));
+      const int most = (int)std::max<int64_t>(1, std::min<int64_t>(fit, pol && pol->step_group > 0 ? std::min(N, pol->step_group) : N));
+      const int groups = (N + most - 1) / most;
+      p.nsets = (N + groups - 1) / groups;
       sbuf *= p.nsets;
     }
   }
@@ -811,12 +820,10 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
           // (the steps of a group of buffer sets are one launch)
           const int group = pair && p.pass.lines ? p.nsets : 1;
           const int64_t want = std::max<int64_t>(1, cus / tiles / group);
-          const int64_t unit = conv_wgrad_tr64_applies(p, y) ? (int64_t)2 * tr64_step_lines(p.Wd) * p.Wd : CW_KS;
-          int64_t per = ((rows + want - 1) / want + unit - 1) / unit * unit;
-          if (per < 4 * unit) per = 4 * unit;
+          const int64_t per = conv_chunk_rows(p, y, rows, want);
           y.cw_per = (int)per;
           y.cw_splits = (int)((rows + per - 1) / per) * group;
-          y.cw_step = group > 1 ? y.cw_splits / group : 0;
+          y.cw_group = group > 1;
           y.cw_floats = (size_t)y.cw_splits * tiles * CW_SLOT;
           y.cw_part = take(sizeof(float) * y.cw_floats);
         }
@@ -1199,7 +1206,7 @@ struct Runner {
                                        g.amax, p.pass.slots * p.pass.per_image);
       else if (const int rc = launch_redo(g, true))
         return rc;
-      if (y0.cw_step) continue;
+      if (y0.cw_group) continue;
       for (int r = q; r < q + per_launch; ++r) {
         const int i = hi - r;
         const float h = (float)(tgrid[i + 1] - tgrid[i]);
@@ -1211,7 +1218,7 @@ struct Runner {
         param_grads(h, taus, grad_theta, cs, nullptr, r);
       }
     }
-    if (y0.cw_step) param_grads(0.f, Coefs{}, grad_theta, Coefs{}, nullptr, 0, n, hi);
+    if (y0.cw_group) param_grads(0.f, Coefs{}, grad_theta, Coefs{}, nullptr, 0, n, hi);
     return RAMPDE_OK;
   }
 
@@ -2015,12 +2022,17 @@ struct Runner {
         c.wt = y.has_time ? f32(y.wt_f) : nullptr;
         c.ldwt = y.Npad;
         c.tpart = tpart_i ? f32(p.tslots) : nullptr;
-        dim3 cgrid(y.Npad / 64, y.Kpad / 64, group ? group * y.cw_step : y.cw_splits);
+        dim3 cgrid(y.Npad / 64, y.Kpad / 64, y.cw_splits);
         if (group) {
+          // (fewer steps than buffer sets, as with a running cost: they have all the private copies, a chunk may use any.
+          // With the chunks of a whole group, 64 channels, 128 images of 16 x 16, f16, 32 RK4 steps took 16937 us per pass,
+          // a pass with a running cost, now 6170)
+          if (group != p.nsets) c.rows_per_split = (int)conv_chunk_rows(p, y, rows, y.cw_splits / group);
+          c.per_step = (int)((rows + c.rows_per_split - 1) / c.rows_per_split);
+          cgrid.z = group * c.per_step;
           c.steptab = f32(p.steptab);
           c.scale_hist = f32(p.scale_hist);
           c.step = first;
-          c.per_step = y.cw_step;
           c.s = s;
         }
         // 64 x 64 channels: both convolutions of the velocity in one launch (the parabolic block's two terms share their

@@ -241,6 +241,28 @@ def test_retry_in_the_middle_of_a_group_of_convolution_steps(step_group):
     par.compare(cfg, gpu, emu, par.TOL_F64[cfg.low], "emulation oracle (amplifying network)")
 
 
+@pytest.mark.parametrize("C,H,B", [(64, 16, 64), (64, 8, 64)])
+def test_weight_gradients_with_a_running_cost_use_the_whole_device(C, H, B):
+    # the steps go one by one then: a step's contraction is dealt out as where a group is one step.  With the chunks of a
+    # step in a full group they took 4 to 16 times as long; the bound leaves 2 for the noise of short launches
+    cfg = wl.CONFIGS["cfg4"].with_(name="convgys", B=B, N=32, C=C, H=H, W=H, tableau="heun", low="bf16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    th, y = (torch.from_numpy(x).to("cuda:0") for x in (theta, y0))
+    gys = torch.zeros((cfg.N + 1,) + tuple(cfg.state_shape), device="cuda:0")
+    ms = {}
+    for group in (0, 1):
+        vel, tab, pol = par.gpu_descriptors(cfg, "none", step_group=group)
+        yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
+        for _ in range(3):
+            rb.rampde_timing_enable(True)
+            rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, yN, grad_ys=gys)
+            t, launches, _ = rb.rampde_timing_read(rb.K_WGRAD_GEMM)
+            rb.rampde_timing_enable(False)
+            assert launches == cfg.N
+            ms[group] = min(t, ms.get(group, t))
+    assert ms[0] <= 2 * ms[1]
+
+
 @pytest.mark.parametrize("scaling", ["dynamic", "none"])
 def test_fewer_convolution_steps_at_once_on_a_smaller_workspace(scaling):
     # the queried workspace holds the stages of all five steps; one with room for fewer takes fewer at once: the bits of a

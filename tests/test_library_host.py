@@ -94,6 +94,15 @@ def test_workspace_of_grouped_steps_under_detection(base, kw):
     assert small <= 200 << 20
 
 
+@pytest.mark.parametrize("N,asked,even", [(5, 4, 3), (9, 8, 5), (7, 3, 3), (33, 0, 17)])
+def test_groups_of_convolution_steps_are_even(N, asked, even):
+    # the last group of a pass is no shorter than it has to be (33 steps: at most 32 at once)
+    cfg = wl.CONFIGS["cfg4"].with_(C=8, H=16, W=16, B=4, N=N)
+    vel, tab, _ = _descr(cfg)
+    size = {g: rb.rampde_workspace_bytes(vel, cfg.B, N, tab, rb.Policy(low=cfg.low, step_group=g), True) for g in (asked, even, even - 1)}
+    assert size[asked] == size[even] > size[even - 1]
+
+
 @pytest.mark.parametrize("widths,B", [((256, 1024, 1024, 256), 1024), ((256, 1024, 1024, 256), 512), ((100, 1000, 1000, 100), 941),
                                       ((128, 512, 512, 512, 128), 2000), ((128, 512, 512, 128), 2048), ((100, 600, 100), 1024)])
 def test_workspace_of_clusters_under_detection(widths, B):
