@@ -123,7 +123,8 @@ typedef enum {
                                      redone by the kernels that do not.  Same results */
 #define RAMPDE_NO_WAITS_AFTER(n) (RAMPDE_NO_WAITS | (unsigned)(n) << 16)  /* test aid, networks whose workgroups share row tiles:
                                      they give up after n (< 65536) evaluations of a pass, with what was computed by then in
-                                     the caller's buffers; other networks: as RAMPDE_NO_WAITS */
+                                     the caller's buffers; convolutions whose workgroups share an image (n > 0): behind n
+                                     exchanges of lines, and later launches do not; other networks: as RAMPDE_NO_WAITS */
 #define RAMPDE_SKEWED_CLUSTERS 32u  /* test aid: workgroups that share row tiles (same notes) take their places as if one XCD had
                                      been given a cluster's worth of them too many: the launch is given up and redone */
 

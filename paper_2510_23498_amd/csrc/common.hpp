@@ -31,7 +31,8 @@ struct Ctl {
   float S_step;        // scale of the most recently accepted step (used by its parameter-gradient kernels)
   int stalled;         // a wait between the workgroups of a launch ran out (they never ran at the same time)
   int cluster_stalled; // ... of a launch whose work the launches behind it redo (cluster.hpp)
-  int pad[3];
+  int redone;          // launches of the pass that conv_redo_* did again (conv_pass.hpp)
+  int pad[2];
 };
 static_assert(sizeof(Ctl) == 64, "control block layout");
 

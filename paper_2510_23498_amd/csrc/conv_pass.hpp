@@ -15,7 +15,7 @@
 // after they have read its e.  While the words are on their way the three taps of the middle line are multiplied.
 //
 // The tiles of an image have to run at the same time: a launch has at most as many workgroups as the device runs at once.
-// If others hold the device a wait ends after `ticks`; the launch then raises `stalled`, and conv_redo_* behind it do the
+// If others hold the device a wait ends after kPassWaitTicks; the launch then raises `stalled`, and conv_redo_* behind it do the
 // work again, one workgroup per image (nothing is left of a launch that was given up: they start from its inputs).  A pass
 // under overflow detection is redone by way of the host instead.  Time weights that are not finite go the same way from the
 // start (pass_reset): beside the contractions here their terms (PairTime::add_odd) cost registers, 137 spilled instead of 5 in
@@ -51,7 +51,7 @@ struct ConvPass {
   const float* steptab;         // [N][1 + s]: step size, stage times rounded to low
   unsigned long long* words;    // [workgroups][2][2][Wd x 16-byte chunks of a pixel x 4]
   uint32_t first;               // number of the launch's first exchange
-  unsigned long long ticks;
+  uint32_t give_up_at;          // number of the exchange at which no workgroup looks for words (RAMPDE_NO_WAITS), 0: none
   int* stalled;
   int H, Wd, d, s, images;
   int64_t n;                    // elements from one stored state to the next
@@ -177,7 +177,7 @@ struct PassTile {
   // the neighbours' lines; false: a wait of this thread ran out
   __device__ __forceinline__ bool collect() const {
     const int side_words = pitch / 4, chunks = W * C8, me0 = me();
-    bool late = g.ticks == 0;
+    bool late = tag == g.give_up_at;
     unsigned long long t0 = 0, v[2][4];
     for (int first = 0; first < 2 * chunks; first += 2 * NT) {
       const unsigned long long* w[2];
@@ -201,7 +201,7 @@ struct PassTile {
           for (int k = 0; k < 4; ++k) there &= !want[i] | ((uint32_t)(v[i][k] >> 32) == tag);
         if (there || late) break;
         if (t0 == 0) t0 = wall_clock64();
-        late = wall_clock64() - t0 >= g.ticks;
+        late = wall_clock64() - t0 >= kPassWaitTicks;
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -640,12 +640,14 @@ struct ConvRedo {
   ConvPairShape sh;                // tiles of one line
   const uint16_t *V1, *V2;         // backward: the transposed fragments W_2^T, W_1^T (g.W1, g.W2: the forward ones)
   uint16_t *Z2, *K, *ZBAR;         // [rows][64]: a second stage input (forward); slopes and cotangents of a step's stages
+  int* redone;
 };
 
 template <class T, int C32>
 __global__ __launch_bounds__(256, 1) void conv_redo_forward(ConvRedo a) {
   const ConvPass& g = a.g;
   if (!*g.stalled) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ++*a.redone;
   extern __shared__ __attribute__((aligned(16))) uint16_t pass_smem[];
   const int HW = g.H * g.Wd;
   for (int img = blockIdx.x; img < g.images; img += gridDim.x) {
@@ -698,6 +700,7 @@ template <class T, int C32>
 __global__ __launch_bounds__(256, 1) void conv_redo_backward(ConvRedo a) {
   const ConvPass& g = a.g;
   if (!*g.stalled) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ++*a.redone;
   extern __shared__ __attribute__((aligned(16))) uint16_t pass_smem[];
   const int HW = g.H * g.Wd;
   const float S = g.ctl->S;
@@ -766,17 +769,18 @@ __global__ __launch_bounds__(256, 1) void conv_redo_backward(ConvRedo a) {
 }
 
 // In front of a pass: no exchange has taken place, nothing is given up unless the kernels cannot do the work (F1, F2: see
-// ConvPair; ctl: under overflow detection), and the head of the step table.
+// ConvPair), and the head of the step table.
 __global__ __launch_bounds__(256) inline void pass_reset(uint4* words, size_t n, int* stalled, const float* F1, const float* F2, Ctl* ctl,
-                                                         FloatChunk c, float* table, int count) {
+                                                         int detect, FloatChunk c, float* table, int count) {
   if (blockIdx.x == 0)
     for (int i = threadIdx.x; i < count; i += 256) table[i] = c.v[i];
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) words[i] = make_uint4(0u, 0u, 0u, 0u);
   if (blockIdx.x != 0 || threadIdx.x >= 64) return;
   const bool odd = __builtin_amdgcn_ballot_w64(F1[threadIdx.x] + F2[threadIdx.x] != 0.f) != 0;
   if (threadIdx.x != 0) return;
+  ctl->redone = 0;
   *stalled = odd;
-  if (odd && ctl) ctl->stalled = ctl->poison = 1;
+  if (odd && detect) ctl->stalled = ctl->poison = 1;
 }
 
 // Behind the chain of a step under overflow detection: accept or reject it, the scale of the next (Alg. 2).  256 threads.

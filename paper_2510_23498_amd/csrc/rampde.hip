@@ -1096,14 +1096,15 @@ struct Runner {
   // ---- whole steps per launch (conv_pass.hpp)
   static constexpr bool kBf16 = std::is_same<T, BF16>::value;
   uint32_t exchanges = 1;  // number of the next launch's first exchange
-  ConvPass conv_pass(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low, Ctl* detecting) {
+  int give_up_after = -1;  // exchanges of the pass behind which a launch is given up, 0: each at its first, -1: none
+  ConvPass conv_pass(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low, int detect) {
     const std::vector<float> t = step_table(tgrid, N, tab, low);
     for (size_t off = 0; off < t.size(); off += 768) {
       FloatChunk c;
       const int cnt = (int)std::min<size_t>(768, t.size() - off);
       memcpy(c.v, t.data() + off, sizeof(float) * cnt);
       if (off == 0) pass_reset<<<256, 256, 0, st>>>((uint4*)(ws + p.words), p.word_bytes / 16, &ctl->cluster_stalled, f32(p.layers[0].bias_f),
-                                                    f32(p.layers[1].bias_f), detecting, c, f32(p.steptab), cnt);
+                                                    f32(p.layers[1].bias_f), ctl, detect, c, f32(p.steptab), cnt);
       else write_floats<<<1, 256, 0, st>>>(c, f32(p.steptab) + off, cnt);
     }
     const Layer &y0 = p.layers[0], &y1 = p.layers[1];
@@ -1118,7 +1119,6 @@ struct Runner {
     g.F2 = f32(y1.bias_f);
     g.steptab = f32(p.steptab);
     g.words = (unsigned long long*)(ws + p.words);
-    g.ticks = wait_ticks ? kPassWaitTicks : 0;
     g.stalled = &ctl->cluster_stalled;
     g.H = p.H; g.Wd = p.Wd; g.d = p.d; g.s = p.s; g.images = (int)p.images();
     g.n = step_elems;
@@ -1134,6 +1134,7 @@ struct Runner {
   int launch_pass(ConvPass& g, ConvPassKind kind, int64_t items, int convolutions, double evaluations) {
     TimeScope ts(RAMPDE_K_VELOCITY_GEMM, evaluations * 4.0 * p.R * 64.0 * 9 * 64, st);
     g.first = exchanges;
+    g.give_up_at = give_up_after < 0 ? 0 : give_up_after == 0 ? g.first : give_up_after + 1;
     exchanges += (uint32_t)((items + p.pass.slots - 1) / p.pass.slots * convolutions);
     HIP_TRY(conv_pass_launch(p.c32(), kBf16, g, p.pass, kind, st));
     return RAMPDE_OK;
@@ -1143,6 +1144,7 @@ struct Runner {
     a.g = g;
     a.sh = conv_pair_tiles(p.c32(), 1, p.H, p.Wd, p.images());
     a.K = u16(p.K);
+    a.redone = &ctl->redone;
     if (backward) {
       const Layer &y0 = p.layers[0], &y1 = p.layers[1];
       a.g.W1 = u16(y0.Wp);
@@ -1160,7 +1162,7 @@ struct Runner {
                    uint16_t* ckpt, float* yN) {
     test_aids(pol->flags);
     cast_weights(theta);
-    ConvPass g = conv_pass(tgrid, N, tab, pol->low, nullptr);
+    ConvPass g = conv_pass(tgrid, N, tab, pol->low, 0);
     g.N = N;
     g.ckpt = ckpt;
     g.y0 = y0;
@@ -1189,7 +1191,7 @@ struct Runner {
     g.detect = detect;
     g.step = hi;
     g.nsteps = n;
-    if (const int rc = launch_pass(g, kPassRecompute, p.images() * n, 2 * p.s, p.s * n)) return rc;
+    if (const int rc = launch_pass(g, kPassRecompute, p.images() * n, 2 * p.s - 1, p.s * n)) return rc;
     g.W1 = u16(y1.WTp);
     g.W2 = u16(y0.WTp);
     const int per_launch = detect ? 1 : n;
@@ -1450,6 +1452,7 @@ struct Runner {
     skewed_clusters = (flags & RAMPDE_SKEWED_CLUSTERS) != 0;
     if (!(flags & RAMPDE_NO_WAITS)) return;
     if (p.cluster) cluster_budget = flags >> 16;
+    else if (p.pass.lines) give_up_after = flags >> 16;
     else wait_ticks = 0;
   }
 
@@ -2331,7 +2334,7 @@ struct Runner {
     };
     ConvPass pass{};
     if (p.pass.lines) {
-      pass = conv_pass(tgrid, N, tab, pol->low, detect ? ctl : nullptr);
+      pass = conv_pass(tgrid, N, tab, pol->low, detect);
       pass_start(N - 1);
     }
     if (p.conv) {

@@ -292,6 +292,67 @@ def test_conv_launches_that_are_given_up(low, scaling):
         assert par.rel_err(b[k], a[k]) <= par.TOL_EMUL
 
 
+def _conv_pass(cfg, theta, y0, **kw):
+    """A training pass on workspaces of its own -> (results, launches redone behind the forward pass and behind the
+    backward pass: a word of the control block at the head of a workspace, launches of the evaluations in all)."""
+    from paper_2510_23498_amd import binding as rb
+    grad_ys = kw.pop("grad_ys", None)
+    vel, tab, pol = par.gpu_descriptors(cfg, **kw)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    gys = None if grad_ys is None else torch.from_numpy(grad_ys).to(dev)
+    ws = [rb.alloc_workspace(vel, cfg.B, cfg.N, tab, pol, b) for b in (False, True)]
+    rb.rampde_timing_enable(True)
+    yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol, workspace=ws[0])
+    gy0, gth, info = rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, yN / yN.numel(), grad_ys=gys, workspace=ws[1])
+    torch.cuda.synchronize()
+    launches = rb.rampde_timing_read(rb.K_VELOCITY_GEMM)[1]
+    rb.rampde_timing_enable(False)
+    out = dict(yN=yN, ckpt=ck.float(), grad_y0=gy0, grad_theta=gth)
+    return {k: v.cpu().numpy() for k, v in out.items()}, [int(w[:64].view(torch.int32)[13]) for w in ws], launches
+
+
+def _same_conv_pass(cfg, got, undisturbed, grad_theta_bits):
+    # (bits: see test_conv_launches_that_are_given_up)
+    for k in ("yN", "ckpt", "grad_y0", "grad_theta"):
+        if cfg.low == "bf16" and (k != "grad_theta" or grad_theta_bits):
+            np.testing.assert_array_equal(got[k], undisturbed[k])
+        assert par.rel_err(got[k], undisturbed[k]) <= par.TOL_EMUL
+
+
+@pytest.mark.parametrize("low,scaling,running_cost", [("bf16", "none", False), ("bf16", "none", True), ("f16", "none", False), ("bf16", "dynamic", False),
+                                                      ("f16", "dynamic", True)])
+@pytest.mark.parametrize("after", [9, 20, 26, 40, 50, 85])
+def test_conv_launches_given_up_in_mid_pass(low, scaling, running_cost, after):
+    # three groups of two steps, each 14 exchanges of recomputation (two rounds over the images) and 16 of the chains: given
+    # up in the recomputation's second round, in both steps of a chain behind a whole recomputation, in later groups, and
+    # with a running cost's cotangents (steps one by one, 7 and 8 exchanges); in the forward pass in four of its steps
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name="convmid", B=3, N=6, C=40, H=19, W=20, tableau="rk4", low=low)
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    gys = (np.random.default_rng(5).standard_normal((cfg.N + 1,) + cfg.state_shape) * 0.01 / y0.size).astype(np.float32) if running_cost else None
+    a, redone, launches = _conv_pass(cfg, theta, y0, scaling=scaling, step_group=2, grad_ys=gys)
+    assert redone == [0, 0]
+    b, redone, more = _conv_pass(cfg, theta, y0, scaling=scaling, step_group=2, grad_ys=gys, flags=rb.no_waits_after(after))
+    assert redone[0] == (1 if after < 48 else 0)
+    assert redone[1] >= 1 if scaling == "none" else more > launches
+    _same_conv_pass(cfg, b, a, scaling == "none")
+
+
+@pytest.mark.parametrize("C,H,W,B,N,tab,after", [(40, 19, 20, 3, 30, "rk4", 100),   # the first of two launches of a forward pass
+                                                 (40, 19, 20, 3, 30, "rk4", 200),   # ... the second
+                                                 (8, 16, 64, 150, 3, "euler", 8)])  # the second of two rounds over the images
+def test_conv_forward_launches_given_up_in_mid_pass(C, H, W, B, N, tab, after):
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name=f"convpieces{C}", B=B, N=N, C=C, H=H, W=W, tableau=tab, low="bf16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    a, redone, _ = _conv_pass(cfg, theta, y0, scaling="none")
+    assert redone == [0, 0]
+    b, redone, _ = _conv_pass(cfg, theta, y0, scaling="none", flags=rb.no_waits_after(after))
+    assert redone[0] == 1
+    _same_conv_pass(cfg, b, a, True)
+
+
 @pytest.mark.parametrize("C,H,W,B,low,scaling", [(40, 19, 20, 3, "bf16", "none"), (64, 20, 33, 2, "f16", "dynamic"), (24, 8, 8, 3, "bf16", "dynamic"),
                                                  (16, 7, 9, 2, "f16", "none"), (21, 12, 10, 2, "bf16", "dynamic")])
 def test_conv_time_weight_that_rounds_to_infinity(C, H, W, B, low, scaling):
