@@ -16,7 +16,8 @@
 //
 // The tiles of an image have to run at the same time: a launch has at most as many workgroups as the device runs at once.
 // If others hold the device a wait ends after kPassWaitTicks; the launch then raises `stalled`, and conv_redo_* behind it do the
-// work again, one workgroup per image (nothing is left of a launch that was given up: they start from its inputs).  A pass
+// work again, one workgroup per image (nothing is left of a launch that was given up: they start from its inputs).  Each group
+// of adjoint steps has a flag of its own: the groups behind a redone one run on these kernels again.  A pass
 // under overflow detection is redone by way of the host instead.  Time weights that are not finite go the same way from the
 // start (pass_reset): beside the contractions here their terms (PairTime::add_odd) cost registers, 137 spilled instead of 5 in
 // the recomputation of 64 channels.
@@ -768,18 +769,18 @@ __global__ __launch_bounds__(256, 1) void conv_redo_backward(ConvRedo a) {
   }
 }
 
-// In front of a pass: no exchange has taken place, nothing is given up unless the kernels cannot do the work (F1, F2: see
-// ConvPair), and the head of the step table.
-__global__ __launch_bounds__(256) inline void pass_reset(uint4* words, size_t n, int* stalled, const float* F1, const float* F2, Ctl* ctl,
+// In front of a pass: no exchange has taken place, nothing is given up (`stalled`: `flags` of them) unless the kernels cannot
+// do the work (F1, F2: see ConvPair), and the head of the step table.
+__global__ __launch_bounds__(256) inline void pass_reset(uint4* words, size_t n, int* stalled, int flags, const float* F1, const float* F2, Ctl* ctl,
                                                          int detect, FloatChunk c, float* table, int count) {
   if (blockIdx.x == 0)
     for (int i = threadIdx.x; i < count; i += 256) table[i] = c.v[i];
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) words[i] = make_uint4(0u, 0u, 0u, 0u);
   if (blockIdx.x != 0 || threadIdx.x >= 64) return;
   const bool odd = __builtin_amdgcn_ballot_w64(F1[threadIdx.x] + F2[threadIdx.x] != 0.f) != 0;
+  for (int i = threadIdx.x; i < flags; i += 64) stalled[i] = odd;
   if (threadIdx.x != 0) return;
   ctl->redone = 0;
-  *stalled = odd;
   if (odd && detect) ctl->stalled = ctl->poison = 1;
 }
 

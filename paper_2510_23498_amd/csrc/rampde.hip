@@ -154,6 +154,7 @@ struct Plan {
   int64_t images() const { return R / ((int64_t)H * Wd); }
   int c32() const { return d <= 32 ? 1 : 2; }
   size_t words = 0, word_bytes = 0; // its exchange
+  size_t stalls = 0;                // a flag per group of adjoint steps
   bool lean = false;                // no choice of kernels for which the workspace alone is larger (see plan_within)
   std::vector<size_t> ACTT, DELTAT;
 };
@@ -597,6 +598,7 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     p.words = take(p.word_bytes);
     p.steptab = take(sizeof(float) * (size_t)N * (1 + p.s));
     if (is_backward) {
+      p.stalls = take(sizeof(int) * (size_t)N);
       // buffer sets: the stages of as many steps as 1 GiB holds are recomputed in one launch, at most 32, and their weight
       // gradients are one contraction.  128 MiB, which the memory-side cache holds, against 1 GiB, us per pass: 64 channels,
       // 128 images of 32 x 32, f16, 16 RK4 steps 7819 / 7429, 40 of them, bf16, 8 steps 1790 / 1545, 16 of 64 x 64 1568 / 1493
@@ -1099,11 +1101,12 @@ struct Runner {
   int give_up_after = -1;  // exchanges of the pass behind which a launch is given up, 0: each at its first, -1: none
   ConvPass conv_pass(const double* tgrid, int N, const rampde_tableau* tab, rampde_dtype low, int detect) {
     const std::vector<float> t = step_table(tgrid, N, tab, low);
+    int* stall_flags = p.stalls ? (int*)(ws + p.stalls) : &ctl->cluster_stalled;
     for (size_t off = 0; off < t.size(); off += 768) {
       FloatChunk c;
       const int cnt = (int)std::min<size_t>(768, t.size() - off);
       memcpy(c.v, t.data() + off, sizeof(float) * cnt);
-      if (off == 0) pass_reset<<<256, 256, 0, st>>>((uint4*)(ws + p.words), p.word_bytes / 16, &ctl->cluster_stalled, f32(p.layers[0].bias_f),
+      if (off == 0) pass_reset<<<256, 256, 0, st>>>((uint4*)(ws + p.words), p.word_bytes / 16, stall_flags, p.stalls ? N : 1, f32(p.layers[0].bias_f),
                                                     f32(p.layers[1].bias_f), ctl, detect, c, f32(p.steptab), cnt);
       else write_floats<<<1, 256, 0, st>>>(c, f32(p.steptab) + off, cnt);
     }
@@ -1119,7 +1122,7 @@ struct Runner {
     g.F2 = f32(y1.bias_f);
     g.steptab = f32(p.steptab);
     g.words = (unsigned long long*)(ws + p.words);
-    g.stalled = &ctl->cluster_stalled;
+    g.stalled = stall_flags;
     g.H = p.H; g.Wd = p.Wd; g.d = p.d; g.s = p.s; g.images = (int)p.images();
     g.n = step_elems;
     g.stage_stride = p.stage_stride;
@@ -1177,8 +1180,9 @@ struct Runner {
     }
     return launch_redo(g, false);
   }
-  // the adjoint of the steps hi, hi - 1, ... hi - n + 1, from a to a_out; g as conv_pass leaves it
-  int backward_steps(ConvPass g, int hi, int n, const rampde_tableau* tab, const rampde_policy* pol, const uint16_t* ckpt, const double* tgrid,
+  // the adjoint of the steps hi, hi - 1, ... hi - n + 1, from a to a_out; g as conv_pass leaves it (group: of the pass.  Under
+  // overflow detection, where groups are begun anew, a launch that is given up ends them all: one flag)
+  int backward_steps(ConvPass g, int group, int hi, int n, const rampde_tableau* tab, const rampde_policy* pol, const uint16_t* ckpt, const double* tgrid,
                      float* (&buf)[2], const float* gys, float* grad_theta, int dynamic, int detect) {
     const Layer &y0 = p.layers[0], &y1 = p.layers[1];
     g.ckpt = const_cast<uint16_t*>(ckpt);
@@ -1189,6 +1193,7 @@ struct Runner {
     g.amax = (unsigned*)(ws + p.amax_slots);
     g.ctl = ctl;
     g.detect = detect;
+    if (!detect) g.stalled += group;
     g.step = hi;
     g.nsteps = n;
     if (const int rc = launch_pass(g, kPassRecompute, p.images() * n, 2 * p.s - 1, p.s * n)) return rc;
@@ -2431,9 +2436,9 @@ struct Runner {
       }
       if (p.pass.lines) {
         pass_start(from);
-        for (int hi = from; hi >= 0;) {
+        for (int hi = from, group = 0; hi >= 0; ++group) {
           const int n = std::min(grad_ys ? 1 : p.nsets, hi + 1);
-          if (const int rc = backward_steps(pass, hi, n, tab, pol, ckpt, tgrid, pass_buf, gys_at(hi), grad_theta, dynamic, detect)) return rc;
+          if (const int rc = backward_steps(pass, group, hi, n, tab, pol, ckpt, tgrid, pass_buf, gys_at(hi), grad_theta, dynamic, detect)) return rc;
           hi -= n;
         }
         a = pass_buf[0];

@@ -339,6 +339,18 @@ def test_conv_launches_given_up_in_mid_pass(low, scaling, running_cost, after):
     _same_conv_pass(cfg, b, a, scaling == "none")
 
 
+@pytest.mark.parametrize("running_cost,groups", [(False, 3), (True, 6)])
+@pytest.mark.parametrize("after", [0, 9, 20, 50])
+def test_conv_groups_behind_one_that_is_given_up(running_cost, groups, after):
+    # only the launches that gave up are done again (0: each group's; else one): those behind them run as ever
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name="convgroups", B=3, N=6, C=40, H=19, W=20, tableau="rk4", low="bf16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    gys = np.full((cfg.N + 1,) + cfg.state_shape, 0.01 / y0.size, np.float32) if running_cost else None
+    _, redone, _ = _conv_pass(cfg, theta, y0, scaling="none", step_group=2, grad_ys=gys, flags=rb.no_waits_after(after))
+    assert redone[1] == (1 if after else groups)
+
+
 @pytest.mark.parametrize("C,H,W,B,N,tab,after", [(40, 19, 20, 3, 30, "rk4", 100),   # the first of two launches of a forward pass
                                                  (40, 19, 20, 3, 30, "rk4", 200),   # ... the second
                                                  (8, 16, 64, 150, 3, "euler", 8)])  # the second of two rounds over the images
