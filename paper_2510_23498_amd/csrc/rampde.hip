@@ -588,8 +588,10 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
     }
   }
   // Whole steps per launch (conv_pass.hpp): 16-byte rows, stages that are a chain, the state kept in 32 bits between the steps.
-  // Not for dL/dt, whose sums need the slopes.
-  if (p.conv_pairs() && allow_resident && allow_clusters && !small && !lean && !p.time_grid && p.d % 8 == 0 && chained_stages(tab) &&
+  // Not for dL/dt, whose sums need the slopes, and not where a pass that is given up is redone as a whole, by way of the host,
+  // and its parameter gradients were added to the caller's step by step (no private copies: conv_wgrad_applies).
+  const bool adds_twice = is_backward && pol && resolve_scaling(pol) != RAMPDE_SCALE_NONE && !conv_wgrad_applies(p);
+  if (p.conv_pairs() && !adds_twice && allow_resident && allow_clusters && !small && !lean && !p.time_grid && p.d % 8 == 0 && chained_stages(tab) &&
       tab->s <= kPassStages && linked_stages(tab) && !(pol && (pol->flags & (RAMPDE_NAIVE_STATE | RAMPDE_ROUND_INCREMENT))))
     p.pass = conv_pass_shape(p.c32(), p.H, p.Wd, p.images(), device_compute_units());
   int sbuf = is_backward ? p.s : 1;  // forward keeps one stage of inputs/activations

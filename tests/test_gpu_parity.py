@@ -351,6 +351,18 @@ def test_conv_groups_behind_one_that_is_given_up(running_cost, groups, after):
     assert redone[1] == (1 if after else groups)
 
 
+@pytest.mark.parametrize("scaling", ["dynamic", "none_safe", "none"])
+def test_conv_parameter_gradients_of_a_pass_that_is_redone(scaling):
+    # image lines that are no multiple of 8 pixels on the generic contraction, which adds to the caller's gradient step by
+    # step: each step's share is in it once
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name="convonce", B=3, N=6, C=40, H=19, W=20, tableau="rk4", low="bf16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    a, b = (_conv_pass(cfg, theta, y0, scaling=scaling, step_group=2, wgrad_tile=64, flags=flags)[0] for flags in (0, rb.no_waits_after(40)))
+    np.testing.assert_array_equal(a["grad_y0"], b["grad_y0"])
+    assert par.rel_err(b["grad_theta"], a["grad_theta"]) <= 1e-5  # (fp32 atomics: about 10^4 terms in any order, 2^-24 each)
+
+
 @pytest.mark.parametrize("C,H,W,B,N,tab,after", [(40, 19, 20, 3, 30, "rk4", 100),   # the first of two launches of a forward pass
                                                  (40, 19, 20, 3, 30, "rk4", 200),   # ... the second
                                                  (8, 16, 64, 150, 3, "euler", 8)])  # the second of two rounds over the images
