@@ -155,7 +155,8 @@ struct Plan {
   int c32() const { return d <= 32 ? 1 : 2; }
   size_t words = 0, word_bytes = 0; // its exchange
   size_t stalls = 0;                // a flag per group of adjoint steps
-  bool lean = false;                // no choice of kernels for which the workspace alone is larger (see plan_within)
+  int lean = 0;                     // 1: no choice of kernels for which the workspace alone is larger (see plan_within); 2: and
+                                    // convolutions without private copies of their weight gradients
   std::vector<size_t> ACTT, DELTAT;
 };
 
@@ -434,7 +435,7 @@ static int64_t conv_chunk_rows(const Plan& p, const Layer& y, int64_t rows, int6
 // choice as it is.  lean: see plan_within
 static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab,
                       const rampde_policy* pol, int is_backward, bool allow_wide = true, bool allow_resident = true,
-                      bool small = false, bool allow_clusters = true, bool lean = false) {
+                      bool small = false, bool allow_clusters = true, int lean = 0) {
   Plan p;
   p.lean = lean;
   p.time_grid = is_backward && !allow_wide;
@@ -823,7 +824,8 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
           const int cus = device_compute_units() / (pair ? 2 : 1);
           // (the steps of a group of buffer sets are one launch)
           const int group = pair && p.pass.lines ? p.nsets : 1;
-          const int64_t want = std::max<int64_t>(1, cus / tiles / group);
+          // (lean: no more chunks than a larger batch has, which may be four fifths: chunks of five units instead of four)
+          const int64_t most = std::max<int64_t>(1, cus / tiles / group), want = lean ? std::max<int64_t>(1, most * 4 / 5) : most;
           const int64_t per = conv_chunk_rows(p, y, rows, want);
           y.cw_per = (int)per;
           y.cw_splits = (int)((rows + per - 1) / per) * group;
@@ -848,14 +850,14 @@ static Plan make_plan(const rampde_velocity* vel, int64_t B, int N, const rampde
   return p;
 }
 
-static bool conv_wgrad_lines_applies(const Plan& p) { return p.conv && !p.fused && p.Wd % 8 == 0 && p.Wd <= 64 && p.R % CW_KS == 0; }
+static bool conv_wgrad_lines_applies(const Plan& p) { return p.conv && p.lean < 2 && !p.fused && p.Wd % 8 == 0 && p.Wd <= 64 && p.R % CW_KS == 0; }
 // (64 x 64 channels, image lines of up to 64 pixels: conv_wgrad's drop-in built on transposing LDS reads.  Not lines of 8
 // pixels, padded to 16 there, where conv_wgrad takes them and the contraction is long enough for its chunks of 512 rows to
 // occupy half of the chip: per pass of 4 RK4 steps, 8 x 8, 64 channels, transposing / conv_wgrad, us: 128 images
 // (32768 rows in the contraction) 1277 / 1301, 256 images 1479 / 1430, 512 1816 / 1796, 2048 4290 / 4233; parabolic block
 // 64 images 2716 / 2750, 256 images 3108 / 2992.  Lines of 24 pixels, 682 images of 8 lines: 3750 / 4052)
 static bool conv_wgrad_tr64_applies(const Plan& p, const Layer& y) {
-  return p.conv && !p.fused && !p.cw_blocks && y.Npad == 64 && y.Kpad == 64 && p.Wd <= 64 &&
+  return p.conv && p.lean < 2 && !p.fused && !p.cw_blocks && y.Npad == 64 && y.Kpad == 64 && p.Wd <= 64 &&
          !(p.Wd == 8 && conv_wgrad_lines_applies(p) && p.s * p.R >= 65536);
 }
 static bool conv_wgrad_applies(const Plan& p) {
@@ -2642,7 +2644,8 @@ size_t rampde_workspace_bytes(const rampde_velocity* vel, int64_t B, int N, cons
 
 // The plan of a call on `bytes` of workspace.  Exchange buffers of clusters, stages of more steps at once, slopes beside them
 // and more copies of the gradients grow the workspace of some batches past that of larger ones (256 -> 2 x 1024 -> 256, f16, 32
-// RK4 steps, 1024 / 4096 rows: backward 674 / 384 MiB, forward 31 / 20): a workspace made for the largest batch of a
+// RK4 steps, 1024 / 4096 rows: backward 674 / 384 MiB, forward 31 / 20), and convolutions have copies of their weight gradients
+// where the number of pixels allows it only (21 channels, 8 x 8, wgrad_tile = 64, 2 / 3 images: 4.7 / 4.5 MiB): a workspace made for the largest batch of a
 // program does not hold them for a smaller one, and that runs on the kernels that need less.
 static Plan plan_within(size_t bytes, const rampde_velocity* vel, int64_t B, int N, const rampde_tableau* tab, const rampde_policy* pol,
                         int is_backward, bool allow_wide, bool allow_resident, bool small = false, bool allow_clusters = true) {
@@ -2653,7 +2656,8 @@ static Plan plan_within(size_t bytes, const rampde_velocity* vel, int64_t B, int
     fewer.step_group = sets;
     p = make_plan(vel, B, N, tab, &fewer, is_backward, allow_wide, allow_resident, small, allow_clusters);
   }
-  if (p.ok && p.total > bytes) p = make_plan(vel, B, N, tab, pol, is_backward, allow_wide, allow_resident, small, allow_clusters, true);
+  for (int lean = 1; lean <= (vel->kind == RAMPDE_VEL_CONV2 || vel->kind == RAMPDE_VEL_PARABOLIC ? 2 : 1) && p.ok && p.total > bytes; ++lean)
+    p = make_plan(vel, B, N, tab, pol, is_backward, allow_wide, allow_resident, small, allow_clusters, lean);
   return p;
 }
 

@@ -1011,6 +1011,24 @@ def test_smaller_batch_on_the_workspace_of_a_larger_one(base, widths, low, tabna
             assert par.rel_err(a.float().cpu().numpy(), b.float().cpu().numpy()) <= par.TOL_EMUL
 
 
+@pytest.mark.parametrize("C,H,W,tab,wgrad_tile,large,B", [(8, 7, 9, "kutta3", 0, 200, 190), (21, 8, 8, "rk4", 0, 200, 190),
+                                                          (21, 8, 8, "heun", 64, 3, 2), (64, 8, 8, "euler", 64, 3, 2)])
+def test_smaller_batch_of_images_on_the_workspace_of_a_larger_one(C, H, W, tab, wgrad_tile, large, B):
+    # fewer private copies of the weight gradients, or none: the same results (32-bit sums in another order)
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name="last_images", B=B, N=3, C=C, H=H, W=W, tableau=tab, low="f16")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    dev = torch.device("cuda:0")
+    th, y = torch.from_numpy(theta).to(dev), torch.from_numpy(y0).to(dev)
+    vel, t, pol = par.gpu_descriptors(cfg, scaling="dynamic", wgrad_tile=wgrad_tile)
+    own, less = (rb.alloc_workspace(vel, b, cfg.N, t, pol, True) for b in (B, large))
+    assert less.numel() < own.numel()
+    yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), t, pol)
+    a, b = (rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), t, pol, ck, yN, workspace=ws)[:2] for ws in (own, less))
+    for x, ref in zip(b, a):
+        assert par.rel_err(x.cpu().numpy(), ref.cpu().numpy()) <= par.TOL_EMUL
+
+
 def test_infinite_slope_that_no_stage_uses():
     # stages that do not build on one another: the second one starts from the stored state although the first one's slope
     # has left the range of 16 bits

@@ -3,6 +3,7 @@ symbol the header declares, sizes parameters and workspaces consistently, and re
 arguments before anything is launched (paper Sec. 3 / Algorithms 1-2 define the arguments:
 time partition, tableau, precision and scaling policy)."""
 import ctypes as C
+import itertools
 import os
 import re
 import subprocess
@@ -283,6 +284,30 @@ def test_workspace_of_a_larger_batch_serves_smaller_ones():
         size_f, size_b = sizes(cfg, low, N, B)
         assert size_b < sizes(cfg, low, N, small)[1]  # (what the smaller batch would take of a workspace of its own)
         assert codes(cfg, low, N, size_f, size_b, small) == [rb.EHIP] * 3, (widths, low, B, small)
+
+
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="the pointers are dummies: only where no device can follow them")
+@pytest.mark.parametrize("shape", [(8, 7, 9), (21, 8, 8), (24, 28, 28), (64, 32, 32), (64, 8, 8), (32, 5, 70), (128, 16, 16)])
+def test_workspace_of_a_larger_batch_of_images_serves_smaller_ones(shape):
+    # (fewer chunks of a larger batch's weight-gradient contraction, or none where its pixels do not divide)
+    lib = rb.load_library()
+    p = lambda x: C.c_void_p(0x100000 * x)
+    for tabname, N, wgrad_tile, scaling in itertools.product(("euler", "rk4", "kutta3"), (1, 5, 33), (0, 64), ("none", "dynamic")):
+        cfg = wl.CONFIGS["cfg4"].with_(C=shape[0], H=shape[1], W=shape[2], tableau=tabname)
+        vel, tab, _ = _descr(cfg)
+        pol = rb.Policy(low="f16", scaling=scaling, wgrad_tile=wgrad_tile)
+        tgp = np.linspace(0.0, 1.0, N + 1).ctypes.data_as(C.POINTER(C.c_double))
+        for B in (1, 3, 20, 200):
+            size = [rb.rampde_workspace_bytes(vel, B, N, tab, pol, b) for b in (False, True)]
+            for part in (1.0, 0.99, 0.95, 0.7, 0.5, 0.02):
+                small = max(1, int(B * part))
+                for yN in (4, 2):  # (not in place and in place)
+                    rc = [lib.rampde_odeint_fwd(C.byref(vel.c), p(1), p(2), small, tgp, N, C.byref(tab.c), C.byref(pol.c), p(3), p(yN), p(5),
+                                                size[0], None)]
+                    for grad_t in (None, p(9)):
+                        rc.append(lib.rampde_odeint_bwd_tgrid(C.byref(vel.c), p(1), small, tgp, N, C.byref(tab.c), C.byref(pol.c), p(3), p(2),
+                                                              None, p(yN), p(7), grad_t, None, None, p(5), size[1], None))
+                    assert rc == [rb.EHIP] * 3, (tabname, N, wgrad_tile, scaling, B, small, yN, rc)
 
 
 def test_backward_rejects_bad_arguments_without_touching_the_device():
