@@ -34,7 +34,8 @@ PEAK_HBM_GBS = 8000.0
 HEADLINE = "cfg3"
 ALL_CONFIGS = [("cfg1", None), ("cfg2", None), ("cfg3", None), ("cfg4", None),
                ("cfg5", "rk4"), ("cfg5", "heun"), ("cfg5", "euler"), ("parab", None), ("cnf", None)]
-# evaluations of the velocity per forward evaluation that a kernel class performs
+# evaluations of the velocity per forward evaluation that a kernel class performs (convolutions: less the second convolution
+# of a step's last stage, whose slope the recomputation leaves out unless dL/dt needs it)
 CLASS_EVALS = {"fused_forward": 1.0, "fused_adjoint_step": 2.0, "wgrad_gemm": 1.0, "velocity_gemm": 3.0}
 
 
@@ -146,6 +147,8 @@ def measure(cfg, steps, warmup, grad_t=False, target_seconds=None):
         t = timing[name]
         if t["ms"] <= 0:
             continue
+        if name == "velocity_gemm" and cfg.kind in ("conv2", "parabolic") and not grad_t:
+            evals -= 0.5 / s
         alg = evals * s * N * eval_flops                      # per pass
         sec = t["ms"] * 1e-3 / steps                          # per pass
         kernels[name] = {

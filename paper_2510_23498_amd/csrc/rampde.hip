@@ -1200,7 +1200,7 @@ struct Runner {
     if (!detect) g.stalled += group;
     g.step = hi;
     g.nsteps = n;
-    if (const int rc = launch_pass(g, kPassRecompute, p.images() * n, 2 * p.s - 1, p.s * n)) return rc;
+    if (const int rc = launch_pass(g, kPassRecompute, p.images() * n, 2 * p.s - 1, n * (p.s - 0.5))) return rc;
     g.W1 = u16(y1.WTp);
     g.W2 = u16(y0.WTp);
     const int per_launch = detect ? 1 : n;

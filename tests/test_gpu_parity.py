@@ -351,6 +351,19 @@ def test_conv_groups_behind_one_that_is_given_up(running_cost, groups, after):
     assert redone[1] == (1 if after else groups)
 
 
+@pytest.mark.parametrize("C", [40, 21])
+def test_conv_work_of_the_launches(C):
+    # whole steps per launch and single evaluations alike: the recomputation leaves out a step's last slope
+    from paper_2510_23498_amd import binding as rb
+    cfg = wl.CONFIGS["cfg4"].with_(name="convwork", B=3, N=5, C=C, H=19, W=20, tableau="rk4", low="f16")
+    theta, y0, target = par.make_inputs(cfg, bias_std=0.1)
+    rb.rampde_timing_enable(True)
+    par.run_gpu(cfg, theta, y0, target, step_group=2)
+    work = rb.rampde_timing_read(rb.K_VELOCITY_GEMM)[2]
+    rb.rampde_timing_enable(False)
+    assert work == cfg.N * (8 + 7 + 8) * 2.0 * 3 * 19 * 20 * 64 * 9 * 64
+
+
 @pytest.mark.parametrize("scaling", ["dynamic", "none_safe", "none"])
 def test_conv_parameter_gradients_of_a_pass_that_is_redone(scaling):
     # image lines that are no multiple of 8 pixels on the generic contraction, which adds to the caller's gradient step by
