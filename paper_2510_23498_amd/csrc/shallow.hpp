@@ -161,10 +161,7 @@ struct ShallowTile {
   // this copy's of a lane's eight hidden units: pair u of words(COPIES)
   template <int COPIES>
   static __device__ __forceinline__ void own(const f32x4 (&acc)[2], int copy, int u, float (&v)[2]) {
-    if constexpr (COPIES == 1) {
-      v[0] = acc[u >> 1][2 * (u & 1)];
-      v[1] = acc[u >> 1][2 * (u & 1) + 1];
-    } else if constexpr (COPIES == 2) {
+    if constexpr (COPIES == 2) {
 #pragma unroll
       for (int r = 0; r < 2; ++r) v[r] = copy ? acc[1][2 * u + r] : acc[0][2 * u + r];
     } else {
@@ -179,8 +176,7 @@ struct ShallowTile {
   template <int COPIES, int K>
   static __device__ __forceinline__ uint32_t word(const uint32_t (&w)[words(COPIES)]) {
     constexpr int owner = K / words(COPIES), other = COPIES == 4 ? owner : owner + 2;  // (lanes 0, 1 and 2, 3 of four)
-    if constexpr (COPIES == 1) return w[K];
-    else return __builtin_amdgcn_update_dpp(0, (int)w[K % words(COPIES)], owner * 5 + other * 0x50, 0xf, 0xf, false);
+    return __builtin_amdgcn_update_dpp(0, (int)w[K % words(COPIES)], owner * 5 + other * 0x50, 0xf, 0xf, false);
   }
   template <int COPIES>
   static __device__ __forceinline__ void whole(const uint32_t (&w)[words(COPIES)], uint32_t (&v)[4]) {
@@ -256,7 +252,7 @@ __global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) v
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, copy = lane % COPIES;
   const int nh = wave * Sh::TPW * 16 + (lane >> 4) * 4;
   const int er = tid / (Sh::NT / 16), ec = (tid % (Sh::NT / 16)) * EPT;  // this thread's state elements
-  const int64_t row = er < ROWS ? (int64_t)blockIdx.x * ROWS + er : g.R;
+  const int64_t row = COPIES == 1 || er < ROWS ? (int64_t)blockIdx.x * ROWS + er : g.R;
   const int64_t n_state = g.R * g.d;
   const int s = g.s;
   typename Tile::Weights w;
@@ -300,26 +296,37 @@ __global__ __launch_bounds__((ShallowShape<NTL, HP>::NT), (HP <= 128 ? 1 : 2)) v
         f32x4 acc[2];
         Tile::start(acc, l, tau, nh, p);
         Tile::pre(acc, w, a, p);
-        uint32_t hq[WORDS], op[4];
+        uint2 hq[2];
+        if constexpr (COPIES > 1) {
+          uint32_t mine[WORDS], op[4];
 #pragma unroll
-        for (int u = 0; u < WORDS; ++u) {
-          float v[2];
-          Tile::template own<COPIES>(acc, copy, u, v);
-          hq[u] = Low<T>::pack2(tanh_fast(v[0]), tanh_fast(v[1]));
+          for (int u = 0; u < WORDS; ++u) {
+            float v[2];
+            Tile::template own<COPIES>(acc, copy, u, v);
+            mine[u] = Low<T>::pack2(tanh_fast(v[0]), tanh_fast(v[1]));
+          }
+          Tile::template whole<COPIES>(mine, op);
+          hq[0] = make_uint2(op[0], op[1]);
+          hq[1] = make_uint2(op[2], op[3]);
         }
-        Tile::template whole<COPIES>(hq, op);
-        if constexpr (TRACE) {
 #pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
+        for (int hh = 0; hh < 2; ++hh) {
+          float v[4];
+          if constexpr (COPIES == 1) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = tanh_fast(acc[hh][r]);
+            hq[hh] = pack4<T>(v);
+          }
+          if constexpr (TRACE) {
             const f32x4 c = *(const RAMPDE_LDS f32x4*)(l.cf + nh + (2 * p + hh) * 16);
-            float v[4];
-            unpack4<T>(make_uint2(op[2 * hh], op[2 * hh + 1]), v);
+            unpack4<T>(hq[hh], v);
 #pragma unroll
             for (int r = 0; r < 4; ++r) tr = fmaf(c[r], fmaf(-v[r], v[r], 1.f), tr);
           }
         }
+        const u16x8 op = Tile::operand(hq[0], hq[1]);
 #pragma unroll
-        for (int n = 0; n < Sh::NS; ++n) out[n] = Low<T>::mfma16(w.V[n][p], Tile::operand(make_uint2(op[0], op[1]), make_uint2(op[2], op[3])), out[n]);
+        for (int n = 0; n < Sh::NS; ++n) out[n] = Low<T>::mfma16(w.V[n][p], op, out[n]);
       }
       Tile::template put_part<COPIES>(out, l, wave, lane);
       if constexpr (TRACE) Tile::template put_trace<COPIES>(tr, l, wave, lane);
