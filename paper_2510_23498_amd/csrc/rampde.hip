@@ -1442,8 +1442,10 @@ struct Runner {
     return RAMPDE_OK;
   }
 
-  // init_adjoint: as few workgroups as read at the device's rate (each posts to the same words)
-  unsigned init_blocks() const { return stream_blocks(p.n / 16, p.n >= (1 << 22) ? 256 : 64); }
+  // init_adjoint: as few workgroups as read at the device's rate (each posts to the same words), and 16 bytes per lane below
+  // that, where a launch is latency.  us with 64 / 128 / 256 / 512 workgroups: 2^18 elements 5.0 / 5.7 / 7.8 / 12.1, 2^20 7.9 /
+  // 7.4 / 8.9 / 13.2, 2^22 19 / 13 / 12 / 15; 10634 elements with 2 / 4 / 8 / 16 4.8 / 3.9 / 3.7 / 3.4
+  unsigned init_blocks() const { return stream_blocks(p.n / 4, p.n < (1 << 20) ? 64 : p.n < (1 << 22) ? 128 : 256); }
   // streaming kernels: 8-wide variants when the state width allows 16-byte accesses
   bool vec8() const { return (p.d & 7) == 0; }
   static unsigned stream_blocks(int64_t groups, int64_t cap = 4096) {  // grid-stride loops
