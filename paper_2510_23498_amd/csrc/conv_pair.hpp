@@ -11,8 +11,8 @@
 //
 // v_mfma_f32_16x16x32 with the weights as the first operand: a lane ends with 4 consecutive output channels of one pixel.
 // A wavefront multiplies all output channels with its MT blocks of 16 pixels: per contraction block of 32 input channels
-// of one tap NCT weight fragments, which come from memory in the order in which they are used (1 KB each, four blocks
-// ahead), and MT pixel fragments from LDS (a tap is a shifted pixel address) for NCT MT matrix instructions.
+// of one tap NCT weight fragments, which come from memory in the order in which they are used (1 KB each, three
+// blocks ahead), and MT pixel fragments from LDS (a tap is a shifted pixel address) for NCT MT matrix instructions.
 //
 // It runs where conv_pass.hpp, which keeps a tile's state on chip over whole steps, does not: channel counts that are no
 // multiple of 8, tableaux whose stages are no chain, dL/dt, calls in place, passes that are redone.  What bounds a launch

@@ -22,8 +22,8 @@
 // start (pass_reset): beside the contractions here their terms (PairTime::add_odd) cost registers, 137 spilled instead of 5 in
 // the recomputation of 64 channels.
 //
-// Measured, us per evaluation of 64 x 32 x 32, 128 images (512 workgroups of 8 lines): forward 30.6, recomputation 23.3, chain
-// 38 (conv_pair.hpp with the passes over memory that it needs beside it 31, 28 and 45); 32 channels 10.2, 11.1 and 13.5;
+// Measured, us per evaluation of 64 x 32 x 32, 128 images (512 workgroups of 8 lines): forward 30.1, recomputation 22.9, chain
+// 36 (conv_pair.hpp with the passes over memory that it needs beside it 31, 28 and 45); 32 channels 10.2, 11.1 and 13.5;
 // 32 channels, 20 x 28 x 28, 4 lines 6.2, 7.3 and 9.4.  Cycles per convolution and workgroup in the first: arithmetic of the
 // epilogue 7100 (tanh, roundings, the next stage's input), matrix instructions 9000 (both workgroups of a compute unit at
 // once), stores and the exchange's 3400, waiting for the neighbours 2800, barriers 1800.  Without any exchange (wrong results)
