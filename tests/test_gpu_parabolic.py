@@ -204,3 +204,21 @@ def test_parabolic_time_grid_gradient_is_refused():
     theta, y0, target = par.make_inputs(cfg)
     out = par.run_gpu(cfg, theta, y0, target, want_grad_t=True, expect_error=True)
     assert out.get("error") == rb.EUNSUPPORTED
+
+
+@pytest.mark.parametrize("pieces", [1, 4])
+def test_parabolic_smaller_batch_on_the_workspace_of_a_larger_one(pieces):
+    # it has no room for private copies of the weight gradients, which the larger batch (pixels that do not divide) does not
+    # take: the same chains, fp32 sums of a gradient in another order
+    import torch
+    from paper_2510_23498_amd import binding as rb
+    cfg = BASE.with_(name="pblast", B=2, C=72, H=8, W=24, N=4, n_intervals=pieces, tableau="kutta3")
+    theta, y0, _ = par.make_inputs(cfg, bias_std=0.1)
+    th, y = torch.from_numpy(theta).to("cuda:0"), torch.from_numpy(y0).to("cuda:0")
+    vel, tab, pol = par.gpu_descriptors(cfg, scaling="dynamic")
+    own, less = (rb.alloc_workspace(vel, b, cfg.N, tab, pol, True) for b in (cfg.B, 3))
+    assert less.numel() < own.numel()
+    yN, ck = rb.rampde_odeint_fwd(vel, th, y, cfg.tgrid(), tab, pol)
+    a, b = ([x.cpu().numpy() for x in rb.rampde_odeint_bwd(vel, th, cfg.tgrid(), tab, pol, ck, yN, workspace=ws)[:2]] for ws in (own, less))
+    np.testing.assert_array_equal(a[0], b[0])
+    assert par.rel_err(b[1], a[1]) <= 1e-5
